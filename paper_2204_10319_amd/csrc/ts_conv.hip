@@ -1196,7 +1196,7 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
     const int cin1 = TWO ? sec.cin1 : cin_pad;
     TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, kTileDepth, TWO>), grid, dim3(kThreads), x,
-              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, kmap->d_perm, kmap->rows_done ? kmap->d_tile_order : nullptr,
+              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, kmap->d_perm, kmap->scan_done || kmap->scan_enqueued ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
               static_cast<const _Float16 *>(ep.bias), static_cast<const _Float16 *>(ep.residual), ep.relu,
               (int)((size_t)kmap->n_in * cin1 * 2), (int)((size_t)kmap->K3 * cin_pad * out->cols * 2), kmap->centre,
@@ -1533,12 +1533,16 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // small to fill the machine with tiles (the coarse levels of a U-Net) are cheaper explicit,
 // everything else fused; the factor and the size limit come from timing both on the layers of
 // the MinkUNet-style benchmark network.
+// The number of pairs is the typical one of surface-like scenes, not the map's own: an asynchronous build does
+// not know its own yet, waiting for it cost a small step three times what its kernels take, and the choice must
+// not depend on whether somebody has asked.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
-    if (resolve(kmap) != TS_OK) return false;   // needs the number of pairs
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
+    const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
+    const double pairs = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;
     const double fused_weight_bytes = (double)kmap->n_tiles * tile_offsets * cin * cout * elem;
-    const double explicit_bytes = (double)kmap->M * (2.0 * cin * elem + 2.0 * cout * sizeof(float));
+    const double explicit_bytes = pairs * (2.0 * cin * elem + 2.0 * cout * sizeof(float));
     return fused_weight_bytes > 0.6 * explicit_bytes;
 }
 

@@ -85,7 +85,7 @@ inline int alloc_n(T **p, size_t n) {
 
 // Waits, if it has not happened yet, for the sizes and error flags of a map built with
 // ts_build_kmap_async, and fills in M / sizes / offs.  Returns TS_OK or the build's error.
-// need_sizes == false: only the error flags are awaited; the put-off part of a stride-1 build is not run.
+// need_sizes == false: only the verdict is awaited; the put-off scan of a stride-1 build is not run.
 int resolve(const struct ::ts_kmap *kmap, bool need_sizes = true);
 
 // Enqueues, without waiting, what an asynchronous build put off (ts_kmap_prepare).
@@ -148,9 +148,8 @@ struct ts_kmap {
     int centre = -1;            // index of the identity offset (odd K, stride 1), else -1
     int stride = 0;             // nbr_stride(K3)
     int64_t n_in = 0, n_out = 0, M = 0;   // M, sizes, offs: valid once ts::resolve has run
-    bool rows_enqueued = false; // the put-off row pass and scan have been enqueued (ts_kmap_prepare); resolve only waits
-    bool rows_done = true;      // false: the row pass (bitmask words, centre entries, rank bitmaps, tile order) and the
-                                // scan have not run yet; ts::resolve runs them (the fused kernel needs none of it)
+    bool scan_enqueued = false; // the scan (ranks, sizes, tile order) has been enqueued; resolve only waits for it
+    bool scan_done = true;      // false: what the scan leaves is not there yet, or not known to be (the fused kernel needs none of it)
     int pending_slot = -1;      // >= 0: sizes and error flags are still on their way to the host
     int error = 0;              // TS_OK, or what the build found wrong with its input
     int32_t out_box_lo[3] = {0, 0, 0}, out_box_hi[3] = {0, 0, 0}, out_box_batches = 0;   // a box that holds every output
@@ -170,7 +169,8 @@ struct ts_kmap {
     // ... and the link between the two views: the pair (k, n) sits at
     // offs[n] + colbase[n][k/64] + popcount(colbits[n][k/64] & ((1 << k%64) - 1)).
     uint64_t *d_colbits = nullptr;        // [K3][n_blocks] bit r: output 64*b + r has offset n
-    int32_t *d_colbase = nullptr;         // [K3][n_blocks] pairs of offset n in the blocks before b
+    int32_t *d_colbase = nullptr;         // [K3][n_blocks] pairs of offset n in the blocks before b (until the scan: in block b)
+    uint32_t *d_wavemask = nullptr;       // [n_blocks] offsets met by any of the block's outputs
     // Optional (ts_kmap_sort_rows): output rows ordered by offset bitmask, so that the rows of a
     // tile of the output-stationary kernel share their offsets.  NULL = natural row order.
     int64_t n_tiles = 0;                  // ceil(n_out / kTileRows)

@@ -39,19 +39,29 @@ namespace {
 
 constexpr int kThreads = 256;
 
-// status words written by the kernels and read back once per build
+// Status words of a build.  They live in pinned host memory: the kernels report there directly (plain
+// system-scope stores, on bad input or once per offset), and the host watches the words instead of waiting
+// for a copy and a stream synchronisation, which cost a small build more than its kernels.
 enum {
     ST_RANGE = 0,       // a coordinate was outside the packable range
     ST_DUP = 1,         // two input rows held the same coordinate
     ST_DCOUNT = 2,      // distinct offset bitmasks seen (ts_kmap_sort_rows)
     ST_OVERFLOW = 3,    // the bitmask table could not hold them all
-    ST_TOTALS = 8,      // [32] per-offset map sizes
+    ST_SEARCHED = 4,    // set once every kernel that raises ST_RANGE or ST_DUP has finished
+    ST_TOTALS = 8,      // [32] per-offset map sizes (-1: not there yet)
     ST_WORDS = 40
 };
 
-// Error flags are raised with a plain store of 1: every writer stores the same value, and the word may
-// live in pinned host memory (a build nobody waits for reports straight to the host, without a copy).
-__device__ __forceinline__ void raise_flag(int *status, int which) { *reinterpret_cast<volatile int *>(&status[which]) = 1; }
+// A word the host reads.  Every writer of a flag stores the same value.
+__device__ __forceinline__ void tell_host(int *status, int which, int value) {
+    __hip_atomic_store(&status[which], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void raise_flag(int *status, int which) { tell_host(status, which, 1); }
+
+__device__ __forceinline__ bool coord_ok(int4 c) {
+    return c.x >= 0 && c.x <= TS_BATCH_MAX && c.y >= TS_COORD_MIN && c.y <= TS_COORD_MAX &&
+           c.z >= TS_COORD_MIN && c.z <= TS_COORD_MAX && c.w >= TS_COORD_MIN && c.w <= TS_COORD_MAX;
+}
 
 // ---- coordinate hash table ------------------------------------------------------------------------
 // Open addressing over two arrays: 64-bit keys (what lookups read) and 32-bit values (read on a
@@ -129,17 +139,6 @@ __device__ __forceinline__ void table_insert(const Table &t, uint64_t key, int32
     }
 }
 
-// First slot holding `want`'s value, or -1: a miss ends at the first empty slot.
-__device__ __forceinline__ int32_t table_find(const Table &t, uint64_t want) {
-    uint32_t slot = home_slot(want, t.shift);
-    for (;;) {
-        const uint64_t found = slot_key(t, slot);
-        if (found == want) return slot_val(t, slot);
-        if (found == kEmptyKey) return -1;
-        slot = next_slot(slot, t.mask);
-    }
-}
-
 // ---- coordinate grid ------------------------------------------------------------------------------------
 // The collision-free table of Sec. 4.4 (`grid`): one int32 cell per coordinate of a box, holding the
 // row of the point there or -1.  An insertion is one store, a lookup one load, whatever the
@@ -176,6 +175,54 @@ __device__ __forceinline__ int32_t table_find(const Grid &g, uint64_t want) {
     return cell < 0 ? -1 : g.vals[cell];
 }
 
+// ---- block table -----------------------------------------------------------------------------------------
+// What 3x3x3 stride-1 builds search: one entry per occupied block of 4x4x4 cells - its key and a 64-bit
+// occupancy mask, 16 bytes that one load fetches - and beside it 64 row numbers, valid where the mask says so.
+// A point's 27 neighbours lie in at most 8 blocks (3.4 on average), so a whole neighbourhood costs that many
+// lookups instead of 26, an absent neighbour costs a bit test, and a LiDAR-like scene of 153 k points has 28 k
+// entries: they stay in the caches where a table of points does not.  Nothing but the entries is cleared.
+struct BlockTable {
+    uint64_t *ent;     // [capacity][2]: block key (kEmptyKey = free), occupancy mask
+    int32_t *rows;     // [capacity][64]
+    uint32_t mask;     // capacity - 1 (capacity: power of two, at least 1.5 per point, >= 1024)
+    int shift;         // 64 - log2(capacity)
+};
+constexpr uint64_t kCellBits = 3ull | (3ull << kFieldBits) | (3ull << (2 * kFieldBits));
+
+__device__ __forceinline__ uint32_t block_home(uint64_t bkey, int shift) { return (uint32_t)((bkey * 0x9E3779B97F4A7C15ull) >> shift); }
+__device__ __forceinline__ uint32_t cell_of(uint64_t key) {
+    return ((uint32_t)key & 3u) | (((uint32_t)(key >> kFieldBits) & 3u) << 2) | (((uint32_t)(key >> (2 * kFieldBits)) & 3u) << 4);
+}
+
+// Stride-1 front end: pack and insert.  Two dependent atomics per point (the block's key, its mask); the mask
+// returned by the second says whether the cell was taken, which is how equal points are found.
+__global__ void __launch_bounds__(kThreads) k_block_insert(const int4 *__restrict__ coords, int64_t n, uint64_t *__restrict__ keys,
+                                                           BlockTable t, int *status) {
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const int4 c = coords[i];
+    if (!coord_ok(c)) {
+        raise_flag(status, ST_RANGE);
+        keys[i] = kEmptyKey;
+        return;
+    }
+    const uint64_t key = pack_key(c.x, c.y, c.z, c.w), bkey = key & ~kCellBits;
+    keys[i] = key;
+    uint32_t slot = block_home(bkey, t.shift);
+    for (;;) {   // the table holds at most one block per point and has half as many slots again: a free one exists
+        uint64_t found = t.ent[2 * (uint64_t)slot];   // a key never changes once set; a stale "free" is decided by the swap
+        if (found == kEmptyKey)
+            found = atomicCAS(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot]), (unsigned long long)kEmptyKey,
+                              (unsigned long long)bkey);
+        if (found == kEmptyKey || found == bkey) break;
+        slot = (slot + 1) & t.mask;
+    }
+    const uint32_t cell = cell_of(key);
+    const unsigned long long bit = 1ull << cell;
+    t.rows[(uint64_t)slot * 64 + cell] = (int32_t)i;
+    if (atomicOr(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot + 1]), bit) & bit) raise_flag(status, ST_DUP);
+}
+
 // Takes the points out again: the cells of `keys` go back to -1.
 __global__ void k_grid_erase(const uint64_t *keys, int64_t n, Grid g) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -198,10 +245,6 @@ struct Bound {
     int32_t hi[3];
 };
 
-__device__ __forceinline__ bool coord_ok(int4 c) {
-    return c.x >= 0 && c.x <= TS_BATCH_MAX && c.y >= TS_COORD_MIN && c.y <= TS_COORD_MAX &&
-           c.z >= TS_COORD_MIN && c.z <= TS_COORD_MAX && c.w >= TS_COORD_MIN && c.w <= TS_COORD_MAX;
-}
 
 __host__ __device__ constexpr int offset_component(int K, int n, int axis) {
     const int r = (K - 1) / 2;
@@ -218,17 +261,19 @@ __host__ __device__ __forceinline__ int floor_div(int a, int s) { return a >= 0 
 // ---- one launch for every buffer that must start at a known value -----------------------------------
 struct FillSeg {
     uint4 *p;
-    uint64_t n_vec;     // 16-byte vectors
-    uint32_t value;     // replicated into every 32-bit word
+    uint64_t n_vec;        // 16-byte vectors
+    uint32_t value, high;  // the 32-bit words of the first and of the second half of every vector
 };
 struct FillArgs {
     FillSeg seg[8];
     int n = 0;
-    void add(void *p, size_t bytes, uint32_t value) {
+    void add(void *p, size_t bytes, uint32_t value) { add_pairs(p, bytes, value, value); }
+    void add_pairs(void *p, size_t bytes, uint32_t value, uint32_t high) {
         if (bytes == 0) return;
         seg[n].p = static_cast<uint4 *>(p);
         seg[n].n_vec = (bytes + 15) / 16;
         seg[n].value = value;
+        seg[n].high = high;
         ++n;
     }
 };
@@ -236,8 +281,8 @@ struct FillArgs {
 __global__ void k_fill(FillArgs a) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (int s = 0; s < a.n; ++s) {
-        const uint32_t v = a.seg[s].value;
-        const uint4 vv = make_uint4(v, v, v, v);
+        const uint32_t v = a.seg[s].value, h = a.seg[s].high;
+        const uint4 vv = make_uint4(v, v, h, h);
         for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < a.seg[s].n_vec; i += stride)
             a.seg[s].p[i] = vv;
     }
@@ -473,6 +518,109 @@ __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict_
     if (lane == 0 && block64 < n_blocks) wavemask[block64] = (uint32_t)any;
 }
 
+// Map search for stride 1, K = 3 (Alg. 1) through the block table: a thread per point.  All block lookups of
+// a thread are in flight together, then all row numbers of its neighbours; rows leave the workgroup through
+// LDS as whole cache lines, with the centre entry and the offset bitmask, and the presence bitmaps of 64
+// outputs come out of the same pass.  What it replaces - a lane per (point, offset below the centre) probing a
+// table of points, mirrored 4-byte stores, and a second pass over the rows - took 17.4 + 9 us for 153 k points.
+__global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__restrict__ keys, int64_t n, BlockTable t,
+                                                           int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
+                                                           int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
+                                                           int64_t n_blocks, int *status) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) tell_host(status, ST_SEARCHED, 1);   // the insertion kernel came before
+    constexpr int K3 = 27, STRIDE = 32, WORDS = 28, PITCH = 29;   // an odd pitch: a thread's writes of its row are conflict-free
+    __shared__ union {
+        struct {
+            uint64_t mask[8][kThreads];
+            uint32_t slot[8][kThreads];
+        } found;                                                  // per octant and thread: the block's mask and slot
+        int32_t rows[kThreads * PITCH];
+    } lds;
+    const int tid = threadIdx.x;
+    const int64_t k = (int64_t)blockIdx.x * kThreads + tid;
+    const uint64_t key = k < n ? keys[k] : kEmptyKey;
+    const bool ok = key != kEmptyKey;
+    const uint64_t bkey = key & ~kCellBits;
+    const uint32_t c[3] = {(uint32_t)(key >> (2 * kFieldBits)) & 3u, (uint32_t)(key >> kFieldBits) & 3u, (uint32_t)key & 3u};
+    // octant o = (ox, oy, oz): the point's own block, or along an axis the block on the side of the nearer face
+    // (a cell inside the block along that axis needs no second block there)
+    int64_t step[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) step[a] = (int64_t)(c[a] == 0 ? -4 : 4) << ((2 - a) * kFieldBits);
+    const uint32_t edge = (c[0] == 0 || c[0] == 3 ? 4u : 0u) | (c[1] == 0 || c[1] == 3 ? 2u : 0u) | (c[2] == 0 || c[2] == 3 ? 1u : 0u);
+    uint32_t slot[8];
+    ulonglong2 got[8];
+    uint32_t pending = 0;
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        if (ok && (o & ~edge) == 0) {
+            pending |= 1u << o;
+            slot[o] = block_home(bkey + (o & 4 ? step[0] : 0) + (o & 2 ? step[1] : 0) + (o & 1 ? step[2] : 0), t.shift);
+            got[o] = reinterpret_cast<const ulonglong2 *>(t.ent)[slot[o]];
+        }
+    }
+    uint32_t present = 0;
+    for (;;) {
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            if ((pending >> o) & 1u) {
+                const uint64_t want = bkey + (o & 4 ? step[0] : 0) + (o & 2 ? step[1] : 0) + (o & 1 ? step[2] : 0);
+                if (got[o].x == want) present |= 1u << o;
+                if (got[o].x == want || got[o].x == kEmptyKey) pending &= ~(1u << o);
+            }
+        }
+        if (__ballot(pending != 0) == 0) break;
+#pragma unroll
+        for (int o = 0; o < 8; ++o) {
+            if ((pending >> o) & 1u) {
+                slot[o] = (slot[o] + 1) & t.mask;
+                got[o] = reinterpret_cast<const ulonglong2 *>(t.ent)[slot[o]];
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+        lds.found.mask[o][tid] = (present >> o) & 1u ? (uint64_t)got[o].y : 0ull;
+        lds.found.slot[o][tid] = slot[o];
+    }
+    // (each thread reads back only what it wrote: indexed by an octant that depends on the lane)
+    uint32_t mask = ok ? 1u << (K3 / 2) : 0u;
+    int32_t j[K3];
+#pragma unroll
+    for (int q = 0; q < K3; ++q) {
+        j[q] = -1;
+        if (q == K3 / 2) continue;
+        const int d[3] = {q / 9 - 1, (q / 3) % 3 - 1, q % 3 - 1};
+        uint32_t o = 0, cell = 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const bool out = (d[a] < 0 && c[a] == 0) || (d[a] > 0 && c[a] == 3);
+            o |= out ? 4u >> a : 0u;
+            cell |= ((c[a] + (uint32_t)d[a]) & 3u) << (2 * (2 - a));
+        }
+        if (ok && ((lds.found.mask[o][tid] >> cell) & 1ull)) {
+            j[q] = t.rows[(uint64_t)lds.found.slot[o][tid] * 64 + cell];
+            mask |= 1u << q;
+        }
+    }
+    if (ok) j[K3 / 2] = (int32_t)k;
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < K3; ++q) lds.rows[tid * PITCH + q] = j[q];
+    lds.rows[tid * PITCH + K3] = (int32_t)mask;
+    __syncthreads();
+    const int64_t first = (int64_t)blockIdx.x * kThreads;
+#pragma unroll
+    for (int v = 0; v < WORDS / 4; ++v) {
+        const int at = v * kThreads + tid, row = at / (WORDS / 4), ch = at % (WORDS / 4);
+        if (first + row < n) {
+            const int32_t *src = &lds.rows[row * PITCH + ch * 4];
+            *reinterpret_cast<int4 *>(nbr + (first + row) * STRIDE + ch * 4) = make_int4(src[0], src[1], src[2], src[3]);
+        }
+    }
+    finish_rows<K3>(mask, colbits, colcnt, wavemask, n_blocks);
+}
+
 // ts_kmap_sort_rows, step 1: register every row's bitmask in the mask table; slot_rank[k] = (table
 // slot, arrival rank among the rows of that mask).  Lanes of a wave holding the same mask share
 // one counter update: first the wave's classes of equal masks (registers only), then every class
@@ -636,16 +784,11 @@ __global__ void __launch_bounds__(kThreads, 3) k_probe(const uint64_t *__restric
     finish_rows<K3>(mask, colbits, colcnt, wavemask, n_blocks);
 }
 
-// Map search for stride 1, K = 3, one lane per (point i, offset n) with n below the centre.
-// A hit (j at p_i + delta_n) gives two entries: (j, i, n) in row i and, by symmetry (Sec. 4.2.1),
-// (i, j, K^3-1-n) in row j; rows start out all -1.  One lookup per lane: a long probe chain
-// delays one wave of 64 lookups, not a wave holding all 26 lookups of 64 points, and the many
-// waves in flight hide the memory round trips.  The 13 offsets of a point sit in neighbouring lanes
-// (16 lanes per point), so a point's own entries land in one cache line of the table: with a lane per
-// point and the offset in the grid's y, every hit was a 4-byte write into a line of its own, and the
-// kernel took 34 us instead of 22.
-template <class TableT>
-__global__ void k_probe_symmetric(const uint64_t *__restrict__ keys, int64_t n_pts, TableT t, int K,
+// Map search for stride 1, K = 3 through the coordinate grid, one lane per (point i, offset n) with n below the
+// centre.  A hit (j at p_i + delta_n) gives two entries: (j, i, n) in row i and, by symmetry (Sec. 4.2.1),
+// (i, j, K^3-1-n) in row j; rows start out all -1.  The 13 offsets of a point sit in neighbouring lanes
+// (16 lanes per point), so a point's own entries land in one cache line of the table.
+__global__ void k_probe_symmetric(const uint64_t *__restrict__ keys, int64_t n_pts, Grid t, int K,
                                   int32_t *__restrict__ nbr, int stride) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t i = g >> 4;
@@ -662,7 +805,7 @@ __global__ void k_probe_symmetric(const uint64_t *__restrict__ keys, int64_t n_p
 }
 
 // Row pass over a neighbour table whose hits have been written into rows that started out as -1
-// (the symmetric probe; the transposition of a forward map): a thread per output row reads its
+// (the symmetric probe of a grid; the transposition of a forward map): a thread per output row reads its
 // row, sets the centre entry where the map has one (stride 1: output k is input k) and the row's
 // offset bitmask, and does what every search kernel does once the bitmask is known.
 template <int K3, bool HAS_CENTRE>
@@ -854,13 +997,12 @@ __global__ void __launch_bounds__(kThreads) k_rank_scatter(const uint64_t *__res
     }
 }
 
-// Block n: exclusive scan of colcnt[n][*] -> colbase[n][b] = pairs of offset n in the 64-row
+// Block n: exclusive scan in place of the counts col[n][*] -> col[n][b] = pairs of offset n in the 64-row
 // blocks before b (relative to the start of the offset's list), and the offset's total (the host
 // turns the totals into offs[], the start of each offset's list, and hands them to later kernels
 // by value).
 constexpr int kScanThreads = 1024, kScanItems = 4;
-__global__ void __launch_bounds__(kScanThreads) k_scan(const int32_t *__restrict__ colcnt, int32_t *__restrict__ colbase,
-                                                       int64_t n_blocks, int *__restrict__ status, int K3,
+__global__ void __launch_bounds__(kScanThreads) k_scan(int32_t *__restrict__ col, int64_t n_blocks, int *status, int K3,
                                                        const uint32_t *__restrict__ wavemask, int64_t n_tiles,
                                                        int32_t *__restrict__ tile_order) {
     if ((int)blockIdx.x == K3) {
@@ -888,27 +1030,26 @@ __global__ void __launch_bounds__(kScanThreads) k_scan(const int32_t *__restrict
         return;
     }
     const int n = blockIdx.x;
-    const int32_t *src = colcnt + (int64_t)n * n_blocks;
-    int32_t *dst = colbase + (int64_t)n * n_blocks;
+    int32_t *c = col + (int64_t)n * n_blocks;
     int run = 0;
     for (int64_t base = 0; base < n_blocks; base += kScanThreads * kScanItems) {
         const int64_t i0 = base + (int64_t)threadIdx.x * kScanItems;
         int v[kScanItems], sum = 0;
 #pragma unroll
         for (int e = 0; e < kScanItems; ++e) {
-            v[e] = i0 + e < n_blocks ? src[i0 + e] : 0;
+            v[e] = i0 + e < n_blocks ? c[i0 + e] : 0;
             sum += v[e];
         }
         int total;
         int at = run + block_exclusive_scan<kScanThreads>(sum, &total);
 #pragma unroll
         for (int e = 0; e < kScanItems; ++e) {
-            if (i0 + e < n_blocks) dst[i0 + e] = at;
+            if (i0 + e < n_blocks) c[i0 + e] = at;
             at += v[e];
         }
         run += total;
     }
-    if (threadIdx.x == 0) status[ST_TOTALS + n] = run;
+    if (threadIdx.x == 0) tell_host(status, ST_TOTALS + n, run);
 }
 
 // ts_kmap_sort_rows, step 2: the distinct bitmasks as a dense list of (sort key, rows), followed
@@ -1070,6 +1211,18 @@ int make_table(Temps &tmp, int64_t entries, Table *t, FillArgs *fill) {
     return TS_OK;
 }
 
+// Allocates the block table; the clearing of its entries (free key, empty mask) is added to `fill`.
+int make_block_table(Temps &tmp, int64_t points, BlockTable *t, FillArgs *fill) {
+    uint64_t cap = 1024;
+    while (2 * cap < (uint64_t)(3 * points)) cap <<= 1;
+    TS_TRY(tmp.get(&t->ent, 2 * cap));
+    TS_TRY(tmp.get(&t->rows, 64 * cap));
+    t->mask = (uint32_t)(cap - 1);
+    t->shift = 64 - __builtin_ctzll(cap);
+    fill->add_pairs(t->ent, cap * 16, 0xFFFFFFFFu, 0u);
+    return TS_OK;
+}
+
 // How a build was asked to run.
 struct BuildOpts {
     bool wait = true;
@@ -1159,55 +1312,111 @@ int make_mask_hash(Temps &tmp, MaskHash *mh, FillArgs *fill) {
     return TS_OK;
 }
 
-// Pinned landing places for the status words of builds whose caller did not wait
-// (ts_build_kmap_async), each with the event that says the copy has arrived.
+// The status words of a build, in pinned host memory (see ST_*).  A map that nobody has asked anything yet
+// keeps its slot; a slot whose map was freed first is handed out again once its build has reported.
 struct StatusSlot {
     int32_t *host = nullptr;
     int32_t *dev = nullptr;     // the same words as kernels address them
-    hipEvent_t ev = nullptr;
-    bool busy = false;          // a copy is in flight or has not been read yet
+    bool busy = false;          // a build reports, or will report, here
+    bool totals = false;        // ... the map sizes as well
+    int K3 = 0;
     const ts_kmap *owner = nullptr;   // NULL while busy: the map was freed before anyone asked
 };
-constexpr int kStatusSlots = 64;
-StatusSlot g_slots[kStatusSlots];
+constexpr int kSlotChunk = 64, kSlotChunks = 1024;   // slots come 64 to an allocation, 65536 at most
+StatusSlot *g_slots[kSlotChunks] = {nullptr};
 
-int slot_acquire() {
-    static int32_t *mem = nullptr;
-    if (!mem) {
-        if (hipHostMalloc(&mem, kStatusSlots * ST_WORDS * sizeof(int32_t), hipHostMallocDefault) != hipSuccess) {
-            (void)hipGetLastError();
-            mem = nullptr;
-            return -1;
+inline StatusSlot &slot_at(int i) { return g_slots[i / kSlotChunk][i % kSlotChunk]; }
+
+// Whether what the slot's build reports has arrived: the verdict on its input, or the sizes too.
+inline bool slot_landed(const StatusSlot &s, bool totals) {
+    const volatile int32_t *h = s.host;
+    if (!totals) return h[ST_SEARCHED] != 0 || (s.totals && slot_landed(s, true));   // sizes come after everything else
+    for (int n = 0; n < s.K3; ++n)
+        if (h[ST_TOTALS + n] < 0) return false;
+    return true;
+}
+
+inline void slot_reset(StatusSlot &s, int K3) {
+    std::memset(s.host, 0, ST_WORDS * sizeof(int32_t));
+    for (int n = 0; n < kMaxK3; ++n) s.host[ST_TOTALS + n] = -1;
+    s.K3 = K3;
+    s.totals = false;
+}
+
+// A free slot, its words reset; -1 with the error set.
+int slot_acquire(int K3) {
+    for (int ch = 0; ch < kSlotChunks; ++ch) {
+        if (!g_slots[ch]) {
+            int32_t *mem = nullptr;
+            void *dview = nullptr;
+            if (hipHostMalloc(&mem, kSlotChunk * ST_WORDS * sizeof(int32_t), hipHostMallocDefault) != hipSuccess ||
+                hipHostGetDevicePointer(&dview, mem, 0) != hipSuccess) {
+                (void)hipGetLastError();
+                if (mem) (void)hipHostFree(mem);
+                fail(TS_ERR_OOM, "no pinned memory for a build's status words");
+                return -1;
+            }
+            StatusSlot *sl = new (std::nothrow) StatusSlot[kSlotChunk];
+            if (!sl) {
+                (void)hipHostFree(mem);
+                fail(TS_ERR_OOM, "host allocation failed");
+                return -1;
+            }
+            for (int i = 0; i < kSlotChunk; ++i) {
+                sl[i].host = mem + i * ST_WORDS;
+                sl[i].dev = static_cast<int32_t *>(dview) + i * ST_WORDS;
+            }
+            g_slots[ch] = sl;
         }
-        void *dview = nullptr;
-        if (hipHostGetDevicePointer(&dview, mem, 0) != hipSuccess) {
-            (void)hipGetLastError();
-            dview = nullptr;
-        }
-        for (int i = 0; i < kStatusSlots; ++i) {
-            g_slots[i].host = mem + i * ST_WORDS;
-            g_slots[i].dev = dview ? static_cast<int32_t *>(dview) + i * ST_WORDS : nullptr;
+        for (int i = 0; i < kSlotChunk; ++i) {
+            StatusSlot &s = g_slots[ch][i];
+            if (s.busy && (s.owner || !slot_landed(s, s.totals))) continue;
+            slot_reset(s, K3);
+            s.busy = true;
+            s.owner = nullptr;
+            return ch * kSlotChunk + i;
         }
     }
-    for (int i = 0; i < kStatusSlots; ++i) {
-        StatusSlot &s = g_slots[i];
-        if (s.busy && !s.owner && hipEventQuery(s.ev) == hipSuccess) s.busy = false;   // orphan whose copy has landed
-        if (s.busy) continue;
-        if (!s.ev && hipEventCreateWithFlags(&s.ev, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            s.ev = nullptr;
-            return -1;
-        }
-        return i;
-    }
-    (void)hipGetLastError();   // hipEventQuery leaves hipErrorNotReady behind
+    fail(TS_ERR_OOM, "more than %d maps await their build's verdict", kSlotChunk * kSlotChunks);
     return -1;
 }
 
-// Status words on the host -> the map's sizes, or its error.
-int take_status(ts_kmap *m, const int32_t *h) {
+inline void slot_release(int i) {
+    slot_at(i).busy = false;
+    slot_at(i).owner = nullptr;
+}
+
+// Watches the slot's words.  The stream is asked now and then whether it has finished or failed, so that a
+// build that cannot report any more (an error of the device) ends the wait.
+int slot_wait(int i, bool totals) {
+    const StatusSlot &s = slot_at(i);
+    for (;;) {
+        for (int spin = 0; spin < 20000; ++spin) {
+            if (slot_landed(s, totals)) return TS_OK;
+            __builtin_ia32_pause();
+        }
+        const hipError_t e = hipStreamQuery(stream());
+        if (e == hipErrorNotReady) {
+            (void)hipGetLastError();
+            continue;
+        }
+        if (slot_landed(s, totals)) return TS_OK;
+        if (e != hipSuccess) return fail(TS_ERR_HIP, "waiting for a map build: %s", hipGetErrorString(e));
+        TS_HIP(hipDeviceSynchronize());   // another stream than the one the build ran on is current
+        if (slot_landed(s, totals)) return TS_OK;
+        return fail(TS_ERR_HIP, "a map build finished without reporting");
+    }
+}
+
+// Status words on the host -> the map's error, or that and its sizes.
+int take_verdict(ts_kmap *m, const int32_t *h) {
     if (h[ST_RANGE]) m->error = TS_ERR_COORD_RANGE;
     else if (h[ST_DUP]) m->error = TS_ERR_DUPLICATE_COORD;
+    return m->error;
+}
+
+int take_status(ts_kmap *m, const int32_t *h) {
+    take_verdict(m, h);
     m->offs[0] = 0;
     for (int n = 0; n < m->K3; ++n) m->offs[n + 1] = m->offs[n] + h[ST_TOTALS + n];
     for (int n = 0; n < m->K3; ++n) m->sizes[n] = m->offs[n + 1] - m->offs[n];
@@ -1244,7 +1453,7 @@ __global__ void __launch_bounds__(kThreads) k_identity_map(int32_t *__restrict__
 
 void destroy(ts_kmap *m) {
     if (!m) return;
-    if (m->pending_slot >= 0) g_slots[m->pending_slot].owner = nullptr;   // the slot frees itself when its copy has landed
+    if (m->pending_slot >= 0) slot_at(m->pending_slot).owner = nullptr;   // handed out again once the build has reported
     if (m->d_out_keys != m->d_in_keys) dev_free(m->d_out_keys);
     dev_free(m->d_in_keys);
     dev_free(m->d_nbr);
@@ -1255,6 +1464,7 @@ void destroy(ts_kmap *m) {
     dev_free(m->d_perm);
     dev_free(m->d_sched);
     dev_free(m->d_tile_order);
+    dev_free(m->d_wavemask);
     delete m;
 }
 
@@ -1269,104 +1479,72 @@ int sort_keys(Temps &tmp, uint64_t *in, uint64_t *out, size_t n) {
 }
 
 template <int MODE, int K>
-void launch_probe(const ts_kmap *m, const Searched &sd, int32_t *colcnt, uint32_t *wavemask) {
+void launch_probe(const ts_kmap *m, const Searched &sd) {
     if (sd.grid)
         TS_LAUNCH("k_probe_grid", (k_probe<MODE, K, Grid>), dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), m->d_out_keys,
-                  m->n_out, sd.g, m->s, m->d_nbr, m->d_colbits, colcnt, wavemask, m->n_blocks);
+                  m->n_out, sd.g, m->s, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks);
     else
         TS_LAUNCH("k_probe", (k_probe<MODE, K, Table>), dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), m->d_out_keys,
-                  m->n_out, sd.t, m->s, m->d_nbr, m->d_colbits, colcnt, wavemask, m->n_blocks);
+                  m->n_out, sd.t, m->s, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks);
 }
 
-// Map search and everything after it.  `table` holds the searched point set (the map's inputs);
-// m->d_out_keys the outputs; the clearing of the status words (and of the neighbour table where the
-// search writes hits only) has been enqueued.
-int deliver_status(ts_kmap *m, int *d_status, bool wait);
-int search_and_finish(ts_kmap *m, Temps &tmp, const Searched &table, int *d_status, bool wait, int early_slot = -1) {
-    hipStream_t st = stream();
-    const int K3 = m->K3, K = m->K;
-    const int64_t n_out = m->n_out;
-    int32_t *colcnt;
-    uint32_t *wavemask;
-    TS_TRY(tmp.get(&colcnt, (size_t)K3 * m->n_blocks));
-    TS_TRY(tmp.get(&wavemask, (size_t)m->n_blocks));
-    const int mode = m->s == 1 ? MODE_SUB : (m->transposed ? MODE_TR : MODE_FWD);
-    // a grid gets its points taken out as soon as the search has been enqueued
-    auto after_search = [&]() {
-        if (!table.grid) return;
+void launch_rows(const ts_kmap *m) {
+    const dim3 grid(blocks_for(m->n_out, kThreads)), block(kThreads);
+#define TS_ROWS(K3, CENTRE) TS_LAUNCH("k_rows", (k_rows<K3, CENTRE>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks)
+    if (m->K3 == 27 && m->centre >= 0) TS_ROWS(27, true);
+    else if (m->K3 == 27) TS_ROWS(27, false);
+    else if (m->K3 == 8) TS_ROWS(8, false);
+    else TS_ROWS(1, false);
+#undef TS_ROWS
+}
+
+// Counts of the 64-row blocks -> ranks, sizes (into the status words at `status`) and tile order.
+void launch_scan(const ts_kmap *m, int32_t *status) {
+    TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), m->d_colbase, m->n_blocks, status, m->K3, m->d_wavemask,
+              m->n_tiles, m->d_tile_order);
+}
+
+// Map search through the hash table or the coordinate grid.  `table` holds the searched point set (the map's
+// inputs), m->d_out_keys the outputs.  Leaves the neighbour rows and the presence bitmaps and counts.
+int search(ts_kmap *m, const Searched &table) {
+    const int K = m->K, mode = m->s == 1 ? MODE_SUB : (m->transposed ? MODE_TR : MODE_FWD);
+    const bool symmetric = mode == MODE_SUB && K == 3;   // only the grid: tables of points search k_block_search's way
+    if (mode == MODE_SUB && K == 1) launch_probe<MODE_SUB, 1>(m, table);
+    else if (symmetric)
+        TS_LAUNCH("k_probe_symmetric_grid", k_probe_symmetric, dim3(blocks_for(m->n_out * 16, kThreads)), dim3(kThreads), m->d_out_keys,
+                  m->n_out, table.g, K, m->d_nbr, m->stride);
+    else if (mode == MODE_FWD && K == 1) launch_probe<MODE_FWD, 1>(m, table);
+    else if (mode == MODE_TR && K == 1) launch_probe<MODE_TR, 1>(m, table);
+    else if (mode == MODE_FWD && K == 2) launch_probe<MODE_FWD, 2>(m, table);
+    else if (mode == MODE_FWD && K == 3) launch_probe<MODE_FWD, 3>(m, table);
+    else if (mode == MODE_TR && K == 2) launch_probe<MODE_TR, 2>(m, table);
+    else if (mode == MODE_TR && K == 3) launch_probe<MODE_TR, 3>(m, table);
+    else return fail(TS_ERR_UNSUPPORTED, "no map search for kernel_size %d, stride %d", K, m->s);
+    if (table.grid) {   // the grid gets its points taken out as soon as the search has been enqueued
         TS_LAUNCH("k_grid_erase", k_grid_erase, dim3(blocks_for(m->n_in, kThreads)), dim3(kThreads), m->d_in_keys, m->n_in, table.g);
         g_grid_dirty = false;
-    };
-    if (mode == MODE_SUB && K == 1) launch_probe<MODE_SUB, 1>(m, table, colcnt, wavemask);
-    else if (mode == MODE_SUB && K == 3) {
-        // 16 lanes per point (13 at work): a point's own entries land in one cache line of the table
-        const dim3 lanes(blocks_for(n_out * 16, kThreads));
-        if (table.grid)
-            TS_LAUNCH("k_probe_symmetric_grid", k_probe_symmetric<Grid>, lanes, dim3(kThreads), m->d_out_keys, n_out, table.g, K,
-                      m->d_nbr, m->stride);
-        else
-            TS_LAUNCH("k_probe_symmetric", k_probe_symmetric<Table>, lanes, dim3(kThreads), m->d_out_keys, n_out, table.t, K,
-                      m->d_nbr, m->stride);
-        after_search();
-        if (!wait) {
-            // A caller that does not wait gets the map with its search done: what the fused layer
-            // kernel reads.  The row pass and the scan (bitmask words, rank bitmaps, sizes, tile order)
-            // run when something first needs them (ts::resolve).  Error flags are known already.
-            // (early_slot: the kernels raised their flags in the slot's pinned words themselves.)
-            const int slot = early_slot >= 0 ? early_slot : slot_acquire();
-            if (slot >= 0) {
-                StatusSlot &sl = g_slots[slot];
-                if (early_slot < 0) TS_HIP(hipMemcpyAsync(sl.host, d_status, ST_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-                TS_HIP(hipEventRecord(sl.ev, st));
-                sl.busy = true;
-                sl.owner = m;
-                m->pending_slot = slot;
-                m->rows_done = false;
-                TS_HIP(hipGetLastError());
-                return TS_OK;
-            }
-        }
-        TS_LAUNCH("k_rows", (k_rows<27, true>), dim3(blocks_for(n_out, kThreads)), dim3(kThreads), m->d_nbr, m->d_out_keys, n_out,
-                  m->d_colbits, colcnt, wavemask, m->n_blocks);
     }
-    else if (mode == MODE_FWD && K == 1) launch_probe<MODE_FWD, 1>(m, table, colcnt, wavemask);
-    else if (mode == MODE_TR && K == 1) launch_probe<MODE_TR, 1>(m, table, colcnt, wavemask);
-    else if (mode == MODE_FWD && K == 2) launch_probe<MODE_FWD, 2>(m, table, colcnt, wavemask);
-    else if (mode == MODE_FWD && K == 3) launch_probe<MODE_FWD, 3>(m, table, colcnt, wavemask);
-    else if (mode == MODE_TR && K == 2) launch_probe<MODE_TR, 2>(m, table, colcnt, wavemask);
-    else if (mode == MODE_TR && K == 3) launch_probe<MODE_TR, 3>(m, table, colcnt, wavemask);
-    else return fail(TS_ERR_UNSUPPORTED, "no map search for kernel_size %d, stride %d", K, m->s);
-    if (!(mode == MODE_SUB && K == 3)) after_search();
-
-    TS_LAUNCH("k_scan", k_scan, dim3(K3 + 1), dim3(kScanThreads), colcnt, m->d_colbase, m->n_blocks, d_status, K3, wavemask,
-              m->n_tiles, m->d_tile_order);
-    return deliver_status(m, d_status, wait);
+    if (symmetric) launch_rows(m);
+    return TS_OK;
 }
 
-// The one host round trip at the end of a build: error flags and map sizes.  A caller that does not wait
-// gets them when it first asks (ts::resolve); the copy lands in a pinned slot of its own meanwhile.
-int deliver_status(ts_kmap *m, int *d_status, bool wait) {
-    hipStream_t st = stream();
-    const int slot = wait ? -1 : slot_acquire();
-    if (slot >= 0) {
-        StatusSlot &sl = g_slots[slot];
-        TS_HIP(hipMemcpyAsync(sl.host, d_status, ST_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        TS_HIP(hipEventRecord(sl.ev, st));
-        sl.busy = true;
-        sl.owner = m;
-        m->pending_slot = slot;
-    } else {
-        int32_t *h = static_cast<int32_t *>(host_staging(ST_WORDS * sizeof(int32_t)));
-        if (!h) return last_fail_code();
-        TS_HIP(hipMemcpyAsync(h, d_status, ST_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        TS_HIP(hipStreamSynchronize(st));
-        if (take_status(m, h) != TS_OK) return report(m);
+// End of a build whose rows and presence bitmaps have been enqueued: the scan, and a wait for the sizes or
+// none.  scan_later: the scan is put off until something needs it (ts_kmap_prepare, ts::resolve); the kernels
+// of such a build report ST_SEARCHED.
+int finish(ts_kmap *m, int slot, bool wait, bool scan_later = false) {
+    StatusSlot &sl = slot_at(slot);
+    if (!scan_later || wait) {
+        launch_scan(m, sl.dev);
+        sl.totals = true;
+        m->scan_enqueued = true;
     }
-
+    m->scan_done = false;
+    sl.owner = m;
+    m->pending_slot = slot;
     TS_HIP(hipGetLastError());
     // temporaries go back to the pool when the caller's Temps dies; later work on the same
-    // stream is ordered after the kernels above, so reuse is safe without another wait
-    return TS_OK;
+    // stream is ordered after the kernels above, so reuse is safe without a wait
+    return wait ? resolve(m) : TS_OK;
 }
 
 // Orders the output rows by offset bitmask (see the head of this file).
@@ -1438,7 +1616,7 @@ int sort_rows(ts_kmap *m) {
 }
 
 // Allocations of the map that depend on n_out only.
-int alloc_outputs(ts_kmap *m, FillArgs *fill, bool rows_cleared_later = false) {
+int alloc_outputs(ts_kmap *m, FillArgs *fill) {
     const int K3 = m->K3;
     m->stride = nbr_stride(K3);
     m->n_blocks = (m->n_out + 63) / 64;
@@ -1447,15 +1625,13 @@ int alloc_outputs(ts_kmap *m, FillArgs *fill, bool rows_cleared_later = false) {
     TS_TRY(alloc_n(&m->d_colbits, (size_t)K3 * m->n_blocks));
     TS_TRY(alloc_n(&m->d_colbase, (size_t)K3 * m->n_blocks));
     TS_TRY(alloc_n(&m->d_tile_order, (size_t)m->n_tiles));
+    TS_TRY(alloc_n(&m->d_wavemask, (size_t)m->n_blocks));
     if (!m->d_sched) {
         TS_TRY(alloc_n(&m->d_sched, (size_t)kMaxSchedSlices * kSchedWords));
         fill->add(m->d_sched, (size_t)kMaxSchedSlices * kSchedWords * sizeof(int32_t), 0u);
     }
-    if (m->s == 1 && K3 == 27 && !rows_cleared_later) fill->add(m->d_nbr, (size_t)m->n_out * m->stride * sizeof(int32_t), 0xFFFFFFFFu);   // the symmetric probe writes hits only
     return TS_OK;
 }
-
-int rows_and_scan(ts_kmap *m, Temps &tmp, int32_t *colcnt, int *d_status);   // defined below the build
 
 int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kmap *m, const BuildOpts &asked) {
     BuildOpts opt = asked;   // a build that measures its bounding box may turn the grid on
@@ -1471,10 +1647,21 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
     m->centre = (s == 1) ? (K3 - 1) / 2 : -1;
     if (N == 0) return TS_OK;
 
-    int *d_status;
-    TS_TRY(tmp.get(&d_status, ST_WORDS));
+    // where the build reports; a build that ends early gives the slot back once nothing can write to it any more
+    struct SlotGuard {
+        int slot;
+        bool committed = false;
+        ~SlotGuard() {
+            if (slot >= 0 && !committed) {
+                (void)hipStreamSynchronize(stream());
+                slot_release(slot);
+            }
+        }
+    } guard{slot_acquire(K3)};
+    if (guard.slot < 0) return last_fail_code();
+    const int slot = guard.slot;
+    int32_t *d_status = slot_at(slot).dev;
     FillArgs fill;
-    fill.add(d_status, ST_WORDS * sizeof(int), 0u);
 
     uint64_t *given;   // keys of the caller's coordinates
     TS_TRY(alloc_n(&given, (size_t)N));
@@ -1482,29 +1669,28 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
 
     Searched table;
     const dim3 per_point(blocks_for(N, kThreads)), block(kThreads);
-    int early_slot = -1;
     if (s == 1) {
         m->n_in = m->n_out = N;
         m->d_out_keys = given;
-        if (!wait && K == 3) {
-            // Nobody waits for this build: its error flags go straight into pinned host words (plain
-            // stores, raised on bad input only), which saves the copy at the end of the build.
-            const int slot = slot_acquire();
-            if (slot >= 0 && g_slots[slot].dev) {
-                std::memset(g_slots[slot].host, 0, ST_WORDS * sizeof(int32_t));
-                d_status = g_slots[slot].dev;
-                early_slot = slot;
-            }
+        TS_TRY(alloc_outputs(m, &fill));
+        const int4 *c4 = reinterpret_cast<const int4 *>(coords);
+        if (K == 3 && !opt.grid) {
+            BlockTable bt;
+            TS_TRY(make_block_table(tmp, N, &bt, &fill));
+            TS_TRY(launch_fill(fill));
+            TS_LAUNCH("k_block_insert", k_block_insert, per_point, block, c4, N, given, bt, d_status);
+            TS_LAUNCH("k_block_search", k_block_search, per_point, block, given, N, bt, m->d_nbr, m->d_colbits, m->d_colbase,
+                      m->d_wavemask, m->n_blocks, d_status);
+            guard.committed = true;
+            return finish(m, slot, wait, true);
         }
-        const bool rows_here = K == 3;   // the insertion kernel clears the neighbour rows of a 3x3x3 map
-        TS_TRY(alloc_outputs(m, &fill, rows_here));
         TS_TRY(make_searched(tmp, opt, N, opt.box.lo, opt.box.hi, &table, &fill));
         TS_TRY(launch_fill(fill));
-        int4 *rows = rows_here ? reinterpret_cast<int4 *>(m->d_nbr) : nullptr;
+        int4 *rows = K == 3 ? reinterpret_cast<int4 *>(m->d_nbr) : nullptr;   // the symmetric probe of the grid writes hits only
         if (table.grid)
-            TS_LAUNCH("k_pack_insert_grid", k_pack_insert<Grid>, per_point, block, reinterpret_cast<const int4 *>(coords), N, given, table.g, d_status, opt.box, rows);
+            TS_LAUNCH("k_pack_insert_grid", k_pack_insert<Grid>, per_point, block, c4, N, given, table.g, d_status, opt.box, rows);
         else
-            TS_LAUNCH("k_pack_insert", k_pack_insert<Table>, per_point, block, reinterpret_cast<const int4 *>(coords), N, given, table.t, d_status, opt.box, rows);
+            TS_LAUNCH("k_pack_insert", k_pack_insert<Table>, per_point, block, c4, N, given, table.t, d_status, opt.box, rows);
     } else {
         // coarse set: the distinct admissible candidates in ascending order (Alg. 3)
         const int A = (K + s - 1) / s, slots = A * A * A;
@@ -1635,7 +1821,6 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             // No candidate passed the modular check (or every coordinate was out of range): a map
             // without pairs.  The inputs are still checked for duplicates and range.
             Table t0;
-            int32_t *colcnt = nullptr;
             TS_TRY(make_table(tmp, N, &t0, &fill));
             if (!transposed) {
                 m->n_in = N;
@@ -1647,18 +1832,16 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
                 m->d_out_keys = given;
                 TS_TRY(alloc_outputs(m, &fill));
                 fill.add(m->d_nbr, (size_t)N * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
-                TS_TRY(tmp.get(&colcnt, (size_t)K3 * m->n_blocks));
             }
             TS_TRY(launch_fill(fill));
             TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, t0, d_status);
-            if (transposed) TS_TRY(rows_and_scan(m, tmp, colcnt, d_status));
-            int32_t *hs = static_cast<int32_t *>(host_staging(ST_WORDS * sizeof(int32_t)));
-            if (!hs) return last_fail_code();
-            TS_HIP(hipMemcpyAsync(hs, d_status, ST_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
+            if (transposed) {
+                launch_rows(m);
+                guard.committed = true;
+                return finish(m, slot, true);
+            }
             TS_HIP(hipStreamSynchronize(st));
-            if (hs[ST_RANGE]) m->error = TS_ERR_COORD_RANGE;
-            else if (hs[ST_DUP]) m->error = TS_ERR_DUPLICATE_COORD;
-            return report(m);
+            return take_verdict(m, slot_at(slot).host) == TS_OK ? TS_OK : report(m);
         }
         uint64_t *coarse;
         TS_TRY(alloc_n(&coarse, (size_t)n_coarse));
@@ -1667,7 +1850,6 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             // No search: an input's admissible candidates are outputs, and an output's row number is the rank
             // of its cell among the marked ones (k_rank_scatter).  Neither hash table nor coordinate grid.
             const dim3 per_cand(blocks_for(N, kThreads), slots);
-            int32_t *colcnt;
             if (!transposed) {
                 m->n_in = N;
                 m->n_out = n_coarse;
@@ -1680,7 +1862,6 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             }
             TS_TRY(alloc_outputs(m, &fill));
             if (!early) fill.add(m->d_nbr, (size_t)m->n_out * m->stride * sizeof(int32_t), 0xFFFFFFFFu);   // (early: cleared by the first launch)
-            TS_TRY(tmp.get(&colcnt, (size_t)K3 * m->n_blocks));
             if (!transposed && !opt.bound.on) {
                 TS_TRY(launch_fill(fill));
                 TS_LAUNCH("k_rank_scatter", k_rank_scatter<false>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
@@ -1712,8 +1893,9 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
                     m->out_box_hi[a] = cbox.lo[a] + (int32_t)cbox.ext[a] - 1;
                 }
             }
-            TS_TRY(rows_and_scan(m, tmp, colcnt, d_status));
-            return deliver_status(m, d_status, wait);
+            launch_rows(m);
+            guard.committed = true;
+            return finish(m, slot, wait);
         }
         if (!transposed) {
             m->n_in = N;
@@ -1741,27 +1923,14 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
         }
     }
-    TS_HIP(hipGetLastError());
-    return search_and_finish(m, tmp, table, d_status, wait, early_slot);
+    TS_TRY(search(m, table));
+    guard.committed = true;
+    return finish(m, slot, wait);
 }
 
 }  // namespace
 
 namespace {
-
-// Row pass (bitmasks, presence bitmaps) and scan over a neighbour table that is already filled in.
-int rows_and_scan(ts_kmap *m, Temps &tmp, int32_t *colcnt, int *d_status) {
-    uint32_t *wavemask;
-    TS_TRY(tmp.get(&wavemask, (size_t)m->n_blocks));
-    const dim3 grid(blocks_for(m->n_out, kThreads)), block(kThreads);
-    if (m->K3 == 27) TS_LAUNCH("k_rows", (k_rows<27, false>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, m->d_colbits, colcnt, wavemask, m->n_blocks);
-    else if (m->K3 == 8) TS_LAUNCH("k_rows", (k_rows<8, false>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, m->d_colbits, colcnt, wavemask, m->n_blocks);
-    else TS_LAUNCH("k_rows", (k_rows<1, false>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, m->d_colbits, colcnt, wavemask, m->n_blocks);
-    TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), colcnt, m->d_colbase, m->n_blocks, d_status, m->K3, wavemask,
-              m->n_tiles, m->d_tile_order);
-    TS_HIP(hipGetLastError());
-    return TS_OK;
-}
 
 // The transposed map of a forward strided map, derived from its neighbour table: no search, and no
 // host round trip either, because the sizes are those of the forward map.
@@ -1785,13 +1954,10 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
     if (m->n_in > 0) TS_HIP(hipMemcpyAsync(m->d_in_keys, f->d_out_keys, (size_t)m->n_in * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
     TS_HIP(hipMemcpyAsync(m->d_out_keys, f->d_in_keys, (size_t)m->n_out * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
     FillArgs fill;
-    int *d_status;
-    int32_t *colcnt;
-    TS_TRY(tmp.get(&d_status, ST_WORDS));
-    fill.add(d_status, ST_WORDS * sizeof(int), 0u);
+    int32_t *sizes;   // written by the scan, known already
+    TS_TRY(tmp.get(&sizes, ST_WORDS));
     TS_TRY(alloc_outputs(m, &fill));
     fill.add(m->d_nbr, (size_t)m->n_out * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
-    TS_TRY(tmp.get(&colcnt, (size_t)K3 * m->n_blocks));
     TS_TRY(launch_fill(fill));
     if (f->n_out > 0) {
         const dim3 gf(blocks_for(f->n_out, kThreads)), block(kThreads);
@@ -1799,7 +1965,10 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         else if (K3 == 8) TS_LAUNCH("k_transpose", k_transpose<8>, gf, block, f->d_nbr, f->n_out, m->d_nbr);
         else TS_LAUNCH("k_transpose", k_transpose<1>, gf, block, f->d_nbr, f->n_out, m->d_nbr);
     }
-    return rows_and_scan(m, tmp, colcnt, d_status);
+    launch_rows(m);
+    launch_scan(m, sizes);
+    TS_HIP(hipGetLastError());
+    return TS_OK;
 }
 
 }  // namespace
@@ -1809,40 +1978,20 @@ namespace ts {
 int resolve(const ts_kmap *kmap, bool need_sizes) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
     if (m->pending_slot >= 0) {
-        StatusSlot &sl = g_slots[m->pending_slot];
-        TS_HIP(hipEventSynchronize(sl.ev));
-        take_status(m, sl.host);
-        sl.busy = false;
-        sl.owner = nullptr;
-        m->pending_slot = -1;
-        if (m->rows_enqueued) {   // ts_kmap_prepare ran the row pass and the scan behind the build; their sizes came with the flags
-            m->rows_enqueued = false;
-            m->rows_done = true;
+        const int slot = m->pending_slot;
+        if (need_sizes && !m->scan_enqueued) TS_TRY(prepare(m));
+        const bool totals = m->scan_enqueued;
+        TS_TRY(slot_wait(slot, totals));
+        if (totals) {
+            take_status(m, slot_at(slot).host);
+            m->scan_done = true;
+        } else {
+            take_verdict(m, slot_at(slot).host);
         }
-    }
-    if (need_sizes && !m->rows_done && m->error == TS_OK) {
-        // the part of a stride-1 build that was put off: row pass, scan, sizes
-        hipStream_t st = stream();
-        Temps tmp;
-        int *d_status;
-        int32_t *colcnt;
-        uint32_t *wavemask;
-        TS_TRY(tmp.get(&d_status, ST_WORDS));
-        TS_TRY(tmp.get(&colcnt, (size_t)m->K3 * m->n_blocks));
-        TS_TRY(tmp.get(&wavemask, (size_t)m->n_blocks));
-        FillArgs fill;
-        fill.add(d_status, ST_WORDS * sizeof(int), 0u);
-        TS_TRY(launch_fill(fill));
-        TS_LAUNCH("k_rows", (k_rows<27, true>), dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), m->d_nbr, m->d_out_keys,
-                  m->n_out, m->d_colbits, colcnt, wavemask, m->n_blocks);
-        TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), colcnt, m->d_colbase, m->n_blocks, d_status, m->K3, wavemask,
-                  m->n_tiles, m->d_tile_order);
-        int32_t *h = static_cast<int32_t *>(host_staging(ST_WORDS * sizeof(int32_t)));
-        if (!h) return last_fail_code();
-        TS_HIP(hipMemcpyAsync(h, d_status, ST_WORDS * sizeof(int32_t), hipMemcpyDeviceToHost, st));
-        TS_HIP(hipStreamSynchronize(st));
-        take_status(m, h);
-        m->rows_done = true;
+        if (totals || m->error != TS_OK) {   // else the slot stays for the sizes
+            slot_release(slot);
+            m->pending_slot = -1;
+        }
     }
     return m->error == TS_OK ? TS_OK : report(m);
 }
@@ -1854,25 +2003,16 @@ void release_grid() {
     g_grid_dirty = false;
 }
 
-// The part of a 3x3x3 stride-1 build that ts_build_kmap_async put off, enqueued without a wait: its
-// sizes land in the pinned words the build's flags went to, and the event is recorded again behind it.
+// The scan that an asynchronous 3x3x3 stride-1 build put off, enqueued without a wait: its sizes land in the
+// words that the build's verdict goes to.
 int prepare(const ts_kmap *kmap) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
-    if (m->rows_done || m->rows_enqueued || m->pending_slot < 0) return TS_OK;   // nothing put off, or resolve will do it
-    StatusSlot &sl = g_slots[m->pending_slot];
-    if (!sl.dev) return TS_OK;
-    Temps tmp;
-    int32_t *colcnt;
-    uint32_t *wavemask;
-    TS_TRY(tmp.get(&colcnt, (size_t)m->K3 * m->n_blocks));
-    TS_TRY(tmp.get(&wavemask, (size_t)m->n_blocks));
-    TS_LAUNCH("k_rows", (k_rows<27, true>), dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), m->d_nbr, m->d_out_keys,
-              m->n_out, m->d_colbits, colcnt, wavemask, m->n_blocks);
-    TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), colcnt, m->d_colbase, m->n_blocks, sl.dev, m->K3, wavemask,
-              m->n_tiles, m->d_tile_order);
-    TS_HIP(hipEventRecord(sl.ev, stream()));
+    if (m->scan_done || m->scan_enqueued || m->pending_slot < 0) return TS_OK;   // nothing put off
+    StatusSlot &sl = slot_at(m->pending_slot);
+    launch_scan(m, sl.dev);
+    sl.totals = true;
+    m->scan_enqueued = true;
     TS_HIP(hipGetLastError());
-    m->rows_enqueued = true;
     return TS_OK;
 }
 
