@@ -185,42 +185,70 @@ struct BlockTable {
     uint64_t *ent;     // [capacity][2]: block key (kEmptyKey = free), occupancy mask
     int32_t *rows;     // [capacity][64]
     uint32_t mask;     // capacity - 1 (capacity: power of two, at least 1.5 per point, >= 1024)
-    int shift;         // 64 - log2(capacity)
+    int shift;         // 64 - log2(capacity / 8)
 };
 constexpr uint64_t kCellBits = 3ull | (3ull << kFieldBits) | (3ull << (2 * kFieldBits));
 
-__device__ __forceinline__ uint32_t block_home(uint64_t bkey, int shift) { return (uint32_t)((bkey * 0x9E3779B97F4A7C15ull) >> shift); }
+// The eight blocks of a 2x2x2 group have their home slots side by side (128 bytes of entries): most lookups of a
+// point's neighbourhood then fall into one or two cache lines.  A collision moves on by 9 slots, as in the table
+// of points above.
+constexpr uint64_t kBlockInGroup = 4ull | (4ull << kFieldBits) | (4ull << (2 * kFieldBits));
+__device__ __forceinline__ uint32_t block_home(uint64_t bkey, int shift) {
+    const uint32_t in_group = ((uint32_t)(bkey >> 2) & 1u) | (((uint32_t)(bkey >> (kFieldBits + 2)) & 1u) << 1) | (((uint32_t)(bkey >> (2 * kFieldBits + 2)) & 1u) << 2);
+    return ((uint32_t)(((bkey & ~kBlockInGroup) * 0x9E3779B97F4A7C15ull) >> shift) << 3) + in_group;
+}
 __device__ __forceinline__ uint32_t cell_of(uint64_t key) {
     return ((uint32_t)key & 3u) | (((uint32_t)(key >> kFieldBits) & 3u) << 2) | (((uint32_t)(key >> (2 * kFieldBits)) & 3u) << 4);
 }
 
-// Stride-1 front end: pack and insert.  Two dependent atomics per point (the block's key, its mask); the mask
-// returned by the second says whether the cell was taken, which is how equal points are found.
+// Stride-1 front end: pack and insert.  Points that follow each other in the same block (scan and raster orders:
+// 2.7 to 3.7 of them) go in together: the first lane of such a run claims the block's entry and sets the run's
+// occupancy bits with one atomic each, because atomics are what bounds this kernel (about 20 G/s over the chip: one
+// claim and one mask update per point took 17.5 us for 153 k points and 46 us for 470 k; by runs 10.4 and 17).
+// A bit that was set before, or twice in a run, is how equal points are found.
 __global__ void __launch_bounds__(kThreads) k_block_insert(const int4 *__restrict__ coords, int64_t n, uint64_t *__restrict__ keys,
                                                            BlockTable t, int *status) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    const int4 c = coords[i];
-    if (!coord_ok(c)) {
-        raise_flag(status, ST_RANGE);
-        keys[i] = kEmptyKey;
-        return;
+    const int lane = threadIdx.x & 63;
+    uint64_t key = kEmptyKey;
+    if (i < n) {
+        const int4 c = coords[i];
+        if (coord_ok(c)) key = pack_key(c.x, c.y, c.z, c.w);
+        else raise_flag(status, ST_RANGE);
+        keys[i] = key;
     }
-    const uint64_t key = pack_key(c.x, c.y, c.z, c.w), bkey = key & ~kCellBits;
-    keys[i] = key;
-    uint32_t slot = block_home(bkey, t.shift);
-    for (;;) {   // the table holds at most one block per point and has half as many slots again: a free one exists
-        uint64_t found = t.ent[2 * (uint64_t)slot];   // a key never changes once set; a stale "free" is decided by the swap
-        if (found == kEmptyKey)
-            found = atomicCAS(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot]), (unsigned long long)kEmptyKey,
-                              (unsigned long long)bkey);
-        if (found == kEmptyKey || found == bkey) break;
-        slot = (slot + 1) & t.mask;
-    }
+    const bool ok = key != kEmptyKey;
+    const uint64_t bkey = ok ? key & ~kCellBits : kEmptyKey;
     const uint32_t cell = cell_of(key);
-    const unsigned long long bit = 1ull << cell;
-    t.rows[(uint64_t)slot * 64 + cell] = (int32_t)i;
-    if (atomicOr(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot + 1]), bit) & bit) raise_flag(status, ST_DUP);
+    // runs of equal block keys: the run's first lane, and the lane behind its last
+    const uint64_t before = (uint64_t)__shfl_up((unsigned long long)bkey, 1, 64);
+    const uint64_t heads = __ballot(lane == 0 || before != bkey);
+    const uint64_t upto = ~0ull >> (63 - lane);
+    const int first = 63 - __clzll((long long)(heads & upto));
+    const uint64_t after = heads & ~upto;
+    const int end = after ? __builtin_ctzll(after) : 64;
+    uint64_t bits = ok ? 1ull << cell : 0ull;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint64_t other = (uint64_t)__shfl_down((unsigned long long)bits, d, 64);
+        if (lane + d < end) bits |= other;
+    }
+    uint32_t slot = 0;
+    if (ok && lane == first) {
+        slot = block_home(bkey, t.shift);
+        for (;;) {   // the table holds at most one block per point and has half as many slots again: a free one exists
+            uint64_t found = t.ent[2 * (uint64_t)slot];   // a key never changes once set; a stale "free" is decided by the swap
+            if (found == kEmptyKey)
+                found = atomicCAS(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot]), (unsigned long long)kEmptyKey,
+                                  (unsigned long long)bkey);
+            if (found == kEmptyKey || found == bkey) break;
+            slot = next_slot(slot, t.mask);
+        }
+        const uint64_t taken = atomicOr(reinterpret_cast<unsigned long long *>(&t.ent[2 * (uint64_t)slot + 1]), (unsigned long long)bits);
+        if ((taken & bits) != 0 || __popcll(bits) != end - lane) raise_flag(status, ST_DUP);
+    }
+    slot = (uint32_t)__shfl((int)slot, first, 64);
+    if (ok) t.rows[(uint64_t)slot * 64 + cell] = (int32_t)i;
 }
 
 // Takes the points out again: the cells of `keys` go back to -1.
@@ -573,7 +601,7 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
 #pragma unroll
         for (int o = 0; o < 8; ++o) {
             if ((pending >> o) & 1u) {
-                slot[o] = (slot[o] + 1) & t.mask;
+                slot[o] = next_slot(slot[o], t.mask);
                 got[o] = reinterpret_cast<const ulonglong2 *>(t.ent)[slot[o]];
             }
         }
@@ -583,13 +611,11 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
         lds.found.mask[o][tid] = (present >> o) & 1u ? (uint64_t)got[o].y : 0ull;
         lds.found.slot[o][tid] = slot[o];
     }
-    // (each thread reads back only what it wrote: indexed by an octant that depends on the lane)
-    uint32_t mask = ok ? 1u << (K3 / 2) : 0u;
-    int32_t j[K3];
+    // Where each neighbour's row number stands, and which neighbours there are.  (A thread reads back only what
+    // it wrote itself, by an octant that depends on the lane; all reads first, then all loads they lead to.)
+    uint32_t mask = 0, at[K3];
 #pragma unroll
     for (int q = 0; q < K3; ++q) {
-        j[q] = -1;
-        if (q == K3 / 2) continue;
         const int d[3] = {q / 9 - 1, (q / 3) % 3 - 1, q % 3 - 1};
         uint32_t o = 0, cell = 0;
 #pragma unroll
@@ -598,10 +624,16 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
             o |= out ? 4u >> a : 0u;
             cell |= ((c[a] + (uint32_t)d[a]) & 3u) << (2 * (2 - a));
         }
-        if (ok && ((lds.found.mask[o][tid] >> cell) & 1ull)) {
-            j[q] = t.rows[(uint64_t)lds.found.slot[o][tid] * 64 + cell];
-            mask |= 1u << q;
-        }
+        const uint64_t m = lds.found.mask[o][tid];
+        at[q] = lds.found.slot[o][tid] * 64 + cell;
+        mask |= (uint32_t)(m >> cell & 1ull) << q;
+    }
+    mask = ok ? mask | 1u << (K3 / 2) : 0u;   // (of two equal points one is not in the table: it still has itself)
+    int32_t j[K3];
+#pragma unroll
+    for (int q = 0; q < K3; ++q) {
+        j[q] = -1;
+        if (q != K3 / 2 && ((mask >> q) & 1u)) j[q] = t.rows[at[q]];
     }
     if (ok) j[K3 / 2] = (int32_t)k;
     __syncthreads();
@@ -1218,7 +1250,7 @@ int make_block_table(Temps &tmp, int64_t points, BlockTable *t, FillArgs *fill) 
     TS_TRY(tmp.get(&t->ent, 2 * cap));
     TS_TRY(tmp.get(&t->rows, 64 * cap));
     t->mask = (uint32_t)(cap - 1);
-    t->shift = 64 - __builtin_ctzll(cap);
+    t->shift = 64 - __builtin_ctzll(cap >> 3);
     fill->add_pairs(t->ent, cap * 16, 0xFFFFFFFFu, 0u);
     return TS_OK;
 }

@@ -77,6 +77,33 @@ def test_kmap_rows_start_clean_in_reused_memory(wait):
         _check_map(sparse, 3, 1, wait=wait).free()
 
 
+@pytest.mark.parametrize("n", [63, 64, 65, 255, 257, 3000])
+@pytest.mark.parametrize("order", ["raster", "shuffled", "column", "far apart"])
+def test_kmap_blocks_of_4x4x4(n, order):
+    """The 3x3x3 stride-1 search looks neighbours up in 4x4x4 blocks: runs of points in one block that cross a wave
+    of 64, full blocks, blocks cut at negative coordinates and at the ends of the range, points alone in theirs; and
+    a point given twice, next to itself and far from itself."""
+    side = int(np.ceil(n ** (1 / 3)))
+    grid = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
+    if order == "column":
+        grid = np.stack([np.arange(n) % 2, np.arange(n) // 4, np.arange(n) // 2 % 2], -1)
+    if order == "far apart":
+        grid = grid * 11
+    xyz = grid + (ts.TS_COORD_MIN if n % 2 else -(side // 2) - 1)
+    if n == 3000:
+        xyz = xyz - xyz.max() + ts.TS_COORD_MAX
+    coords = np.concatenate([np.zeros((n, 1), np.int64), xyz], 1).astype(np.int32)
+    if order == "shuffled":
+        coords = coords[np.random.Generator(np.random.PCG64(n)).permutation(n)]
+    _check_map(coords, 3, 1).free()
+    for at, of in ((1, 0), (n - 1, 0), (n // 2, n // 2 + 1)):
+        twice = coords.copy()
+        twice[at] = twice[of]
+        with pytest.raises(ts.TsError) as e:
+            ts.ts_build_kmap(to_dev(twice), 3, 1)
+        assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
+
+
 def test_kmap_errors():
     dup = np.array([[0, 1, 2, 3], [0, 5, 5, 5], [0, 1, 2, 3]], dtype=np.int32)
     with pytest.raises(ts.TsError) as e:
