@@ -1056,6 +1056,7 @@ int check_layer(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap 
     TS_TRY(check_tensor(out, "out"));
     if (feats->dtype != weights->dtype || feats->dtype != out->dtype)
         return fail(TS_ERR_SHAPE, "feats, weights and out must share one dtype");
+    TS_TRY(resolve_count(kmap));
     if (feats->rows != kmap->n_in) return fail(TS_ERR_SHAPE, "feats has %lld rows, the map expects %lld", (long long)feats->rows, (long long)kmap->n_in);
     if (out->rows != kmap->n_out) return fail(TS_ERR_SHAPE, "out has %lld rows, the map produces %lld", (long long)out->rows, (long long)kmap->n_out);
     if (weights->rows != (int64_t)kmap->K3 * feats->cols)

@@ -88,6 +88,9 @@ inline int alloc_n(T **p, size_t n) {
 // need_sizes == false: only the verdict is awaited; the put-off scan of a stride-1 build is not run.
 int resolve(const struct ::ts_kmap *kmap, bool need_sizes = true);
 
+// Waits, if it has not happened yet, for a map's number of outputs alone (n_out).
+int resolve_count(const struct ::ts_kmap *kmap);
+
 // Enqueues, without waiting, what an asynchronous build put off (ts_kmap_prepare).
 int prepare(const struct ::ts_kmap *kmap);
 
@@ -151,6 +154,8 @@ struct ts_kmap {
     bool scan_enqueued = false; // the scan (ranks, sizes, tile order) has been enqueued; resolve only waits for it
     bool scan_done = true;      // false: what the scan leaves is not there yet, or not known to be (the fused kernel needs none of it)
     int pending_slot = -1;      // >= 0: sizes and error flags are still on their way to the host
+    bool count_pending = false; // n_out is not known yet (-1): ts::resolve_count reads it
+    bool one_pair_per_input = false;   // 2x2x2, stride 2: fewer pairs than inputs means equal inputs
     int error = 0;              // TS_OK, or what the build found wrong with its input
     int32_t out_box_lo[3] = {0, 0, 0}, out_box_hi[3] = {0, 0, 0}, out_box_batches = 0;   // a box that holds every output
                                 // coordinate (a strided forward build that marked its candidates in one); batches 0: unknown
@@ -171,6 +176,7 @@ struct ts_kmap {
     uint64_t *d_colbits = nullptr;        // [K3][n_blocks] bit r: output 64*b + r has offset n
     int32_t *d_colbase = nullptr;         // [K3][n_blocks] pairs of offset n in the blocks before b (until the scan: in block b)
     uint32_t *d_wavemask = nullptr;       // [n_blocks] offsets met by any of the block's outputs
+    int32_t *d_parent = nullptr;          // [n_in] output of every input (-1: none), 2x2x2 stride-2 maps only (else NULL)
     // Optional (ts_kmap_sort_rows): output rows ordered by offset bitmask, so that the rows of a
     // tile of the output-stationary kernel share their offsets.  NULL = natural row order.
     int64_t n_tiles = 0;                  // ceil(n_out / kTileRows)

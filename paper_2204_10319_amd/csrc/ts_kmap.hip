@@ -48,8 +48,10 @@ enum {
     ST_DCOUNT = 2,      // distinct offset bitmasks seen (ts_kmap_sort_rows)
     ST_OVERFLOW = 3,    // the bitmask table could not hold them all
     ST_SEARCHED = 4,    // set once every kernel that raises ST_RANGE or ST_DUP has finished
+    ST_COUNT = 5,       // output points of a 2x2x2 stride-2 map (-1: not there yet, kBoxTooLarge: build it by sorting)
     ST_TOTALS = 8,      // [32] per-offset map sizes (-1: not there yet)
-    ST_WORDS = 40
+    ST_BOX = 40,        // [7] lo, hi, batches of the box of a 2x2x2 stride-2 map's outputs, there with ST_COUNT
+    ST_WORDS = 48
 };
 
 // A word the host reads.  Every writer of a flag stores the same value.
@@ -320,6 +322,8 @@ __global__ void k_fill(FillArgs a) {
 // on cache lines of their own (atomics on one line are served one after the other), each 7 running
 // maxima: -x, -y, -z, x, y, z, batch.  The host folds the 64.
 constexpr int kBoxSlots = 64, kBoxSlotWords = 32;
+
+constexpr int kBoxTooLarge = -2;
 
 // keys[i] = pack(coords[i]); out-of-range rows get the empty key and raise ST_RANGE.
 __global__ void __launch_bounds__(kThreads) k_pack(const int4 *coords, int64_t n, uint64_t *keys, int *status, Box box, int32_t *bbox) {
@@ -840,11 +844,17 @@ __global__ void k_probe_symmetric(const uint64_t *__restrict__ keys, int64_t n_p
 // (the symmetric probe of a grid; the transposition of a forward map): a thread per output row reads its
 // row, sets the centre entry where the map has one (stride 1: output k is input k) and the row's
 // offset bitmask, and does what every search kernel does once the bitmask is known.
+// `count`, if given, holds the number of rows on the device; n_out is then a bound on it.
 template <int K3, bool HAS_CENTRE>
 __global__ void __launch_bounds__(kThreads) k_rows(int32_t *__restrict__ nbr, const uint64_t *__restrict__ keys, int64_t n_out,
-                                                   uint64_t *__restrict__ colbits, int32_t *__restrict__ colcnt,
-                                                   uint32_t *__restrict__ wavemask, int64_t n_blocks) {
+                                                   const int32_t *__restrict__ count, uint64_t *__restrict__ colbits,
+                                                   int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask, int64_t n_blocks) {
     constexpr int STRIDE = nbr_stride(K3), CHUNKS = (K3 + 3) / 4, CENTRE = (K3 - 1) / 2;
+    if (count) {
+        n_out = *count;
+        n_blocks = (n_out + 63) / 64;
+        if ((int64_t)blockIdx.x * kThreads >= n_out) return;
+    }
     const int64_t k = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const bool ok = k < n_out && keys[k] != kEmptyKey;
     uint32_t mask = 0;
@@ -1029,6 +1039,256 @@ __global__ void __launch_bounds__(kThreads) k_rank_scatter(const uint64_t *__res
     }
 }
 
+// ---- 2x2x2 stride-2 maps ------------------------------------------------------------------------------------
+// Every input has exactly one output, the cell (x >> 1, y >> 1, z >> 1), and meets it through the offset made of
+// its three parity bits.  The whole build is enqueued at once: what its kernels do not know beforehand - the
+// box of the points, the number of outputs - they leave for one another in this header, and the host reads
+// the number of outputs from a pinned word when it needs it.  (With the host in between, once for the box and
+// once for the count, 153 k points took about 110 us, half of that in two waits and the gaps behind them.)
+// Since every input owns one entry, equal points show as fewer entries than inputs: no atomics in the scatter.
+struct DownHead {
+    int32_t lo[3];       // coarse cell 0 of the bitmap
+    uint32_t ext[3];     // cells per axis
+    int32_t n_words;     // 64-cell words of the bitmap; 0: no valid point, or the box is too large
+    int32_t too_large;
+    int32_t count;       // output points
+};
+constexpr int kDownPack = 512;      // workgroups that pack: as many partial boxes
+constexpr int kDownSweep = 1024;    // workgroups that sweep the bitmap
+constexpr int kDownWaves = kDownSweep * (kThreads / 64);   // each wave sweeps a stretch of whole 64-word steps: no
+                                                           // barriers, which would wait for the step's stores
+
+__device__ __forceinline__ int down_stretch(const DownHead &h) {   // words per wave (a bitmap has at most 2^24)
+    return (h.n_words + kDownWaves * 64 - 1) / (kDownWaves * 64) * 64;
+}
+__device__ __forceinline__ uint32_t down_cell(const DownHead &h, uint64_t key) {   // at most 2^30 cells
+    int32_t c[4];
+    unpack_key(key, c);
+    return (((uint32_t)c[0] * h.ext[0] + (uint32_t)((c[1] >> 1) - h.lo[0])) * h.ext[1] + (uint32_t)((c[2] >> 1) - h.lo[1])) * h.ext[2] +
+           (uint32_t)((c[3] >> 1) - h.lo[2]);
+}
+__device__ __forceinline__ int down_offset(uint64_t key) {
+    return ((int)(key >> (2 * kFieldBits)) & 1) * 4 + ((int)(key >> kFieldBits) & 1) * 2 + ((int)key & 1);
+}
+
+// Keys, and the box of the valid points in one part per workgroup: 8 words, the maxima of -x, -y, -z, x, y, z, batch.
+__global__ void __launch_bounds__(kThreads) k_down_pack(const int4 *__restrict__ coords, int64_t n, uint64_t *__restrict__ keys,
+                                                        int *status, Box box, int4 *__restrict__ parts) {
+    __shared__ int32_t sh[kThreads / 64][8];
+    int32_t v[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] = INT32_MIN;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) {
+        const int4 c = coords[i];
+        uint64_t key = kEmptyKey;
+        if (!coord_ok(c) || !in_box(c, box)) {
+            raise_flag(status, ST_RANGE);
+        } else {
+            key = pack_key(c.x, c.y, c.z, c.w);
+            const int32_t w[7] = {-c.y, -c.z, -c.w, c.y, c.z, c.w, c.x};
+#pragma unroll
+            for (int q = 0; q < 7; ++q) v[q] = max(v[q], w[q]);
+        }
+        keys[i] = key;
+    }
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+        for (int d = 32; d >= 1; d >>= 1) v[q] = max(v[q], __shfl_xor(v[q], d, 64));
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q) sh[threadIdx.x >> 6][q] = v[q];
+    }
+    __syncthreads();
+    if (threadIdx.x < 7) {
+        int32_t m = sh[0][threadIdx.x];
+        for (int w = 1; w < kThreads / 64; ++w) m = max(m, sh[w][threadIdx.x]);
+        reinterpret_cast<int32_t *>(parts)[blockIdx.x * 8 + threadIdx.x] = m;
+    }
+}
+
+// Folds the partial boxes (every workgroup for itself: 16 KB from L2), clears the bitmap over the box and the
+// map's tile counters; the first workgroup leaves the header, and the box for the host.
+__global__ void __launch_bounds__(kThreads) k_down_clear(const int4 *__restrict__ parts, int n_parts, Box box, uint64_t max_words,
+                                                         uint4 *__restrict__ words, uint4 *__restrict__ sched, DownHead *head, int *status) {
+    __shared__ int32_t sh[kThreads / 64][8];
+    int32_t v[7];
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] = INT32_MIN;
+    for (int i = threadIdx.x; i < n_parts; i += kThreads) {
+        const int4 a = parts[2 * i], b = parts[2 * i + 1];
+        const int32_t w[7] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z};
+#pragma unroll
+        for (int q = 0; q < 7; ++q) v[q] = max(v[q], w[q]);
+    }
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+        for (int d = 32; d >= 1; d >>= 1) v[q] = max(v[q], __shfl_xor(v[q], d, 64));
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q) sh[threadIdx.x >> 6][q] = v[q];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 7; ++q) v[q] = max(max(sh[0][q], sh[1][q]), max(sh[2][q], sh[3][q]));
+    const bool none = v[6] == INT32_MIN;   // no valid point
+    DownHead h;
+    int32_t hi[3];
+    uint64_t cells = none ? 0 : (uint64_t)(box.on ? box.batches : v[6] + 1);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        h.lo[a] = none ? 0 : (box.on ? box.lo[a] : -v[a]) >> 1;
+        hi[a] = none ? 0 : (box.on ? box.hi[a] : v[3 + a]) >> 1;
+        h.ext[a] = (uint32_t)(hi[a] - h.lo[a] + 1);
+        cells *= h.ext[a];
+    }
+    const uint64_t n_words = (cells + 63) / 64;
+    h.too_large = n_words > max_words;
+    h.n_words = h.too_large ? 0 : (int32_t)n_words;
+    h.count = 0;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *head = h;
+        for (int a = 0; a < 3; ++a) {
+            tell_host(status, ST_BOX + a, h.lo[a]);
+            tell_host(status, ST_BOX + 3 + a, hi[a]);
+        }
+        tell_host(status, ST_BOX + 6, none ? 0 : box.on ? box.batches : v[6] + 1);
+    }
+    const uint4 zero = make_uint4(0, 0, 0, 0);
+    const int64_t first = (int64_t)blockIdx.x * kThreads + threadIdx.x, step = (int64_t)gridDim.x * kThreads;
+    for (int64_t i = first; i < ((int64_t)h.n_words + 1) / 2; i += step) words[i] = zero;
+    for (int64_t i = first; i < kMaxSchedSlices * kSchedWords / 4; i += step) sched[i] = zero;
+}
+
+__global__ void __launch_bounds__(kThreads) k_down_mark(const uint64_t *__restrict__ keys, int64_t n, const DownHead *__restrict__ head,
+                                                        uint32_t *__restrict__ bits) {
+    const DownHead h = *head;
+    if (h.n_words == 0) return;
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const uint64_t key = i < n ? keys[i] : kEmptyKey;
+    const uint32_t cell = key == kEmptyKey ? ~0u : down_cell(h, key);
+    // a lane whose predecessor marks the same cell stays silent
+    const uint32_t before = __shfl_up(cell, 1, 64);
+    if (cell == ~0u || ((threadIdx.x & 63) != 0 && before == cell)) return;
+    atomicOr(&bits[cell >> 5], 1u << (cell & 31));
+}
+
+__global__ void __launch_bounds__(kThreads) k_down_count(const uint64_t *__restrict__ words, const DownHead *__restrict__ head,
+                                                         int32_t *__restrict__ totals) {
+    const DownHead h = *head;
+    const int wave = (int)blockIdx.x * (kThreads / 64) + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int len = down_stretch(h), first = wave * len, end = min(first + len, h.n_words);
+    int mine = 0;
+    for (int w = first + lane; w < end; w += 64) mine += __popcll(words[w]);
+    for (int d = 32; d >= 1; d >>= 1) mine += __shfl_xor(mine, d, 64);
+    if (lane == 0) totals[wave] = mine;
+}
+
+// Every set bit becomes the key of its cell at the rank of the bit (see k_bits_expand), and the neighbour rows of
+// the outputs found start out as "no neighbour": only as many rows are cleared as there are.  The positions of a
+// step's bits go through LDS, so that a lane makes one output at a time (a lane making all outputs of its word
+// kept its wave for up to 64 of them where points are dense: 14 us for 153 k points).
+__global__ void __launch_bounds__(kThreads) k_down_expand(const uint64_t *__restrict__ words, const int4 *__restrict__ totals,
+                                                          DownHead *__restrict__ head, uint64_t *__restrict__ out_keys,
+                                                          int32_t *__restrict__ word_base, int4 *__restrict__ nbr, int *status) {
+    __shared__ int sums[kThreads / 64];
+    __shared__ uint16_t places[kThreads / 64][64 * 64];
+    uint16_t *place = places[threadIdx.x >> 6];
+    const DownHead h = *head;
+    const int wave = (int)blockIdx.x * (kThreads / 64) + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int len = down_stretch(h), first = wave * len, end = min(first + len, h.n_words);
+    const bool last = blockIdx.x == kDownSweep - 1;
+    if ((int)blockIdx.x * (kThreads / 64) * len >= h.n_words && !last) return;
+    // outputs before this wave's stretch: the workgroup adds up the waves of all workgroups before it
+    const int4 own = totals[blockIdx.x];
+    int part = 0;
+    for (int i = threadIdx.x; i < (int)blockIdx.x; i += kThreads) {
+        const int4 t = totals[i];
+        part += t.x + t.y + t.z + t.w;
+    }
+    for (int d = 32; d >= 1; d >>= 1) part += __shfl_xor(part, d, 64);
+    if (lane == 0) sums[threadIdx.x >> 6] = part;
+    __syncthreads();
+    int before = sums[0] + sums[1] + sums[2] + sums[3];
+    const int q = threadIdx.x >> 6;
+    before += (q > 0 ? own.x : 0) + (q > 1 ? own.y : 0) + (q > 2 ? own.z : 0);
+    for (int base = first; base < end; base += 64) {
+        const int w = base + lane;
+        uint64_t bits = w < end ? words[w] : 0;
+        const int mine = __popcll(bits);
+        int incl = mine;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += up;
+        }
+        const int total = __shfl(incl, 63, 64);
+        if (w < end) word_base[w] = before + incl - mine;
+        for (int at = incl - mine; bits; bits &= bits - 1) place[at++] = (uint16_t)(lane * 64 + __builtin_ctzll(bits));
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < total; i += 64) {
+            uint32_t cell = (uint32_t)base * 64u + place[i];
+            const int32_t z = (int32_t)(cell % h.ext[2]) + h.lo[2];
+            cell /= h.ext[2];
+            const int32_t y = (int32_t)(cell % h.ext[1]) + h.lo[1];
+            cell /= h.ext[1];
+            out_keys[before + i] = pack_key((int32_t)(cell / h.ext[0]), (int32_t)(cell % h.ext[0]) + h.lo[0], y, z);
+        }
+        for (int i = lane; i < total * (nbr_stride(8) / 4); i += 64)
+            nbr[(int64_t)before * (nbr_stride(8) / 4) + i] = make_int4(-1, -1, -1, -1);
+        __builtin_amdgcn_wave_barrier();
+        before += total;
+    }
+    if (last && threadIdx.x == kThreads - 64) {   // the last stretch, empty or not
+        head->count = before;
+        tell_host(status, ST_COUNT, h.too_large ? kBoxTooLarge : before);
+    }
+}
+
+// nbr[output][offset] = input, and the input's output, which is all that a transposed map needs.
+__global__ void __launch_bounds__(kThreads) k_down_scatter(const uint64_t *__restrict__ keys, int64_t n, const DownHead *__restrict__ head,
+                                                           const uint64_t *__restrict__ words, const int32_t *__restrict__ word_base,
+                                                           int32_t *__restrict__ nbr, int32_t *__restrict__ parent) {
+    const DownHead h = *head;
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n || h.n_words == 0) return;
+    const uint64_t key = keys[i];
+    int32_t k = -1;
+    if (key != kEmptyKey) {
+        const uint32_t cell = down_cell(h, key);
+        k = word_base[cell >> 6] + __popcll(words[cell >> 6] & ((1ull << (cell & 63)) - 1ull));
+        nbr[(int64_t)k * nbr_stride(8) + down_offset(key)] = (int32_t)i;
+    }
+    parent[i] = k;
+}
+
+// The transposed map of such a map, in one pass over the fine points: a row has the one entry (offset of the
+// point, its coarse cell).  Keys of both point sets are copied and the tile counters cleared on the way.
+// (By scattering the forward rows into cleared rows and reading those again it took five launches.)
+__global__ void __launch_bounds__(kThreads) k_up_rows(const uint64_t *__restrict__ fine, const int32_t *__restrict__ parent, int64_t n,
+                                                      const uint64_t *__restrict__ coarse, int64_t n_coarse,
+                                                      uint64_t *__restrict__ fine_copy, uint64_t *__restrict__ coarse_copy,
+                                                      int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
+                                                      int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
+                                                      int64_t n_blocks, uint4 *__restrict__ sched) {
+    constexpr int STRIDE = nbr_stride(8);
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    for (int64_t v = i; v < kMaxSchedSlices * kSchedWords / 4; v += (int64_t)gridDim.x * kThreads) sched[v] = make_uint4(0, 0, 0, 0);
+    if (i < n_coarse) coarse_copy[i] = coarse[i];   // (never more coarse points than fine ones)
+    uint32_t mask = 0;
+    if (i < n) {
+        const uint64_t key = fine[i];
+        const int32_t k = parent[i];
+        const int q = down_offset(key);
+        fine_copy[i] = key;
+        if (k >= 0) mask = 1u << q;
+        int4 *row = reinterpret_cast<int4 *>(nbr + i * STRIDE);
+        const int none = -1;
+        row[0] = make_int4(q == 0 ? k : none, q == 1 ? k : none, q == 2 ? k : none, q == 3 ? k : none);
+        row[1] = make_int4(q == 4 ? k : none, q == 5 ? k : none, q == 6 ? k : none, q == 7 ? k : none);
+        row[2] = make_int4((int)mask, none, none, none);
+    }
+    finish_rows<8>(mask, colbits, colcnt, wavemask, n_blocks);
+}
+
 // Block n: exclusive scan in place of the counts col[n][*] -> col[n][b] = pairs of offset n in the 64-row
 // blocks before b (relative to the start of the offset's list), and the offset's total (the host
 // turns the totals into offs[], the start of each offset's list, and hands them to later kernels
@@ -1036,7 +1296,11 @@ __global__ void __launch_bounds__(kThreads) k_rank_scatter(const uint64_t *__res
 constexpr int kScanThreads = 1024, kScanItems = 4;
 __global__ void __launch_bounds__(kScanThreads) k_scan(int32_t *__restrict__ col, int64_t n_blocks, int *status, int K3,
                                                        const uint32_t *__restrict__ wavemask, int64_t n_tiles,
-                                                       int32_t *__restrict__ tile_order) {
+                                                       int32_t *__restrict__ tile_order, const int32_t *__restrict__ count) {
+    if (count) {   // the number of rows is on the device only
+        n_blocks = ((int64_t)*count + 63) / 64;
+        n_tiles = ((int64_t)*count + kTileRows - 1) / kTileRows;
+    }
     if ((int)blockIdx.x == K3) {
         // The extra block: tiles of 128 outputs (two waves of the search) in descending order of
         // the number of offsets they meet, a counting sort.  The fused kernel takes tiles in this
@@ -1359,10 +1623,13 @@ StatusSlot *g_slots[kSlotChunks] = {nullptr};
 
 inline StatusSlot &slot_at(int i) { return g_slots[i / kSlotChunk][i % kSlotChunk]; }
 
-// Whether what the slot's build reports has arrived: the verdict on its input, or the sizes too.
-inline bool slot_landed(const StatusSlot &s, bool totals) {
+// Whether what the slot's build reports has arrived: the number of its outputs (2x2x2 stride-2 maps), the verdict
+// on its input, or the sizes too.
+enum Awaited { kCount, kVerdict, kSizes };
+inline bool slot_landed(const StatusSlot &s, Awaited what) {
     const volatile int32_t *h = s.host;
-    if (!totals) return h[ST_SEARCHED] != 0 || (s.totals && slot_landed(s, true));   // sizes come after everything else
+    if (what == kCount) return h[ST_COUNT] != -1;
+    if (what == kVerdict) return h[ST_SEARCHED] != 0 || (s.totals && slot_landed(s, kSizes));   // sizes come after everything else
     for (int n = 0; n < s.K3; ++n)
         if (h[ST_TOTALS + n] < 0) return false;
     return true;
@@ -1371,6 +1638,7 @@ inline bool slot_landed(const StatusSlot &s, bool totals) {
 inline void slot_reset(StatusSlot &s, int K3) {
     std::memset(s.host, 0, ST_WORDS * sizeof(int32_t));
     for (int n = 0; n < kMaxK3; ++n) s.host[ST_TOTALS + n] = -1;
+    s.host[ST_COUNT] = -1;
     s.K3 = K3;
     s.totals = false;
 }
@@ -1402,7 +1670,7 @@ int slot_acquire(int K3) {
         }
         for (int i = 0; i < kSlotChunk; ++i) {
             StatusSlot &s = g_slots[ch][i];
-            if (s.busy && (s.owner || !slot_landed(s, s.totals))) continue;
+            if (s.busy && (s.owner || !slot_landed(s, s.totals ? kSizes : kVerdict))) continue;
             slot_reset(s, K3);
             s.busy = true;
             s.owner = nullptr;
@@ -1420,11 +1688,11 @@ inline void slot_release(int i) {
 
 // Watches the slot's words.  The stream is asked now and then whether it has finished or failed, so that a
 // build that cannot report any more (an error of the device) ends the wait.
-int slot_wait(int i, bool totals) {
+int slot_wait(int i, Awaited what) {
     const StatusSlot &s = slot_at(i);
     for (;;) {
         for (int spin = 0; spin < 20000; ++spin) {
-            if (slot_landed(s, totals)) return TS_OK;
+            if (slot_landed(s, what)) return TS_OK;
             __builtin_ia32_pause();
         }
         const hipError_t e = hipStreamQuery(stream());
@@ -1432,10 +1700,10 @@ int slot_wait(int i, bool totals) {
             (void)hipGetLastError();
             continue;
         }
-        if (slot_landed(s, totals)) return TS_OK;
+        if (slot_landed(s, what)) return TS_OK;
         if (e != hipSuccess) return fail(TS_ERR_HIP, "waiting for a map build: %s", hipGetErrorString(e));
         TS_HIP(hipDeviceSynchronize());   // another stream than the one the build ran on is current
-        if (slot_landed(s, totals)) return TS_OK;
+        if (slot_landed(s, what)) return TS_OK;
         return fail(TS_ERR_HIP, "a map build finished without reporting");
     }
 }
@@ -1453,6 +1721,7 @@ int take_status(ts_kmap *m, const int32_t *h) {
     for (int n = 0; n < m->K3; ++n) m->offs[n + 1] = m->offs[n] + h[ST_TOTALS + n];
     for (int n = 0; n < m->K3; ++n) m->sizes[n] = m->offs[n + 1] - m->offs[n];
     m->M = m->offs[m->K3];
+    if (m->one_pair_per_input && m->error == TS_OK && m->M < m->n_in) m->error = TS_ERR_DUPLICATE_COORD;
     return m->error;
 }
 
@@ -1497,6 +1766,7 @@ void destroy(ts_kmap *m) {
     dev_free(m->d_sched);
     dev_free(m->d_tile_order);
     dev_free(m->d_wavemask);
+    dev_free(m->d_parent);
     delete m;
 }
 
@@ -1522,7 +1792,7 @@ void launch_probe(const ts_kmap *m, const Searched &sd) {
 
 void launch_rows(const ts_kmap *m) {
     const dim3 grid(blocks_for(m->n_out, kThreads)), block(kThreads);
-#define TS_ROWS(K3, CENTRE) TS_LAUNCH("k_rows", (k_rows<K3, CENTRE>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks)
+#define TS_ROWS(K3, CENTRE) TS_LAUNCH("k_rows", (k_rows<K3, CENTRE>), grid, block, m->d_nbr, m->d_out_keys, m->n_out, nullptr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks)
     if (m->K3 == 27 && m->centre >= 0) TS_ROWS(27, true);
     else if (m->K3 == 27) TS_ROWS(27, false);
     else if (m->K3 == 8) TS_ROWS(8, false);
@@ -1533,7 +1803,7 @@ void launch_rows(const ts_kmap *m) {
 // Counts of the 64-row blocks -> ranks, sizes (into the status words at `status`) and tile order.
 void launch_scan(const ts_kmap *m, int32_t *status) {
     TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), m->d_colbase, m->n_blocks, status, m->K3, m->d_wavemask,
-              m->n_tiles, m->d_tile_order);
+              m->n_tiles, m->d_tile_order, nullptr);
 }
 
 // Map search through the hash table or the coordinate grid.  `table` holds the searched point set (the map's
@@ -1653,22 +1923,305 @@ int alloc_outputs(ts_kmap *m, FillArgs *fill) {
     m->stride = nbr_stride(K3);
     m->n_blocks = (m->n_out + 63) / 64;
     m->n_tiles = (m->n_out + kTileRows - 1) / kTileRows;
-    if (!m->d_nbr) TS_TRY(alloc_n(&m->d_nbr, (size_t)m->n_out * m->stride));   // (a build may have made it early, for a bound on n_out)
+    TS_TRY(alloc_n(&m->d_nbr, (size_t)m->n_out * m->stride));
     TS_TRY(alloc_n(&m->d_colbits, (size_t)K3 * m->n_blocks));
     TS_TRY(alloc_n(&m->d_colbase, (size_t)K3 * m->n_blocks));
     TS_TRY(alloc_n(&m->d_tile_order, (size_t)m->n_tiles));
     TS_TRY(alloc_n(&m->d_wavemask, (size_t)m->n_blocks));
-    if (!m->d_sched) {
-        TS_TRY(alloc_n(&m->d_sched, (size_t)kMaxSchedSlices * kSchedWords));
-        fill->add(m->d_sched, (size_t)kMaxSchedSlices * kSchedWords * sizeof(int32_t), 0u);
-    }
+    TS_TRY(alloc_n(&m->d_sched, (size_t)kMaxSchedSlices * kSchedWords));
+    if (fill) fill->add(m->d_sched, (size_t)kMaxSchedSlices * kSchedWords * sizeof(int32_t), 0u);   // (else the caller's kernel clears them)
     return TS_OK;
 }
 
-int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kmap *m, const BuildOpts &asked) {
+// The device-driven build of a 2x2x2 stride-2 map (see DownHead): arrays for the most outputs there can be, all
+// launches, no wait.  The bitmap of a box that has to be measured first holds as many cells as one may have.
+int build_down(Temps &tmp, const int32_t *coords, int64_t N, ts_kmap *m, const BuildOpts &opt, int slot) {
+    StatusSlot &sl = slot_at(slot);
+    uint64_t max_cells = kAutoGridCells;
+    if (opt.grid) {
+        max_cells = (uint64_t)opt.box.batches;
+        for (int a = 0; a < 3; ++a) {
+            max_cells *= (uint64_t)((opt.box.hi[a] >> 1) - (opt.box.lo[a] >> 1) + 1);
+            if (max_cells > kMaxGridCells)
+                return fail(TS_ERR_UNSUPPORTED, "the grid bounds span more than %llu cells", (unsigned long long)kMaxGridCells);
+        }
+    }
+    const uint64_t max_words = (max_cells + 63) / 64;
+    uint64_t *words;
+    int32_t *word_base, *totals;
+    int4 *parts;
+    DownHead *head;
+    TS_TRY(tmp.get(&words, max_words + 1));   // (cleared two at a time)
+    TS_TRY(tmp.get(&word_base, max_words));
+    TS_TRY(tmp.get(&totals, kDownWaves));
+    TS_TRY(tmp.get(&parts, 2 * kDownPack));
+    TS_TRY(tmp.get(&head, 1));
+    m->n_in = N;
+    m->n_out = N;   // what the arrays are made for
+    TS_TRY(alloc_outputs(m, nullptr));
+    TS_TRY(alloc_n(&m->d_out_keys, (size_t)N));
+    TS_TRY(alloc_n(&m->d_parent, (size_t)N));
+    const unsigned n_parts = blocks_for(N, kThreads) < kDownPack ? blocks_for(N, kThreads) : kDownPack;
+    const dim3 per_point(blocks_for(N, kThreads)), sweep(kDownSweep), block(kThreads);
+    TS_LAUNCH("k_down_pack", k_down_pack, dim3(n_parts), block, reinterpret_cast<const int4 *>(coords), N, m->d_in_keys, sl.dev, opt.box, parts);
+    TS_LAUNCH("k_down_clear", k_down_clear, sweep, block, parts, (int)n_parts, opt.box, max_words, reinterpret_cast<uint4 *>(words),
+              reinterpret_cast<uint4 *>(m->d_sched), head, sl.dev);
+    TS_LAUNCH("k_down_mark", k_down_mark, per_point, block, m->d_in_keys, N, head, reinterpret_cast<uint32_t *>(words));
+    TS_LAUNCH("k_down_count", k_down_count, sweep, block, words, head, totals);
+    TS_LAUNCH("k_down_expand", k_down_expand, sweep, block, words, reinterpret_cast<const int4 *>(totals), head, m->d_out_keys, word_base, reinterpret_cast<int4 *>(m->d_nbr), sl.dev);
+    TS_LAUNCH("k_down_scatter", k_down_scatter, per_point, block, m->d_in_keys, N, head, words, word_base, m->d_nbr, m->d_parent);
+    TS_LAUNCH("k_rows", (k_rows<8, false>), per_point, block, m->d_nbr, m->d_out_keys, N, &head->count, m->d_colbits, m->d_colbase, m->d_wavemask, (int64_t)0);
+    TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), m->d_colbase, (int64_t)0, sl.dev, m->K3, m->d_wavemask, (int64_t)0,
+              m->d_tile_order, &head->count);
+    m->n_out = -1;
+    m->count_pending = true;
+    m->one_pair_per_input = true;
+    m->scan_enqueued = true;
+    m->scan_done = false;
+    sl.totals = true;
+    sl.owner = m;
+    m->pending_slot = slot;
+    TS_HIP(hipGetLastError());
+    return TS_OK;
+}
+
+// A strided build that the host takes part in: it waits for the box of the points where that is measured, and for
+// the number of coarse points.  coords == NULL: `given` holds the keys already.  *reports is set once all that
+// writes to the slot has been enqueued and the map owns it.
+int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N, ts_kmap *m, const BuildOpts &asked, int slot,
+                  bool *reports) {
     BuildOpts opt = asked;   // a build that measures its bounding box may turn the grid on
     const bool wait = opt.wait;
+    const int K = m->K, s = m->s, transposed = m->transposed;
     hipStream_t st = stream();
+    int32_t *d_status = slot_at(slot).dev;
+    FillArgs fill;
+    Searched table;
+    const dim3 per_point(blocks_for(N, kThreads)), block(kThreads);
+    // coarse set: the distinct admissible candidates in ascending order (Alg. 3)
+    const int A = (K + s - 1) / s, slots = A * A * A;
+    const size_t n_cand = (size_t)N * slots;
+    uint64_t *uniq;
+    int64_t *d_count;
+    TS_TRY(tmp.get(&uniq, n_cand));
+    TS_TRY(tmp.get(&d_count, 1));
+    int32_t *d_bbox = nullptr;
+    if (opt.measure && !opt.grid) {
+        TS_TRY(tmp.get(&d_bbox, (size_t)kBoxSlots * kBoxSlotWords));
+        fill.add(d_bbox, (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t), 0x80000000u);
+    }
+    Grid cbox = {};
+    uint64_t *words = nullptr;
+    int32_t *word_base = nullptr, *block_total = nullptr;
+    int64_t n_words = 0, n_wblocks = 0;
+    auto bitmap_over_box = [&]() -> int {
+        // the coarse points lie in the box of the fine ones, moved by less than K and divided by s
+        uint64_t cells = (uint64_t)opt.box.batches;
+        for (int a = 0; a < 3; ++a) {
+            cbox.lo[a] = floor_div(opt.box.lo[a] - K, s);
+            cbox.ext[a] = (uint32_t)(floor_div(opt.box.hi[a] + K, s) - cbox.lo[a] + 1);
+            cells *= cbox.ext[a];
+            if (cells > kMaxGridCells)
+                return fail(TS_ERR_UNSUPPORTED, "the grid bounds span more than %llu cells", (unsigned long long)kMaxGridCells);
+        }
+        cbox.batches = (uint32_t)opt.box.batches;
+        n_words = (int64_t)((cells + 63) / 64);
+        n_wblocks = (n_words + kThreads - 1) / kThreads;
+        TS_TRY(tmp.get(&words, (size_t)n_words));
+        TS_TRY(tmp.get(&word_base, (size_t)n_words));
+        TS_TRY(tmp.get(&block_total, (size_t)n_wblocks));
+        fill.add(words, (size_t)n_words * sizeof(uint64_t), 0u);
+        return TS_OK;
+    };
+    TS_TRY(launch_fill(fill));
+    fill = FillArgs();
+    if (coords) TS_LAUNCH("k_pack", k_pack, per_point, block, reinterpret_cast<const int4 *>(coords), N, given, d_status, opt.box, d_bbox);
+    if (d_bbox) {
+        // one more host round trip buys a build without a sort and a search without collisions
+        const size_t bytes = (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t);
+        int32_t *hb = static_cast<int32_t *>(host_staging(bytes));
+        if (!hb) return last_fail_code();
+        TS_HIP(hipMemcpyAsync(hb, d_bbox, bytes, hipMemcpyDeviceToHost, st));
+        TS_HIP(hipStreamSynchronize(st));
+        int32_t top[7];
+        for (int q = 0; q < 7; ++q) {
+            top[q] = INT32_MIN;
+            for (int sl = 0; sl < kBoxSlots; ++sl) top[q] = hb[sl * kBoxSlotWords + q] > top[q] ? hb[sl * kBoxSlotWords + q] : top[q];
+        }
+        if (top[6] != INT32_MIN) {   // at least one valid point
+            // the bitmap has one bit per cell of the box the outputs can lie in
+            Box bx = {};
+            uint64_t cells = (uint64_t)top[6] + 1;
+            for (int a = 0; a < 3; ++a) {
+                bx.lo[a] = -top[a];
+                bx.hi[a] = top[3 + a];
+                cells *= (uint64_t)((int64_t)floor_div(bx.hi[a] + K, s) - floor_div(bx.lo[a] - K, s) + 1);
+                if (cells > kAutoGridCells) cells = kAutoGridCells + 1;
+            }
+            bx.batches = top[6] + 1;
+            if (cells <= kAutoGridCells) {
+                opt.grid = true;
+                opt.box = bx;   // on stays 0: nothing to check, the box is the points' own
+            }
+        }
+    }
+    // the coarse points lie in the box of the fine ones, moved by less than K and divided by s
+    int32_t clo[3] = {0, 0, 0}, chi[3] = {0, 0, 0};
+    for (int a = 0; a < 3; ++a) {
+        clo[a] = floor_div(opt.box.lo[a] - K, s);
+        chi[a] = floor_div(opt.box.hi[a] + K, s);
+    }
+    const bool ranked = opt.grid;   // outputs found through the bitmap: the map follows without a search
+    if (opt.grid) {
+        // bounds are stated or measured: mark the candidates' cells in a bitmap and read the set bits
+        // off in order, which sorts and removes duplicates at once
+        TS_TRY(bitmap_over_box());
+        TS_TRY(launch_fill(fill));
+        fill = FillArgs();
+        TS_LAUNCH("k_candidates_mark", k_candidates_mark, dim3(blocks_for(N, kThreads), slots), block, given, N, K, s, A, opt.bound,
+                  cbox, reinterpret_cast<uint32_t *>(words), d_status);
+        TS_LAUNCH("k_bits_count", k_bits_count, dim3((unsigned)n_wblocks), block, words, n_words, block_total);
+        // up to a few thousand blocks every block sums the totals before it by itself; beyond, a scan launch
+        const int self_scan = n_wblocks <= 8192;
+        if (!self_scan) TS_LAUNCH("k_bits_scan", k_bits_scan, dim3(1), block, block_total, n_wblocks, d_count);
+        TS_LAUNCH("k_bits_expand", k_bits_expand, dim3((unsigned)n_wblocks), block, words, n_words, block_total, cbox, uniq,
+                  word_base, self_scan, d_count);
+    } else {
+        // candidates -> sort -> unique (the empty key, if present, sorts last)
+        uint64_t *cand, *sorted;
+        TS_TRY(tmp.get(&cand, n_cand));
+        TS_TRY(tmp.get(&sorted, n_cand));
+        TS_LAUNCH("k_candidates", k_candidates, dim3(blocks_for(N, kThreads), slots), block, given, N, K, s, A, opt.bound, cand);
+        TS_TRY(sort_keys(tmp, cand, sorted, n_cand));
+        size_t bytes = 0;
+        TS_HIP(rocprim::unique(nullptr, bytes, sorted, uniq, d_count, n_cand, rocprim::equal_to<uint64_t>(), st));
+        void *ws;
+        TS_TRY(tmp.get((char **)&ws, bytes));
+        {
+            ProfScope ps("unique_keys");
+            TS_HIP(rocprim::unique(ws, bytes, sorted, uniq, d_count, n_cand, rocprim::equal_to<uint64_t>(), st));
+        }
+        // the empty key, if any candidate was rejected, is the last unique value: do not count it
+        TS_LAUNCH("k_drop_empty_key", k_drop_empty_key, dim3(1), dim3(1), uniq, d_count);
+    }
+    int64_t *h = static_cast<int64_t *>(host_staging(64));
+    if (!h) return last_fail_code();
+    TS_HIP(hipMemcpyAsync(h, d_count, sizeof(int64_t), hipMemcpyDeviceToHost, st));
+    TS_HIP(hipStreamSynchronize(st));
+    const int64_t n_coarse = h[0];
+    if (n_coarse == 0) {
+        // No candidate passed the modular check (or every coordinate was out of range): a map
+        // without pairs.  The inputs are still checked for duplicates and range.
+        Table t0;
+        TS_TRY(make_table(tmp, N, &t0, &fill));
+        if (!transposed) {
+            m->n_in = N;
+            m->n_out = 0;
+        } else {
+            m->n_in = 0;
+            m->n_out = N;
+            m->d_in_keys = nullptr;
+            m->d_out_keys = given;
+            TS_TRY(alloc_outputs(m, &fill));
+            fill.add(m->d_nbr, (size_t)N * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
+        }
+        TS_TRY(launch_fill(fill));
+        TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, t0, d_status);
+        if (transposed) {
+            launch_rows(m);
+            *reports = true;
+            return finish(m, slot, true);
+        }
+        TS_HIP(hipStreamSynchronize(st));
+        return take_verdict(m, slot_at(slot).host) == TS_OK ? TS_OK : report(m);
+    }
+    uint64_t *coarse;
+    TS_TRY(alloc_n(&coarse, (size_t)n_coarse));
+    TS_HIP(hipMemcpyAsync(coarse, uniq, (size_t)n_coarse * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
+    if (ranked) {
+        // No search: an input's admissible candidates are outputs, and an output's row number is the rank
+        // of its cell among the marked ones (k_rank_scatter).  Neither hash table nor coordinate grid.
+        const dim3 per_cand(blocks_for(N, kThreads), slots);
+        if (!transposed) {
+            m->n_in = N;
+            m->n_out = n_coarse;
+            m->d_out_keys = coarse;
+        } else {
+            m->n_in = n_coarse;
+            m->n_out = N;
+            m->d_in_keys = coarse;
+            m->d_out_keys = given;
+        }
+        TS_TRY(alloc_outputs(m, &fill));
+        fill.add(m->d_nbr, (size_t)m->n_out * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
+        if (!transposed && !opt.bound.on) {
+            TS_TRY(launch_fill(fill));
+            TS_LAUNCH("k_rank_scatter", k_rank_scatter<false>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
+                      m->d_nbr, m->stride, d_status);
+        } else if (!transposed) {
+            // with a boundary an input may lose all its candidates and then meets nobody in the table: equal
+            // points are found through a hash table here as well
+            Table fine_table;
+            TS_TRY(make_table(tmp, N, &fine_table, &fill));
+            TS_TRY(launch_fill(fill));
+            TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
+            TS_LAUNCH("k_rank_scatter", k_rank_scatter<false>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
+                      m->d_nbr, m->stride, d_status);
+        } else {
+            // rows belong to the given points here, so equal points do not meet in an entry: they are found
+            // by inserting the points into a hash table, which nothing else uses
+            Table fine_table;
+            TS_TRY(make_table(tmp, N, &fine_table, &fill));
+            TS_TRY(launch_fill(fill));
+            TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
+            TS_LAUNCH("k_rank_scatter", k_rank_scatter<true>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
+                      m->d_nbr, m->stride, d_status);
+        }
+        // where the next level's points can lie, for a caller that builds a pyramid
+        if (!transposed) {
+            m->out_box_batches = (int32_t)cbox.batches;
+            for (int a = 0; a < 3; ++a) {
+                m->out_box_lo[a] = cbox.lo[a];
+                m->out_box_hi[a] = cbox.lo[a] + (int32_t)cbox.ext[a] - 1;
+            }
+        }
+        launch_rows(m);
+        *reports = true;
+        return finish(m, slot, wait);
+    }
+    if (!transposed) {
+        m->n_in = N;
+        m->n_out = n_coarse;
+        m->d_out_keys = coarse;
+        TS_TRY(alloc_outputs(m, &fill));
+        TS_TRY(make_searched(tmp, opt, N, opt.box.lo, opt.box.hi, &table, &fill));
+        TS_TRY(launch_fill(fill));
+        if (table.grid) TS_LAUNCH("k_insert_grid", k_insert<Grid>, per_point, block, given, N, table.g, d_status);
+        else TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, table.t, d_status);
+    } else {
+        m->n_in = n_coarse;
+        m->n_out = N;
+        m->d_in_keys = coarse;
+        m->d_out_keys = given;
+        TS_TRY(alloc_outputs(m, &fill));
+        // duplicates among the fine points are found by inserting them as well
+        Table fine_table;
+        TS_TRY(make_table(tmp, N, &fine_table, &fill));
+        TS_TRY(make_searched(tmp, opt, n_coarse, clo, chi, &table, &fill));
+        TS_TRY(launch_fill(fill));
+        TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
+        const dim3 per_coarse(blocks_for(n_coarse, kThreads));
+        if (table.grid) TS_LAUNCH("k_insert_grid", k_insert<Grid>, per_coarse, block, coarse, n_coarse, table.g, d_status);
+        else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
+    }
+    TS_TRY(search(m, table));
+    *reports = true;
+    return finish(m, slot, wait);
+}
+
+int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kmap *m, const BuildOpts &asked) {
+    const BuildOpts &opt = asked;
+    const bool wait = opt.wait;
     Temps tmp;
     const int K3 = K * K * K;
     m->K = K;
@@ -1723,241 +2276,16 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             TS_LAUNCH("k_pack_insert_grid", k_pack_insert<Grid>, per_point, block, c4, N, given, table.g, d_status, opt.box, rows);
         else
             TS_LAUNCH("k_pack_insert", k_pack_insert<Table>, per_point, block, c4, N, given, table.t, d_status, opt.box, rows);
-    } else {
-        // coarse set: the distinct admissible candidates in ascending order (Alg. 3)
-        const int A = (K + s - 1) / s, slots = A * A * A;
-        const size_t n_cand = (size_t)N * slots;
-        uint64_t *uniq;
-        int64_t *d_count;
-        TS_TRY(tmp.get(&uniq, n_cand));
-        TS_TRY(tmp.get(&d_count, 1));
-        int32_t *d_bbox = nullptr;
-        if (opt.measure && !opt.grid) {
-            TS_TRY(tmp.get(&d_bbox, (size_t)kBoxSlots * kBoxSlotWords));
-            fill.add(d_bbox, (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t), 0x80000000u);
-        }
-        // Box known before the first launch, one candidate per input (K <= s), forward map: there are at most N
-        // outputs, so the neighbour table is made for N rows now and everything that must start at a known
-        // value - status words, bitmap, table rows, tile counters - is cleared by the one launch below.
-        const bool early = opt.grid && slots == 1 && !transposed && !opt.bound.on;
-        Grid cbox = {};
-        uint64_t *words = nullptr;
-        int32_t *word_base = nullptr, *block_total = nullptr;
-        int64_t n_words = 0, n_wblocks = 0;
-        auto bitmap_over_box = [&]() -> int {
-            // the coarse points lie in the box of the fine ones, moved by less than K and divided by s
-            uint64_t cells = (uint64_t)opt.box.batches;
-            for (int a = 0; a < 3; ++a) {
-                cbox.lo[a] = floor_div(opt.box.lo[a] - K, s);
-                cbox.ext[a] = (uint32_t)(floor_div(opt.box.hi[a] + K, s) - cbox.lo[a] + 1);
-                cells *= cbox.ext[a];
-                if (cells > kMaxGridCells)
-                    return fail(TS_ERR_UNSUPPORTED, "the grid bounds span more than %llu cells", (unsigned long long)kMaxGridCells);
-            }
-            cbox.batches = (uint32_t)opt.box.batches;
-            n_words = (int64_t)((cells + 63) / 64);
-            n_wblocks = (n_words + kThreads - 1) / kThreads;
-            TS_TRY(tmp.get(&words, (size_t)n_words));
-            TS_TRY(tmp.get(&word_base, (size_t)n_words));
-            TS_TRY(tmp.get(&block_total, (size_t)n_wblocks));
-            fill.add(words, (size_t)n_words * sizeof(uint64_t), 0u);
-            return TS_OK;
-        };
-        if (early) {
-            TS_TRY(bitmap_over_box());
-            m->stride = nbr_stride(K3);
-            TS_TRY(alloc_n(&m->d_nbr, (size_t)N * m->stride));
-            TS_TRY(alloc_n(&m->d_sched, (size_t)kMaxSchedSlices * kSchedWords));
-            fill.add(m->d_nbr, (size_t)N * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
-            fill.add(m->d_sched, (size_t)kMaxSchedSlices * kSchedWords * sizeof(int32_t), 0u);
-        }
-        TS_TRY(launch_fill(fill));
-        fill = FillArgs();
-        TS_LAUNCH("k_pack", k_pack, per_point, block, reinterpret_cast<const int4 *>(coords), N, given, d_status, opt.box, d_bbox);
-        if (d_bbox) {
-            // one more host round trip buys a build without a sort and a search without collisions
-            const size_t bytes = (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t);
-            int32_t *hb = static_cast<int32_t *>(host_staging(bytes));
-            if (!hb) return last_fail_code();
-            TS_HIP(hipMemcpyAsync(hb, d_bbox, bytes, hipMemcpyDeviceToHost, st));
-            TS_HIP(hipStreamSynchronize(st));
-            int32_t top[7];
-            for (int q = 0; q < 7; ++q) {
-                top[q] = INT32_MIN;
-                for (int sl = 0; sl < kBoxSlots; ++sl) top[q] = hb[sl * kBoxSlotWords + q] > top[q] ? hb[sl * kBoxSlotWords + q] : top[q];
-            }
-            if (top[6] != INT32_MIN) {   // at least one valid point
-                // the bitmap has one bit per cell of the box the outputs can lie in
-                Box bx = {};
-                uint64_t cells = (uint64_t)top[6] + 1;
-                for (int a = 0; a < 3; ++a) {
-                    bx.lo[a] = -top[a];
-                    bx.hi[a] = top[3 + a];
-                    cells *= (uint64_t)((int64_t)floor_div(bx.hi[a] + K, s) - floor_div(bx.lo[a] - K, s) + 1);
-                    if (cells > kAutoGridCells) cells = kAutoGridCells + 1;
-                }
-                bx.batches = top[6] + 1;
-                if (cells <= kAutoGridCells) {
-                    opt.grid = true;
-                    opt.box = bx;   // on stays 0: nothing to check, the box is the points' own
-                }
-            }
-        }
-        // the coarse points lie in the box of the fine ones, moved by less than K and divided by s
-        int32_t clo[3] = {0, 0, 0}, chi[3] = {0, 0, 0};
-        for (int a = 0; a < 3; ++a) {
-            clo[a] = floor_div(opt.box.lo[a] - K, s);
-            chi[a] = floor_div(opt.box.hi[a] + K, s);
-        }
-        const bool ranked = opt.grid;   // outputs found through the bitmap: the map follows without a search
-        if (opt.grid) {
-            // bounds are stated or measured: mark the candidates' cells in a bitmap and read the set bits
-            // off in order, which sorts and removes duplicates at once
-            if (!early) {
-                TS_TRY(bitmap_over_box());
-                TS_TRY(launch_fill(fill));
-                fill = FillArgs();
-            }
-            TS_LAUNCH("k_candidates_mark", k_candidates_mark, dim3(blocks_for(N, kThreads), slots), block, given, N, K, s, A, opt.bound,
-                      cbox, reinterpret_cast<uint32_t *>(words), d_status);
-            TS_LAUNCH("k_bits_count", k_bits_count, dim3((unsigned)n_wblocks), block, words, n_words, block_total);
-            // up to a few thousand blocks every block sums the totals before it by itself; beyond, a scan launch
-            const int self_scan = n_wblocks <= 8192;
-            if (!self_scan) TS_LAUNCH("k_bits_scan", k_bits_scan, dim3(1), block, block_total, n_wblocks, d_count);
-            TS_LAUNCH("k_bits_expand", k_bits_expand, dim3((unsigned)n_wblocks), block, words, n_words, block_total, cbox, uniq,
-                      word_base, self_scan, d_count);
-        } else {
-            // candidates -> sort -> unique (the empty key, if present, sorts last)
-            uint64_t *cand, *sorted;
-            TS_TRY(tmp.get(&cand, n_cand));
-            TS_TRY(tmp.get(&sorted, n_cand));
-            TS_LAUNCH("k_candidates", k_candidates, dim3(blocks_for(N, kThreads), slots), block, given, N, K, s, A, opt.bound, cand);
-            TS_TRY(sort_keys(tmp, cand, sorted, n_cand));
-            size_t bytes = 0;
-            TS_HIP(rocprim::unique(nullptr, bytes, sorted, uniq, d_count, n_cand, rocprim::equal_to<uint64_t>(), st));
-            void *ws;
-            TS_TRY(tmp.get((char **)&ws, bytes));
-            {
-                ProfScope ps("unique_keys");
-                TS_HIP(rocprim::unique(ws, bytes, sorted, uniq, d_count, n_cand, rocprim::equal_to<uint64_t>(), st));
-            }
-            // the empty key, if any candidate was rejected, is the last unique value: do not count it
-            TS_LAUNCH("k_drop_empty_key", k_drop_empty_key, dim3(1), dim3(1), uniq, d_count);
-        }
-        int64_t *h = static_cast<int64_t *>(host_staging(64));
-        if (!h) return last_fail_code();
-        TS_HIP(hipMemcpyAsync(h, d_count, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-        TS_HIP(hipStreamSynchronize(st));
-        const int64_t n_coarse = h[0];
-        if (n_coarse == 0) {
-            // No candidate passed the modular check (or every coordinate was out of range): a map
-            // without pairs.  The inputs are still checked for duplicates and range.
-            Table t0;
-            TS_TRY(make_table(tmp, N, &t0, &fill));
-            if (!transposed) {
-                m->n_in = N;
-                m->n_out = 0;
-            } else {
-                m->n_in = 0;
-                m->n_out = N;
-                m->d_in_keys = nullptr;
-                m->d_out_keys = given;
-                TS_TRY(alloc_outputs(m, &fill));
-                fill.add(m->d_nbr, (size_t)N * m->stride * sizeof(int32_t), 0xFFFFFFFFu);
-            }
-            TS_TRY(launch_fill(fill));
-            TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, t0, d_status);
-            if (transposed) {
-                launch_rows(m);
-                guard.committed = true;
-                return finish(m, slot, true);
-            }
-            TS_HIP(hipStreamSynchronize(st));
-            return take_verdict(m, slot_at(slot).host) == TS_OK ? TS_OK : report(m);
-        }
-        uint64_t *coarse;
-        TS_TRY(alloc_n(&coarse, (size_t)n_coarse));
-        TS_HIP(hipMemcpyAsync(coarse, uniq, (size_t)n_coarse * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
-        if (ranked) {
-            // No search: an input's admissible candidates are outputs, and an output's row number is the rank
-            // of its cell among the marked ones (k_rank_scatter).  Neither hash table nor coordinate grid.
-            const dim3 per_cand(blocks_for(N, kThreads), slots);
-            if (!transposed) {
-                m->n_in = N;
-                m->n_out = n_coarse;
-                m->d_out_keys = coarse;
-            } else {
-                m->n_in = n_coarse;
-                m->n_out = N;
-                m->d_in_keys = coarse;
-                m->d_out_keys = given;
-            }
-            TS_TRY(alloc_outputs(m, &fill));
-            if (!early) fill.add(m->d_nbr, (size_t)m->n_out * m->stride * sizeof(int32_t), 0xFFFFFFFFu);   // (early: cleared by the first launch)
-            if (!transposed && !opt.bound.on) {
-                TS_TRY(launch_fill(fill));
-                TS_LAUNCH("k_rank_scatter", k_rank_scatter<false>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
-                          m->d_nbr, m->stride, d_status);
-            } else if (!transposed) {
-                // with a boundary an input may lose all its candidates and then meets nobody in the table: equal
-                // points are found through a hash table here as well
-                Table fine_table;
-                TS_TRY(make_table(tmp, N, &fine_table, &fill));
-                TS_TRY(launch_fill(fill));
-                TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
-                TS_LAUNCH("k_rank_scatter", k_rank_scatter<false>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
-                          m->d_nbr, m->stride, d_status);
-            } else {
-                // rows belong to the given points here, so equal points do not meet in an entry: they are found
-                // by inserting the points into a hash table, which nothing else uses
-                Table fine_table;
-                TS_TRY(make_table(tmp, N, &fine_table, &fill));
-                TS_TRY(launch_fill(fill));
-                TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
-                TS_LAUNCH("k_rank_scatter", k_rank_scatter<true>, per_cand, block, given, N, K, s, A, opt.bound, cbox, words, word_base,
-                          m->d_nbr, m->stride, d_status);
-            }
-            // where the next level's points can lie, for a caller that builds a pyramid
-            if (!transposed) {
-                m->out_box_batches = (int32_t)cbox.batches;
-                for (int a = 0; a < 3; ++a) {
-                    m->out_box_lo[a] = cbox.lo[a];
-                    m->out_box_hi[a] = cbox.lo[a] + (int32_t)cbox.ext[a] - 1;
-                }
-            }
-            launch_rows(m);
-            guard.committed = true;
-            return finish(m, slot, wait);
-        }
-        if (!transposed) {
-            m->n_in = N;
-            m->n_out = n_coarse;
-            m->d_out_keys = coarse;
-            TS_TRY(alloc_outputs(m, &fill));
-            TS_TRY(make_searched(tmp, opt, N, opt.box.lo, opt.box.hi, &table, &fill));
-            TS_TRY(launch_fill(fill));
-            if (table.grid) TS_LAUNCH("k_insert_grid", k_insert<Grid>, per_point, block, given, N, table.g, d_status);
-            else TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, table.t, d_status);
-        } else {
-            m->n_in = n_coarse;
-            m->n_out = N;
-            m->d_in_keys = coarse;
-            m->d_out_keys = given;
-            TS_TRY(alloc_outputs(m, &fill));
-            // duplicates among the fine points are found by inserting them as well
-            Table fine_table;
-            TS_TRY(make_table(tmp, N, &fine_table, &fill));
-            TS_TRY(make_searched(tmp, opt, n_coarse, clo, chi, &table, &fill));
-            TS_TRY(launch_fill(fill));
-            TS_LAUNCH("k_insert", k_insert<Table>, per_point, block, given, N, fine_table, d_status);
-            const dim3 per_coarse(blocks_for(n_coarse, kThreads));
-            if (table.grid) TS_LAUNCH("k_insert_grid", k_insert<Grid>, per_coarse, block, coarse, n_coarse, table.g, d_status);
-            else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
-        }
+        TS_TRY(search(m, table));
+        guard.committed = true;
+        return finish(m, slot, wait);
     }
-    TS_TRY(search(m, table));
-    guard.committed = true;
-    return finish(m, slot, wait);
+    if (K == 2 && s == 2 && !transposed && !opt.bound.on && (opt.grid || opt.measure)) {
+        TS_TRY(build_down(tmp, coords, N, m, opt, slot));
+        guard.committed = true;
+        return wait ? resolve(m) : TS_OK;
+    }
+    return build_strided(tmp, coords, given, N, m, opt, slot, &guard.committed);
 }
 
 }  // namespace
@@ -1983,6 +2311,17 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
     if (m->n_out == 0) return TS_OK;
     TS_TRY(alloc_n(&m->d_in_keys, (size_t)m->n_in));
     TS_TRY(alloc_n(&m->d_out_keys, (size_t)m->n_out));
+    if (f->d_parent) {
+        int32_t *sizes;   // written by the scan, known already
+        TS_TRY(tmp.get(&sizes, ST_WORDS));
+        TS_TRY(alloc_outputs(m, nullptr));
+        TS_LAUNCH("k_up_rows", k_up_rows, dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), f->d_in_keys, f->d_parent, m->n_out,
+                  f->d_out_keys, m->n_in, m->d_out_keys, m->d_in_keys, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks,
+                  reinterpret_cast<uint4 *>(m->d_sched));
+        launch_scan(m, sizes);
+        TS_HIP(hipGetLastError());
+        return TS_OK;
+    }
     if (m->n_in > 0) TS_HIP(hipMemcpyAsync(m->d_in_keys, f->d_out_keys, (size_t)m->n_in * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
     TS_HIP(hipMemcpyAsync(m->d_out_keys, f->d_in_keys, (size_t)m->n_out * sizeof(uint64_t), hipMemcpyDeviceToDevice, st));
     FillArgs fill;
@@ -2007,13 +2346,60 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
 
 namespace ts {
 
+// The number of outputs of a map whose build left it to be read here (build_down).  A box too large for the bitmap
+// ends in a build by sorting, from the keys.
+int resolve_count(const ts_kmap *kmap) {
+    ts_kmap *m = const_cast<ts_kmap *>(kmap);
+    if (!m->count_pending) return TS_OK;
+    const int slot = m->pending_slot;
+    TS_TRY(slot_wait(slot, kCount));
+    int32_t *h = slot_at(slot).host;
+    if (h[ST_COUNT] >= 0) {
+        m->n_out = h[ST_COUNT];
+        m->n_blocks = (m->n_out + 63) / 64;
+        m->n_tiles = (m->n_out + kTileRows - 1) / kTileRows;
+        m->out_box_batches = h[ST_BOX + 6];
+        for (int a = 0; a < 3; ++a) {
+            m->out_box_lo[a] = h[ST_BOX + a];
+            m->out_box_hi[a] = h[ST_BOX + 3 + a];
+        }
+        m->count_pending = false;
+        return TS_OK;
+    }
+    TS_TRY(slot_wait(slot, kSizes));   // nothing more is written there
+    TS_HIP(hipStreamSynchronize(stream()));
+    for (int n = 0; n < kMaxK3; ++n) h[ST_TOTALS + n] = -1;
+    slot_at(slot).totals = false;
+    m->count_pending = m->one_pair_per_input = m->scan_enqueued = false;
+    for (void *p : {(void *)m->d_nbr, (void *)m->d_colbits, (void *)m->d_colbase, (void *)m->d_tile_order, (void *)m->d_wavemask,
+                    (void *)m->d_sched, (void *)m->d_parent, (void *)m->d_out_keys})
+        dev_free(p);
+    m->d_nbr = m->d_colbase = m->d_tile_order = m->d_sched = m->d_parent = nullptr;
+    m->d_colbits = m->d_out_keys = nullptr;
+    m->d_wavemask = nullptr;
+    Temps tmp;
+    BuildOpts opt;
+    opt.wait = false;
+    bool reports = false;
+    const int rc = build_strided(tmp, nullptr, m->d_in_keys, m->n_in, m, opt, slot, &reports);
+    if (rc != TS_OK) {
+        (void)hipStreamSynchronize(stream());
+        slot_release(slot);
+        m->pending_slot = -1;
+        m->n_out = 0;
+        m->error = rc;
+    }
+    return rc;
+}
+
 int resolve(const ts_kmap *kmap, bool need_sizes) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
+    TS_TRY(resolve_count(m));
     if (m->pending_slot >= 0) {
         const int slot = m->pending_slot;
         if (need_sizes && !m->scan_enqueued) TS_TRY(prepare(m));
         const bool totals = m->scan_enqueued;
-        TS_TRY(slot_wait(slot, totals));
+        TS_TRY(slot_wait(slot, totals ? kSizes : kVerdict));
         if (totals) {
             take_status(m, slot_at(slot).host);
             m->scan_done = true;
@@ -2230,12 +2616,13 @@ int ts_kmap_sort_rows(ts_kmap *kmap) {
 }
 
 int64_t ts_kmap_num_in(const ts_kmap *kmap) { return kmap ? kmap->n_in : -1; }
-int64_t ts_kmap_num_out(const ts_kmap *kmap) { return kmap ? kmap->n_out : -1; }
+int64_t ts_kmap_num_out(const ts_kmap *kmap) { return kmap && ts::resolve_count(kmap) == TS_OK ? kmap->n_out : -1; }
 int64_t ts_kmap_num_pairs(const ts_kmap *kmap) { return kmap && ts::resolve(kmap) == TS_OK ? kmap->M : -1; }
 int ts_kmap_kernel_volume(const ts_kmap *kmap) { return kmap ? kmap->K3 : -1; }
 
 int ts_kmap_out_coords(const ts_kmap *kmap, int32_t *dst) {
     if (!kmap) return fail(TS_ERR_INVALID_ARG, "kmap is NULL");
+    TS_TRY(ts::resolve_count(kmap));
     if (kmap->n_out == 0) return TS_OK;
     if (!kmap->d_out_keys) return fail(TS_ERR_UNSUPPORTED, "a map made by ts_identity_kmap holds no coordinates");
     if (!dst || (reinterpret_cast<uintptr_t>(dst) & 15)) return fail(TS_ERR_INVALID_ARG, "dst is NULL or not 16-byte aligned");
@@ -2246,6 +2633,7 @@ int ts_kmap_out_coords(const ts_kmap *kmap, int32_t *dst) {
 
 int ts_kmap_out_box(const ts_kmap *kmap, int32_t *lo, int32_t *hi, int32_t *batches) {
     if (!kmap || !lo || !hi || !batches) return fail(TS_ERR_INVALID_ARG, "NULL argument");
+    TS_TRY(ts::resolve_count(kmap));
     if (kmap->out_box_batches <= 0) return fail(TS_ERR_UNSUPPORTED, "this map's build did not bound its output coordinates");
     for (int a = 0; a < 3; ++a) {
         lo[a] = kmap->out_box_lo[a];

@@ -35,23 +35,23 @@ class SparseNet:
         levels = {0: coords}
         boxes = {0: box}
         maps = {}
+        # Nothing below waits for a build's end.  A level's strided map is enqueued first, then its 3x3x3 map: the
+        # number of coarse points, which the next level needs, is on the host before the device has run out of work.
         top = max(level for _, level in kinds)
-        hint = None     # where a level's points can lie, as the strided build of the level above bounded them
         for level in range(top + 1):
+            down = None
             if ("down", level) in kinds or ("up", level) in kinds:
-                down = ts.ts_build_kmap(levels[level], 2, 2, False, wait=False, grid=boxes[level],
-                                        box=hint if boxes[level] is None else None)
-                maps[("down", level)] = down
+                down = maps[("down", level)] = ts.ts_build_kmap(levels[level], 2, 2, False, wait=False, grid=boxes[level])
+            if ("sub", level) in kinds:
+                maps[("sub", level)] = ts.ts_build_kmap(levels[level], 3, 1, False, wait=False, grid=boxes.get(level))
+                if sort_rows:
+                    maps[("sub", level)].sort_rows()
+            if down is not None:
                 levels[level + 1] = down.out_coords()
-                hint = down.out_box()     # the next strided build need not measure its box
                 b = boxes[level]
                 boxes[level + 1] = None if b is None else (tuple(v // 2 for v in b[0]), tuple(v // 2 for v in b[1]), b[2])
         for kind, level in kinds:
-            if kind == "sub":
-                maps[(kind, level)] = ts.ts_build_kmap(levels[level], 3, 1, False, wait=False, grid=boxes.get(level))
-                if sort_rows:
-                    maps[(kind, level)].sort_rows()
-            elif kind == "id":
+            if kind == "id":
                 # a 1x1x1 convolution takes input k to output k whatever the coordinates are; that the points of
                 # the level are distinct is checked by the other builds on them
                 maps[(kind, level)] = ts.ts_identity_kmap(levels[level].shape[0])

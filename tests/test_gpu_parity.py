@@ -104,6 +104,35 @@ def test_kmap_blocks_of_4x4x4(n, order):
         assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
 
 
+@pytest.mark.parametrize("n,span", [(1, 1), (255, 6), (257, 40), (4096, 8), (140000, 60), (600, 700), (600, 40000)])
+def test_kmap_2x2x2_that_nobody_waited_for(n, span):
+    """The 2x2x2 stride-2 build leaves the box and the number of outputs on the device: one workgroup and more than
+    pack or sweep at a time, one output and full ones, a box with more than one sweep step per workgroup, one that
+    is too large for the bitmap; and the transposed map made from each, before and after anything was asked."""
+    rng = np.random.Generator(np.random.PCG64(n + span))
+    coords = np.concatenate([rng.integers(0, 3, (4 * n, 1)), rng.integers(-span, span + 1, (4 * n, 3))], 1).astype(np.int32)
+    coords = np.unique(coords, axis=0)
+    coords = coords[rng.permutation(len(coords))[:n]]
+    _check_map(coords, 2, 2, wait=False)
+    fwd = ts.ts_build_kmap(to_dev(coords), 2, 2, wait=False)
+    tr = fwd.transpose()
+    _, out_c, tri = oracle_map(coords, 2, 2, True)
+    assert tr.num_in == fwd.num_out and np.array_equal(tr.out_coords().cpu().numpy(), out_c)
+    assert np.array_equal(tr.in_coords().cpu().numpy(), fwd.out_coords().cpu().numpy())
+    assert np.array_equal(gpu_triples(tr), tri) and np.array_equal(tr.sizes(), fwd.sizes())
+    if n > 1:
+        twice = ts.ts_build_kmap(to_dev(np.concatenate([coords, coords[:1]])), 2, 2, wait=False)
+        assert twice.num_out == fwd.num_out
+        with pytest.raises(ts.TsError) as e:
+            twice.status()
+        assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
+    bad = ts.ts_build_kmap(to_dev(np.full((n, 4), ts.TS_COORD_MAX + 1, np.int32)), 2, 2, wait=False)
+    assert bad.num_out == 0
+    with pytest.raises(ts.TsError) as e:
+        bad.status()
+    assert e.value.code == ts.TS_ERR_COORD_RANGE
+
+
 def test_kmap_errors():
     dup = np.array([[0, 1, 2, 3], [0, 5, 5, 5], [0, 1, 2, 3]], dtype=np.int32)
     with pytest.raises(ts.TsError) as e:
