@@ -1,7 +1,8 @@
-"""ctypes binding of libts.so: argument marshalling only, same names as ``include/ts.h``.
+"""Binding of libts.so: argument marshalling only, same names as ``include/ts.h``.
 
 PyTorch supplies device memory (tensors) and the stream; every step of the layer runs in
-the library's HIP kernels.  There is no fallback: if ``libts.so`` has not been built or
+the library's HIP kernels.  The calls made once per layer or per map go through ``_native.so``
+(``csrc/ts_python.cpp``), the others through ctypes.  There is no fallback: if ``libts.so`` has not been built or
 cannot be loaded, the first call raises.
 """
 from __future__ import annotations
@@ -23,6 +24,7 @@ TS_BATCH_MAX, TS_COORD_MIN, TS_COORD_MAX = 8190, -65528, 65527
 
 _LIB_PATH = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libts.so")
 _lib = None
+_nat = None
 
 EXPORTS = [
     "ts_build_kmap", "ts_build_kmap_async", "ts_build_kmap_ex", "ts_identity_kmap", "ts_kmap_status", "ts_kmap_prepare", "ts_free", "ts_kmap_sort_rows", "ts_kmap_transpose", "ts_kmap_num_in", "ts_kmap_num_out", "ts_kmap_num_pairs",
@@ -149,6 +151,20 @@ def load_library(path: str | None = None):
     return lib
 
 
+def _native():
+    """The extension module with the per-layer and per-map calls; it works on the same libts.so."""
+    global _nat
+    if _nat is None:
+        load_library()
+        try:
+            from . import _native as nat
+        except ImportError as e:
+            raise RuntimeError("_native.so is missing or cannot be loaded: build it with `python -m paper_2204_10319_amd.build`") from e
+        nat.set_error(TsError)
+        _nat = nat
+    return _nat
+
+
 def _check(rc: int):
     if rc != TS_OK:
         raise TsError(rc, load_library().ts_last_error().decode())
@@ -171,7 +187,7 @@ def _as_ts(t: torch.Tensor, rows: int | None = None, cols: int | None = None) ->
 
 
 def _use_current_stream():
-    _check(load_library().ts_set_stream(torch.cuda.current_stream().cuda_stream))
+    _native().use_current_stream()
 
 
 def ts_set_stream(stream: torch.cuda.Stream | None):
@@ -290,8 +306,7 @@ class KMap:
 
     def prepare(self):
         """Enqueues, without waiting, what an asynchronous build put off (ts_kmap_prepare)."""
-        _use_current_stream()
-        _check(load_library().ts_kmap_prepare(self.handle))
+        _native().prepare(self.handle)
         return self
 
     def transpose(self) -> "KMap":
@@ -321,56 +336,46 @@ def ts_build_kmap(coords: torch.Tensor, kernel_size: int, stride: int = 1, trans
     TS_SEARCH_GRID).  search=TS_SEARCH_HASH keeps a strided build on the hash table.  boundary=(bx, by, bz): Alg. 3's boundary check for a strided map.
     box=(lo[3], hi[3], batches): a box holding the coordinates, stated so that a strided build on the default route
     need not measure one (ignored at stride 1)."""
+    if grid is None and boundary is None and search == TS_SEARCH_AUTO and box is None:
+        return KMap(_native().build(coords, kernel_size, stride, transposed, wait))
     if coords.dtype != torch.int32 or coords.dim() != 2 or coords.shape[1] != 4:
         raise ValueError("coords must be int32 [N,4]")
     if not coords.is_cuda or not coords.is_contiguous():
         raise ValueError("coords must be a contiguous device tensor")
     _use_current_stream()
     h = ctypes.c_void_p()
-    if grid is not None or boundary is not None or search != TS_SEARCH_AUTO or box is not None:
-        opt = KMapOptions()
-        opt.wait = int(bool(wait))
-        opt.search = int(search)
-        if box is not None and grid is None:
-            lo, hi, batches = box
-            opt.grid_lo = (ctypes.c_int32 * 3)(*[int(v) for v in lo])
-            opt.grid_hi = (ctypes.c_int32 * 3)(*[int(v) for v in hi])
-            opt.grid_batches = int(batches)
-        if grid is not None:
-            lo, hi, batches = grid
-            opt.search = TS_SEARCH_GRID
-            opt.grid_lo = (ctypes.c_int32 * 3)(*[int(v) for v in lo])
-            opt.grid_hi = (ctypes.c_int32 * 3)(*[int(v) for v in hi])
-            opt.grid_batches = int(batches)
-        if boundary is not None:
-            opt.has_boundary = 1
-            opt.boundary = (ctypes.c_int32 * 3)(*[int(v) for v in boundary])
-        rc = load_library().ts_build_kmap_ex(coords.data_ptr() if coords.numel() else None, coords.shape[0],
-                                             int(kernel_size), int(stride), int(bool(transposed)), ctypes.byref(opt),
-                                             ctypes.byref(h))
-        _check(rc)
-        return KMap(h.value)
-    fn = load_library().ts_build_kmap if wait else load_library().ts_build_kmap_async
-    rc = fn(coords.data_ptr() if coords.numel() else None, coords.shape[0], int(kernel_size), int(stride),
-            int(bool(transposed)), ctypes.byref(h))
+    opt = KMapOptions()
+    opt.wait = int(bool(wait))
+    opt.search = int(search)
+    if box is not None and grid is None:
+        lo, hi, batches = box
+        opt.grid_lo = (ctypes.c_int32 * 3)(*[int(v) for v in lo])
+        opt.grid_hi = (ctypes.c_int32 * 3)(*[int(v) for v in hi])
+        opt.grid_batches = int(batches)
+    if grid is not None:
+        lo, hi, batches = grid
+        opt.search = TS_SEARCH_GRID
+        opt.grid_lo = (ctypes.c_int32 * 3)(*[int(v) for v in lo])
+        opt.grid_hi = (ctypes.c_int32 * 3)(*[int(v) for v in hi])
+        opt.grid_batches = int(batches)
+    if boundary is not None:
+        opt.has_boundary = 1
+        opt.boundary = (ctypes.c_int32 * 3)(*[int(v) for v in boundary])
+    rc = load_library().ts_build_kmap_ex(coords.data_ptr() if coords.numel() else None, coords.shape[0],
+                                         int(kernel_size), int(stride), int(bool(transposed)), ctypes.byref(opt),
+                                         ctypes.byref(h))
     _check(rc)
     return KMap(h.value)
 
 
 def ts_identity_kmap(n: int) -> KMap:
     """The map of a 1x1x1, stride-1 convolution over n distinct points (output k <- input k); holds no coordinates."""
-    _use_current_stream()
-    handle = ctypes.c_void_p()
-    _check(load_library().ts_identity_kmap(int(n), ctypes.byref(handle)))
-    return KMap(handle.value)
+    return KMap(_native().identity(n))
 
 
 def ts_kmap_transpose(forward: KMap) -> KMap:
     """The transposed map of a forward strided map, derived without another search."""
-    _use_current_stream()
-    handle = ctypes.c_void_p()
-    _check(load_library().ts_kmap_transpose(forward.handle, ctypes.byref(handle)))
-    return KMap(handle.value)
+    return KMap(_native().transpose(forward.handle))
 
 
 def ts_kmap_sort_rows(kmap: KMap):
@@ -384,10 +389,7 @@ def ts_free(kmap: KMap):
 
 
 def ts_kmap_out_coords(kmap: KMap) -> torch.Tensor:
-    _use_current_stream()
-    dst = torch.empty((kmap.num_out, 4), dtype=torch.int32, device="cuda")
-    _check(load_library().ts_kmap_out_coords(kmap.handle, dst.data_ptr() if dst.numel() else None))
-    return dst
+    return _native().out_coords(kmap.handle)
 
 
 def ts_kmap_in_coords(kmap: KMap) -> torch.Tensor:
@@ -422,17 +424,7 @@ def _weights_ts(weights: torch.Tensor) -> ts_tensor:
 def ts_sparse_conv(feats: torch.Tensor, weights: torch.Tensor, kmap: KMap, out: torch.Tensor | None = None,
                    dataflow: int = TS_DATAFLOW_AUTO) -> torch.Tensor:
     """feats [num_in, C_in], weights [K^3, C_in, C_out] -> out [num_out, C_out] (same dtype)."""
-    _use_current_stream()
-    if out is None:
-        out = torch.empty((kmap.num_out, weights.shape[2]), dtype=feats.dtype, device=feats.device)
-    f, w, o = _as_ts(feats), _weights_ts(weights), _as_ts(out)
-    lib = load_library()
-    if dataflow == TS_DATAFLOW_AUTO:
-        rc = lib.ts_sparse_conv(ctypes.byref(f), ctypes.byref(w), kmap.handle, ctypes.byref(o))
-    else:
-        rc = lib.ts_sparse_conv_ex(ctypes.byref(f), ctypes.byref(w), kmap.handle, ctypes.byref(o), int(dataflow))
-    _check(rc)
-    return out
+    return _native().conv(feats, weights, kmap.handle, out, dataflow)
 
 
 def ts_sparse_conv_static(feats: torch.Tensor, weights: torch.Tensor, kmap: KMap, out: torch.Tensor) -> torch.Tensor:
@@ -498,34 +490,14 @@ def ts_sparse_conv_prepared(feats: torch.Tensor, weights: Weights, kmap: KMap, b
                             residual: torch.Tensor | None = None, relu: bool = False,
                             out: torch.Tensor | None = None) -> torch.Tensor:
     """ts_sparse_conv_act with weights from ts_weights_prepare."""
-    _use_current_stream()
-    if out is None:
-        out = torch.empty((kmap.num_out, weights.c_out), dtype=feats.dtype, device=feats.device)
-    f, o = _as_ts(feats), _as_ts(out)
-    r = _as_ts(residual) if residual is not None else None
-    _check(load_library().ts_sparse_conv_prepared(ctypes.byref(f), weights.handle, kmap.handle,
-                                                  bias.data_ptr() if bias is not None else None,
-                                                  ctypes.byref(r) if r is not None else None, int(bool(relu)),
-                                                  ctypes.byref(o)))
-    return out
+    return _native().conv_prepared(feats, None, weights.handle, weights.c_out, kmap.handle, bias, residual, relu, out)
 
 
 def ts_sparse_conv_prepared2(feats: torch.Tensor, feats2: torch.Tensor | None, weights: Weights, kmap: KMap,
                              bias: torch.Tensor | None = None, residual: torch.Tensor | None = None,
                              relu: bool = False, out: torch.Tensor | None = None) -> torch.Tensor:
     """ts_sparse_conv_prepared on the channel concatenation [feats | feats2], which is never formed."""
-    _use_current_stream()
-    if out is None:
-        out = torch.empty((kmap.num_out, weights.c_out), dtype=feats.dtype, device=feats.device)
-    f, o = _as_ts(feats), _as_ts(out)
-    f2 = _as_ts(feats2) if feats2 is not None else None
-    r = _as_ts(residual) if residual is not None else None
-    _check(load_library().ts_sparse_conv_prepared2(ctypes.byref(f), ctypes.byref(f2) if f2 is not None else None,
-                                                   weights.handle, kmap.handle,
-                                                   bias.data_ptr() if bias is not None else None,
-                                                   ctypes.byref(r) if r is not None else None, int(bool(relu)),
-                                                   ctypes.byref(o)))
-    return out
+    return _native().conv_prepared(feats, feats2, weights.handle, weights.c_out, kmap.handle, bias, residual, relu, out)
 
 
 _ALLOC_FN = ctypes.CFUNCTYPE(ctypes.c_void_p, ctypes.c_size_t, ctypes.c_void_p)

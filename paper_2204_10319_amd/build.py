@@ -1,8 +1,9 @@
-"""Build libts.so (the HIP C-ABI library) in-tree with hipcc for gfx950."""
+"""Build libts.so (the HIP C-ABI library, hipcc for gfx950) and _native.so (its Python calls, g++) in-tree."""
 from __future__ import annotations
 
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -44,6 +45,8 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
     shared object.  With force every source is compiled again, otherwise only those older than what they
     include."""
     if not force and not is_stale():
+        if native_is_stale():
+            build_native(verbose)
         return LIB
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     os.makedirs(OBJDIR, exist_ok=True)
@@ -75,7 +78,36 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
         print(res.stderr)
     if res.returncode != 0:
         raise RuntimeError("hipcc failed linking libts.so")
+    build_native(verbose)
     return LIB
+
+
+NATIVE = os.path.join(HERE, "_native.so")
+NATIVE_SOURCE = os.path.join(CSRC, "ts_python.cpp")
+
+
+def native_is_stale() -> bool:
+    return not os.path.exists(NATIVE) or os.path.getmtime(NATIVE) < max(
+        os.path.getmtime(f) for f in (NATIVE_SOURCE, os.path.join(HERE, "..", "include", "ts.h")))
+
+
+def build_native(verbose: bool = False) -> str:
+    """Compile the extension module (host code only), linked against libts.so beside it."""
+    import torch
+    root = os.path.dirname(torch.__file__)
+    includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                "/opt/rocm/include", sysconfig.get_paths()["include"]]
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI)]
+    cmd += [f"-I{d}" for d in includes] + [NATIVE_SOURCE, "-o", NATIVE, "-L" + os.path.join(root, "lib"), "-ltorch_python",
+                                           "-ltorch_cpu", "-lc10", "-lc10_hip", "-L" + HERE, "-l:libts.so", "-Wl,-rpath,$ORIGIN"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if verbose or res.returncode != 0:
+        print(res.stdout)
+        print(res.stderr)
+    if res.returncode != 0:
+        raise RuntimeError("g++ failed building _native.so")
+    return NATIVE
 
 
 SAN_LIB = os.path.join(OBJDIR, "libts_hostsan.so")

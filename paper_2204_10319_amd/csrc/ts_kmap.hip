@@ -2232,6 +2232,10 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
     m->centre = (s == 1) ? (K3 - 1) / 2 : -1;
     if (N == 0) return TS_OK;
 
+    uint64_t *given;   // keys of the caller's coordinates
+    TS_TRY(alloc_n(&given, (size_t)N));
+    m->d_in_keys = given;   // provisional owner, so that an early error frees it
+
     // where the build reports; a build that ends early gives the slot back once nothing can write to it any more
     struct SlotGuard {
         int slot;
@@ -2247,10 +2251,6 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
     const int slot = guard.slot;
     int32_t *d_status = slot_at(slot).dev;
     FillArgs fill;
-
-    uint64_t *given;   // keys of the caller's coordinates
-    TS_TRY(alloc_n(&given, (size_t)N));
-    m->d_in_keys = given;   // provisional owner, so that an early error frees it
 
     Searched table;
     const dim3 per_point(blocks_for(N, kThreads)), block(kThreads);
