@@ -292,7 +292,8 @@ __global__ void __launch_bounds__(kThreads) k_fused(const T *__restrict__ X, con
 // output channels.  A stage is one (offset, KC-channel chunk) of the tile: its weight slab, kept
 // in global memory in operand order, goes global -> registers -> LDS once for the four waves.
 // What a wave pays for is dependent memory round trips, so the loads of a stage are issued DEPTH
-// stages before their use and rotate through DEPTH register sets; one barrier per stage.
+// stages before their use and rotate through DEPTH register sets; one barrier per stage.  (DEPTH = 2;
+// 3 took registers that two more waves can have and measured 2 to 4 % slower.)
 // Rows of an output are added in offset order whatever the tile holds, so results do not depend
 // on how rows are grouped.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
@@ -314,7 +315,7 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
 template <int NCO, int KSTEPS, int DEPTH, bool TWO = false>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCO * KSTEPS <= 8 ? 3 : 2))) k_conv_tile(const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf,
                                                         const int32_t *__restrict__ nbr, int stride,
-                                                        const int32_t *__restrict__ perm,
+                                                        const int32_t *__restrict__ perm, int from_end,
                                                         const int32_t *__restrict__ tile_order, int64_t n_out,
                                                         _Float16 *__restrict__ out, int *__restrict__ sched,
                                                         int cin, int cout, int K3, const _Float16 *__restrict__ bias,
@@ -328,7 +329,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     constexpr int KC = KSTEPS * 32, FRAGS = NCO * KSTEPS, SLAB = FRAGS * 64;   // slab in 16-byte vectors
     constexpr int WV = (SLAB + kThreads - 1) / kThreads;
     __shared__ u32x4 lds_w[2][SLAB];
-    __shared__ int32_t lds_j[kMaxK3][kTileRows];
+    __shared__ int32_t lds_j[kMaxK3][kTileRows], s_row[kTileRows];
     __shared__ uint32_t s_mask;
     __shared__ int s_tile;
     // The launch holds as many workgroups as stay resident at once.  Workgroup b starts with tile b;
@@ -345,44 +346,50 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     // the map build prepared (tiles of rows in input order by descending number of offsets); rows
     // sorted by bitmask put the tiles with the most offsets last, so those are taken from the end.
     int64_t turn = blockIdx.x;
+    // The rows of a tile, known one tile ahead (where they go through perm, that is a memory latency less per tile):
+    // in the prologue, the 16-byte chunks of a table row go to neighbouring lanes, so that one load instruction
+    // covers whole rows (a row touched by several instructions costs a request each).
+    const int row_chunks = stride / 4;                                           // 8, 4 or 1 lanes per row
+    const int row_ch = threadIdx.x % row_chunks, row_sub = threadIdx.x / row_chunks;
+    const int rows_per_pass = kThreads / row_chunks;                             // 32, 64 or 256
+    int32_t kk[4];                                                               // -2: no row of the tile in this pass
+    auto rows_of = [&](int64_t t) __attribute__((always_inline)) {
+        const int64_t tile = from_end ? n_tiles - 1 - t : (tile_order ? tile_order[t] : t);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int col = i * rows_per_pass + row_sub;
+            const int64_t pos = tile * kTileRows + col;
+            kk[i] = -2;
+            if (col < kTileRows) kk[i] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
+        }
+    };
+    if (turn < n_tiles) rows_of(turn);
     while (turn < n_tiles) {
-    const int64_t tile = perm ? n_tiles - 1 - turn : (tile_order ? tile_order[turn] : turn);
     // ask for the next tile now; the answer is needed when this one is done
     int ticket = 0;
     if (threadIdx.x == 0) ticket = atomicAdd(&sched[xcd * 32], 1);
 
-    // Neighbour rows of the tile's outputs -> LDS (offset-major), and the OR of their offset
-    // bitmasks.  The 16-byte chunks of a table row go to neighbouring lanes, so that one load
-    // instruction covers whole rows (a row touched by several instructions costs a request each).
+    // Neighbour rows of the tile's outputs -> LDS (offset-major), and the OR of their offset bitmasks.
     if (threadIdx.x == 0) s_mask = 0;
     __syncthreads();
     {
-        const int chunks = stride / 4;                       // 8, 4 or 1 lanes per row
-        const int ch = threadIdx.x % chunks, sub = threadIdx.x / chunks;
-        const int rows_per_pass = kThreads / chunks;         // 32, 64 or 256
         int4 v[4];
-        int32_t kk[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int col = i * rows_per_pass + sub;
-            const int64_t pos = tile * kTileRows + col;
-            kk[i] = -2;                                      // -2: no row of the tile in this pass
-            if (col < kTileRows) kk[i] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
             v[i] = make_int4(-1, -1, -1, -1);
-            if (kk[i] >= 0) v[i] = reinterpret_cast<const int4 *>(nbr + (int64_t)kk[i] * stride)[ch];
+            if (kk[i] >= 0) v[i] = reinterpret_cast<const int4 *>(nbr + (int64_t)kk[i] * stride)[row_ch];
         }
         uint32_t mm = 0;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             if (kk[i] == -2) continue;
-            const int col = i * rows_per_pass + sub;
+            const int col = i * rows_per_pass + row_sub;
             const int32_t k = kk[i];
+            if (row_ch == 0) s_row[col] = k;
             const int32_t e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int idx = ch * 4 + q;
-                // the row's offsets are read off its entries (the bitmask word of the table and
-                // the centre entry may not have been written yet: a map's row pass runs on demand)
+                const int idx = row_ch * 4 + q;
                 if (idx < K3) {
                     const int32_t j = idx == centre ? k : (k >= 0 ? e[q] : -1);
                     lds_j[idx][col] = j;
@@ -515,6 +522,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         for (int s0 = 0; s0 < nstage; s0 += DEPTH) static_for<DEPTH>([&](auto dc) __attribute__((always_inline)) { run(s0 + decltype(dc)::value, dc); });
     }
 
+    const int32_t out_row[2] = {s_row[r0], s_row[r1]};
+    if (threadIdx.x == 0) s_tile = ticket;
+    __syncthreads();   // the tile's LDS is free; s_tile is set
+    turn = (int64_t)gridDim.x + xcd + 8 * (int64_t)s_tile;
+    if (turn < n_tiles) rows_of(turn);
+
     // lane l holds, per block, output channels 4 * (l / 16) + 0..3 of rows r0 (c2 = 0) and r1 (c2 = 1).
     // What the tail adds is asked for in one go per kind (all blocks' bias words, then all blocks' residual
     // words of a row) and used afterwards: a load placed next to its use costs a round trip per block.
@@ -531,8 +544,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     }
 #pragma unroll
     for (int c2 = 0; c2 < 2; ++c2) {
-        const int64_t pos = tile * kTileRows + (c2 ? r1 : r0);
-        const int64_t row = perm ? perm[pos] : (pos < n_out ? pos : -1);
+        const int64_t row = out_row[c2];
         if (row < 0) continue;
         const int64_t at = row * cout + cb0 * 16 + g * 4;
         // the layer's own result, rounded once to fp16 (the accumulators' registers are free from here on) ...
@@ -563,9 +575,6 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
 #pragma unroll
         for (int cb = 0; cb < NCO; ++cb) *reinterpret_cast<half4 *>(out + at + cb * 16) = v[cb];
     }
-    if (threadIdx.x == 0) s_tile = ticket;
-    __syncthreads();   // the tile's LDS is free; s_tile is set
-    turn = (int64_t)gridDim.x + xcd + 8 * (int64_t)s_tile;
     }
     // the last workgroup to leave rearms the counters for the next launch on this map
     if (threadIdx.x == 0 && atomicAdd(&sched[8 * 32], 1) == (int)gridDim.x - 1) {
@@ -1152,7 +1161,7 @@ int run_fused_staged(const ts_tensor *feats, const ts_tensor *weights, const ts_
     return TS_OK;
 }
 
-constexpr int kTileDepth = 3;
+constexpr int kTileDepth = 2;
 
 // What follows the layer's sum, if anything: y = act(conv + bias + residual) (see ts_sparse_conv_act).
 struct Epilogue {
@@ -1196,8 +1205,10 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     const int64_t resident = (int64_t)compute_units() * per_cu;
     dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
     const int cin1 = TWO ? sec.cin1 : cin_pad;
+    const int32_t *perm = kmap->d_perm ? kmap->d_perm : kmap->d_window_perm;
     TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, kTileDepth, TWO>), grid, dim3(kThreads), x,
-              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, kmap->d_perm, kmap->scan_done || kmap->scan_enqueued ? kmap->d_tile_order : nullptr,
+              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
+              !perm && (kmap->scan_done || kmap->scan_enqueued) ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
               static_cast<const _Float16 *>(ep.bias), static_cast<const _Float16 *>(ep.residual), ep.relu,
               (int)((size_t)kmap->n_in * cin1 * 2), (int)((size_t)kmap->K3 * cin_pad * out->cols * 2), kmap->centre,
@@ -1270,6 +1281,15 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             return TS_OK;
         }
     }
+    // Rows ordered by the offsets they meet (5 to 9 us, once per map) make a layer 7 to 20 % faster on scans and
+    // surfaces of more than about a tile per compute unit and 25 to 45 % faster on scattered points (153 k LiDAR
+    // points: 64 channels 43.9 -> 40.9 us, 96: 62 -> 55, 128: 92 -> 73); below that the longest tile decides.
+    // A map that has served a layer will serve more; one that has not is ordered only for a layer that gains more
+    // than the ordering takes.  (Not for a caller that cannot allocate.)
+    if (!wbuf && kmap->n_tiles > compute_units() &&
+        (kmap->uses > 0 || (kmap->n_tiles > 2 * compute_units() && cin_pad * cout >= 128 * 128)))
+        order_windows(kmap);
+    ++const_cast<ts_kmap *>(kmap)->uses;
     // Output channels per workgroup: as many as divide C_out (every slice gathers the rows again), fewer
     // when the launch would leave most of the chip idle: a lone workgroup per CU walks its stages one
     // after the other, and a stage of eight output blocks takes twice as long as one of four.

@@ -94,6 +94,13 @@ int resolve_count(const struct ::ts_kmap *kmap);
 // Enqueues, without waiting, what an asynchronous build put off (ts_kmap_prepare).
 int prepare(const struct ::ts_kmap *kmap);
 
+// Enqueues the ordering of a map's rows for the output-stationary kernel (d_window_perm).  Without effect, and
+// without an error, where it cannot be done: no bitmasks by row, no memory, a stream that is being captured.
+void order_windows(const struct ::ts_kmap *kmap);
+
+// Whether the library's stream is being captured into a graph.
+bool stream_capturing();
+
 // Makes sure the offset-major pair lists of a map exist (they are derived on first use).
 int ensure_pairs(const struct ::ts_kmap *kmap);
 
@@ -176,6 +183,11 @@ struct ts_kmap {
     uint64_t *d_colbits = nullptr;        // [K3][n_blocks] bit r: output 64*b + r has offset n
     int32_t *d_colbase = nullptr;         // [K3][n_blocks] pairs of offset n in the blocks before b (until the scan: in block b)
     uint32_t *d_wavemask = nullptr;       // [n_blocks] offsets met by any of the block's outputs
+    uint32_t *d_rowmask = nullptr;        // [n_out] offsets met by every output, 3x3x3 stride-1 maps searched in blocks (else NULL)
+    // The same rows in another order, for the output-stationary kernel (ts::order_windows): inside a window of
+    // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it.
+    int32_t *d_window_perm = nullptr;     // [n_tiles*kTileRows] position -> output row, -1 = padding; tiles longest first
+    int uses = 0;                         // layers that the output-stationary kernel has run on this map
     int32_t *d_parent = nullptr;          // [n_in] output of every input (-1: none), 2x2x2 stride-2 maps only (else NULL)
     // Optional (ts_kmap_sort_rows): output rows ordered by offset bitmask, so that the rows of a
     // tile of the output-stationary kernel share their offsets.  NULL = natural row order.

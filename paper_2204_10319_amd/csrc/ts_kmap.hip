@@ -558,7 +558,7 @@ __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict_
 __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__restrict__ keys, int64_t n, BlockTable t,
                                                            int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
                                                            int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
-                                                           int64_t n_blocks, int *status) {
+                                                           int64_t n_blocks, uint32_t *__restrict__ rowmask, int *status) {
     if (blockIdx.x == 0 && threadIdx.x == 0) tell_host(status, ST_SEARCHED, 1);   // the insertion kernel came before
     constexpr int K3 = 27, STRIDE = 32, WORDS = 28, PITCH = 29;   // an odd pitch: a thread's writes of its row are conflict-free
     __shared__ union {
@@ -640,6 +640,7 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
         if (q != K3 / 2 && ((mask >> q) & 1u)) j[q] = t.rows[at[q]];
     }
     if (ok) j[K3 / 2] = (int32_t)k;
+    if (k < n) rowmask[k] = mask;
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < K3; ++q) lds.rows[tid * PITCH + q] = j[q];
@@ -655,6 +656,117 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
         }
     }
     finish_rows<K3>(mask, colbits, colcnt, wavemask, n_blocks);
+}
+
+// Row order for the output-stationary kernel: a tile of 128 rows walks every offset that any of its rows meets
+// (natural order of a LiDAR scan: 15.5 of 27, 1.85 times the matrix work there is), so rows that meet the same
+// offsets should share tiles.  Sorting all rows by bitmask does that best but costs as much as a map; inside a
+// window of 4096 rows one counting sort by 12 bits of the bitmask gets nearly there (7.4 offsets per tile, 1.2): the
+// three z levels met first, then the nine (x, y) columns, which beats the bitmask as a number.  A workgroup per
+// window; the tiles of all windows are dealt out longest first, window by window, so that the longest start first.
+// 9 us for 153 k rows, most of it latency (additions in LDS that return, three scans); it was 15 us with lanes on
+// neighbouring rows.  Where a row ends up among rows of equal keys depends on arrival; no result depends on that.
+constexpr int kWindowRows = 4096, kWindowThreads = 512, kWindowPer = kWindowRows / kWindowThreads, kWindowBins = 4096;
+constexpr int kWindowTiles = kWindowRows / kTileRows;
+__device__ __forceinline__ uint32_t window_key(uint32_t m) {
+    uint32_t z = m | m >> 9 | m >> 18;
+    z |= z >> 3 | z >> 6;
+    uint32_t c = (m | m >> 1 | m >> 2) & 0x01249249u;   // bit 3 c: column c is met; then the nine bits are moved together
+    c = (c | c >> 2) & 0x030C30C3u;
+    c = (c | c >> 4) & 0x0300F00Fu;
+    c = (c | c >> 8) & 0xFF0000FFu;
+    c = (c | c >> 16) & 0x1FFu;
+    return (z & 7u) << 9 | c;
+}
+__global__ void __launch_bounds__(kWindowThreads) k_window_sort(const uint32_t *__restrict__ rowmask, int64_t n, int32_t *__restrict__ perm) {
+    __shared__ int bins[kWindowBins];
+    __shared__ uint32_t smask[kWindowRows];
+    __shared__ uint16_t srow[kWindowRows];
+    __shared__ int wave_sum[kWindowThreads / 64], length[kWindowTiles], place[kWindowTiles];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kWindowRows;
+    const int rows = (int)min((int64_t)kWindowRows, n - base), tiles = (rows + kTileRows - 1) / kTileRows;
+    // Neighbouring rows often have one key, and additions to one word of LDS are served one after the other: the
+    // lanes of a wave take rows that are far apart.
+    const int mine = (lane * (kWindowThreads / 64) + wave) * kWindowPer;
+    uint32_t m[kWindowPer], key[kWindowPer];
+#pragma unroll
+    for (int i = 0; i < kWindowPer; i += 4) {   // (the array is padded to whole vectors)
+        uint4 v = make_uint4(0, 0, 0, 0);
+        if (mine + i < rows) v = *reinterpret_cast<const uint4 *>(rowmask + base + mine + i);
+        m[i] = v.x, m[i + 1] = v.y, m[i + 2] = v.z, m[i + 3] = v.w;
+    }
+#pragma unroll
+    for (int i = 0; i < kWindowBins / kWindowThreads; ++i) bins[i * kWindowThreads + tid] = 0;
+    __syncthreads();
+    int rank[kWindowPer];
+#pragma unroll
+    for (int i = 0; i < kWindowPer; ++i) {
+        key[i] = window_key(m[i]);
+        rank[i] = mine + i < rows ? atomicAdd(&bins[key[i]], 1) : 0;
+    }
+    __syncthreads();
+    // bins -> where each begins
+    constexpr int B = kWindowBins / kWindowThreads;
+    int v[B], sum = 0;
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        v[i] = bins[tid * B + i];
+        sum += v[i];
+    }
+    int incl = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += up;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    int at = incl - sum;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+#pragma unroll
+    for (int i = 0; i < B; ++i) {
+        bins[tid * B + i] = at;
+        at += v[i];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kWindowPer; ++i) {
+        if (mine + i < rows) {
+            const int pos = bins[key[i]] + rank[i];
+            smask[pos] = m[i];
+            srow[pos] = (uint16_t)(mine + i);
+        }
+    }
+    __syncthreads();
+    constexpr int TPW = kWindowTiles / (kWindowThreads / 64);   // tiles per wave, side by side
+    uint32_t any[TPW];
+#pragma unroll
+    for (int q = 0; q < TPW; ++q) {
+        const int p = (wave * TPW + q) * kTileRows + lane;
+        any[q] = (p < rows ? smask[p] : 0u) | (p + 64 < rows ? smask[p + 64] : 0u);
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1)
+#pragma unroll
+        for (int q = 0; q < TPW; ++q) any[q] |= (uint32_t)__shfl_xor((int)any[q], d, 64);
+    if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < TPW; ++q) length[wave * TPW + q] = __builtin_popcount(any[q]);
+    }
+    __syncthreads();
+    if (tid < tiles) {
+        int s = 0;
+        const int own = length[tid];
+#pragma unroll
+        for (int o = 0; o < kWindowTiles; ++o) s += o < tiles && (length[o] > own || (length[o] == own && o < tid));
+        // the s-th longest tiles of all windows come before the (s + 1)-th; the last window has fewer of them
+        const int windows = (int)gridDim.x;
+        const int64_t last = (n - (int64_t)(windows - 1) * kWindowRows + kTileRows - 1) / kTileRows;
+        place[tid] = (int)(s < last ? s * (int64_t)windows + blockIdx.x : last * windows + (s - last) * (windows - 1) + blockIdx.x);
+    }
+    __syncthreads();
+    for (int p = tid; p < tiles * kTileRows; p += kWindowThreads)
+        perm[(int64_t)place[p / kTileRows] * kTileRows + p % kTileRows] = p < rows ? (int32_t)(base + srow[p]) : -1;
 }
 
 // ts_kmap_sort_rows, step 1: register every row's bitmask in the mask table; slot_rank[k] = (table
@@ -1767,6 +1879,8 @@ void destroy(ts_kmap *m) {
     dev_free(m->d_tile_order);
     dev_free(m->d_wavemask);
     dev_free(m->d_parent);
+    dev_free(m->d_rowmask);
+    dev_free(m->d_window_perm);
     delete m;
 }
 
@@ -2264,8 +2378,9 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             TS_TRY(make_block_table(tmp, N, &bt, &fill));
             TS_TRY(launch_fill(fill));
             TS_LAUNCH("k_block_insert", k_block_insert, per_point, block, c4, N, given, bt, d_status);
+            TS_TRY(alloc_n(&m->d_rowmask, ((size_t)N + 3) & ~size_t(3)));
             TS_LAUNCH("k_block_search", k_block_search, per_point, block, given, N, bt, m->d_nbr, m->d_colbits, m->d_colbase,
-                      m->d_wavemask, m->n_blocks, d_status);
+                      m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
             guard.committed = true;
             return finish(m, slot, wait, true);
         }
@@ -2432,6 +2547,13 @@ int prepare(const ts_kmap *kmap) {
     m->scan_enqueued = true;
     TS_HIP(hipGetLastError());
     return TS_OK;
+}
+
+void order_windows(const ts_kmap *kmap) {
+    ts_kmap *m = const_cast<ts_kmap *>(kmap);
+    if (!m->d_rowmask || m->d_window_perm || m->d_perm || m->n_out == 0 || stream_capturing()) return;
+    if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) return;
+    TS_LAUNCH("k_window_sort", k_window_sort, dim3(blocks_for(m->n_out, kWindowRows)), dim3(kWindowThreads), m->d_rowmask, m->n_out, m->d_window_perm);
 }
 
 Offs offs_of(const ts_kmap *kmap) {

@@ -88,6 +88,8 @@ bool capturing() {
 }
 }  // namespace
 
+bool stream_capturing() { return capturing(); }
+
 // A freed block goes back to work only in stream order.  Blocks given back on the stream the library is on
 // now are reused at once (later work on that stream comes after whatever still uses them).  A block given
 // back on another stream is taken only after that stream has drained, and never while the current stream

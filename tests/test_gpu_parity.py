@@ -816,6 +816,28 @@ def test_sorted_rows_give_the_same_result(lidar_coords, K, s, transposed):
                    "sorted rows")
 
 
+@pytest.mark.parametrize("n", [32768, 32769, 36864, 36865, 36864 + 4095, 40000])
+@pytest.mark.parametrize("c", [64, 96])
+def test_rows_of_a_map_in_use_are_reordered(n, c):
+    """From its second layer on, a large enough map has its rows ordered by the offsets they meet inside windows of
+    4096: whole windows, a window of one row, a last tile of one row.  Same bits as the first layer; a ReLU layer with
+    bias and residual on the reordered rows; and the ordering of ts_kmap_sort_rows on top of it."""
+    coords = _rand_coords(9000 + n, n, -22, 23)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1, wait=False)
+    x = to_dev(features(n, n, c, np.float16))
+    w = ts.ts_weights_prepare(to_dev(conv_weights(n + 1, 27, c, 64, np.float16)))
+    bias, res = to_dev(features(3, 1, 64, np.float16)[0].copy()), to_dev(features(4, n, 64, np.float16))
+    fresh = ts.ts_build_kmap(to_dev(coords), 3, 1)
+    tail = ts.ts_sparse_conv_prepared(x, w, fresh, bias, res, relu=True)
+    first = ts.ts_sparse_conv_prepared(x, w, kmap)
+    for _ in range(2):
+        assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), first)
+    assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap, bias, res, relu=True), tail)
+    kmap.sort_rows()
+    assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), first)
+    check_features(first, oracle_conv(coords, x.cpu().numpy(), conv_weights(n + 1, 27, c, 64, np.float16), 3, 1), torch.float16)
+
+
 def test_sorted_rows_many_distinct_masks():
     """Uniform random occupancy gives more distinct bitmasks than the mask table ranks (the radix-sort path)."""
     coords = _rand_coords(91, 120000, 0, 64)
