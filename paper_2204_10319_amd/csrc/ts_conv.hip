@@ -310,10 +310,78 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
     static_for_impl(fn, std::make_integer_sequence<int, N>{});
 }
 
+// Epilogue of the two kernels below.  A lane holds, per block of 16 output channels, channels 4 (l / 16) .. +3 of rows
+// l % 16 and 16 + l % 16 of the wave's 32: stored from there, an instruction writes 32 bytes each of 16 rows, in
+// 64 separate accesses.  Through LDS (16 rows at a time, `buf`: NCO KiB / 2 that only this wave touches, 16-byte units
+// swizzled by row) rows leave, and the residual's come in, as whole lines.
+template <int NCO>
+struct RowStore {
+    static constexpr int UPR = NCO * 2, PER = NCO / 2;   // 16-byte units per row; units per lane and half of the rows
+    typedef _Float16 half8u __attribute__((ext_vector_type(8)));
+    half4 sum[2][NCO];
+    int32_t row[2][PER];
+    half8u res[2][PER];
+    __device__ __forceinline__ static int swizzle(int r) { return NCO % 4 == 0 ? r & 7 : r & 3; }
+    // rows: the lane's two output rows (-1: none).  Takes the layer's own result, rounded once to fp16, and asks for
+    // the residual.
+    __device__ __forceinline__ void open(const floatx4 (&acc)[NCO][2], const int32_t (&rows)[2], const _Float16 *residual, int cout, int co0) {
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+            for (int cb = 0; cb < NCO; ++cb)
+                sum[c2][cb] = half4{(_Float16)acc[cb][c2][0], (_Float16)acc[cb][c2][1], (_Float16)acc[cb][c2][2], (_Float16)acc[cb][c2][3]};
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));   // what follows from the lane number is worked out here, not kept through the stage loop
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2)
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                row[c2][i] = __shfl(rows[c2], (i * 64 + lane) / UPR, 64);
+                if (residual && row[c2][i] >= 0)
+                    res[c2][i] = *reinterpret_cast<const half8u *>(residual + (int64_t)row[c2][i] * cout + co0 + (i * 64 + lane) % UPR * 8);
+            }
+    }
+    __device__ __forceinline__ void store(u32x4 *buf, _Float16 *out, const _Float16 *bias, bool residual,
+                                          int relu, int cout, int co0) const {
+        int lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));
+        const int m16 = lane & 15, g = lane >> 4;
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) {
+#pragma unroll
+            for (int cb = 0; cb < NCO; ++cb)
+                reinterpret_cast<half4 *>(buf + m16 * UPR + ((cb * 2 + (g >> 1)) ^ swizzle(m16)))[g & 1] = sum[c2][cb];
+            __builtin_amdgcn_wave_barrier();   // LDS serves a wave's accesses in order
+#pragma unroll
+            for (int i = 0; i < PER; ++i) {
+                const int r = (i * 64 + lane) / UPR, c = (i * 64 + lane) % UPR;
+                half8u v;
+                const u32x4 raw = buf[r * UPR + (c ^ swizzle(r))];
+                __builtin_memcpy(&v, &raw, 16);
+                if (row[c2][i] < 0) continue;
+                // if asked for, what ts_bias_act would do with it: fp32 sum, ReLU, one rounding
+                if (bias || residual || relu) {
+                    half8u bv;
+                    if (bias) bv = *reinterpret_cast<const half8u *>(bias + co0 + c * 8);
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        float f = (float)v[e];
+                        if (bias) f += (float)bv[e];
+                        if (residual) f += (float)res[c2][i][e];
+                        v[e] = (_Float16)(relu && f < 0.f ? 0.f : f);
+                    }
+                }
+                *reinterpret_cast<half8u *>(out + (int64_t)row[c2][i] * cout + co0 + c * 8) = v;
+            }
+            __builtin_amdgcn_wave_barrier();
+        }
+    }
+};
+
 // (Three waves per SIMD are asked for wherever the accumulators leave room: left to itself the compiler
 // takes a few registers more than that allows for the six- and eight-block single-step variants.)
-template <int NCO, int KSTEPS, int DEPTH, bool TWO = false>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCO * KSTEPS <= 8 ? 3 : 2))) k_conv_tile(const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf,
+template <int NCO, int KSTEPS, int LKS, int DEPTH, bool TWO = false>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCO * KSTEPS <= 8 && NCO < 8 ? 3 : 2))) k_conv_tile(const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf,
                                                         const int32_t *__restrict__ nbr, int stride,
                                                         const int32_t *__restrict__ perm, int from_end,
                                                         const int32_t *__restrict__ tile_order, int64_t n_out,
@@ -431,12 +499,15 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
     constexpr int kNoRow = (int)0x80000000u;   // beyond any buffer this kernel is launched with
     const int row_bytes = cin1 * 2, xlane = g * 16;
-    int wlane[WV];
+    // A fragment of the slab (16 output channels, 32 input channels) is 1 KiB; in memory LKS steps of one block of
+    // output channels follow each other, of which a stage takes KSTEPS.
+    int wlane[WV], wslot[WV];
 #pragma unroll
     for (int v = 0; v < WV; ++v) {
         int idx = threadIdx.x + v * kThreads;
         if (SLAB % kThreads != 0) idx = idx < SLAB ? idx : SLAB - 1;   // surplus threads repeat the last vector
-        wlane[v] = idx * 16;
+        wslot[v] = idx;
+        wlane[v] = ((idx >> 6) / KSTEPS * LKS + (idx >> 6) % KSTEPS) * 1024 + (idx & 63) * 16;
     }
     uint32_t it_rem = mask ? mask : 1u;   // offsets not issued yet; the lowest set bit is the one being issued
     int it_ch = 0;                        // its chunk
@@ -460,7 +531,8 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         }
         pj0 = lds_j[__builtin_ctz(it_rem)][r0];
         pj1 = lds_j[__builtin_ctz(it_rem)][r1];
-        const int wsoff = (((n * nchunks + ch) * cblocks + cb0) * KSTEPS) * 1024;
+        const uint32_t per = LKS / KSTEPS, group = (uint32_t)(n * nchunks + ch) / per;   // (an offset's chunks are whole groups)
+        const int wsoff = ((int)group * cblocks + cb0) * (LKS * 1024) + (n * nchunks + ch - (int)(group * per)) * (KSTEPS * 1024);
 #pragma unroll
         for (int v = 0; v < WV; ++v) wreg[d][v] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane[v], wsoff, 0);
         xlive[d] = real && __ballot(j0 >= 0 || j1 >= 0) != 0;   // false: none of the wave's rows has this offset
@@ -493,7 +565,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         constexpr int d = decltype(dc)::value;
         u32x4 *slab = lds_w[s & 1];
 #pragma unroll
-        for (int v = 0; v < WV; ++v) slab[wlane[v] >> 4] = wreg[d][v];
+        for (int v = 0; v < WV; ++v) slab[wslot[v]] = wreg[d][v];
         __syncthreads();   // slab complete; everybody is done with the other slab
         if (xlive[d]) {
 #pragma unroll
@@ -523,58 +595,17 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
     }
 
     const int32_t out_row[2] = {s_row[r0], s_row[r1]};
+    RowStore<NCO> rows;
+    rows.open(acc, out_row, residual, cout, cb0 * 16);
     if (threadIdx.x == 0) s_tile = ticket;
     __syncthreads();   // the tile's LDS is free; s_tile is set
     turn = (int64_t)gridDim.x + xcd + 8 * (int64_t)s_tile;
     if (turn < n_tiles) rows_of(turn);
-
-    // lane l holds, per block, output channels 4 * (l / 16) + 0..3 of rows r0 (c2 = 0) and r1 (c2 = 1).
-    // What the tail adds is asked for in one go per kind (all blocks' bias words, then all blocks' residual
-    // words of a row) and used afterwards: a load placed next to its use costs a round trip per block.
-    half4 bv[NCO];
-#pragma unroll
-    for (int cb = 0; cb < NCO; ++cb) bv[cb] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
-    if (bias) {
-        // (the pointer is made opaque per tile: loads the compiler can prove the same for every tile move to the
-        // top of the kernel and hold registers through the stage loop, which has none to spare)
-        const _Float16 *bp = bias;
-        asm volatile("" : "+s"(bp));
-#pragma unroll
-        for (int cb = 0; cb < NCO; ++cb) bv[cb] = *reinterpret_cast<const half4 *>(bp + cb0 * 16 + cb * 16 + g * 4);
-    }
-#pragma unroll
-    for (int c2 = 0; c2 < 2; ++c2) {
-        const int64_t row = out_row[c2];
-        if (row < 0) continue;
-        const int64_t at = row * cout + cb0 * 16 + g * 4;
-        // the layer's own result, rounded once to fp16 (the accumulators' registers are free from here on) ...
-        half4 v[NCO];
-#pragma unroll
-        for (int cb = 0; cb < NCO; ++cb)
-            v[cb] = half4{(_Float16)acc[cb][c2][0], (_Float16)acc[cb][c2][1], (_Float16)acc[cb][c2][2], (_Float16)acc[cb][c2][3]};
-        // ... then, if asked for, what ts_bias_act would do with it: fp32 sum, ReLU, one rounding
-        if (bias || residual || relu) {
-            half4 rv[NCO];
-#pragma unroll
-            for (int cb = 0; cb < NCO; ++cb) rv[cb] = half4{(_Float16)0.f, (_Float16)0.f, (_Float16)0.f, (_Float16)0.f};
-            if (residual) {
-#pragma unroll
-                for (int cb = 0; cb < NCO; ++cb) rv[cb] = *reinterpret_cast<const half4 *>(residual + at + cb * 16);
-            }
-#pragma unroll
-            for (int cb = 0; cb < NCO; ++cb) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    float f = (float)v[cb][e];
-                    if (bias) f += (float)bv[cb][e];
-                    if (residual) f += (float)rv[cb][e];
-                    v[cb][e] = (_Float16)(relu && f < 0.f ? 0.f : f);
-                }
-            }
-        }
-#pragma unroll
-        for (int cb = 0; cb < NCO; ++cb) *reinterpret_cast<half4 *>(out + at + cb * 16) = v[cb];
-    }
+    // (the pointer is made opaque per tile: loads the compiler can prove the same for every tile move to the
+    // top of the kernel and hold registers through the stage loop, which has none to spare)
+    const _Float16 *bp = bias;
+    asm volatile("" : "+s"(bp));
+    rows.store(&lds_w[0][0] + wave * (NCO * 32), out, bp, residual != nullptr, relu, cout, cb0 * 16);
     }
     // the last workgroup to leave rearms the counters for the next launch on this map
     if (threadIdx.x == 0 && atomicAdd(&sched[8 * 32], 1) == (int)gridDim.x - 1) {
@@ -731,33 +762,15 @@ __global__ void __launch_bounds__(kResThreads) k_conv_res(const _Float16 *__rest
         // the reads of lds_j issued last belong to no stage: they must have returned before the next unit overwrites it
         __builtin_amdgcn_wave_barrier();
 
+        int32_t out_row[2];
 #pragma unroll
         for (int c2 = 0; c2 < 2; ++c2) {
             const int64_t pos = unit * kResRows + (c2 ? r1 : r0);
-            const int64_t row = perm ? perm[pos] : (pos < n_out ? pos : -1);
-            if (row < 0) continue;
-            const int64_t at = row * cout + cb0 * 16 + g * 4;
-#pragma unroll
-            for (int cb = 0; cb < NCO; ++cb) {
-                half4 v = {(_Float16)acc[cb][c2][0], (_Float16)acc[cb][c2][1], (_Float16)acc[cb][c2][2], (_Float16)acc[cb][c2][3]};
-                if (bias || residual || relu) {
-                    float f[4] = {(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
-                    if (bias) {
-                        const half4 b = *reinterpret_cast<const half4 *>(bias + cb0 * 16 + cb * 16 + g * 4);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) f[e] += (float)b[e];
-                    }
-                    if (residual) {
-                        const half4 r = *reinterpret_cast<const half4 *>(residual + at + cb * 16);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e) f[e] += (float)r[e];
-                    }
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) v[e] = (_Float16)(relu && f[e] < 0.f ? 0.f : f[e]);
-                }
-                *reinterpret_cast<half4 *>(out + at + cb * 16) = v;
-            }
+            out_row[c2] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
         }
+        RowStore<NCO> rows;
+        rows.open(acc, out_row, residual, cout, cb0 * 16);
+        rows.store(reinterpret_cast<u32x4 *>(lds_j), out, bias, residual != nullptr, relu, cout, cb0 * 16);
         ticket = __builtin_amdgcn_readfirstlane(ticket);
         turn = n_waves + xcd + 8 * (int64_t)ticket;
     }
@@ -1163,6 +1176,11 @@ int run_fused_staged(const ts_tensor *feats, const ts_tensor *weights, const ts_
 
 constexpr int kTileDepth = 2;
 
+// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes, except
+// that stages of 96 channels are taken only while there is at most a tile per compute unit, where a stage's latency
+// decides (20 k points, 96 -> 96: 23.9 -> 19.8 us against stages of 32); on larger maps they cost a wave per SIMD.
+inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : cin_pad % 96 == 0 ? 3 : 1; }
+
 // What follows the layer's sum, if anything: y = act(conv + bias + residual) (see ts_sparse_conv_act).
 struct Epilogue {
     const void *bias = nullptr;
@@ -1189,14 +1207,14 @@ struct Second {
     int cin1 = 0;
 };
 
-template <int NCO, int KSTEPS, bool TWO = false>
+template <int NCO, int KSTEPS, bool TWO = false, int LKS = KSTEPS>
 void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap, ts_tensor *out, int cin_pad,
                       const Epilogue &ep, const Second &sec = Second()) {
     // as many workgroups as stay resident at once, fewer for small maps
     static int per_cu = 0;   // per instantiation
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_tile<NCO, KSTEPS, kTileDepth, TWO>, kThreads, 0) != hipSuccess || n <= 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>, kThreads, 0) != hipSuccess || n <= 0) {
             (void)hipGetLastError();
             n = 2;
         }
@@ -1206,7 +1224,7 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
     const int cin1 = TWO ? sec.cin1 : cin_pad;
     const int32_t *perm = kmap->d_perm ? kmap->d_perm : kmap->d_window_perm;
-    TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, kTileDepth, TWO>), grid, dim3(kThreads), x,
+    TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>), grid, dim3(kThreads), x,
               reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
               !perm && (kmap->scan_done || kmap->scan_enqueued) ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
@@ -1245,7 +1263,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     typedef _Float16 T;
     const int cin = feats->cols, cout = out->cols;
     const int cin_pad = (cin + 31) / 32 * 32;
-    const int ksteps = cin_pad % 64 == 0 ? 2 : 1;
+    const int ksteps = tile_ksteps(cin_pad);
     // the kernel addresses features and weights with 31-bit byte offsets
     if ((size_t)kmap->n_in * cin_pad * 2 >= (1ull << 31) || (size_t)kmap->K3 * cin_pad * cout * 2 >= (1ull << 31)) {
         if (ep.any()) return fail(TS_ERR_UNSUPPORTED, "feature matrix of 2 GiB or more: call ts_sparse_conv and ts_bias_act");
@@ -1271,6 +1289,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         x = xp;
     }
     const int cblocks = cout / 16;
+    const bool one_step = ksteps == 3 && kmap->n_tiles > compute_units();
     // 32 input channels and 27 offsets: the kernel with resident weights (for 2x2x2 maps and for 64 -> 32 it
     // measured no faster than k_conv_tile, and 64 -> 64 in two slices of output channels much slower: every
     // slice gathers all rows again)
@@ -1306,8 +1325,12 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     if (nco == N) {                                                                                \
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);    \
+            else if (one_step) launch_conv_tile<N, 1, true, 3>(x, wf, kmap, out, cin_pad, ep, sec); \
+            else if (ksteps == 3) launch_conv_tile<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \
             else launch_conv_tile<N, 1, true>(x, wf, kmap, out, cin_pad, ep, sec);                \
         } else if (ksteps == 2) launch_conv_tile<N, 2>(x, wf, kmap, out, cin_pad, ep);            \
+        else if (one_step) launch_conv_tile<N, 1, false, 3>(x, wf, kmap, out, cin_pad, ep);       \
+        else if (ksteps == 3) launch_conv_tile<N, 3>(x, wf, kmap, out, cin_pad, ep);              \
         else launch_conv_tile<N, 1>(x, wf, kmap, out, cin_pad, ep);                                \
     }
     TS_TILE_CASE(8) TS_TILE_CASE(6) TS_TILE_CASE(4) TS_TILE_CASE(2)
@@ -1736,7 +1759,7 @@ int ts_weights_prepare(const ts_tensor *weights, int kernel_volume, ts_weights *
     else
         TS_LAUNCH("k_pack_weights", k_pack_weights<float>, dim3(blocks_for((int64_t)n_wt, kThreads)), dim3(kThreads), static_cast<const float *>(weights->data), static_cast<float *>(w->wt), kernel_volume, cin, cin_wt, cout);
     if (f16) {
-        const int cin_tile = (cin + 31) / 32 * 32, ksteps = cin_tile % 64 == 0 ? 2 : 1;
+        const int cin_tile = (cin + 31) / 32 * 32, ksteps = tile_ksteps(cin_tile);
         const size_t n_tile = (size_t)kernel_volume * cout * cin_tile;
         w->tile = dev_alloc(n_tile * 2);
         if (!w->tile) {
