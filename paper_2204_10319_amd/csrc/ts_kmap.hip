@@ -555,6 +555,8 @@ __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict_
 // LDS as whole cache lines, with the centre entry and the offset bitmask, and the presence bitmaps of 64
 // outputs come out of the same pass.  What it replaces - a lane per (point, offset below the centre) probing a
 // table of points, mirrored 4-byte stores, and a second pass over the rows - took 17.4 + 9 us for 153 k points.
+// At: what holds the position of a row number in the table; 32 bits reach 2^26 entries (44.7 M points).
+template <typename At>
 __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__restrict__ keys, int64_t n, BlockTable t,
                                                            int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
                                                            int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
@@ -617,7 +619,8 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
     }
     // Where each neighbour's row number stands, and which neighbours there are.  (A thread reads back only what
     // it wrote itself, by an octant that depends on the lane; all reads first, then all loads they lead to.)
-    uint32_t mask = 0, at[K3];
+    uint32_t mask = 0;
+    At at[K3];
 #pragma unroll
     for (int q = 0; q < K3; ++q) {
         const int d[3] = {q / 9 - 1, (q / 3) % 3 - 1, q % 3 - 1};
@@ -629,7 +632,7 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
             cell |= ((c[a] + (uint32_t)d[a]) & 3u) << (2 * (2 - a));
         }
         const uint64_t m = lds.found.mask[o][tid];
-        at[q] = lds.found.slot[o][tid] * 64 + cell;
+        at[q] = (At)lds.found.slot[o][tid] * 64 + cell;
         mask |= (uint32_t)(m >> cell & 1ull) << q;
     }
     mask = ok ? mask | 1u << (K3 / 2) : 0u;   // (of two equal points one is not in the table: it still has itself)
@@ -2379,8 +2382,12 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             TS_TRY(launch_fill(fill));
             TS_LAUNCH("k_block_insert", k_block_insert, per_point, block, c4, N, given, bt, d_status);
             TS_TRY(alloc_n(&m->d_rowmask, ((size_t)N + 3) & ~size_t(3)));
-            TS_LAUNCH("k_block_search", k_block_search, per_point, block, given, N, bt, m->d_nbr, m->d_colbits, m->d_colbase,
-                      m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
+            if (bt.mask >> 26 == 0)
+                TS_LAUNCH("k_block_search", k_block_search<uint32_t>, per_point, block, given, N, bt, m->d_nbr, m->d_colbits,
+                          m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
+            else
+                TS_LAUNCH("k_block_search", k_block_search<uint64_t>, per_point, block, given, N, bt, m->d_nbr, m->d_colbits,
+                          m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
             guard.committed = true;
             return finish(m, slot, wait, true);
         }

@@ -3,6 +3,8 @@
 Kernel maps must equal the oracle's bit-exactly as sorted (in, out, offset) triples;
 features must agree within a relative L2 error of 1e-5 (fp32) / 2e-3 (fp16 in, fp32 accumulate).
 """
+import math
+
 import numpy as np
 import pytest
 import torch
@@ -102,6 +104,28 @@ def test_kmap_blocks_of_4x4x4(n, order):
         with pytest.raises(ts.TsError) as e:
             ts.ts_build_kmap(to_dev(twice), 3, 1)
         assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
+
+
+def test_kmap_of_more_points_than_32_bit_positions_reach():
+    """A cube of 356^3 = 45.1 M points: the block table has 2^27 entries of 64 row numbers.  In a full cube in raster
+    order every offset's pairs are known: their number, and that output k takes input k + a constant."""
+    side = 356
+    ax = torch.arange(side, dtype=torch.int32, device="cuda")
+    coords = torch.zeros((side ** 3, 4), dtype=torch.int32, device="cuda")
+    for a, g in enumerate(torch.meshgrid(ax, ax, ax, indexing="ij")):
+        coords[:, 1 + a] = g.reshape(-1)
+    kmap = ts.ts_build_kmap(coords, 3, 1)
+    offs = [(i, j, k) for i in (-1, 0, 1) for j in (-1, 0, 1) for k in (-1, 0, 1)]
+    sizes = [math.prod(side - abs(v) for v in d) for d in offs]
+    assert list(kmap.sizes()) == sizes
+    src, dst = (torch.empty(sum(sizes), dtype=torch.int32, device="cuda") for _ in range(2))
+    assert ts.load_library().ts_kmap_pairs(kmap.handle, src.data_ptr(), dst.data_ptr()) == ts.TS_OK
+    at = 0
+    for d, m in zip(offs, sizes):
+        assert bool(((src[at:at + m] - dst[at:at + m]) == (d[0] * side + d[1]) * side + d[2]).all())
+        at += m
+    kmap.free()
+    ts.ts_release_cache()
 
 
 @pytest.mark.parametrize("n,span", [(1, 1), (255, 6), (257, 40), (4096, 8), (140000, 60), (600, 700), (600, 40000)])
