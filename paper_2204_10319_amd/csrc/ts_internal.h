@@ -160,6 +160,8 @@ struct ts_kmap {
     int64_t n_in = 0, n_out = 0, M = 0;   // M, sizes, offs: valid once ts::resolve has run
     bool scan_enqueued = false; // the scan (ranks, sizes, tile order) has been enqueued; resolve only waits for it
     bool scan_done = true;      // false: what the scan leaves is not there yet, or not known to be (the fused kernel needs none of it)
+    bool rows_put_off = false;  // the row pass (bitmask words, centre entries, presence bitmaps) has not been enqueued: it
+                                // goes with the scan (the fused kernels need none of it)
     int pending_slot = -1;      // >= 0: sizes and error flags are still on their way to the host
     bool count_pending = false; // n_out is not known yet (-1): ts::resolve_count reads it
     bool one_pair_per_input = false;   // 2x2x2, stride 2: fewer pairs than inputs means equal inputs

@@ -940,8 +940,9 @@ __global__ void __launch_bounds__(kThreads, 3) k_probe(const uint64_t *__restric
 // (i, j, K^3-1-n) in row j; rows start out all -1.  The 13 offsets of a point sit in neighbouring lanes
 // (16 lanes per point), so a point's own entries land in one cache line of the table.
 __global__ void k_probe_symmetric(const uint64_t *__restrict__ keys, int64_t n_pts, Grid t, int K,
-                                  int32_t *__restrict__ nbr, int stride) {
+                                  int32_t *__restrict__ nbr, int stride, int *status) {
     const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (g == 0) tell_host(status, ST_SEARCHED, 1);   // the insertion kernel came before
     const int64_t i = g >> 4;
     const int n = (int)(g & 15), K3 = K * K * K;
     if (i >= n_pts || n >= K3 / 2) return;
@@ -1924,14 +1925,15 @@ void launch_scan(const ts_kmap *m, int32_t *status) {
 }
 
 // Map search through the hash table or the coordinate grid.  `table` holds the searched point set (the map's
-// inputs), m->d_out_keys the outputs.  Leaves the neighbour rows and the presence bitmaps and counts.
-int search(ts_kmap *m, const Searched &table) {
+// inputs), m->d_out_keys the outputs.  Leaves the neighbour rows and the presence bitmaps and counts; those of the
+// grid's symmetric search come from the row pass, which is left to the caller or to ts::prepare (rows_put_off).
+int search(ts_kmap *m, const Searched &table, int *status) {
     const int K = m->K, mode = m->s == 1 ? MODE_SUB : (m->transposed ? MODE_TR : MODE_FWD);
     const bool symmetric = mode == MODE_SUB && K == 3;   // only the grid: tables of points search k_block_search's way
     if (mode == MODE_SUB && K == 1) launch_probe<MODE_SUB, 1>(m, table);
     else if (symmetric)
         TS_LAUNCH("k_probe_symmetric_grid", k_probe_symmetric, dim3(blocks_for(m->n_out * 16, kThreads)), dim3(kThreads), m->d_out_keys,
-                  m->n_out, table.g, K, m->d_nbr, m->stride);
+                  m->n_out, table.g, K, m->d_nbr, m->stride, status);
     else if (mode == MODE_FWD && K == 1) launch_probe<MODE_FWD, 1>(m, table);
     else if (mode == MODE_TR && K == 1) launch_probe<MODE_TR, 1>(m, table);
     else if (mode == MODE_FWD && K == 2) launch_probe<MODE_FWD, 2>(m, table);
@@ -1943,7 +1945,7 @@ int search(ts_kmap *m, const Searched &table) {
         TS_LAUNCH("k_grid_erase", k_grid_erase, dim3(blocks_for(m->n_in, kThreads)), dim3(kThreads), m->d_in_keys, m->n_in, table.g);
         g_grid_dirty = false;
     }
-    if (symmetric) launch_rows(m);
+    m->rows_put_off = symmetric;
     return TS_OK;
 }
 
@@ -1953,6 +1955,8 @@ int search(ts_kmap *m, const Searched &table) {
 int finish(ts_kmap *m, int slot, bool wait, bool scan_later = false) {
     StatusSlot &sl = slot_at(slot);
     if (!scan_later || wait) {
+        if (m->rows_put_off) launch_rows(m);
+        m->rows_put_off = false;
         launch_scan(m, sl.dev);
         sl.totals = true;
         m->scan_enqueued = true;
@@ -2331,7 +2335,7 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
         if (table.grid) TS_LAUNCH("k_insert_grid", k_insert<Grid>, per_coarse, block, coarse, n_coarse, table.g, d_status);
         else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
     }
-    TS_TRY(search(m, table));
+    TS_TRY(search(m, table, d_status));
     *reports = true;
     return finish(m, slot, wait);
 }
@@ -2398,9 +2402,9 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
             TS_LAUNCH("k_pack_insert_grid", k_pack_insert<Grid>, per_point, block, c4, N, given, table.g, d_status, opt.box, rows);
         else
             TS_LAUNCH("k_pack_insert", k_pack_insert<Table>, per_point, block, c4, N, given, table.t, d_status, opt.box, rows);
-        TS_TRY(search(m, table));
+        TS_TRY(search(m, table, d_status));
         guard.committed = true;
-        return finish(m, slot, wait);
+        return finish(m, slot, wait, m->rows_put_off);   // (9 us for 153 k points that a layer does not need)
     }
     if (K == 2 && s == 2 && !transposed && !opt.bound.on && (opt.grid || opt.measure)) {
         TS_TRY(build_down(tmp, coords, N, m, opt, slot));
@@ -2549,6 +2553,8 @@ int prepare(const ts_kmap *kmap) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
     if (m->scan_done || m->scan_enqueued || m->pending_slot < 0) return TS_OK;   // nothing put off
     StatusSlot &sl = slot_at(m->pending_slot);
+    if (m->rows_put_off) launch_rows(m);
+    m->rows_put_off = false;
     launch_scan(m, sl.dev);
     sl.totals = true;
     m->scan_enqueued = true;
