@@ -1145,6 +1145,33 @@ constexpr int fused_group(int ncb, int ksteps) {
     return ncb * ksteps <= 2 ? 4 : (ncb * ksteps <= 8 ? 3 : 1);
 }
 
+inline int compute_units() {
+    static int n = 0;
+    if (n == 0) {
+        int dev = 0;
+        hipDeviceProp_t prop;
+        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
+        if (n <= 0) n = 256;
+    }
+    return n;
+}
+
+// Rows ordered by the offsets they meet (5 to 9 us, once per map) make a layer 7 to 20 % faster on scans and
+// surfaces of more than about a tile per compute unit and 25 to 45 % faster on scattered points (153 k LiDAR
+// points: 64 channels 43.9 -> 40.9 us, 96: 62 -> 55, 128: 92 -> 73); below that the longest tile decides.
+// Single precision gains more, a pair's work there takes some ten times as long: 153 k LiDAR points, 32 -> 32 channels
+// 63 -> 47 us, 64 -> 64 192 -> 127; 200 k scattered points 120 -> 64, 403 -> 195; 40 k LiDAR points 29 -> 27, 80 -> 71.
+// A map that has served a layer will serve more; one that has not is ordered only for a layer that gains more than
+// the ordering takes (at_once).
+inline void order_for_layer(const ts_kmap *kmap, bool at_once) {
+    if (kmap->n_tiles > compute_units() && (kmap->uses > 0 || at_once)) order_windows(kmap);
+}
+inline bool order_at_once(const ts_kmap *kmap, int cin, int cout, size_t elem) {
+    // (fp32, first layer on a map: 97 k surface points, 32 -> 32 channels, 0.8 M, gains 8 us and pays 7; 153 k LiDAR points, 1.2 M, gains 16)
+    if (elem == 4) return kmap->n_tiles * cin * cout >= 1200000;
+    return kmap->n_tiles > 2 * compute_units() && cin * cout >= 128 * 128;
+}
+
 template <class T>
 struct FusedLaunch {
     const Prepared &pr;
@@ -1157,7 +1184,7 @@ struct FusedLaunch {
         constexpr int G = fused_group(NCB, KSTEPS);
         dim3 grid((unsigned)kmap->n_tiles, out->cols / (NCB * 32));
         TS_LAUNCH("k_fused", (k_fused<T, NCB, KC, G>), grid, dim3(kThreads), static_cast<const T *>(pr.x),
-                  static_cast<const T *>(pr.wt), kmap->d_nbr, kmap->stride, kmap->d_perm, kmap->n_out,
+                  static_cast<const T *>(pr.wt), kmap->d_nbr, kmap->stride, kmap->d_perm ? kmap->d_perm : kmap->d_window_perm, kmap->n_out,
                   static_cast<T *>(out->data), zero, pr.cin_pad, out->cols, kmap->K3, kmap->centre);
     }
 };
@@ -1169,6 +1196,8 @@ int run_fused_staged(const ts_tensor *feats, const ts_tensor *weights, const ts_
     TS_TRY(prepare<T>(feats, weights, kmap, &pr, pw, wbuf));
     const T *zero = static_cast<const T *>(zeros ? zeros : zero_row());
     if (!zero) return last_fail_code();
+    if (!wbuf) order_for_layer(kmap, order_at_once(kmap, pr.cin_pad, out->cols, sizeof(T)));
+    ++const_cast<ts_kmap *>(kmap)->uses;
     dispatch_shape(pick_ncb(out->cols), pick_ksteps(pr.cin_pad, Elem<T>::KSTEP), FusedLaunch<T>{pr, kmap, out, zero});
     TS_HIP(hipGetLastError());
     return TS_OK;
@@ -1188,17 +1217,6 @@ struct Epilogue {
     int relu = 0;
     bool any() const { return bias || residual || relu; }
 };
-
-inline int compute_units() {
-    static int n = 0;
-    if (n == 0) {
-        int dev = 0;
-        hipDeviceProp_t prop;
-        if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess) n = prop.multiProcessorCount;
-        if (n <= 0) n = 256;
-    }
-    return n;
-}
 
 // The second half of a layer input that is the channel concatenation [x | x2] of two tensors (never
 // formed): x has cin1 channels per row, x2 the rest.  x2 == nullptr: one tensor, as usual.
@@ -1300,14 +1318,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             return TS_OK;
         }
     }
-    // Rows ordered by the offsets they meet (5 to 9 us, once per map) make a layer 7 to 20 % faster on scans and
-    // surfaces of more than about a tile per compute unit and 25 to 45 % faster on scattered points (153 k LiDAR
-    // points: 64 channels 43.9 -> 40.9 us, 96: 62 -> 55, 128: 92 -> 73); below that the longest tile decides.
-    // A map that has served a layer will serve more; one that has not is ordered only for a layer that gains more
-    // than the ordering takes.  (Not for a caller that cannot allocate.)
-    if (!wbuf && kmap->n_tiles > compute_units() &&
-        (kmap->uses > 0 || (kmap->n_tiles > 2 * compute_units() && cin_pad * cout >= 128 * 128)))
-        order_windows(kmap);
+    if (!wbuf) order_for_layer(kmap, order_at_once(kmap, cin_pad, cout, sizeof(T)));
     ++const_cast<ts_kmap *>(kmap)->uses;
     // Output channels per workgroup: as many as divide C_out (every slice gathers the rows again), fewer
     // when the launch would leave most of the chip idle: a lone workgroup per CU walks its stages one

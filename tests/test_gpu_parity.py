@@ -862,6 +862,22 @@ def test_rows_of_a_map_in_use_are_reordered(n, c):
     check_features(first, oracle_conv(coords, x.cpu().numpy(), conv_weights(n + 1, 27, c, 64, np.float16), 3, 1), torch.float16)
 
 
+@pytest.mark.parametrize("n", [32769, 36865, 40000])
+@pytest.mark.parametrize("c_out", [32, 96])
+def test_rows_of_a_map_in_use_are_reordered_f32(n, c_out):
+    """The same in single precision: a first layer too small to order the rows, one large enough, and later ones."""
+    coords = _rand_coords(9100 + n, n, -22, 23)
+    x, wn = features(n, n, 32, np.float32), conv_weights(n + 1, 27, 32, c_out, np.float32)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1, wait=False)
+    first = ts.ts_sparse_conv(to_dev(x), to_dev(wn), kmap)
+    for _ in range(2):
+        assert torch.equal(ts.ts_sparse_conv(to_dev(x), to_dev(wn), kmap), first)
+    check_features(first, oracle_conv(coords, x, wn, 3, 1), torch.float32)
+    wide = ts.ts_weights_prepare(to_dev(conv_weights(n + 2, 27, 32, 256, np.float32)))
+    fresh = ts.ts_build_kmap(to_dev(coords), 3, 1)
+    assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x), wide, fresh), ts.ts_sparse_conv_prepared(to_dev(x), wide, kmap))
+
+
 def test_sorted_rows_many_distinct_masks():
     """Uniform random occupancy gives more distinct bitmasks than the mask table ranks (the radix-sort path)."""
     coords = _rand_coords(91, 120000, 0, 64)
