@@ -49,6 +49,7 @@ enum {
     ST_OVERFLOW = 3,    // the bitmask table could not hold them all
     ST_SEARCHED = 4,    // set once every kernel that raises ST_RANGE or ST_DUP has finished
     ST_COUNT = 5,       // output points of a 2x2x2 stride-2 map (-1: not there yet, kBoxTooLarge: build it by sorting)
+    ST_TILES = 6,       // set once the tile order is complete
     ST_TOTALS = 8,      // [32] per-offset map sizes (-1: not there yet)
     ST_BOX = 40,        // [7] lo, hi, batches of the box of a 2x2x2 stride-2 map's outputs, there with ST_COUNT
     ST_WORDS = 48
@@ -57,6 +58,13 @@ enum {
 // A word the host reads.  Every writer of a flag stores the same value.
 __device__ __forceinline__ void tell_host(int *status, int which, int value) {
     __hip_atomic_store(&status[which], value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+// A word that says that what the workgroup has written is complete: whoever has read it may use that, on any stream.
+// (All of the workgroup's threads call it.  Kernels that ran before on the stream are complete anyway.)
+__device__ __forceinline__ void tell_host_done(int *status, int which, int value) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // a barrier alone does not wait for the stores of the other waves
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(&status[which], value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 __device__ __forceinline__ void raise_flag(int *status, int which) { tell_host(status, which, 1); }
 
@@ -1408,7 +1416,8 @@ __global__ void __launch_bounds__(kThreads) k_up_rows(const uint64_t *__restrict
 // Block n: exclusive scan in place of the counts col[n][*] -> col[n][b] = pairs of offset n in the 64-row
 // blocks before b (relative to the start of the offset's list), and the offset's total (the host
 // turns the totals into offs[], the start of each offset's list, and hands them to later kernels
-// by value).
+// by value).  The host takes the totals and ST_TILES for the end of the build, and may hand the map to another stream
+// then: they are told after everything else, by workgroup.
 constexpr int kScanThreads = 1024, kScanItems = 4;
 __global__ void __launch_bounds__(kScanThreads) k_scan(int32_t *__restrict__ col, int64_t n_blocks, int *status, int K3,
                                                        const uint32_t *__restrict__ wavemask, int64_t n_tiles,
@@ -1439,6 +1448,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan(int32_t *__restrict__ col
         }
         __syncthreads();
         for (int64_t t = threadIdx.x; t < n_tiles; t += kScanThreads) tile_order[atomicAdd(&base[offsets_of(t)], 1)] = (int32_t)t;
+        tell_host_done(status, ST_TILES, 1);
         return;
     }
     const int n = blockIdx.x;
@@ -1461,7 +1471,7 @@ __global__ void __launch_bounds__(kScanThreads) k_scan(int32_t *__restrict__ col
         }
         run += total;
     }
-    if (threadIdx.x == 0) tell_host(status, ST_TOTALS + n, run);
+    tell_host_done(status, ST_TOTALS + n, run);
 }
 
 // ts_kmap_sort_rows, step 2: the distinct bitmasks as a dense list of (sort key, rows), followed
@@ -1748,7 +1758,7 @@ inline bool slot_landed(const StatusSlot &s, Awaited what) {
     if (what == kVerdict) return h[ST_SEARCHED] != 0 || (s.totals && slot_landed(s, kSizes));   // sizes come after everything else
     for (int n = 0; n < s.K3; ++n)
         if (h[ST_TOTALS + n] < 0) return false;
-    return true;
+    return h[ST_TILES] != 0;
 }
 
 inline void slot_reset(StatusSlot &s, int K3) {
@@ -2495,6 +2505,7 @@ int resolve_count(const ts_kmap *kmap) {
     TS_TRY(slot_wait(slot, kSizes));   // nothing more is written there
     TS_HIP(hipStreamSynchronize(stream()));
     for (int n = 0; n < kMaxK3; ++n) h[ST_TOTALS + n] = -1;
+    h[ST_TILES] = 0;
     slot_at(slot).totals = false;
     m->count_pending = m->one_pair_per_input = m->scan_enqueued = false;
     for (void *p : {(void *)m->d_nbr, (void *)m->d_colbits, (void *)m->d_colbase, (void *)m->d_tile_order, (void *)m->d_wavemask,
