@@ -1079,6 +1079,7 @@ int check_layer(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap 
     if (feats->dtype != weights->dtype || feats->dtype != out->dtype)
         return fail(TS_ERR_SHAPE, "feats, weights and out must share one dtype");
     TS_TRY(resolve_count(kmap));
+    TS_TRY(settle(kmap));
     if (feats->rows != kmap->n_in) return fail(TS_ERR_SHAPE, "feats has %lld rows, the map expects %lld", (long long)feats->rows, (long long)kmap->n_in);
     if (out->rows != kmap->n_out) return fail(TS_ERR_SHAPE, "out has %lld rows, the map produces %lld", (long long)out->rows, (long long)kmap->n_out);
     if (weights->rows != (int64_t)kmap->K3 * feats->cols)
@@ -1244,7 +1245,7 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     const int32_t *perm = kmap->d_perm ? kmap->d_perm : kmap->d_window_perm;
     TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>), grid, dim3(kThreads), x,
               reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
-              !perm && (kmap->scan_done || kmap->scan_enqueued) ? kmap->d_tile_order : nullptr,
+              !perm && (kmap->scan_done || (kmap->scan_enqueued && kmap->stream == stream())) ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
               static_cast<const _Float16 *>(ep.bias), static_cast<const _Float16 *>(ep.residual), ep.relu,
               (int)((size_t)kmap->n_in * cin1 * 2), (int)((size_t)kmap->K3 * cin_pad * out->cols * 2), kmap->centre,

@@ -91,6 +91,10 @@ int resolve(const struct ::ts_kmap *kmap, bool need_sizes = true);
 // Waits, if it has not happened yet, for a map's number of outputs alone (n_out).
 int resolve_count(const struct ::ts_kmap *kmap);
 
+// Call before work on a map is enqueued: waits for the map's build where the host has been told its verdict, its
+// search may still be running, and another stream than the build's is current.
+int settle(const struct ::ts_kmap *kmap);
+
 // Enqueues, without waiting, what an asynchronous build put off (ts_kmap_prepare).
 int prepare(const struct ::ts_kmap *kmap);
 
@@ -162,6 +166,8 @@ struct ts_kmap {
     bool scan_done = true;      // false: what the scan leaves is not there yet, or not known to be (the fused kernel needs none of it)
     bool rows_put_off = false;  // the row pass (bitmask words, centre entries, presence bitmaps) has not been enqueued: it
                                 // goes with the scan (the fused kernels need none of it)
+    hipStream_t stream = nullptr;   // where the build's last kernel (the scan, once that has been enqueued) was enqueued
+    bool verdict_only = false;  // the host knows the build's verdict, which comes before the end of its search
     int pending_slot = -1;      // >= 0: sizes and error flags are still on their way to the host
     bool count_pending = false; // n_out is not known yet (-1): ts::resolve_count reads it
     bool one_pair_per_input = false;   // 2x2x2, stride 2: fewer pairs than inputs means equal inputs

@@ -1972,6 +1972,7 @@ int finish(ts_kmap *m, int slot, bool wait, bool scan_later = false) {
         m->scan_enqueued = true;
     }
     m->scan_done = false;
+    m->stream = stream();
     sl.owner = m;
     m->pending_slot = slot;
     TS_HIP(hipGetLastError());
@@ -2110,6 +2111,7 @@ int build_down(Temps &tmp, const int32_t *coords, int64_t N, ts_kmap *m, const B
     m->scan_enqueued = true;
     m->scan_done = false;
     sl.totals = true;
+    m->stream = stream();
     sl.owner = m;
     m->pending_slot = slot;
     TS_HIP(hipGetLastError());
@@ -2529,12 +2531,40 @@ int resolve_count(const ts_kmap *kmap) {
     return rc;
 }
 
+// The host waits for a stream that is not the current one (which may be being captured).
+static int wait_for(hipStream_t other) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(other, &st) != hipSuccess) (void)hipGetLastError();
+    if (st != hipStreamCaptureStatusNone)
+        return fail(TS_ERR_UNSUPPORTED, "a map's build must have finished before its stream is captured and the map is used on another one");
+    const bool capturing = stream_capturing();
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (capturing) TS_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+    hipError_t e = hipStreamSynchronize(other);
+    if (e != hipSuccess) {   // e.g. a stream that no longer exists
+        (void)hipGetLastError();
+        e = hipDeviceSynchronize();
+    }
+    if (capturing) TS_HIP(hipThreadExchangeStreamCaptureMode(&mode));
+    return e == hipSuccess ? TS_OK : fail(TS_ERR_HIP, "waiting for a map build: %s", hipGetErrorString(e));
+}
+
+int settle(const ts_kmap *kmap) {
+    if (!kmap->verdict_only || kmap->stream == stream()) return TS_OK;
+    TS_TRY(wait_for(kmap->stream));
+    const_cast<ts_kmap *>(kmap)->verdict_only = false;
+    return TS_OK;
+}
+
 int resolve(const ts_kmap *kmap, bool need_sizes) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
     TS_TRY(resolve_count(m));
     if (m->pending_slot >= 0) {
         const int slot = m->pending_slot;
-        if (need_sizes && !m->scan_enqueued) TS_TRY(prepare(m));
+        if (need_sizes && !m->scan_enqueued) {
+            if (m->stream != stream()) TS_TRY(wait_for(m->stream));   // the scan reads what the search leaves
+            TS_TRY(prepare(m));
+        }
         const bool totals = m->scan_enqueued;
         TS_TRY(slot_wait(slot, totals ? kSizes : kVerdict));
         if (totals) {
@@ -2543,6 +2573,7 @@ int resolve(const ts_kmap *kmap, bool need_sizes) {
         } else {
             take_verdict(m, slot_at(slot).host);
         }
+        m->verdict_only = !totals;
         if (totals || m->error != TS_OK) {   // else the slot stays for the sizes
             slot_release(slot);
             m->pending_slot = -1;
@@ -2563,12 +2594,14 @@ void release_grid() {
 int prepare(const ts_kmap *kmap) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
     if (m->scan_done || m->scan_enqueued || m->pending_slot < 0) return TS_OK;   // nothing put off
+    TS_TRY(settle(m));
     StatusSlot &sl = slot_at(m->pending_slot);
     if (m->rows_put_off) launch_rows(m);
     m->rows_put_off = false;
     launch_scan(m, sl.dev);
     sl.totals = true;
     m->scan_enqueued = true;
+    m->stream = stream();
     TS_HIP(hipGetLastError());
     return TS_OK;
 }

@@ -43,3 +43,41 @@ def test_map_of_a_waiting_build_on_another_stream(K, s, transposed, dtype):
             assert torch.equal(got, want)
             assert all(torch.equal(p, q) for p, q in zip(pairs, want_pairs))
         assert np.array_equal(gpu_triples(kmap), oracle_map(coords, K, s, transposed)[2])
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_map_whose_verdict_is_known_on_another_stream(dtype):
+    """An asynchronous 3x3x3 build reports its verdict before its search has ended: after ts_kmap_status, layers,
+    what the build put off, and sizes come on other streams; and sizes without a verdict before them."""
+    a, b, c = (torch.cuda.Stream() for _ in range(3))
+    nd = np_dtype(dtype)
+    w = ts.ts_weights_prepare(to_dev(conv_weights(4, 27, 64, 64, nd)))
+    for i, n in enumerate((500, 80000, 250000)):
+        coords = _coords(950 + i, n, 90)
+        dev = to_dev(coords)
+        x = to_dev(features(i, n, 64, nd))
+        ref = ts.ts_build_kmap(dev, 3, 1)
+        want, sizes = ts.ts_sparse_conv_prepared(x, w, ref), ref.sizes()
+        torch.cuda.synchronize()
+
+        def build():
+            with torch.cuda.stream(a):
+                return ts.ts_build_kmap(dev, 3, 1, wait=False)
+
+        def layer(kmap, stream):
+            with torch.cuda.stream(stream):
+                got = ts.ts_sparse_conv_prepared(x, w, kmap)
+            stream.synchronize()
+            return got
+
+        assert torch.equal(layer(build().status(), b), want)
+        kmap = build().status()
+        with torch.cuda.stream(b):
+            kmap.prepare()
+        assert torch.equal(layer(kmap, c), want) and np.array_equal(kmap.sizes(), sizes)
+        kmap = build()
+        with torch.cuda.stream(b):
+            pairs = kmap.pairs()
+        b.synchronize()
+        assert all(torch.equal(p, q) for p, q in zip(pairs, ref.pairs())) and np.array_equal(kmap.sizes(), sizes)
+        assert torch.equal(layer(kmap, c), want)
