@@ -1185,7 +1185,7 @@ struct FusedLaunch {
         constexpr int G = fused_group(NCB, KSTEPS);
         dim3 grid((unsigned)kmap->n_tiles, out->cols / (NCB * 32));
         TS_LAUNCH("k_fused", (k_fused<T, NCB, KC, G>), grid, dim3(kThreads), static_cast<const T *>(pr.x),
-                  static_cast<const T *>(pr.wt), kmap->d_nbr, kmap->stride, kmap->d_perm ? kmap->d_perm : kmap->d_window_perm, kmap->n_out,
+                  static_cast<const T *>(pr.wt), kmap->d_nbr, kmap->stride, row_order(kmap), kmap->n_out,
                   static_cast<T *>(out->data), zero, pr.cin_pad, out->cols, kmap->K3, kmap->centre);
     }
 };
@@ -1242,7 +1242,7 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     const int64_t resident = (int64_t)compute_units() * per_cu;
     dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
     const int cin1 = TWO ? sec.cin1 : cin_pad;
-    const int32_t *perm = kmap->d_perm ? kmap->d_perm : kmap->d_window_perm;
+    const int32_t *perm = row_order(kmap);
     TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>), grid, dim3(kThreads), x,
               reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
               !perm && (kmap->scan_done || (kmap->scan_enqueued && kmap->stream == stream())) ? kmap->d_tile_order : nullptr,

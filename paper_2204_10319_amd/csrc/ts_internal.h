@@ -102,8 +102,13 @@ int prepare(const struct ::ts_kmap *kmap);
 // without an error, where it cannot be done: no bitmasks by row, no memory, a stream that is being captured.
 void order_windows(const struct ::ts_kmap *kmap);
 
-// Whether the library's stream is being captured into a graph.
-bool stream_capturing();
+// The row order of a map that a layer on the current stream may read, or NULL for the natural one: what
+// ts_kmap_sort_rows made (complete when that call returned), else what order_windows enqueued, if that was on this
+// stream or has finished.
+const int32_t *row_order(const struct ::ts_kmap *kmap);
+
+// Whether a stream is being captured into a graph.
+bool stream_capturing(hipStream_t s);
 
 // Makes sure the offset-major pair lists of a map exist (they are derived on first use).
 int ensure_pairs(const struct ::ts_kmap *kmap);
@@ -195,6 +200,8 @@ struct ts_kmap {
     // The same rows in another order, for the output-stationary kernel (ts::order_windows): inside a window of
     // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it.
     int32_t *d_window_perm = nullptr;     // [n_tiles*kTileRows] position -> output row, -1 = padding; tiles longest first
+    hipStream_t window_stream = nullptr;  // where that order was enqueued
+    bool window_settled = false;          // it is known to be there: other streams may read it
     int uses = 0;                         // layers that the output-stationary kernel has run on this map
     int32_t *d_parent = nullptr;          // [n_in] output of every input (-1: none), 2x2x2 stride-2 maps only (else NULL)
     // Optional (ts_kmap_sort_rows): output rows ordered by offset bitmask, so that the rows of a

@@ -78,17 +78,17 @@ Scratch g_scratch[8];
 void *g_host = nullptr;
 size_t g_host_bytes = 0;
 
-bool capturing() {
+bool capturing() { return stream_capturing(g_stream); }
+}  // namespace
+
+bool stream_capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(g_stream, &st) != hipSuccess) {
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
     return st != hipStreamCaptureStatusNone;
 }
-}  // namespace
-
-bool stream_capturing() { return capturing(); }
 
 // A freed block goes back to work only in stream order.  Blocks given back on the stream the library is on
 // now are reused at once (later work on that stream comes after whatever still uses them).  A block given

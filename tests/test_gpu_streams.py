@@ -81,3 +81,38 @@ def test_map_whose_verdict_is_known_on_another_stream(dtype):
         b.synchronize()
         assert all(torch.equal(p, q) for p, q in zip(pairs, ref.pairs())) and np.array_equal(kmap.sizes(), sizes)
         assert torch.equal(layer(kmap, c), want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_row_order_of_a_map_in_use_on_other_streams(dtype):
+    """The second layer on a large map enqueues the ordering of its rows: layers that follow at once on other streams,
+    eager or recorded into a graph, give the bits of the natural order, as does the one that enqueued it."""
+    a, b, c = (torch.cuda.Stream() for _ in range(3))
+    nd = np_dtype(dtype)
+    w = ts.ts_weights_prepare(to_dev(conv_weights(5, 27, 64, 64, nd)))
+    for i, n in enumerate((40000, 200000)):
+        dev, x = to_dev(_coords(970 + i, n, 80)), to_dev(features(i, n, 64, nd))
+        want = ts.ts_sparse_conv_prepared(x, w, ts.ts_build_kmap(dev, 3, 1))
+        outs = [torch.zeros_like(want) for _ in range(4)]
+        graph = torch.cuda.CUDAGraph()
+        for rep in range(3):
+            kmap = ts.ts_build_kmap(dev, 3, 1)
+            torch.cuda.synchronize()
+            for out, stream in zip(outs, (a, b, c, a)):
+                if dtype == torch.float16:
+                    stream.wait_stream(a)      # fp16 layers on one map share its tile counters: one after the other
+                    stream.wait_stream(b)
+                    stream.wait_stream(c)
+                with torch.cuda.stream(stream):
+                    ts.ts_sparse_conv_prepared(x, w, kmap, out=out.zero_())
+            torch.cuda.synchronize()
+            assert all(torch.equal(out, want) for out in outs)
+        with torch.cuda.graph(graph, stream=c):
+            ts.ts_sparse_conv_prepared(x, w, kmap, out=outs[0])
+        for _ in range(3):
+            outs[0].zero_()
+            graph.replay()
+            assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), want)   # eager work between the replays
+            torch.cuda.synchronize()
+            assert torch.equal(outs[0], want)
+        del graph
