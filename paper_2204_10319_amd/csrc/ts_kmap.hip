@@ -2485,10 +2485,11 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
 namespace ts {
 
 // The number of outputs of a map whose build left it to be read here (build_down).  A box too large for the bitmap
-// ends in a build by sorting, from the keys.
+// ends in a build by sorting, from the keys.  That runs on the stream that is current now, while the caller orders his
+// work by the stream he built the map on: it is waited for (the host takes part in it twice anyway).
 int resolve_count(const ts_kmap *kmap) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
-    if (!m->count_pending) return TS_OK;
+    if (!m->count_pending) return m->n_out >= 0 ? TS_OK : fail(m->error, "the build of this map failed after its outputs had been asked for");
     const int slot = m->pending_slot;
     TS_TRY(slot_wait(slot, kCount));
     int32_t *h = slot_at(slot).host;
@@ -2520,12 +2521,15 @@ int resolve_count(const ts_kmap *kmap) {
     BuildOpts opt;
     opt.wait = false;
     bool reports = false;
-    const int rc = build_strided(tmp, nullptr, m->d_in_keys, m->n_in, m, opt, slot, &reports);
-    if (rc != TS_OK) {
+    int rc = build_strided(tmp, nullptr, m->d_in_keys, m->n_in, m, opt, slot, &reports);
+    if (rc == TS_OK && reports) rc = slot_wait(slot, kSizes);
+    if (rc != TS_OK || !reports) {
         (void)hipStreamSynchronize(stream());
         slot_release(slot);
         m->pending_slot = -1;
-        m->n_out = 0;
+    }
+    if (rc != TS_OK) {
+        m->n_out = -1;
         m->error = rc;
     }
     return rc;

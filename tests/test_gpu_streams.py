@@ -116,3 +116,37 @@ def test_row_order_of_a_map_in_use_on_other_streams(dtype):
             torch.cuda.synchronize()
             assert torch.equal(outs[0], want)
         del graph
+
+
+def _far_spread(seed, n):
+    """Points whose box is too large for the bitmap of a 2x2x2 stride-2 build: it is built by sorting once its number of
+    outputs is asked for."""
+    rng = np.random.Generator(np.random.PCG64(seed))
+    xyz = np.unique(rng.integers(-40000, 40000, (n, 3)) // 8, axis=0)
+    xyz = np.concatenate([xyz, xyz + [[0, 0, 1]], [[60000, 60000, 60000], [-60000, -60000, -60000]]])
+    xyz = np.unique(xyz, axis=0)
+    return np.concatenate([np.zeros((len(xyz), 1)), xyz[rng.permutation(len(xyz))]], 1).astype(np.int32)
+
+
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("n", [300, 60000])
+def test_map_rebuilt_when_its_outputs_are_asked_for_elsewhere(n, dtype):
+    """The number of outputs of such a map is asked for on another stream, which rebuilds the map there; the stream it was
+    built on uses it at once, as include/ts.h allows."""
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    coords, nd, lib = _far_spread(n, n), np_dtype(dtype), ts.load_library()
+    dev = to_dev(coords)
+    x, w = features(1, len(coords), 32, nd), conv_weights(2, 8, 32, 64, nd)
+    xd, wd = to_dev(x), ts.ts_weights_prepare(to_dev(w))
+    want = oracle_conv(coords, x, w, 2, 2)
+    for _ in range(3):
+        with torch.cuda.stream(a):
+            kmap = ts.ts_build_kmap(dev, 2, 2, wait=False)
+        a.synchronize()
+        ts.ts_set_stream(b)
+        assert lib.ts_kmap_num_out(kmap.handle) == want.shape[0]
+        with torch.cuda.stream(a):
+            got = ts.ts_sparse_conv_prepared(xd, wd, kmap)
+        a.synchronize()
+        check_features(got, want, dtype)
+    assert np.array_equal(gpu_triples(kmap), oracle_map(coords, 2, 2)[2])
