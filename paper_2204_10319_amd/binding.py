@@ -274,8 +274,20 @@ class KMap:
         return self._h
 
     num_in = property(lambda self: load_library().ts_kmap_num_in(self.handle))
-    num_out = property(lambda self: load_library().ts_kmap_num_out(self.handle))
-    num_pairs = property(lambda self: load_library().ts_kmap_num_pairs(self.handle))
+
+    @property
+    def num_out(self):
+        _use_current_stream()       # counting may build the map
+        n = load_library().ts_kmap_num_out(self.handle)
+        if n < 0:
+            _check(int(n))
+        return n
+
+    @property
+    def num_pairs(self):
+        _use_current_stream()       # counting may run what the build put off
+        return load_library().ts_kmap_num_pairs(self.handle)
+
     kernel_volume = property(lambda self: load_library().ts_kmap_kernel_volume(self.handle))
 
     def out_coords(self) -> torch.Tensor:
@@ -286,6 +298,7 @@ class KMap:
 
     def out_box(self):
         """(lo[3], hi[3], batches) holding every output coordinate, or None when the build bounded nothing."""
+        _use_current_stream()
         lo, hi, b = (ctypes.c_int32 * 3)(), (ctypes.c_int32 * 3)(), ctypes.c_int32()
         rc = load_library().ts_kmap_out_box(self.handle, lo, hi, ctypes.byref(b))
         if rc == TS_ERR_UNSUPPORTED:
@@ -301,6 +314,7 @@ class KMap:
 
     def status(self):
         """Waits for an asynchronous build's verdict; raises TsError if the input was bad."""
+        _use_current_stream()
         _check(load_library().ts_kmap_status(self.handle))
         return self
 
@@ -400,6 +414,7 @@ def ts_kmap_in_coords(kmap: KMap) -> torch.Tensor:
 
 
 def ts_kmap_sizes(kmap: KMap) -> np.ndarray:
+    _use_current_stream()
     dst = (ctypes.c_int64 * kmap.kernel_volume)()
     _check(load_library().ts_kmap_sizes(kmap.handle, dst))
     return np.array(list(dst), dtype=np.int64)

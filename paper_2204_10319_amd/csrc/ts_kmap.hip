@@ -2814,7 +2814,11 @@ int ts_kmap_sort_rows(ts_kmap *kmap) {
 }
 
 int64_t ts_kmap_num_in(const ts_kmap *kmap) { return kmap ? kmap->n_in : -1; }
-int64_t ts_kmap_num_out(const ts_kmap *kmap) { return kmap && ts::resolve_count(kmap) == TS_OK ? kmap->n_out : -1; }
+int64_t ts_kmap_num_out(const ts_kmap *kmap) {
+    if (!kmap) return fail(TS_ERR_INVALID_ARG, "kmap is NULL");
+    const int rc = ts::resolve_count(kmap);
+    return rc == TS_OK ? kmap->n_out : rc;
+}
 int64_t ts_kmap_num_pairs(const ts_kmap *kmap) { return kmap && ts::resolve(kmap) == TS_OK ? kmap->M : -1; }
 int ts_kmap_kernel_volume(const ts_kmap *kmap) { return kmap ? kmap->K3 : -1; }
 

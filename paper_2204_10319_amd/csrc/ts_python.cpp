@@ -91,11 +91,13 @@ struct Output {
         if (out != Py_None) return describe(out, &d);
         const at::Tensor &f = THPVariable_Unpack(feats);
         int64_t rows;
+        void *const st = current_stream();
         Py_BEGIN_ALLOW_THREADS
+        ts_set_stream(st);              // counting may build the map
         rows = ts_kmap_num_out(kmap);   // may wait for the build to say
         Py_END_ALLOW_THREADS
         if (rows < 0) {
-            raise_ts(TS_ERR_HIP);
+            raise_ts((int)rows);
             return false;
         }
         made = at::empty({rows, cols}, f.options());
@@ -252,13 +254,14 @@ PyObject *out_coords(PyObject *, PyObject *arg) {
     ts_kmap *m;
     if (!pointer(arg, &m)) return nullptr;
     int64_t rows;
+    void *const st = current_stream();
     Py_BEGIN_ALLOW_THREADS
+    ts_set_stream(st);
     rows = ts_kmap_num_out(m);
     Py_END_ALLOW_THREADS
-    if (rows < 0) return raise_ts(TS_ERR_HIP);
+    if (rows < 0) return raise_ts((int)rows);
     at::Tensor dst = at::empty({rows, 4}, at::TensorOptions().dtype(at::kInt).device(at::kCUDA));
     int rc;
-    void *const st = current_stream();
     int32_t *const p = rows ? static_cast<int32_t *>(dst.data_ptr()) : nullptr;
     Py_BEGIN_ALLOW_THREADS
     ts_set_stream(st);

@@ -132,7 +132,7 @@ def _far_spread(seed, n):
 @pytest.mark.parametrize("n", [300, 60000])
 def test_map_rebuilt_when_its_outputs_are_asked_for_elsewhere(n, dtype):
     """The number of outputs of such a map is asked for on another stream, which rebuilds the map there; the stream it was
-    built on uses it at once, as include/ts.h allows."""
+    built on uses it at once, as include/ts.h allows.  The same with a layer, first thing on the other stream."""
     a, b = torch.cuda.Stream(), torch.cuda.Stream()
     coords, nd, lib = _far_spread(n, n), np_dtype(dtype), ts.load_library()
     dev = to_dev(coords)
@@ -149,4 +149,29 @@ def test_map_rebuilt_when_its_outputs_are_asked_for_elsewhere(n, dtype):
             got = ts.ts_sparse_conv_prepared(xd, wd, kmap)
         a.synchronize()
         check_features(got, want, dtype)
+        with torch.cuda.stream(a):
+            kmap = ts.ts_build_kmap(dev, 2, 2, wait=False)
+        a.synchronize()
+        with torch.cuda.stream(b):      # a layer asks for itself
+            got = ts.ts_sparse_conv_prepared(xd, wd, kmap)
+        b.synchronize()
+        check_features(got, want, dtype)
     assert np.array_equal(gpu_triples(kmap), oracle_map(coords, 2, 2)[2])
+
+
+def test_a_count_that_fails_says_why():
+    """No memory for the rebuild of such a map: that is the error of whatever asked for its outputs, then and later."""
+    coords = to_dev(_far_spread(7, 5000))
+    x, w = torch.zeros((coords.shape[0], 32), dtype=torch.float16, device="cuda"), torch.zeros((8, 32, 32), dtype=torch.float16, device="cuda")
+    asks = [lambda m: m.num_out, lambda m: m.out_coords(), lambda m: ts.ts_sparse_conv(x, w, m), lambda m: m.out_box()]
+    for first in asks:
+        kmap = ts.ts_build_kmap(coords, 2, 2, wait=False)
+        ts.ts_set_allocator(lambda size: 0, lambda ptr: None)
+        try:
+            for ask in [first] + asks:
+                with pytest.raises(ts.TsError) as e:
+                    ask(kmap)
+                assert e.value.code == ts.TS_ERR_OOM
+        finally:
+            ts.ts_set_allocator(None, None)
+        kmap.free()
