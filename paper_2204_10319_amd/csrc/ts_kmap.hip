@@ -24,6 +24,7 @@
 // goes to (first position of its bitmask) + (arrival rank).
 #include "ts_internal.h"
 
+#include <chrono>
 #include <cstdlib>
 #include <cstring>
 #include <new>
@@ -1743,6 +1744,8 @@ struct StatusSlot {
     bool totals = false;        // ... the map sizes as well
     int K3 = 0;
     const ts_kmap *owner = nullptr;   // NULL while busy: the map was freed before anyone asked
+    bool recorded = false;      // a graph reports here, at every replay: the slot stays its own
+    hipStream_t stream = nullptr;     // where that was recorded
 };
 constexpr int kSlotChunk = 64, kSlotChunks = 1024;   // slots come 64 to an allocation, 65536 at most
 StatusSlot *g_slots[kSlotChunks] = {nullptr};
@@ -1767,6 +1770,13 @@ inline void slot_reset(StatusSlot &s, int K3) {
     s.host[ST_COUNT] = -1;
     s.K3 = K3;
     s.totals = false;
+}
+
+// Call when work that reports to the slot is enqueued.
+inline void slot_recorded(StatusSlot &s) {
+    if (s.recorded || !stream_capturing(stream())) return;
+    s.recorded = true;
+    s.stream = stream();
 }
 
 // A free slot, its words reset; -1 with the error set.
@@ -1796,10 +1806,11 @@ int slot_acquire(int K3) {
         }
         for (int i = 0; i < kSlotChunk; ++i) {
             StatusSlot &s = g_slots[ch][i];
-            if (s.busy && (s.owner || !slot_landed(s, s.totals ? kSizes : kVerdict))) continue;
+            if (s.recorded || (s.busy && (s.owner || !slot_landed(s, s.totals ? kSizes : kVerdict)))) continue;
             slot_reset(s, K3);
             s.busy = true;
             s.owner = nullptr;
+            slot_recorded(s);
             return ch * kSlotChunk + i;
         }
     }
@@ -1813,13 +1824,24 @@ inline void slot_release(int i) {
 }
 
 // Watches the slot's words.  The stream is asked now and then whether it has finished or failed, so that a
-// build that cannot report any more (an error of the device) ends the wait.
+// build that cannot report any more (an error of the device) ends the wait.  A stream that is being captured must
+// not be asked: what was enqueued before reports all the same, what is being recorded does not.
+constexpr int kCaptureWaitSeconds = 20;
 int slot_wait(int i, Awaited what) {
     const StatusSlot &s = slot_at(i);
+    std::chrono::steady_clock::time_point begin{};
     for (;;) {
         for (int spin = 0; spin < 20000; ++spin) {
             if (slot_landed(s, what)) return TS_OK;
             __builtin_ia32_pause();
+        }
+        if (s.recorded && stream_capturing(s.stream))
+            return fail(TS_ERR_UNSUPPORTED, "the build of this map is being recorded into a graph and reports nothing before that runs");
+        if (stream_capturing(stream())) {
+            const auto now = std::chrono::steady_clock::now();
+            if (begin == std::chrono::steady_clock::time_point{}) begin = now;
+            if (now - begin > std::chrono::seconds(kCaptureWaitSeconds)) return fail(TS_ERR_HIP, "a map build has not reported for %d s", kCaptureWaitSeconds);
+            continue;
         }
         const hipError_t e = hipStreamQuery(stream());
         if (e == hipErrorNotReady) {
@@ -2505,6 +2527,8 @@ int resolve_count(const ts_kmap *kmap) {
         m->count_pending = false;
         return TS_OK;
     }
+    if (stream_capturing(stream()))
+        return fail(TS_ERR_UNSUPPORTED, "the box of this map's points is too large for a bitmap: its number of outputs must have been asked for before the stream is captured");
     TS_TRY(slot_wait(slot, kSizes));   // nothing more is written there
     TS_HIP(hipStreamSynchronize(stream()));
     for (int n = 0; n < kMaxK3; ++n) h[ST_TOTALS + n] = -1;
@@ -2564,6 +2588,8 @@ int resolve(const ts_kmap *kmap, bool need_sizes) {
     if (m->pending_slot >= 0) {
         const int slot = m->pending_slot;
         if (need_sizes && !m->scan_enqueued) {
+            if (stream_capturing(stream()))
+                return fail(TS_ERR_UNSUPPORTED, "the sizes of a map must have been asked for, or ts_kmap_prepare called, before the stream is captured");
             if (m->stream != stream()) TS_TRY(wait_for(m->stream));   // the scan reads what the search leaves
             TS_TRY(prepare(m));
         }
@@ -2600,6 +2626,7 @@ int prepare(const ts_kmap *kmap) {
     StatusSlot &sl = slot_at(m->pending_slot);
     if (m->rows_put_off) launch_rows(m);
     m->rows_put_off = false;
+    slot_recorded(sl);
     launch_scan(m, sl.dev);
     sl.totals = true;
     m->scan_enqueued = true;

@@ -175,3 +175,68 @@ def test_a_count_that_fails_says_why():
         finally:
             ts.ts_set_allocator(None, None)
         kmap.free()
+
+
+@pytest.mark.parametrize("layer", [ts.ts_sparse_conv, ts.ts_sparse_conv_static])
+def test_layer_recorded_on_a_map_still_being_built(layer):
+    """A layer is recorded while the build of its 2x2x2 map, whose number of outputs nobody has asked for, waits on the
+    device behind other work: it waits for the count without touching the capture.  Where that map has to be built by
+    sorting, the layer is refused and the capture, the map and a later layer are none the worse."""
+    side = torch.cuda.Stream()
+    w = to_dev(conv_weights(8, 8, 32, 64, np.float16))
+    heavy = torch.randn(4096, 4096, device="cuda")
+    for coords, refused in ((_coords(990, 120000, 70), False), (_far_spread(991, 60000), True)):
+        dev, x = to_dev(coords), to_dev(features(9, len(coords), 32, np.float16))
+        with torch.cuda.stream(side):
+            want = ts.ts_sparse_conv(x, w, ts.ts_build_kmap(dev, 2, 2), dataflow=ts.TS_DATAFLOW_FUSED)
+            out = torch.zeros_like(want)
+            layer(x, w, ts.ts_build_kmap(dev, 2, 2), out)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.stream(side):
+            for _ in range(8):
+                heavy @ heavy
+            kmap = ts.ts_build_kmap(dev, 2, 2, wait=False)
+            graph.capture_begin(capture_error_mode="thread_local")
+            try:
+                out.zero_()
+                if refused:
+                    with pytest.raises(ts.TsError) as e:
+                        layer(x, w, kmap, out)
+                    assert e.value.code == ts.TS_ERR_UNSUPPORTED
+                else:
+                    layer(x, w, kmap, out)
+            finally:
+                graph.capture_end()
+        torch.cuda.synchronize()
+        for _ in range(3):
+            out.fill_(1)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(out, torch.zeros_like(out) if refused else want)
+            with torch.cuda.stream(side):
+                assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), want)
+            side.synchronize()
+        del graph
+
+
+def test_sizes_asked_for_while_recording():
+    """What a 3x3x3 build put off is not run inside a capture: the request is refused, and served after it."""
+    side = torch.cuda.Stream()
+    dev = to_dev(_coords(995, 5000, 30))
+    sizes = ts.ts_build_kmap(dev, 3, 1).sizes()
+    out = torch.zeros(64, device="cuda")
+    with torch.cuda.stream(side):
+        kmap = ts.ts_build_kmap(dev, 3, 1, wait=False)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=side):
+        out.fill_(3)
+        with pytest.raises(ts.TsError) as e:
+            kmap.sizes()
+        assert e.value.code == ts.TS_ERR_UNSUPPORTED
+        kmap.status()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert out.eq(3).all() and np.array_equal(kmap.sizes(), sizes)
+    del graph
