@@ -878,6 +878,35 @@ def test_rows_of_a_map_in_use_are_reordered_f32(n, c_out):
     assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x), wide, fresh), ts.ts_sparse_conv_prepared(to_dev(x), wide, kmap))
 
 
+@pytest.mark.parametrize("wait", [True, False])
+@pytest.mark.parametrize("scene,n,c,want", [("solid", 8000, 256, "fused"), ("solid", 800, 512, "fetched"), ("scattered", 7500, 128, "fetched"), ("scattered", 7500, 64, "fused")])
+def test_automatic_dataflow_goes_by_the_maps_own_pairs(scene, n, c, want, wait):
+    """Full cubes have up to 27 pairs a point, scattered points 3: layers on either side of the line that the weights and
+    the pairs' rows draw, on waiting builds and on asynchronous ones whose sizes have been asked for.  The dataflows differ in bits."""
+    side = round(n ** (1 / 3)) if scene == "solid" else 46
+    flat = np.random.Generator(np.random.PCG64(n)).permutation(side ** 3)[:n]
+    coords = np.stack([0 * flat, flat // side ** 2, flat // side % side, flat % side], 1).astype(np.int32)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1, wait=wait)
+    kmap.sizes()
+    x, w = to_dev(features(n, len(coords), c, np.float16)), to_dev(conv_weights(n + 1, 27, c, c, np.float16))
+    fused, fetched = (ts.ts_sparse_conv(x, w, kmap, dataflow=d) for d in (ts.TS_DATAFLOW_FUSED, ts.TS_DATAFLOW_FETCH))
+    assert not torch.equal(fused, fetched)
+    assert torch.equal(ts.ts_sparse_conv(x, w, kmap), fused if want == "fused" else fetched)
+    assert torch.equal(ts.ts_sparse_conv_prepared(x, ts.ts_weights_prepare(w), kmap), fused if want == "fused" else fetched)
+
+
+@pytest.mark.parametrize("c", [64, 256])
+def test_layers_run_on_a_map_of_bad_input_that_nobody_asked(c):
+    """An asynchronous map of points given twice is safe to use until its verdict is asked for, whatever the width."""
+    coords = _rand_coords(77, 3000, 0, 30)
+    kmap = ts.ts_build_kmap(to_dev(np.concatenate([coords, coords[:1]])), 3, 1, wait=False)
+    x, w = torch.zeros((3001, c), dtype=torch.float16, device="cuda"), torch.zeros((27, c, c), dtype=torch.float16, device="cuda")
+    assert ts.ts_sparse_conv(x, w, kmap).eq(0).all()
+    with pytest.raises(ts.TsError) as e:
+        kmap.status()
+    assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
+
+
 def test_sorted_rows_many_distinct_masks():
     """Uniform random occupancy gives more distinct bitmasks than the mask table ranks (the radix-sort path)."""
     coords = _rand_coords(91, 120000, 0, 64)
