@@ -1589,25 +1589,24 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // small to fill the machine with tiles (the coarse levels of a U-Net) are cheaper explicit,
 // everything else fused; the factor and the size limit come from timing both on the layers of
 // the MinkUNet-style benchmark network.
-// The number of pairs is the map's own where it is known: maps differ ninefold in it (3 a point where points are
-// scattered, 7 to 9 on scans and surfaces, up to 27 in a solid), and the wrong dataflow costs up to three times the
-// right one (fp16, 192 -> 192 on 32 k points of a solid 97 us fused, 307 fetched; 128 -> 128 on 7.5 k scattered ones
-// 27 and 21).  An asynchronous build that nobody has asked does not know it yet, and waiting for it costs a
-// small step three times what its kernels take: that of surface-like scenes decides then whether the explicit
-// dataflow, which waits for the map's own in any case, comes into question.  (A build that found bad input, or whose
-// sizes cannot be had now, leaves the fused kernel, which needs none.)
+// The number of pairs is that of surface-like scenes, or the map's own where that is larger: a solid has up to 27 a point
+// where scans and surfaces have 7 to 9, and fetching them costs three times the fused kernel (fp16, 192 -> 192 on 32 k
+// points of a solid 307 us and 97, 256 -> 256 on 20 k 266 and 133).  An asynchronous build that nobody has asked does not know
+// its own yet, and waiting for it costs a small step three times what its kernels take; where the layer comes out
+// fused by the surface-like number it does so by any larger one, so nothing is waited for there, and where it does
+// not, the explicit dataflow waits for the map's own in any case: whether somebody has asked never decides.  That is why a
+// smaller number (scattered points have 3) does not count, though fetching would gain there (128 -> 128 on 7.5 k scattered
+// points: 27 us fused, 21 fetched).  (A build that found bad input, or whose sizes cannot be had now, leaves the fused
+// kernel, which needs none.)
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
+    const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
+    const double typical = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;
     const double fused_weight_bytes = (double)kmap->n_tiles * tile_offsets * cin * cout * elem;
     const double bytes_per_pair = 2.0 * cin * elem + 2.0 * cout * sizeof(float);
-    if (!kmap->scan_done) {
-        const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
-        const double pairs = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;
-        if (fused_weight_bytes <= 0.6 * pairs * bytes_per_pair) return false;
-    }
-    if (resolve(kmap) != TS_OK) return false;
-    return fused_weight_bytes > 0.6 * (double)kmap->M * bytes_per_pair;
+    if (fused_weight_bytes <= 0.6 * typical * bytes_per_pair || resolve(kmap) != TS_OK) return false;
+    return (double)kmap->M <= typical || fused_weight_bytes > 0.6 * (double)kmap->M * bytes_per_pair;
 }
 
 // ---- the layer for callers that cannot allocate -----------------------------------------------------------

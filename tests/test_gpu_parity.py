@@ -878,21 +878,22 @@ def test_rows_of_a_map_in_use_are_reordered_f32(n, c_out):
     assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x), wide, fresh), ts.ts_sparse_conv_prepared(to_dev(x), wide, kmap))
 
 
-@pytest.mark.parametrize("wait", [True, False])
-@pytest.mark.parametrize("scene,n,c,want", [("solid", 8000, 256, "fused"), ("solid", 800, 512, "fetched"), ("scattered", 7500, 128, "fetched"), ("scattered", 7500, 64, "fused")])
-def test_automatic_dataflow_goes_by_the_maps_own_pairs(scene, n, c, want, wait):
-    """Full cubes have up to 27 pairs a point, scattered points 3: layers on either side of the line that the weights and
-    the pairs' rows draw, on waiting builds and on asynchronous ones whose sizes have been asked for.  The dataflows differ in bits."""
+@pytest.mark.parametrize("build", ["waiting", "asked", "nobody asked"])
+@pytest.mark.parametrize("scene,n,c,want", [("solid", 8000, 256, "fused"), ("solid", 800, 512, "fetched"), ("scattered", 7500, 128, "fused"), ("scattered", 7500, 256, "fetched")])
+def test_automatic_dataflow_goes_by_the_maps_own_pairs(scene, n, c, want, build):
+    """Full cubes have up to 27 pairs a point, scattered points 3, which count as a surface's 7.5: layers on either side of
+    the line that the weights and the pairs' rows draw, whether or not the sizes are known.  The dataflows differ in bits."""
     side = round(n ** (1 / 3)) if scene == "solid" else 46
     flat = np.random.Generator(np.random.PCG64(n)).permutation(side ** 3)[:n]
     coords = np.stack([0 * flat, flat // side ** 2, flat // side % side, flat % side], 1).astype(np.int32)
-    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1, wait=wait)
-    kmap.sizes()
-    x, w = to_dev(features(n, len(coords), c, np.float16)), to_dev(conv_weights(n + 1, 27, c, c, np.float16))
+    kmap, x, w = ts.ts_build_kmap(to_dev(coords), 3, 1), to_dev(features(n, len(coords), c, np.float16)), to_dev(conv_weights(n + 1, 27, c, c, np.float16))
     fused, fetched = (ts.ts_sparse_conv(x, w, kmap, dataflow=d) for d in (ts.TS_DATAFLOW_FUSED, ts.TS_DATAFLOW_FETCH))
     assert not torch.equal(fused, fetched)
-    assert torch.equal(ts.ts_sparse_conv(x, w, kmap), fused if want == "fused" else fetched)
-    assert torch.equal(ts.ts_sparse_conv_prepared(x, ts.ts_weights_prepare(w), kmap), fused if want == "fused" else fetched)
+    for layer in (lambda m: ts.ts_sparse_conv(x, w, m), lambda m: ts.ts_sparse_conv_prepared(x, ts.ts_weights_prepare(w), m)):
+        kmap = ts.ts_build_kmap(to_dev(coords), 3, 1, wait=build == "waiting")
+        if build == "asked":
+            kmap.sizes()
+        assert torch.equal(layer(kmap), fused if want == "fused" else fetched)
 
 
 @pytest.mark.parametrize("c", [64, 256])

@@ -53,7 +53,7 @@ def test_map_whose_verdict_is_known_on_another_stream(dtype):
     nd = np_dtype(dtype)
     w = ts.ts_weights_prepare(to_dev(conv_weights(4, 27, 64, 64, nd)))
     for i, n in enumerate((500, 80000, 250000)):
-        coords = _coords(950 + i, n, 90 if n > 500 else 10)     # (so dense that the layer is fused, asked for sizes or not)
+        coords = _coords(950 + i, n, 90)
         dev = to_dev(coords)
         x = to_dev(features(i, n, 64, nd))
         ref = ts.ts_build_kmap(dev, 3, 1)
