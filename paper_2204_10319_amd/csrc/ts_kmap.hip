@@ -49,10 +49,12 @@ enum {
     ST_DCOUNT = 2,      // distinct offset bitmasks seen (ts_kmap_sort_rows)
     ST_OVERFLOW = 3,    // the bitmask table could not hold them all
     ST_SEARCHED = 4,    // set once every kernel that raises ST_RANGE or ST_DUP has finished
-    ST_COUNT = 5,       // output points of a 2x2x2 stride-2 map (-1: not there yet, kBoxTooLarge: build it by sorting)
+    ST_COUNT = 5,       // coarse points of a strided build (-1: not there yet, kBoxTooLarge: build the map by sorting)
     ST_TILES = 6,       // set once the tile order is complete
+    ST_BOXED = 7,       // set once the box of the points, which a strided build chooses its route by, is at ST_BOX
     ST_TOTALS = 8,      // [32] per-offset map sizes (-1: not there yet)
-    ST_BOX = 40,        // [7] lo, hi, batches of the box of a 2x2x2 stride-2 map's outputs, there with ST_COUNT
+    ST_BOX = 40,        // [7] lo, hi, batches of the box of a 2x2x2 stride-2 map's outputs, there with ST_COUNT; or, with
+                        // ST_BOXED, the maxima of -x, -y, -z, x, y, z, batch over the valid points (INT32_MIN: none)
     ST_WORDS = 48
 };
 
@@ -327,41 +329,16 @@ __global__ void k_fill(FillArgs a) {
     }
 }
 
-// Bounding box of the valid coordinates, for builds that choose their search by it: 64 partial boxes
-// on cache lines of their own (atomics on one line are served one after the other), each 7 running
-// maxima: -x, -y, -z, x, y, z, batch.  The host folds the 64.
-constexpr int kBoxSlots = 64, kBoxSlotWords = 32;
-
 constexpr int kBoxTooLarge = -2;
 
 // keys[i] = pack(coords[i]); out-of-range rows get the empty key and raise ST_RANGE.
-__global__ void __launch_bounds__(kThreads) k_pack(const int4 *coords, int64_t n, uint64_t *keys, int *status, Box box, int32_t *bbox) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int32_t v[7];
-#pragma unroll
-    for (int q = 0; q < 7; ++q) v[q] = INT32_MIN;
-    if (i < n) {
-        int4 c = coords[i];
-        if (!coord_ok(c) || !in_box(c, box)) {
-            raise_flag(status, ST_RANGE);
-            keys[i] = kEmptyKey;
-        } else {
-            keys[i] = pack_key(c.x, c.y, c.z, c.w);
-            v[0] = -c.y, v[1] = -c.z, v[2] = -c.w, v[3] = c.y, v[4] = c.z, v[5] = c.w, v[6] = c.x;
-        }
-    }
-    if (!bbox) return;
-#pragma unroll
-    for (int q = 0; q < 7; ++q)
-        for (int d = 32; d >= 1; d >>= 1) v[q] = max(v[q], __shfl_xor(v[q], d, 64));
-    const int lane = threadIdx.x & 63;
-    const int slot = (int)((blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6)) % kBoxSlots);
-    if (lane < 7) {
-        int32_t mine = v[0];
-#pragma unroll
-        for (int q = 1; q < 7; ++q) mine = lane == q ? v[q] : mine;
-        if (mine != INT32_MIN) atomicMax(&bbox[slot * kBoxSlotWords + lane], mine);
-    }
+__global__ void __launch_bounds__(kThreads) k_pack(const int4 *coords, int64_t n, uint64_t *keys, int *status, Box box) {
+    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n) return;
+    const int4 c = coords[i];
+    const bool ok = coord_ok(c) && in_box(c, box);
+    if (!ok) raise_flag(status, ST_RANGE);
+    keys[i] = ok ? pack_key(c.x, c.y, c.z, c.w) : kEmptyKey;
 }
 
 // Insert (keys[i] -> i).
@@ -452,8 +429,11 @@ __global__ void k_candidates_mark(const uint64_t *keys, int64_t n, int K, int s,
     atomicOr(&bits[cell >> 5], 1u << (cell & 31));
 }
 
-__global__ void k_drop_empty_key(const uint64_t *uniq, int64_t *count) {
-    if (*count > 0 && uniq[*count - 1] == kEmptyKey) --*count;
+// The number of distinct candidates for the host.  The empty key, if any candidate was rejected, is the last of them:
+// it is not counted.
+__global__ void k_tell_count(const uint64_t *uniq, const int64_t *count, int *status) {
+    const int64_t n = *count;
+    tell_host(status, ST_COUNT, (int)(n - (n > 0 && uniq[n - 1] == kEmptyKey)));
 }
 
 __global__ void k_unpack(const uint64_t *keys, int64_t n, int4 *coords) {
@@ -1058,8 +1038,8 @@ __global__ void __launch_bounds__(kThreads) k_bits_count(const uint64_t *__restr
     if (threadIdx.x == 0) block_total[blockIdx.x] = total;
 }
 
-// One block: block_total[] -> its exclusive prefix in place, and the grand total.
-__global__ void __launch_bounds__(kThreads) k_bits_scan(int32_t *__restrict__ block_total, int64_t n, int64_t *__restrict__ count) {
+// One block: block_total[] -> its exclusive prefix in place, and the grand total for the host.
+__global__ void __launch_bounds__(kThreads) k_bits_scan(int32_t *__restrict__ block_total, int64_t n, int *status) {
     int64_t run = 0;
     for (int64_t base = 0; base < n; base += kThreads) {
         const int64_t i = base + threadIdx.x;
@@ -1069,7 +1049,7 @@ __global__ void __launch_bounds__(kThreads) k_bits_scan(int32_t *__restrict__ bl
         if (i < n) block_total[i] = (int32_t)(run + before);
         run += total;
     }
-    if (threadIdx.x == 0) *count = run;
+    if (threadIdx.x == 0) tell_host(status, ST_COUNT, (int)run);
 }
 
 // Every set bit becomes the key of its cell, at the rank of the bit: cells are numbered in
@@ -1077,11 +1057,11 @@ __global__ void __launch_bounds__(kThreads) k_bits_scan(int32_t *__restrict__ bl
 // first set bit (the number of set bits before the word): the rank of any marked cell is then one load
 // of it, one of the word, and a popcount.  self_scan: block_total[] still holds the per-block counts and
 // every block sums the ones before it itself (a few thousand L2-resident words), which saves the scan
-// launch in between; the last block then also writes the grand total.
+// launch in between; the last block then also tells the host the grand total.
 __global__ void __launch_bounds__(kThreads) k_bits_expand(const uint64_t *__restrict__ words, int64_t n_words,
                                                           const int32_t *__restrict__ block_base, Grid cbox,
                                                           uint64_t *__restrict__ out_keys, int32_t *__restrict__ word_base,
-                                                          int self_scan, int64_t *__restrict__ count) {
+                                                          int self_scan, int *status) {
     const int64_t w = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     uint64_t bits = w < n_words ? words[w] : 0;
     int64_t before = 0;
@@ -1096,7 +1076,7 @@ __global__ void __launch_bounds__(kThreads) k_bits_expand(const uint64_t *__rest
     }
     int total;
     int64_t at = before + block_exclusive_scan(__popcll(bits), &total);
-    if (self_scan && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *count = before + total;
+    if (self_scan && blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) tell_host(status, ST_COUNT, (int)(before + total));
     if (w < n_words) word_base[w] = (int32_t)at;
     if (bits == 0) return;
     // coordinates of the word's first cell once (a box holds at most 2^30 cells: 32-bit arithmetic),
@@ -1231,12 +1211,9 @@ __global__ void __launch_bounds__(kThreads) k_down_pack(const int4 *__restrict__
     }
 }
 
-// Folds the partial boxes (every workgroup for itself: 16 KB from L2), clears the bitmap over the box and the
-// map's tile counters; the first workgroup leaves the header, and the box for the host.
-__global__ void __launch_bounds__(kThreads) k_down_clear(const int4 *__restrict__ parts, int n_parts, Box box, uint64_t max_words,
-                                                         uint4 *__restrict__ words, uint4 *__restrict__ sched, DownHead *head, int *status) {
+// The partial boxes folded, by every thread's workgroup for itself (16 KB from L2).
+__device__ __forceinline__ void fold_parts(const int4 *__restrict__ parts, int n_parts, int32_t (&v)[7]) {
     __shared__ int32_t sh[kThreads / 64][8];
-    int32_t v[7];
 #pragma unroll
     for (int q = 0; q < 7; ++q) v[q] = INT32_MIN;
     for (int i = threadIdx.x; i < n_parts; i += kThreads) {
@@ -1255,6 +1232,25 @@ __global__ void __launch_bounds__(kThreads) k_down_clear(const int4 *__restrict_
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < 7; ++q) v[q] = max(max(sh[0][q], sh[1][q]), max(sh[2][q], sh[3][q]));
+}
+
+// One workgroup: the box of the points, for the host.
+__global__ void __launch_bounds__(kThreads) k_tell_box(const int4 *__restrict__ parts, int n_parts, int *status) {
+    int32_t v[7];
+    fold_parts(parts, n_parts, v);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int q = 0; q < 7; ++q) tell_host(status, ST_BOX + q, v[q]);
+    }
+    tell_host_done(status, ST_BOXED, 1);
+}
+
+// Folds the partial boxes, clears the bitmap over the box and the map's tile counters; the first workgroup leaves the
+// header, and the box for the host.
+__global__ void __launch_bounds__(kThreads) k_down_clear(const int4 *__restrict__ parts, int n_parts, Box box, uint64_t max_words,
+                                                         uint4 *__restrict__ words, uint4 *__restrict__ sched, DownHead *head, int *status) {
+    int32_t v[7];
+    fold_parts(parts, n_parts, v);
     const bool none = v[6] == INT32_MIN;   // no valid point
     DownHead h;
     int32_t hi[3];
@@ -1752,11 +1748,12 @@ StatusSlot *g_slots[kSlotChunks] = {nullptr};
 
 inline StatusSlot &slot_at(int i) { return g_slots[i / kSlotChunk][i % kSlotChunk]; }
 
-// Whether what the slot's build reports has arrived: the number of its outputs (2x2x2 stride-2 maps), the verdict
-// on its input, or the sizes too.
-enum Awaited { kCount, kVerdict, kSizes };
+// Whether what the slot's build reports has arrived: the box of its points or the number of coarse ones (strided
+// builds), the verdict on its input, or the sizes too.
+enum Awaited { kBox, kCount, kVerdict, kSizes };
 inline bool slot_landed(const StatusSlot &s, Awaited what) {
     const volatile int32_t *h = s.host;
+    if (what == kBox) return h[ST_BOXED] != 0;
     if (what == kCount) return h[ST_COUNT] != -1;
     if (what == kVerdict) return h[ST_SEARCHED] != 0 || (s.totals && slot_landed(s, kSizes));   // sizes come after everything else
     for (int n = 0; n < s.K3; ++n)
@@ -2157,14 +2154,10 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
     const int A = (K + s - 1) / s, slots = A * A * A;
     const size_t n_cand = (size_t)N * slots;
     uint64_t *uniq;
-    int64_t *d_count;
     TS_TRY(tmp.get(&uniq, n_cand));
-    TS_TRY(tmp.get(&d_count, 1));
-    int32_t *d_bbox = nullptr;
-    if (opt.measure && !opt.grid) {
-        TS_TRY(tmp.get(&d_bbox, (size_t)kBoxSlots * kBoxSlotWords));
-        fill.add(d_bbox, (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t), 0x80000000u);
-    }
+    const bool measure = coords && opt.measure && !opt.grid;
+    int4 *parts = nullptr;
+    if (measure) TS_TRY(tmp.get(&parts, 2 * kDownPack));
     Grid cbox = {};
     uint64_t *words = nullptr;
     int32_t *word_base = nullptr, *block_total = nullptr;
@@ -2188,21 +2181,17 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
         fill.add(words, (size_t)n_words * sizeof(uint64_t), 0u);
         return TS_OK;
     };
-    TS_TRY(launch_fill(fill));
-    fill = FillArgs();
-    if (coords) TS_LAUNCH("k_pack", k_pack, per_point, block, reinterpret_cast<const int4 *>(coords), N, given, d_status, opt.box, d_bbox);
-    if (d_bbox) {
+    // What the host needs on the way it reads off the status words too.  Copies and stream synchronisations instead cost
+    // 30 us here (153 k points, 3x3x3 stride 2: 131 us and 101, with a boundary 144 and 115): behind a build that was waited
+    // for by its words, of which the runtime knows nothing, they take longer still than by themselves (128 and 141).
+    const int4 *c4 = reinterpret_cast<const int4 *>(coords);
+    if (measure) {
         // one more host round trip buys a build without a sort and a search without collisions
-        const size_t bytes = (size_t)kBoxSlots * kBoxSlotWords * sizeof(int32_t);
-        int32_t *hb = static_cast<int32_t *>(host_staging(bytes));
-        if (!hb) return last_fail_code();
-        TS_HIP(hipMemcpyAsync(hb, d_bbox, bytes, hipMemcpyDeviceToHost, st));
-        TS_HIP(hipStreamSynchronize(st));
-        int32_t top[7];
-        for (int q = 0; q < 7; ++q) {
-            top[q] = INT32_MIN;
-            for (int sl = 0; sl < kBoxSlots; ++sl) top[q] = hb[sl * kBoxSlotWords + q] > top[q] ? hb[sl * kBoxSlotWords + q] : top[q];
-        }
+        const unsigned n_parts = blocks_for(N, kThreads) < kDownPack ? blocks_for(N, kThreads) : kDownPack;
+        TS_LAUNCH("k_down_pack", k_down_pack, dim3(n_parts), block, c4, N, given, d_status, opt.box, parts);
+        TS_LAUNCH("k_tell_box", k_tell_box, dim3(1), block, parts, (int)n_parts, d_status);
+        TS_TRY(slot_wait(slot, kBox));
+        const volatile int32_t *top = slot_at(slot).host + ST_BOX;
         if (top[6] != INT32_MIN) {   // at least one valid point
             // the bitmap has one bit per cell of the box the outputs can lie in
             Box bx = {};
@@ -2219,6 +2208,8 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
                 opt.box = bx;   // on stays 0: nothing to check, the box is the points' own
             }
         }
+    } else if (coords) {
+        TS_LAUNCH("k_pack", k_pack, per_point, block, c4, N, given, d_status, opt.box);
     }
     // the coarse points lie in the box of the fine ones, moved by less than K and divided by s
     int32_t clo[3] = {0, 0, 0}, chi[3] = {0, 0, 0};
@@ -2238,12 +2229,14 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
         TS_LAUNCH("k_bits_count", k_bits_count, dim3((unsigned)n_wblocks), block, words, n_words, block_total);
         // up to a few thousand blocks every block sums the totals before it by itself; beyond, a scan launch
         const int self_scan = n_wblocks <= 8192;
-        if (!self_scan) TS_LAUNCH("k_bits_scan", k_bits_scan, dim3(1), block, block_total, n_wblocks, d_count);
+        if (!self_scan) TS_LAUNCH("k_bits_scan", k_bits_scan, dim3(1), block, block_total, n_wblocks, d_status);
         TS_LAUNCH("k_bits_expand", k_bits_expand, dim3((unsigned)n_wblocks), block, words, n_words, block_total, cbox, uniq,
-                  word_base, self_scan, d_count);
+                  word_base, self_scan, d_status);
     } else {
         // candidates -> sort -> unique (the empty key, if present, sorts last)
         uint64_t *cand, *sorted;
+        int64_t *d_count;
+        TS_TRY(tmp.get(&d_count, 1));
         TS_TRY(tmp.get(&cand, n_cand));
         TS_TRY(tmp.get(&sorted, n_cand));
         TS_LAUNCH("k_candidates", k_candidates, dim3(blocks_for(N, kThreads), slots), block, given, N, K, s, A, opt.bound, cand);
@@ -2256,14 +2249,10 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
             ProfScope ps("unique_keys");
             TS_HIP(rocprim::unique(ws, bytes, sorted, uniq, d_count, n_cand, rocprim::equal_to<uint64_t>(), st));
         }
-        // the empty key, if any candidate was rejected, is the last unique value: do not count it
-        TS_LAUNCH("k_drop_empty_key", k_drop_empty_key, dim3(1), dim3(1), uniq, d_count);
+        TS_LAUNCH("k_tell_count", k_tell_count, dim3(1), dim3(1), uniq, d_count, d_status);
     }
-    int64_t *h = static_cast<int64_t *>(host_staging(64));
-    if (!h) return last_fail_code();
-    TS_HIP(hipMemcpyAsync(h, d_count, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-    TS_HIP(hipStreamSynchronize(st));
-    const int64_t n_coarse = h[0];
+    TS_TRY(slot_wait(slot, kCount));
+    const int64_t n_coarse = slot_at(slot).host[ST_COUNT];
     if (n_coarse == 0) {
         // No candidate passed the modular check (or every coordinate was out of range): a map
         // without pairs.  The inputs are still checked for duplicates and range.
@@ -2533,6 +2522,7 @@ int resolve_count(const ts_kmap *kmap) {
     TS_HIP(hipStreamSynchronize(stream()));
     for (int n = 0; n < kMaxK3; ++n) h[ST_TOTALS + n] = -1;
     h[ST_TILES] = 0;
+    h[ST_COUNT] = -1;
     slot_at(slot).totals = false;
     m->count_pending = m->one_pair_per_input = m->scan_enqueued = false;
     for (void *p : {(void *)m->d_nbr, (void *)m->d_colbits, (void *)m->d_colbase, (void *)m->d_tile_order, (void *)m->d_wavemask,

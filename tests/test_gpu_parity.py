@@ -471,6 +471,21 @@ def test_kmap_strided_wide_box_through_the_bitmap():
             _check_map(coords, K, s, tr, wait=False)
 
 
+@pytest.mark.parametrize("K,s,transposed", [(3, 2, False), (1, 2, False), (2, 2, True)])
+@pytest.mark.parametrize("n", [1, 256, 257, 512 * 256 + 1])
+def test_kmap_strided_by_the_box_and_the_count_the_device_reports(K, s, transposed, n):
+    """Edges of the partial boxes (256 points a workgroup, 512 of them, then a second round), far from the origin; the hash
+    route counts the same outputs.  A point out of range is in no box, and there is no box where all are."""
+    coords = _rand_coords(400 + n, n, -30000, -29997 + 3 * round(n ** (1 / 3)), batches=2)
+    for search in (ts.TS_SEARCH_AUTO, ts.TS_SEARCH_HASH):
+        _check_map(coords, K, s, transposed, search=search)
+    bad = np.array([[0, 70000, 0, 0]], np.int32)
+    for given in (np.concatenate([coords, bad]), bad):
+        with pytest.raises(ts.TsError) as e:
+            ts.ts_build_kmap(to_dev(given), K, s, transposed)
+        assert e.value.code == ts.TS_ERR_COORD_RANGE
+
+
 def test_kmap_strided_duplicates_are_found_on_every_route():
     """Equal input points must be reported whether they share an output entry (forward), own a row each
     (transposed) or lose all their candidates to the boundary."""
