@@ -14,7 +14,7 @@ namespace ts {
 // ---- errors -------------------------------------------------------------------------------
 int fail(int code, const char *fmt, ...) __attribute__((format(printf, 2, 3)));
 // The code of this thread's last fail(): what a caller returns when a helper that reports through a
-// null pointer (dev_alloc, scratch, zero_row, host_staging) has failed.
+// null pointer (dev_alloc, scratch, zero_row) has failed.
 int last_fail_code();
 
 #define TS_HIP(call)                                                                        \
@@ -49,9 +49,6 @@ void *scratch(int slot, size_t bytes);
 
 // 4 KiB of device zeros (a feature row of any supported width), allocated once.
 const void *zero_row();
-
-// Pinned host staging area (at least `bytes` long), one per process.
-void *host_staging(size_t bytes);
 
 // Optional per-kernel timing (ts_profile_enable): an event pair around the enclosed launches.
 struct ProfScope {

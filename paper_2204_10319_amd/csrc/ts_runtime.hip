@@ -75,8 +75,6 @@ struct Scratch {
     Foreign how = {nullptr, nullptr};
 };
 Scratch g_scratch[8];
-void *g_host = nullptr;
-size_t g_host_bytes = 0;
 
 bool capturing() { return stream_capturing(g_stream); }
 }  // namespace
@@ -223,21 +221,6 @@ const void *zero_row() {
     }
     z = p;
     return z;
-}
-
-void *host_staging(size_t bytes) {
-    if (g_host_bytes >= bytes) return g_host;
-    if (g_host) (void)hipHostFree(g_host);
-    g_host = nullptr;
-    g_host_bytes = 0;
-    size_t want = bytes < 4096 ? 4096 : bytes;
-    if (hipHostMalloc(&g_host, want, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        fail(TS_ERR_OOM, "hipHostMalloc(%zu) failed", want);
-        return nullptr;
-    }
-    g_host_bytes = want;
-    return g_host;
 }
 
 // ---- per-kernel timing --------------------------------------------------------------------------

@@ -240,3 +240,21 @@ def test_sizes_asked_for_while_recording():
     torch.cuda.synchronize()
     assert out.eq(3).all() and np.array_equal(kmap.sizes(), sizes)
     del graph
+
+
+@pytest.mark.parametrize("n,side", [(3000, 30), (120000, 64)])
+def test_sorted_rows_on_another_stream(n, side):
+    """ts_kmap_sort_rows returns when the order is complete: a layer on another stream comes right after it.  The second map
+    has more distinct bitmasks than the table ranks, so that its rows are sorted."""
+    a, b = torch.cuda.Stream(), torch.cuda.Stream()
+    dev, x = to_dev(_coords(980, n, side)), to_dev(features(6, n, 64, np.float16))
+    w = ts.ts_weights_prepare(to_dev(conv_weights(7, 27, 64, 64, np.float16)))
+    want = ts.ts_sparse_conv_prepared(x, w, ts.ts_build_kmap(dev, 3, 1).sort_rows())
+    torch.cuda.synchronize()
+    for _ in range(3):
+        with torch.cuda.stream(a):
+            kmap = ts.ts_build_kmap(dev, 3, 1).sort_rows()
+        with torch.cuda.stream(b):
+            got = ts.ts_sparse_conv_prepared(x, w, kmap)
+        b.synchronize()
+        assert torch.equal(got, want)
