@@ -1646,6 +1646,7 @@ int static_scratch(unsigned char **ptr) {
 extern "C" {
 
 int ts_sparse_conv_static(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap *kmap, ts_tensor *out) {
+    if (kmap) TS_TRY(resolve_count(kmap, false));
     TS_TRY(check_layer(feats, weights, kmap, out));
     const bool f16 = feats->dtype == TS_F16;
     const int cin = feats->cols, cout = out->cols, step = f16 ? 32 : Elem<float>::KSTEP;

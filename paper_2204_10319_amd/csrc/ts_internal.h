@@ -85,8 +85,9 @@ inline int alloc_n(T **p, size_t n) {
 // need_sizes == false: only the verdict is awaited; the put-off scan of a stride-1 build is not run.
 int resolve(const struct ::ts_kmap *kmap, bool need_sizes = true);
 
-// Waits, if it has not happened yet, for a map's number of outputs alone (n_out).
-int resolve_count(const struct ::ts_kmap *kmap);
+// Waits, if it has not happened yet, for a map's number of outputs alone (n_out).  A map whose box turned out too large
+// for a bitmap is built by sorting then; may_build == false: that is TS_ERR_UNSUPPORTED and the map stays as it is.
+int resolve_count(const struct ::ts_kmap *kmap, bool may_build = true);
 
 // Call before work on a map is enqueued: waits for the map's build where the host has been told its verdict, its
 // search may still be running, and another stream than the build's is current.

@@ -2503,7 +2503,7 @@ namespace ts {
 // The number of outputs of a map whose build left it to be read here (build_down).  A box too large for the bitmap
 // ends in a build by sorting, from the keys.  That runs on the stream that is current now, while the caller orders his
 // work by the stream he built the map on: it is waited for (the host takes part in it twice anyway).
-int resolve_count(const ts_kmap *kmap) {
+int resolve_count(const ts_kmap *kmap, bool may_build) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
     if (!m->count_pending) return m->n_out >= 0 ? TS_OK : fail(m->error, "the build of this map failed after its outputs had been asked for");
     const int slot = m->pending_slot;
@@ -2521,6 +2521,8 @@ int resolve_count(const ts_kmap *kmap) {
         m->count_pending = false;
         return TS_OK;
     }
+    if (!may_build)
+        return fail(TS_ERR_UNSUPPORTED, "the box of this map's points is too large for a bitmap: building it needs memory, which this call must not take; ask ts_kmap_num_out first");
     if (stream_capturing(stream()))
         return fail(TS_ERR_UNSUPPORTED, "the box of this map's points is too large for a bitmap: its number of outputs must have been asked for before the stream is captured");
     TS_TRY(slot_wait(slot, kSizes));   // nothing more is written there

@@ -220,6 +220,25 @@ def test_layer_recorded_on_a_map_still_being_built(layer):
         del graph
 
 
+def test_layer_without_allocations_does_not_build_the_map():
+    """A 2x2x2 map over a box too large for the bitmap, whose number of outputs nobody has asked for, has yet to be built:
+    ts_sparse_conv_static refuses it, asks for no memory, and leaves the map to whoever asks for the number."""
+    coords = _far_spread(992, 3000)
+    dev, x, w = to_dev(coords), to_dev(features(9, len(coords), 32, np.float16)), to_dev(conv_weights(8, 8, 32, 64, np.float16))
+    want = ts.ts_sparse_conv(x, w, ts.ts_build_kmap(dev, 2, 2), dataflow=ts.TS_DATAFLOW_FUSED)
+    kmap, out, asked = ts.ts_build_kmap(dev, 2, 2, wait=False), torch.zeros_like(want), []
+    ts.ts_set_allocator(lambda size: asked.append(size) or 0, lambda ptr: None)
+    try:
+        for _ in range(2):
+            with pytest.raises(ts.TsError) as e:
+                ts.ts_sparse_conv_static(x, w, kmap, out)
+            assert e.value.code == ts.TS_ERR_UNSUPPORTED and not asked
+    finally:
+        ts.ts_set_allocator(None, None)
+    assert kmap.num_out == len(want)
+    assert torch.equal(ts.ts_sparse_conv_static(x, w, kmap, out), want)
+
+
 def test_sizes_asked_for_while_recording():
     """What a 3x3x3 build put off is not run inside a capture: the request is refused, and served after it."""
     side = torch.cuda.Stream()
