@@ -196,7 +196,9 @@ __device__ __forceinline__ int32_t table_find(const Grid &g, uint64_t want) {
 // entries: they stay in the caches where a table of points does not.  Nothing but the entries is cleared.
 struct BlockTable {
     uint64_t *ent;     // [capacity][2]: block key (kEmptyKey = free), occupancy mask
-    int32_t *rows;     // [capacity][64]
+    int32_t *rows;     // [capacity][64], valid where the mask says so; or, packed, [points]: those of an entry's set bits
+                       // one after the other
+    int32_t *base;     // packed rows: [capacity], where an entry's begin (else NULL)
     uint32_t mask;     // capacity - 1 (capacity: power of two, at least 1.5 per point, >= 1024)
     int shift;         // 64 - log2(capacity / 8)
 };
@@ -219,8 +221,10 @@ __device__ __forceinline__ uint32_t cell_of(uint64_t key) {
 // occupancy bits with one atomic each, because atomics are what bounds this kernel (about 20 G/s over the chip: one
 // claim and one mask update per point took 17.5 us for 153 k points and 46 us for 470 k; by runs 10.4 and 17).
 // A bit that was set before, or twice in a run, is how equal points are found.
+// Packed rows have no place before all bits are set: the points' slots are kept instead (slots).
+template <bool PACKED>
 __global__ void __launch_bounds__(kThreads) k_block_insert(const int4 *__restrict__ coords, int64_t n, uint64_t *__restrict__ keys,
-                                                           BlockTable t, int *status) {
+                                                           BlockTable t, uint32_t *__restrict__ slots, int *status) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     const int lane = threadIdx.x & 63;
     uint64_t key = kEmptyKey;
@@ -261,7 +265,61 @@ __global__ void __launch_bounds__(kThreads) k_block_insert(const int4 *__restric
         if ((taken & bits) != 0 || __popcll(bits) != end - lane) raise_flag(status, ST_DUP);
     }
     slot = (uint32_t)__shfl((int)slot, first, 64);
-    if (ok) t.rows[(uint64_t)slot * 64 + cell] = (int32_t)i;
+    if (!ok) return;
+    if constexpr (PACKED) slots[i] = slot;
+    else t.rows[(uint64_t)slot * 64 + cell] = (int32_t)i;
+}
+
+// Packed rows: where those of every entry begin.  A thread takes the eight slots of a group of blocks, so that their
+// rows stand together; workgroups take stretches off a counter.
+constexpr int kBlockBasePer = 8;
+__global__ void __launch_bounds__(kThreads) k_block_base(BlockTable t, int32_t *counter) {
+    __shared__ int wave_sum[kThreads / 64], s_first;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint64_t first = ((uint64_t)blockIdx.x * kThreads + tid) * kBlockBasePer;
+    int count[kBlockBasePer], sum = 0;
+#pragma unroll
+    for (int v = 0; v < kBlockBasePer; ++v) count[v] = first <= t.mask ? __popcll((long long)t.ent[2 * (first + v) + 1]) : 0;
+#pragma unroll
+    for (int v = 0; v < kBlockBasePer; ++v) sum += count[v];
+    int incl = sum;
+    for (int d = 1; d < 64; d <<= 1) {
+        const int up = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += up;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    if (tid == 0) {
+        int all = 0;
+        for (int w = 0; w < kThreads / 64; ++w) all += wave_sum[w];
+        s_first = atomicAdd(counter, all);
+    }
+    __syncthreads();
+    int at = s_first + incl - sum;
+    for (int w = 0; w < wave; ++w) at += wave_sum[w];
+    if (first > t.mask) return;
+#pragma unroll
+    for (int v = 0; v < kBlockBasePer; v += 4) {
+        int4 b;
+        b.x = at;
+        b.y = b.x + count[v];
+        b.z = b.y + count[v + 1];
+        b.w = b.z + count[v + 2];
+        at = b.w + count[v + 3];
+        *reinterpret_cast<int4 *>(t.base + first + v) = b;
+    }
+}
+
+__device__ __forceinline__ uint32_t bits_below(uint64_t mask, uint32_t cell) { return (uint32_t)__popcll(mask & ((1ull << cell) - 1ull)); }
+
+// Packed rows: every point's number to its place.  (Of two equal points one stays; there are as many places as cells.)
+__global__ void __launch_bounds__(kThreads) k_block_place(const uint64_t *__restrict__ keys, const uint32_t *__restrict__ slots, int64_t n, BlockTable t) {
+    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    if (i >= n) return;
+    const uint64_t key = keys[i];
+    if (key == kEmptyKey) return;
+    const uint64_t slot = slots[i];
+    t.rows[(uint32_t)t.base[slot] + bits_below(t.ent[2 * slot + 1], cell_of(key))] = (int32_t)i;
 }
 
 // Takes the points out again: the cells of `keys` go back to -1.
@@ -545,7 +603,7 @@ __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict_
 // outputs come out of the same pass.  What it replaces - a lane per (point, offset below the centre) probing a
 // table of points, mirrored 4-byte stores, and a second pass over the rows - took 17.4 + 9 us for 153 k points.
 // At: what holds the position of a row number in the table; 32 bits reach 2^26 entries (44.7 M points).
-template <typename At>
+template <bool PACKED, typename At>
 __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__restrict__ keys, int64_t n, BlockTable t,
                                                            int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
                                                            int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
@@ -556,7 +614,7 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
         struct {
             uint64_t mask[8][kThreads];
             uint32_t slot[8][kThreads];
-        } found;                                                  // per octant and thread: the block's mask and slot
+        } found;                                                  // per octant and thread: the block's mask and slot (packed rows: their base)
         int32_t rows[kThreads * PITCH];
     } lds;
     const int tid = threadIdx.x;
@@ -601,6 +659,11 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
             }
         }
     }
+    if constexpr (PACKED) {
+#pragma unroll
+        for (int o = 0; o < 8; ++o)
+            if ((present >> o) & 1u) slot[o] = (uint32_t)t.base[slot[o]];
+    }
 #pragma unroll
     for (int o = 0; o < 8; ++o) {
         lds.found.mask[o][tid] = (present >> o) & 1u ? (uint64_t)got[o].y : 0ull;
@@ -621,7 +684,8 @@ __global__ void __launch_bounds__(kThreads) k_block_search(const uint64_t *__res
             cell |= ((c[a] + (uint32_t)d[a]) & 3u) << (2 * (2 - a));
         }
         const uint64_t m = lds.found.mask[o][tid];
-        at[q] = (At)lds.found.slot[o][tid] * 64 + cell;
+        if constexpr (PACKED) at[q] = lds.found.slot[o][tid] + bits_below(m, cell);
+        else at[q] = (At)lds.found.slot[o][tid] * 64 + cell;
         mask |= (uint32_t)(m >> cell & 1ull) << q;
     }
     mask = ok ? mask | 1u << (K3 / 2) : 0u;   // (of two equal points one is not in the table: it still has itself)
@@ -1631,11 +1695,24 @@ int make_table(Temps &tmp, int64_t entries, Table *t, FillArgs *fill) {
 }
 
 // Allocates the block table; the clearing of its entries (free key, empty mask) is added to `fill`.
-int make_block_table(Temps &tmp, int64_t points, BlockTable *t, FillArgs *fill) {
+// A row number per cell of every slot takes 384 to 768 bytes per point, nearly all of it never touched, and is gone when
+// the build is.  Where that much cannot be had the rows are packed, which takes 10 to 16: two launches more, over the
+// entries and over the points (LiDAR scenes: 153 k points 26 us and 35, 1.5 M 178 and 245, 15 M 1.87 ms and 2.33).
+// counter: what k_block_base counts with then.
+int make_block_table(Temps &tmp, int64_t points, BlockTable *t, int32_t **counter, FillArgs *fill) {
     uint64_t cap = 1024;
     while (2 * cap < (uint64_t)(3 * points)) cap <<= 1;
     TS_TRY(tmp.get(&t->ent, 2 * cap));
-    TS_TRY(tmp.get(&t->rows, 64 * cap));
+    t->base = nullptr;
+    int rc = tmp.get(&t->rows, 64 * cap);
+    if (rc == TS_ERR_OOM) {
+        TS_TRY(tmp.get(&t->rows, (size_t)points));
+        TS_TRY(tmp.get(&t->base, cap));
+        TS_TRY(tmp.get(counter, 4));
+        fill->add(*counter, 16, 0u);
+    } else if (rc != TS_OK) {
+        return rc;
+    }
     t->mask = (uint32_t)(cap - 1);
     t->shift = 64 - __builtin_ctzll(cap >> 3);
     fill->add_pairs(t->ent, cap * 16, 0xFFFFFFFFu, 0u);
@@ -2410,16 +2487,22 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
         const int4 *c4 = reinterpret_cast<const int4 *>(coords);
         if (K == 3 && !opt.grid) {
             BlockTable bt;
-            TS_TRY(make_block_table(tmp, N, &bt, &fill));
+            int32_t *counter = nullptr;
+            TS_TRY(alloc_n(&m->d_rowmask, ((size_t)N + 3) & ~size_t(3)));   // what the map keeps comes before what the build can do without
+            TS_TRY(make_block_table(tmp, N, &bt, &counter, &fill));
             TS_TRY(launch_fill(fill));
-            TS_LAUNCH("k_block_insert", k_block_insert, per_point, block, c4, N, given, bt, d_status);
-            TS_TRY(alloc_n(&m->d_rowmask, ((size_t)N + 3) & ~size_t(3)));
-            if (bt.mask >> 26 == 0)
-                TS_LAUNCH("k_block_search", k_block_search<uint32_t>, per_point, block, given, N, bt, m->d_nbr, m->d_colbits,
-                          m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
-            else
-                TS_LAUNCH("k_block_search", k_block_search<uint64_t>, per_point, block, given, N, bt, m->d_nbr, m->d_colbits,
-                          m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status);
+#define TS_BLOCK_SEARCH(...) TS_LAUNCH("k_block_search", (k_block_search<__VA_ARGS__>), per_point, block, given, N, bt, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status)
+            if (bt.base) {   // (the points' slots stand where the search puts the bitmasks)
+                TS_LAUNCH("k_block_insert", k_block_insert<true>, per_point, block, c4, N, given, bt, m->d_rowmask, d_status);
+                TS_LAUNCH("k_block_base", k_block_base, dim3(blocks_for((int64_t)bt.mask + 1, kThreads * kBlockBasePer)), block, bt, counter);
+                TS_LAUNCH("k_block_place", k_block_place, per_point, block, given, m->d_rowmask, N, bt);
+                TS_BLOCK_SEARCH(true, uint32_t);
+            } else {
+                TS_LAUNCH("k_block_insert", k_block_insert<false>, per_point, block, c4, N, given, bt, nullptr, d_status);
+                if (bt.mask >> 26 == 0) TS_BLOCK_SEARCH(false, uint32_t);
+                else TS_BLOCK_SEARCH(false, uint64_t);
+            }
+#undef TS_BLOCK_SEARCH
             guard.committed = true;
             return finish(m, slot, wait, true);
         }

@@ -3,6 +3,7 @@
 Kernel maps must equal the oracle's bit-exactly as sorted (in, out, offset) triples;
 features must agree within a relative L2 error of 1e-5 (fp32) / 2e-3 (fp16 in, fp32 accumulate).
 """
+import contextlib
 import math
 
 import numpy as np
@@ -79,6 +80,26 @@ def test_kmap_rows_start_clean_in_reused_memory(wait):
         _check_map(sparse, 3, 1, wait=wait).free()
 
 
+@contextlib.contextmanager
+def _no_block_above(limit):
+    """An allocator that has no block of `limit` bytes or more; yields the sizes it refused."""
+    held, refused = {}, []
+
+    def alloc(size):
+        if size >= limit:
+            refused.append(size)
+            return 0
+        block = torch.full((size,), 0x5A, dtype=torch.uint8, device="cuda")      # memory is never clean
+        held[block.data_ptr()] = block
+        return block.data_ptr()
+
+    ts.ts_set_allocator(alloc, lambda ptr: held.pop(ptr, None))
+    try:
+        yield refused
+    finally:
+        ts.ts_set_allocator(None, None)
+
+
 @pytest.mark.parametrize("n", [63, 64, 65, 255, 257, 3000])
 @pytest.mark.parametrize("order", ["raster", "shuffled", "column", "far apart"])
 def test_kmap_blocks_of_4x4x4(n, order):
@@ -104,6 +125,30 @@ def test_kmap_blocks_of_4x4x4(n, order):
         with pytest.raises(ts.TsError) as e:
             ts.ts_build_kmap(to_dev(twice), 3, 1)
         assert e.value.code == ts.TS_ERR_DUPLICATE_COORD
+
+
+@pytest.mark.parametrize("n", [1, 255, 1365, 1366, 60000])
+@pytest.mark.parametrize("span", [2, 9, 4000])
+def test_kmap_blocks_without_memory_for_a_row_number_per_cell(n, span):
+    """A 3x3x3 map whose block table cannot have its row numbers by cell has them packed: full blocks, blocks with
+    a few points and with one, on both sides of a size of the table (1024 entries up to 682 points, 2048 up to
+    1365); points given twice or out of range; then a map is built the usual way again."""
+    side = max(int(np.ceil(n ** (1 / 3))), round(n ** (1 / 3) * span / 2))
+    coords = _rand_coords(7300 + n + span, n, -side // 2, side // 2 + 1, batches=2)
+    cap = 1024
+    while 2 * cap < 3 * n:
+        cap *= 2
+    with _no_block_above(cap * 64 * 4) as refused:
+        for wait in (True, False):
+            _check_map(coords, 3, 1, wait=wait).free()
+        assert len(refused) == 2
+        bad = coords[:1] + np.array([[0, 200000, 0, 0]], np.int32)
+        for rows, code in ((np.concatenate([coords, coords[n // 2:n // 2 + 1]]), ts.TS_ERR_DUPLICATE_COORD),
+                           (np.concatenate([coords, bad]), ts.TS_ERR_COORD_RANGE)):
+            with pytest.raises(ts.TsError) as e:
+                ts.ts_build_kmap(to_dev(rows), 3, 1)
+            assert e.value.code == code
+    _check_map(coords, 3, 1).free()
 
 
 def test_kmap_of_more_points_than_32_bit_positions_reach():
