@@ -1167,9 +1167,16 @@ inline int compute_units() {
 inline void order_for_layer(const ts_kmap *kmap, bool at_once) {
     if (kmap->n_tiles > compute_units() && (kmap->uses > 0 || at_once)) order_windows(kmap);
 }
+// Single precision, map and first layer together, with the order and without it (us), by tiles * C_in * C_out, which the
+// gain follows; the ordering itself takes 5 to 9:
+//   0.8 M (100 k points, 32 -> 32)    LiDAR  66, 65    surfaces 66, 65    scattered  77, 101
+//   1.0 M (125 k points, 32 -> 32)           73, 79             75, 78               83, 105
+//   1.2 M (153 k points, 32 -> 32)           79, 88             86, 97               98, 123
+//   1.4 M ( 45 k points, 64 -> 64)           94, 105           106, 107             111, 138
+// With hardly more than a tile per compute unit the longest tile decides once more: 258 tiles, 64 -> 64, 84 and 77 us
+// on a scan, 98 and 83 on surfaces; from 282 on every layer gains.
 inline bool order_at_once(const ts_kmap *kmap, int cin, int cout, size_t elem) {
-    // (fp32, first layer on a map: 97 k surface points, 32 -> 32 channels, 0.8 M, gains 8 us and pays 7; 153 k LiDAR points, 1.2 M, gains 16)
-    if (elem == 4) return kmap->n_tiles * cin * cout >= 1200000;
+    if (elem == 4) return kmap->n_tiles > compute_units() * 17 / 16 && kmap->n_tiles * cin * cout >= 1000000;
     return kmap->n_tiles > 2 * compute_units() && cin * cout >= 128 * 128;
 }
 
