@@ -38,9 +38,19 @@
  * (default: the null stream).  The stream, the scratch areas and the memory pool are per process: one
  * stream is in use at a time.  Changing the stream is allowed between calls; memory the library freed
  * on the previous stream is reused on the new one only after the previous stream has drained (the
- * library waits for it then, except under stream capture, where it allocates instead).  A ts_kmap must
- * be used on the stream it was built on, or after that stream has been synchronised.  Calls from several
- * host threads at once are not supported.
+ * library waits for it then, except under stream capture, where it allocates instead).  A ts_kmap may be
+ * used on the stream it was built on at any time, and on any other stream
+ *   - after ts_build_kmap (or wait != 0) has returned, or any call that waits for the map's sizes;
+ *   - after ts_kmap_status has returned: the first call on another stream waits on the host for the
+ *     build's stream, once;
+ *   - otherwise after the build's stream has been synchronised.
+ * Several layers of TS_F16 on one map share its tile counters: on different streams the caller orders them
+ * one after the other.  Calls from several host threads at once are not supported.
+ *
+ * Stream capture: layers may be recorded into a HIP graph.  What would need memory, launches outside the
+ * graph or a synchronisation then is refused with TS_ERR_UNSUPPORTED and leaves the capture as it is: scratch
+ * memory that must grow, the sizes of an asynchronous 3x3x3 map that have not been asked for, the number
+ * of outputs of a 2x2x2 map that has to be built by sorting (see ts_kmap_num_out).
  */
 #ifndef TS_H
 #define TS_H
@@ -95,7 +105,11 @@ typedef struct ts_tensor {
     int32_t dtype;  /* TS_F32 or TS_F16 */
 } ts_tensor;
 
-/* Opaque, immutable, device-resident kernel map (Sec. 2.1: the maps M plus P_out). */
+/*
+ * Opaque, device-resident kernel map (Sec. 2.1: the maps M plus P_out).  What it maps never changes; the library
+ * adds to it what later calls can use, when it is first wanted: sizes, pair lists, and on large 3x3x3 maps that
+ * serve more than one layer an order of the output rows (4 bytes per output; results do not depend on it).
+ */
 typedef struct ts_kmap ts_kmap;
 
 /* ---- mapping (Sec. 2.1; Alg. 1, Alg. 3) ---------------------------------------------------- */
@@ -106,32 +120,43 @@ typedef struct ts_kmap ts_kmap;
  *   kernel_size  1, 2 or 3 (stride 1 requires odd kernel_size); stride 1 or 2.
  *   transposed   0 or 1 (1 requires stride > 1), see the header comment.
  *   out_kmap     receives the new map; *out_kmap = NULL on error.
- * Internally: pack coordinates to 64-bit keys, insert inputs into an open-addressing hash
- * table, probe s*q_k + delta_n for every output and offset (one row of neighbour indices
- * per output), count per offset.  A strided build first finds its output coordinates
- * (Alg. 3) and chooses its route by the bounding box of its input, see ts_build_kmap_ex
- * (TS_SEARCH_AUTO).  The
- * per-offset pair lists are derived from that when first asked for (ts_kmap_pairs, the
- * explicit dataflow).  Synchronises the stream (it must learn N_out and the map sizes and
- * report bad input).  The map may be reused by any number of ts_sparse_conv calls.
+ * Internally: coordinates are packed to 64-bit keys.  A 3x3x3 stride-1 map is searched in a table of the occupied
+ * blocks of 4x4x4 cells, one thread per point (at most 8 lookups for the 27 offsets), and leaves one row of neighbour
+ * indices per output.  A strided build first finds its output coordinates (Alg. 3) and chooses its route by the
+ * bounding box of its input, see ts_build_kmap_ex (TS_SEARCH_AUTO).  The sizes are counted per offset after that; the
+ * per-offset pair lists are derived when first asked for (ts_kmap_pairs, the explicit dataflow).
+ * Waits until the map is complete, which any stream may use then, and its sizes and the verdict on the input are on
+ * the host.  (The wait is for words that the build's last kernel writes to pinned memory.  Other work on the stream is
+ * complete as far as it was enqueued before; that the runtime has noticed is not promised.)  The map may be reused by
+ * any number of ts_sparse_conv calls.
+ * Memory: the map keeps about 145 bytes per point (3x3x3) or 86 (2x2x2; a stride-2 map counts its inputs, which
+ * bound its outputs).  A 3x3x3 stride-1 build takes another 408 to 816 bytes per point while it runs, or, where that
+ * cannot be had, 34 to 64 and a sixth to a third more time.
  */
 int ts_build_kmap(const int32_t *coords, int64_t N, int kernel_size, int stride, int transposed,
                   ts_kmap **out_kmap);
 
 /*
- * ts_build_kmap without the wait at the end, where the build allows it: the map is returned as soon
- * as its kernels are enqueued, and its sizes and the error flags of its input (duplicate or
- * out-of-range coordinates) reach the host when something first needs them: ts_kmap_status,
- * ts_kmap_num_pairs / _sizes / _pairs, the explicit dataflow, ts_kmap_sort_rows, ts_kmap_transpose.
- * For a 3x3x3 stride-1 map the part of the build that only those need (the pass that counts each
+ * ts_build_kmap without the wait at the end: the map is returned as soon as its kernels are enqueued, and its
+ * sizes and the error flags of its input (duplicate or out-of-range coordinates) are waited for by what first
+ * needs them: ts_kmap_num_pairs / _sizes / _pairs, ts_kmap_sort_rows, ts_kmap_transpose and the explicit
+ * dataflow wait for the sizes, ts_kmap_status for the flags alone.
+ * For a 3x3x3 stride-1 map the part of the build that only the sizes need (the pass that counts each
  * offset's pairs) is put off until then as well.  The fused layer kernel needs none of it, so a
- * build followed by ts_sparse_conv runs on the device without a host round trip in between.  A map whose input was bad is safe to use (rows of
- * bad points have no neighbours) but its results are meaningless: call ts_kmap_status before
- * trusting them.  Strided maps still wait once inside (for the number of output points).
+ * build followed by ts_sparse_conv runs on the device without a host round trip in between.  A map whose input was
+ * bad is safe to use (rows of bad points have no neighbours) but its results are meaningless: call ts_kmap_status
+ * before trusting them.
+ * A 2x2x2 stride-2 map (TS_SEARCH_AUTO, or a box stated; no boundary) is enqueued whole as well.  Its number of
+ * outputs is waited for by what needs it: ts_kmap_num_out, ts_kmap_out_coords, ts_kmap_out_box, everything that waits
+ * for the sizes or the flags, and every layer (see ts_kmap_num_out).  Other strided and transposed builds wait inside,
+ * for the box of the points where that has to be measured and for the number of coarse points.
  */
 int ts_build_kmap_async(const int32_t *coords, int64_t N, int kernel_size, int stride, int transposed,
                         ts_kmap **out_kmap);
-/* Waits for an asynchronous build's verdict: TS_OK, TS_ERR_DUPLICATE_COORD or TS_ERR_COORD_RANGE. */
+/*
+ * Waits for an asynchronous build's verdict: TS_OK, TS_ERR_DUPLICATE_COORD or TS_ERR_COORD_RANGE.  The search of a
+ * 3x3x3 stride-1 build may still be running then (see Threading/streams above for other streams).
+ */
 int ts_kmap_status(const ts_kmap *kmap);
 /*
  * Optional, for a map from ts_build_kmap_async that will serve more than a fused layer: enqueues, without
@@ -156,18 +181,20 @@ int ts_identity_kmap(int64_t n, ts_kmap **out_kmap);
 /*
  * ts_build_kmap with the choices the paper leaves to each layer (Sec. 4.4; Alg. 3).  options == NULL
  * is ts_build_kmap.  The map built is the same whatever `search` says.
- *   search        TS_SEARCH_AUTO (what ts_build_kmap does): stride 1 searches the hash table.  A strided
- *                 build measures the bounding box of its coordinates on the device (one more host
- *                 round trip; none if the caller states the box: grid_batches > 0 with grid_lo / grid_hi
+ *   search        TS_SEARCH_AUTO (what ts_build_kmap does): stride 1 searches the table of blocks (3x3x3) or
+ *                 of points (1x1x1).  A strided build measures the bounding box of its coordinates on the
+ *                 device (one more host round trip, except for 2x2x2 stride-2 maps, which leave the box on the
+ *                 device; none if the caller states the box: grid_batches > 0 with grid_lo / grid_hi
  *                 as below, ignored at stride 1) and, when its outputs can lie in at most 2^28 cells,
  *                 marks its candidates in a bitmap over those cells (32 MiB at most, a temporary) and
  *                 reads the set bits off in order: the sorted distinct outputs without a sort.  The map
  *                 then follows without a search either: every kept candidate of an input is an output,
  *                 whose row number is the rank of its cell among the marked ones.  Larger boxes take the
  *                 hash route.
- *                 TS_SEARCH_HASH: the open-addressing table (a temporary of the build: a power of two
+ *                 TS_SEARCH_HASH: the open-addressing table of points (a temporary of the build: a power of two
  *                 of 12-byte slots, four per searched point or more; at most 2^26 points); a strided
- *                 build finds its output coordinates by sorting the candidates.  TS_SEARCH_GRID: the collision-free
+ *                 build finds its output coordinates by sorting the candidates.  3x3x3 stride-1 maps are searched in
+ *                 blocks here too.  TS_SEARCH_GRID: the collision-free
  *                 grid of Sec. 4.4, one int32 cell per coordinate of the box the caller states
  *                 with grid_lo / grid_hi (inclusive bounds of x, y, z over the rows of `coords`) and
  *                 grid_batches (batch indices are below it): one memory access per insertion and per
@@ -203,7 +230,8 @@ int ts_build_kmap_ex(const int32_t *coords, int64_t N, int kernel_size, int stri
  * ts_build_kmap(fine coords, kernel_size, stride, 1) yields for the coordinates `forward` was built
  * from, derived from `forward` without another search.  A network's upsampling layer takes this
  * instead of building its map from coordinates (maps are shared between layers, Sec. 2.3).
- * `forward` is not modified and need not outlive the result.  Does not synchronise.
+ * `forward` need not outlive the result.  Waits for the sizes of `forward` where they are not known yet; the
+ * transposed map itself is enqueued without a wait.
  */
 int ts_kmap_transpose(const ts_kmap *forward, ts_kmap **out_kmap);
 
@@ -212,7 +240,8 @@ int ts_kmap_transpose(const ts_kmap *forward, ts_kmap **out_kmap);
  * so that the 128 rows a workgroup of the output-stationary kernel handles share their offsets and
  * absent ones are skipped per tile (Sec. 4.2 argues the same way for grouping by map size).  It
  * costs about as much as the search itself, so it pays for maps that serve several layers; results
- * of ts_sparse_conv do not depend on it bit for bit.  Idempotent.  Synchronises the stream.
+ * of ts_sparse_conv do not depend on it bit for bit.  Idempotent.  Waits until the order is complete, which any stream
+ * may use then.
  */
 int ts_kmap_sort_rows(ts_kmap *kmap);
 
@@ -220,15 +249,21 @@ int ts_kmap_sort_rows(ts_kmap *kmap);
 void ts_free(ts_kmap *kmap);
 
 int64_t ts_kmap_num_in(const ts_kmap *kmap);        /* rows of X_in the map expects               */
-int64_t ts_kmap_num_out(const ts_kmap *kmap);       /* rows of X_out it produces                  */
-int64_t ts_kmap_num_pairs(const ts_kmap *kmap);     /* |M| = sum of the per-offset sizes          */
+/*
+ * Rows of X_out it produces.  Waits for an asynchronous 2x2x2 stride-2 build to report them.  Such a build whose outputs can
+ * lie in more than 2^28 cells has found that out on the device; it is then built by sorting here, on the current
+ * stream, which takes memory and ends complete.  A negative ts_status when that failed (asked again, it keeps failing).
+ */
+int64_t ts_kmap_num_out(const ts_kmap *kmap);
+int64_t ts_kmap_num_pairs(const ts_kmap *kmap);     /* |M| = sum of the per-offset sizes; -1 on error */
 int     ts_kmap_kernel_volume(const ts_kmap *kmap); /* K^3                                        */
 
-/* Output coordinates P_out: dst is device int32 [num_out][4].  (For a transposed map: the fine coords.) */
+/* Output coordinates P_out: dst is device int32 [num_out][4].  (For a transposed map: the fine coords.)  Waits as ts_kmap_num_out does. */
 int ts_kmap_out_coords(const ts_kmap *kmap, int32_t *dst);
 /*
- * A box that holds every output coordinate of a strided forward map, known on the host without a wait
- * when the build marked its candidates in a bitmap over such a box (the default route and TS_SEARCH_GRID):
+ * A box that holds every output coordinate of a strided forward map, known
+ * when the build marked its candidates in a bitmap over such a box (the default route and TS_SEARCH_GRID).  Waits as
+ * ts_kmap_num_out does.
  * lo, hi (host, 3 values each, inclusive x, y, z) and *batches (batch indices are below it).  It is what
  * the build of the next level of a pyramid can be given as its box (ts_kmap_options: TS_SEARCH_AUTO with
  * grid_lo / grid_hi / grid_batches stated), which then need not measure one.  TS_ERR_UNSUPPORTED for maps
@@ -257,7 +292,9 @@ int ts_kmap_pairs(const ts_kmap *kmap, int32_t *in_idx, int32_t *out_idx);
  * C_out must be a multiple of 32; C_in may be anything (rows narrower than the kernels' operand step -
  * 32 channels for TS_F16, 8 for TS_F32 - are zero-extended in library scratch: the 4-channel stem of a
  * network); both at most 1024 (TS_ERR_UNSUPPORTED beyond).
- * Never synchronises.  Uses library-owned scratch memory (repacked weights, padded features, the
+ * Does not wait for its own work.  It waits for the number of outputs of an asynchronous 2x2x2 map (ts_kmap_num_out), and,
+ * where it takes the explicit dataflow, for the sizes of an asynchronous map: wide layers on maps of few points.
+ * Uses library-owned scratch memory (repacked weights, padded features, the
  * buffers F and G of the explicit dataflows) that grows on demand with hipMalloc; an outgrown area stays
  * allocated, unused, until ts_release_cache, because work already enqueued or a HIP graph captured earlier
  * may still address it.  While the stream is being captured nothing can grow: a call that would need to
@@ -321,12 +358,15 @@ int ts_sparse_conv_ex(const ts_tensor *feats, const ts_tensor *weights, const ts
  * piece of memory ts_sparse_conv takes from the library's grow-on-demand scratch - the weights repacked
  * into the order the kernels read, plus a row of zeros for TS_F32 - lives in a fixed array inside the
  * library's code object (4 MiB + 4 KiB on every GPU the library runs on, held until the process ends).
- * The call reaches no hipMalloc, hipFree or other allocating routine, and never synchronises.
+ * The call reaches no hipMalloc, hipFree or other allocating routine, and does not wait for the device, except for a
+ * map whose build nobody has waited for: for the number of outputs of an asynchronous 2x2x2 map, and on another stream
+ * than the build's where ts_kmap_status alone was asked.
  * Limits (TS_ERR_UNSUPPORTED beyond them, with the figures in ts_last_error):
  *   K^3 * C_in * C_out * element size <= 4 MiB (e.g. 27 x 256 x 256 fp16, 27 x 192 x 192 fp32);
  *   C_in a multiple of 32 (TS_F16) or 8 (TS_F32): narrower rows would need a padded copy of feats;
  *   features and weights below 2 GiB each.
- * The map must come from a build that has finished its own allocations (any map ts_build_kmap* returned).
+ * The map must come from a build that has finished its own allocations: any map ts_build_kmap* returned, but for an
+ * asynchronous 2x2x2 one that has yet to be built by sorting (TS_ERR_UNSUPPORTED until ts_kmap_num_out has been asked).
  * The first call on a device looks the array's address up (hipGetSymbolAddress); make that call outside a
  * capture.  Every call on a GPU shares that GPU's array and overwrites it: calls that overlap on one GPU
  * (two streams, two host threads) race; calls on one stream are ordered and safe.

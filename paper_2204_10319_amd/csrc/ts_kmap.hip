@@ -1,20 +1,26 @@
 // Kernel-map construction (paper Sec. 2.1: output coordinates, Alg. 3; map search, Alg. 1).
 //
-// Pipeline on the device, one stream:
-//   fill     one launch clears the hash table, the counters and (stride 1) the neighbour table
-//   pack     (b,x,y,z) -> order-preserving 64-bit keys       (one integer per coordinate, Sec. 2.1.2)
-//   stride>1: candidate keys (p - delta)/s, radix sort, unique -> P_out           (Alg. 3, stages 1-4)
-//   insert   the searched point set into an open-addressing table (64-bit CAS)
-//   search   s*q_k + delta_n for every output k and offset n (Alg. 1).  Stride 1, K = 3: one thread
-//            per (point, offset below the centre), the mirrored entry written alongside
-//            (Sec. 4.2.1), then a pass over the rows; otherwise one thread per output.  Leaves per
-//            output the row of neighbour indices and its offset bitmask, and per 64 outputs and
-//            offset a presence bitmap with its count
-//   scan     per-offset exclusive scan of the block counts -> where each pair sits in the
-//            offset-major lists, and the per-offset totals
-// The host waits once, after `scan`, for the map sizes and error flags.
-// The searched set can also be held in a coordinate grid (`grid` of Sec. 4.4: collision-free, one
-// memory access per insertion and per lookup) when the caller states the bounds of its coordinates;
+// Keys: (b,x,y,z) -> order-preserving 64 bits, one integer per coordinate (Sec. 2.1.2).  Every build leaves, per output,
+// the row of neighbour indices and its offset bitmask, and per 64 outputs and offset a presence bitmap with its count.
+// By kind of map, on one stream:
+//   3x3x3, stride 1   fill (clears the block entries), block_insert (pack, insert by blocks of 4x4x4 cells), block_search
+//            (a thread per point: Alg. 1's 27 offsets from at most 8 blocks).  Row numbers are packed, by block_base and
+//            block_place, only where memory for one per cell is lacking.
+//   2x2x2, stride 2   down_pack, _clear, _mark, _count, _expand, _scatter, rows: the box, the number of outputs and what
+//            is sized by them stay on the device, nothing waits in between; its transposed map: up_rows
+//   other strided and transposed maps   pack; candidate keys (p - delta)/s (Alg. 3, stages 1-4), made distinct and sorted
+//            either in a bitmap over their box, whose ranks then are the map (rank_scatter, rows), or by radix sort and
+//            unique, with a search through a hash table of points (insert, probe).  The host waits for the box, where
+//            that is measured, and for the number of outputs.
+//   1x1x1    pack_insert, probe: the hash table of points (64-bit CAS)
+//   stride 1 in a coordinate grid (`grid` of Sec. 4.4: collision-free, one memory access per insertion and per lookup), when
+//            the caller states the bounds of its coordinates: pack_insert, probe_symmetric (one thread per point and
+//            offset below the centre, the mirrored entry written alongside, Sec. 4.2.1), grid_erase; rows goes with the scan
+// and for all of them
+//   scan     per-offset exclusive scan of the block counts -> where each pair sits in the offset-major lists, and the
+//            per-offset totals; the order of the tiles.  Put off for 3x3x3 stride-1 maps that nobody has asked for sizes.
+// The kernels tell the host what it needs (verdict on the input, number of outputs, sizes) in pinned words, which it
+// watches when something first asks.
 // Alg. 3's boundary check is applied where the candidates are formed.
 //   compact  pair lists M[W_n] (in, out), ordered by output index inside an offset: derived from
 //            the above when first asked for (ts_kmap_pairs, the explicit dataflow's gather)
