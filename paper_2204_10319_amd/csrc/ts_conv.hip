@@ -1596,24 +1596,39 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // small to fill the machine with tiles (the coarse levels of a U-Net) are cheaper explicit,
 // everything else fused; the factor and the size limit come from timing both on the layers of
 // the MinkUNet-style benchmark network.
-// The number of pairs is that of surface-like scenes, or the map's own where that is larger: a solid has up to 27 a point
-// where scans and surfaces have 7 to 9, and fetching them costs three times the fused kernel (fp16, 192 -> 192 on 32 k
-// points of a solid 307 us and 97, 256 -> 256 on 20 k 266 and 133).  An asynchronous build that nobody has asked does not know
-// its own yet, and waiting for it costs a small step three times what its kernels take; where the layer comes out
-// fused by the surface-like number it does so by any larger one, so nothing is waited for there, and where it does
-// not, the explicit dataflow waits for the map's own in any case: whether somebody has asked never decides.  That is why a
-// smaller number (scattered points have 3) does not count, though fetching would gain there (128 -> 128 on 7.5 k scattered
-// points: 27 us fused, 21 fetched).  (A build that found bad input, or whose sizes cannot be had now, leaves the fused
-// kernel, which needs none.)
+// What the line is drawn by is the number of pairs.  An asynchronous build that nobody has asked does not know its own yet,
+// and waiting for it costs a step of a small map and one layer 6 to 20 us.  Whether somebody has asked must not decide, the
+// dataflows differ in bits.  So:
+//   - fp16 goes by the typical number of surface-like scenes, or the map's own where that is larger: a solid has up to 27 a
+//     point where scans and surfaces have 7 to 9, and fetching them costs three times the fused kernel (192 -> 192 on 32 k points
+//     of a solid 307 us and 97, 256 -> 256 on 20 k 266 and 133).  Where the layer comes out fused by the typical number it
+//     does so by any larger one, and nothing is waited for; where it does not, the explicit dataflow waits in any case.
+//     On so few points that the pairs' bytes are less than 40 times the weights that one workgroup goes through, fetching stays
+//     ahead however dense they are (192 -> 192, fused and fetched, surfaces 1 k 24 us and 20, 3 k (41 times) 24 and 25, a solid of
+//     1 k 46 and 30, of 8 k (300 times) 51 and 77).
+//     A smaller number does not count, though fetching gains on scattered points, which have 3 (96 -> 96 on 1 k points 20 us
+//     fused and 13 fetched, on 32 k 35 and 29; 128 -> 128 on 8 k 27 and 21; nothing on a thinned-out scan): the wait would take more
+//     from a step (96 -> 96 on 1 k scattered points 31 us without it and 40 with it, on 8 k of a scan 34 and 53).
+//   - Single precision with weights of 16 KiB an offset and more goes by its own number, and waits for it: the fused kernel
+//     walks a tile's offsets at 2.3 us each (64 -> 64; 8.6 at 128 -> 128), however few tiles there are, so that what decides is
+//     the pairs' bytes against the weights that one workgroup goes through, a thousand to one by the rates measured: 64 -> 64,
+//     fused and fetched, scattered 1 k 67 us and 14, scan 8 k 58 and 20, surfaces 32 k (0.92 of the line) 69 and 55, a solid
+//     of 32 k (2.6) 74 and 122; 128 -> 128, surfaces 16 k 199 and 78.  Narrower ones gain less than the wait takes.
+//     (Recorded on a map without pair lists, which need memory, such a layer goes by the typical number.)
+// (A build that found bad input, or whose sizes cannot be had now, leaves the fused kernel, which needs none.)
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
     const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
     const double typical = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;
-    const double fused_weight_bytes = (double)kmap->n_tiles * tile_offsets * cin * cout * elem;
+    const double slabs = tile_offsets * cin * cout * elem, fused_weight_bytes = (double)kmap->n_tiles * slabs;
     const double bytes_per_pair = 2.0 * cin * elem + 2.0 * cout * sizeof(float);
-    if (fused_weight_bytes <= 0.6 * typical * bytes_per_pair || resolve(kmap) != TS_OK) return false;
-    return (double)kmap->M <= typical || fused_weight_bytes > 0.6 * (double)kmap->M * bytes_per_pair;
+    const bool wide_f32 = elem == 4 && kmap->s == 1 && kmap->K3 == 27 && cin * cout >= 4096 && (kmap->d_in_idx || !stream_capturing(stream()));
+    if (!wide_f32 && fused_weight_bytes <= 0.6 * typical * bytes_per_pair) return false;
+    if (resolve(kmap) != TS_OK) return false;
+    const double pair_bytes = (double)kmap->M * bytes_per_pair;
+    if (wide_f32) return pair_bytes < 1000 * slabs;
+    return (double)kmap->M <= typical || fused_weight_bytes > 0.6 * pair_bytes || pair_bytes < 40 * slabs;
 }
 
 // ---- the layer for callers that cannot allocate -----------------------------------------------------------

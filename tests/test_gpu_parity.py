@@ -939,14 +939,19 @@ def test_rows_of_a_map_in_use_are_reordered_f32(n, c_out):
 
 
 @pytest.mark.parametrize("build", ["waiting", "asked", "nobody asked"])
-@pytest.mark.parametrize("scene,n,c,want", [("solid", 8000, 256, "fused"), ("solid", 800, 512, "fetched"), ("scattered", 7500, 128, "fused"), ("scattered", 7500, 256, "fetched")])
-def test_automatic_dataflow_goes_by_the_maps_own_pairs(scene, n, c, want, build):
-    """Full cubes have up to 27 pairs a point, scattered points 3, which count as a surface's 7.5: layers on either side of
-    the line that the weights and the pairs' rows draw, whether or not the sizes are known.  The dataflows differ in bits."""
+@pytest.mark.parametrize("scene,n,c,dtype,want", [
+    ("solid", 8000, 256, np.float16, "fused"), ("solid", 800, 512, np.float16, "fetched"), ("solid", 1000, 192, np.float16, "fetched"), ("solid", 8000, 192, np.float16, "fused"),
+    ("scattered", 7500, 128, np.float16, "fused"), ("scattered", 7500, 256, np.float16, "fetched"),
+    ("scattered", 7500, 32, np.float32, "fused"), ("scattered", 7500, 64, np.float32, "fetched"),
+    ("solid", 8000, 64, np.float32, "fetched"), ("solid", 32768, 64, np.float32, "fused")])
+def test_automatic_dataflow_goes_by_the_maps_own_pairs(scene, n, c, dtype, want, build):
+    """Full cubes have up to 27 pairs a point, scattered points 3, which in half precision count as a surface's 7.5: layers on
+    either side of the lines that the weights and the pairs' rows draw, whether or not the sizes are known.  The dataflows
+    differ in bits."""
     side = round(n ** (1 / 3)) if scene == "solid" else 46
     flat = np.random.Generator(np.random.PCG64(n)).permutation(side ** 3)[:n]
     coords = np.stack([0 * flat, flat // side ** 2, flat // side % side, flat % side], 1).astype(np.int32)
-    kmap, x, w = ts.ts_build_kmap(to_dev(coords), 3, 1), to_dev(features(n, len(coords), c, np.float16)), to_dev(conv_weights(n + 1, 27, c, c, np.float16))
+    kmap, x, w = ts.ts_build_kmap(to_dev(coords), 3, 1), to_dev(features(n, len(coords), c, dtype)), to_dev(conv_weights(n + 1, 27, c, c, dtype))
     fused, fetched = (ts.ts_sparse_conv(x, w, kmap, dataflow=d) for d in (ts.TS_DATAFLOW_FUSED, ts.TS_DATAFLOW_FETCH))
     assert not torch.equal(fused, fetched)
     for layer in (lambda m: ts.ts_sparse_conv(x, w, m), lambda m: ts.ts_sparse_conv_prepared(x, ts.ts_weights_prepare(w), m)):

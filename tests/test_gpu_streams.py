@@ -261,6 +261,33 @@ def test_sizes_asked_for_while_recording():
     del graph
 
 
+def test_single_precision_layer_recorded_with_and_without_pair_lists():
+    """A 64 -> 64 layer on few points is fetched, which takes the map's pair lists.  Recorded on a map that has none yet it
+    takes no memory and is fused; once the layer has run eagerly the recording is what the eager layer is."""
+    dev, x = to_dev(_coords(996, 3000, 30)), to_dev(features(9, 3000, 64, np.float32))
+    plain = to_dev(conv_weights(8, 27, 64, 64, np.float32))
+    w = ts.ts_weights_prepare(plain)
+    ref = ts.ts_build_kmap(dev, 3, 1)
+    fused, fetched = (ts.ts_sparse_conv(x, plain, ref, dataflow=d) for d in (ts.TS_DATAFLOW_FUSED, ts.TS_DATAFLOW_FETCH))
+    assert not torch.equal(fused, fetched)
+    out, side = torch.zeros_like(fused), torch.cuda.Stream()
+    for wait in (True, False):
+        kmap = ts.ts_build_kmap(dev, 3, 1, wait=wait)
+        torch.cuda.synchronize()
+        for want in (fused, fetched):
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=side):
+                ts.ts_sparse_conv_prepared(x, w, kmap, out=out)
+            for _ in range(3):
+                out.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(out, want)
+                assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), fetched)
+                torch.cuda.synchronize()
+            del graph
+
+
 @pytest.mark.parametrize("n,side", [(3000, 30), (120000, 64)])
 def test_sorted_rows_on_another_stream(n, side):
     """ts_kmap_sort_rows returns when the order is complete: a layer on another stream comes right after it.  The second map
