@@ -9,12 +9,12 @@
 //              written once).
 //  fused     - one output-stationary kernel.  A workgroup owns 128 outputs (sorted by
 //              neighbour bitmask so that they share offsets), walks the offsets present in
-//              the tile, stages W_n in LDS, loads the neighbours' feature rows straight into
-//              the MFMA operand registers and keeps the sum over offsets in the accumulators.
+//              the tile, brings the neighbours' feature rows into LDS or straight into the MFMA
+//              operand registers and keeps the sum over offsets in the accumulators.
 //              Neither F nor G exists; every output row is written once.
 //
-// MFMA orientation: D[co][m] += Wt[co][ci] * X[m][ci]  (32x32 tiles, "A" = transposed weights
-// from LDS, "B" = gathered feature rows).  A lane then owns 4 consecutive output channels of
+// MFMA orientation: D[co][m] += Wt[co][ci] * X[m][ci]  ("A" = transposed weights, "B" = gathered
+// feature rows).  A lane then owns 4 consecutive output channels of
 // one row per accumulator quad, which makes the stores 8-16 bytes wide.
 #include "ts_internal.h"
 
@@ -283,19 +283,6 @@ __global__ void __launch_bounds__(kThreads) k_fused(const T *__restrict__ X, con
     }
 }
 
-// ---- fused output-stationary kernel, fp16, deep software pipeline ---------------------------------
-// D[co][m] += Wt[co][ci] * X[m][ci] with v_mfma_f32_16x16x32_f16: lane l of a wave holds, of the
-// "B" operand, 8 consecutive input channels (8 * (l / 16) + 0..7 of a 32-channel step) of
-// output row l % 16, i.e. 16 contiguous bytes of the neighbour's feature row, so gathered rows
-// go from memory straight into the operand registers, 4 lanes per 64 bytes of a row.  A wave owns
-// 32 output rows (two 16-column blocks), a workgroup 128; the accumulators hold NCO blocks of 16
-// output channels.  A stage is one (offset, KC-channel chunk) of the tile: its weight slab, kept
-// in global memory in operand order, goes global -> registers -> LDS once for the four waves.
-// What a wave pays for is dependent memory round trips, so the loads of a stage are issued DEPTH
-// stages before their use and rotate through DEPTH register sets; one barrier per stage.  (DEPTH = 2;
-// 3 took registers that two more waves can have and measured 2 to 4 % slower.)
-// Rows of an output are added in offset order whatever the tile holds, so results do not depend
-// on how rows are grouped.
 typedef _Float16 half8v __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));   // native vector: arrays of it stay in registers
 
@@ -310,7 +297,7 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
     static_for_impl(fn, std::make_integer_sequence<int, N>{});
 }
 
-// Epilogue of the two kernels below.  A lane holds, per block of 16 output channels, channels 4 (l / 16) .. +3 of rows
+// Epilogue of k_conv_res.  A lane holds, per block of 16 output channels, channels 4 (l / 16) .. +3 of rows
 // l % 16 and 16 + l % 16 of the wave's 32: stored from there, an instruction writes 32 bytes each of 16 rows, in
 // 64 separate accesses.  Through LDS (16 rows at a time, `buf`: NCO KiB / 2 that only this wave touches, 16-byte units
 // swizzled by row) rows leave, and the residual's come in, as whole lines.
@@ -378,234 +365,408 @@ struct RowStore {
     }
 };
 
-// (Three waves per SIMD are asked for wherever the accumulators leave room: left to itself the compiler
-// takes a few registers more than that allows for the six- and eight-block single-step variants.)
-template <int NCO, int KSTEPS, int LKS, int DEPTH, bool TWO = false>
-__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCO * KSTEPS <= 8 && NCO < 8 ? 3 : 2))) k_conv_tile(const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf,
-                                                        const int32_t *__restrict__ nbr, int stride,
-                                                        const int32_t *__restrict__ perm, int from_end,
-                                                        const int32_t *__restrict__ tile_order, int64_t n_out,
-                                                        _Float16 *__restrict__ out, int *__restrict__ sched,
-                                                        int cin, int cout, int K3, const _Float16 *__restrict__ bias,
-                                                        const _Float16 *__restrict__ residual, int relu, int x_bytes,
-                                                        int w_bytes, int centre, const _Float16 *__restrict__ X2,
-                                                        int x2_bytes, int cin1) {
-    // TWO: the layer's input is the channel concatenation [X | X2], which is never formed: input channels
-    // below cin1 are read from X (rows of cin1 channels), the others from X2 (rows of cin - cin1 channels);
-    // cin1 is a multiple of 32, so each 32-channel operand step lies in one of the two.  Otherwise X2,
-    // x2_bytes are unused and cin1 = cin.
-    constexpr int KC = KSTEPS * 32, FRAGS = NCO * KSTEPS, SLAB = FRAGS * 64;   // slab in 16-byte vectors
-    constexpr int WV = (SLAB + kThreads - 1) / kThreads;
-    __shared__ u32x4 lds_w[2][SLAB];
-    __shared__ int32_t lds_j[kMaxK3][kTileRows], s_row[kTileRows];
-    __shared__ uint32_t s_mask;
+// ---- fused output-stationary kernel, fp16 -----------------------------------------------------------------
+// D[co][m] += Wt[co][ci] * X[m][ci] with v_mfma_f32_16x16x32_f16.  A workgroup of four waves owns 128 output rows and
+// 16 NCO output channels, a wave RB blocks of 16 rows and CB of 16 channels of them; a stage is one (offset, 32 KS
+// channels), with HALF also the 32 channels that are left over at the end of a row.  The accumulators stay in registers across all stages; rows of an output are added in offset order whatever
+// the tile holds, so results do not depend on how rows are grouped.
+//
+// What bounds it, and the layout that follows (MI355X, measured):
+//  - A vector load costs the address unit 16 cycles per KiB when neighbouring lanes read neighbouring bytes (31 TB/s out of
+//    L2 over the chip), 40 to 48 when 16 neighbouring lanes are 16 rows, as an MFMA operand wants them (13 TB/s).  So the
+//    rows of a stage go from memory straight into LDS, whole lines at a time (eight lanes a row of 64 channels), and operands
+//    are read from there, 16-byte units being swizzled so that 16 lanes meet 16 different banks.  Rows for the next stage are
+//    under way while this one is multiplied.  Only blocks of 16 rows that meet the offset are fetched, read and multiplied.
+//  - Weights are not shared through LDS: in operand order a wave reads its own channels' as whole KiB, a stage ahead.
+//  - The neighbour table's rows of a tile are brought into LDS the same way while the tile before is stored.
+//  - A stage has one barrier and some 150 instructions around 16 to 32 MFMAs; three workgroups per CU are what hides that
+//    (two: 15 to 20 % slower), so registers are held to 168.
+//  - The next tile is asked for shortly before this one ends: asked for at its start, the workgroups with the longest
+//    tiles took as many more as the others.
+// Layers with their tail on kept maps, against a kernel that loaded rows as operands and weights through LDS (us; 64 -> 64,
+// 128 -> 128, 96 -> 96): 153 k points of a scan 39 -> 31, 79 -> 60, 61 -> 57; 97 k of surfaces 34 -> 27, 69 -> 54, 51 -> 46;
+// 1.53 M of scans 311 -> 282, 705 -> 595, 546 -> 551; 64 k after one halving 26 -> 22, 52 -> 46, 41 -> 36.
+
+// A raw buffer descriptor for load_to_lds, in scalar registers.
+__device__ __forceinline__ u32x4 lds_source(const void *p, int bytes) {
+    const uint64_t a = reinterpret_cast<uint64_t>(p);
+    return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, (uint32_t)bytes, 0x00020000u};
+}
+
+// 16 bytes per lane from a buffer straight into LDS, lane l's to dst + l (dst: the same in all lanes); an offset beyond the
+// buffer gives zeros.  The compiler does not count this load: whoever reads dst has waited for it (vmcnt) himself.  (With
+// the builtin, which it counts, it waits for all of them wherever one of them is issued under a condition.)
+__device__ __forceinline__ void load_to_lds(const u32x4 &src, u32x4 *dst, int lane_offset, int offset) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds" : : "s"(at), "v"(lane_offset), "s"(src), "s"(offset) : "memory", "m0");
+#endif
+}
+
+// The same from an address of its own per lane.
+__device__ __forceinline__ void load_to_lds(const void *src, u32x4 *dst) {
+#ifdef __HIP_DEVICE_COMPILE__
+    const uint32_t at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)dst;
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" : : "s"(at), "v"(src) : "memory", "m0");
+#endif
+}
+
+// A value whose origin the compiler does not see: what follows from it is worked out where it stands, and not kept in
+// registers through the loops before.
+__device__ __forceinline__ int fresh(int v) {
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
+// Bitwise or over the 16 lanes of a row: rotations by 1, 2, 4 and 8 lanes.
+__device__ __forceinline__ uint32_t or_row16(uint32_t v) {
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x121, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x122, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x124, 0xf, 0xf, false);
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, false);
+    return v;
+}
+
+// Waits for this wave's vector memory, and for its LDS accesses too, in a form that the compiler counts with.
+constexpr int kWaitVm0 = 0x0F70, kWaitAll = 0x0070;
+
+// Waves that share the columns: with 8 blocks of output channels every wave takes all rows and 2 blocks; with fewer, two
+// waves share rows, so that operands are read twice, not four times, and weights loaded twice.
+template <int NCO, int KS>
+struct TileShape {
+    static constexpr int WC = NCO == 8 ? 4 : 2, WR = kWaves / WC;
+    static constexpr int RB = kTileRows / 16 / WR, CB = NCO / WC;
+    static constexpr int GB = KS == 1 || (KS == 3 && NCO >= 6) ? 2 : 4;      // row blocks whose operands are read together
+    static constexpr int UN = KS * 4;                            // 16-byte units of a row in a stage
+    static constexpr int ROWS = kTileRows * UN;                  // units of a stage's rows
+    static constexpr int UPR = NCO * 2;                          // units of a result row
+    static constexpr int XROW = 2 * ROWS > kTileRows * UPR ? 2 * ROWS : kTileRows * UPR;
+    static constexpr int WAVES_PER_EU = KS == 3 ? 2 : 3;
+};
+
+template <int NCO, int KS, bool TWO, bool HALF>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(TileShape<NCO, KS>::WAVES_PER_EU))) k_conv_tile(
+    const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf, const int32_t *__restrict__ nbr, int row_shift,
+    const int32_t *__restrict__ perm, int from_end, const int32_t *__restrict__ tile_order, int64_t n_out,
+    _Float16 *__restrict__ out, int *__restrict__ sched, int cin, int cout, int K3, const _Float16 *__restrict__ bias,
+    const _Float16 *__restrict__ residual, int relu, int x_bytes, int w_bytes, int centre, const _Float16 *__restrict__ X2,
+    int x2_bytes, int cin1) {
+    // TWO: the layer's input is the channel concatenation [X | X2], which is never formed: input channels below cin1 are
+    // read from X (rows of cin1 channels), the others from X2 (rows of cin - cin1 channels); cin1 is a multiple of 32.
+    // Otherwise X2, x2_bytes are unused and cin1 = cin.
+    typedef TileShape<NCO, KS> S;
+    constexpr int TR = kTileRows, WC = S::WC, RB = S::RB, CB = S::CB, GB = S::GB, UN = S::UN, UPR = S::UPR;
+    constexpr int kAskAhead = 10;          // stages before the end of a tile that the next one is asked for
+    constexpr int kNoRow = (int)0x80000000u;   // beyond any buffer this kernel is launched with
+    __shared__ u32x4 xrow[S::XROW], tab[TR * 8];
+    __shared__ int32_t s_row[2 * TR];
+    __shared__ uint32_t s_m16[TR / 16];
     __shared__ int s_tile;
-    // The launch holds as many workgroups as stay resident at once.  Workgroup b starts with tile b;
-    // the tiles beyond the grid are handed out through counters, so nobody waits for a second
-    // round of workgroups.  One counter per XCD (blockIdx % 8), on cache lines of their own:
-    // atomics on one address are served one after the other.
-    const int64_t n_tiles = (n_out + kTileRows - 1) / kTileRows;
+    // The launch holds as many workgroups as stay resident at once.  Workgroup b starts with tile b; the tiles beyond the
+    // grid are handed out through counters, so nobody waits for a second round of workgroups.  One counter per XCD
+    // (blockIdx % 8), on cache lines of their own: atomics on one address are served one after the other.  Longest tiles
+    // come first, so that they do not start when everything else is done: by the order that the map build prepared (tiles
+    // of rows in input order by descending number of offsets); rows sorted by bitmask put the tiles with the most offsets
+    // last, so those are taken from the end.
+    const int n_tiles = (int)((n_out + TR - 1) / TR);
     sched += kSchedWords * blockIdx.y;
     const int xcd = blockIdx.x & 7;
-    const int cb0 = blockIdx.y * NCO;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
-    const int r0 = wave * kWaveRows + m16, r1 = r0 + 16;   // the lane's two output rows (tile slots)
-    // Longest tiles first, so that they do not start when everything else is done: by the order
-    // the map build prepared (tiles of rows in input order by descending number of offsets); rows
-    // sorted by bitmask put the tiles with the most offsets last, so those are taken from the end.
-    int64_t turn = blockIdx.x;
-    // The rows of a tile, known one tile ahead (where they go through perm, that is a memory latency less per tile):
-    // in the prologue, the 16-byte chunks of a table row go to neighbouring lanes, so that one load instruction
-    // covers whole rows (a row touched by several instructions costs a request each).
-    const int row_chunks = stride / 4;                                           // 8, 4 or 1 lanes per row
-    const int row_ch = threadIdx.x % row_chunks, row_sub = threadIdx.x / row_chunks;
-    const int rows_per_pass = kThreads / row_chunks;                             // 32, 64 or 256
-    int32_t kk[4];                                                               // -2: no row of the tile in this pass
-    auto rows_of = [&](int64_t t) __attribute__((always_inline)) {
-        const int64_t tile = from_end ? n_tiles - 1 - t : (tile_order ? tile_order[t] : t);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
+    const int wr = wave / WC, wc = wave % WC;
+    const int cblocks = cout / 16, nk = cin / 32, cb0 = blockIdx.y * NCO + wc * CB, co0 = blockIdx.y * (NCO * 16);
+    const u32x4 xrsrc = lds_source(X, x_bytes), xrsrc2 = lds_source(TWO ? X2 : X, TWO ? x2_bytes : x_bytes);
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
+    const int row_bytes = cin1 * 2, row_bytes2 = (cin - cin1) * 2;
+    const int nch1 = (cin1 + 63) / 64, nch = HALF ? nch1 + (cin - cin1 + 63) / 64 : nk / KS;   // stages per offset, with HALF those of X first
+
+    // The neighbour table's rows of a tile lie in LDS as they do in memory, 1 << row_shift units of 16 bytes each, unit c of
+    // row r at place c ^ (r % their number).  The lanes' rows are known a stage or more before they are needed.
+    const int table_units = TR << row_shift, unit_mask = (1 << row_shift) - 1;
+    int32_t kk[4];
+    auto rows_of = [&](int t) __attribute__((always_inline)) {
+        const int l = fresh(threadIdx.x & 63);
+        const int tile = from_end ? n_tiles - 1 - t : (tile_order ? tile_order[t] : t);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int col = i * rows_per_pass + row_sub;
-            const int64_t pos = tile * kTileRows + col;
-            kk[i] = -2;
-            if (col < kTileRows) kk[i] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
+            const int u = (i * kWaves + wave) * 64;
+            kk[i] = -1;
+            if (u < table_units) {
+                const int64_t pos = (int64_t)tile * TR + ((u + l) >> row_shift);
+                kk[i] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
+            }
         }
     };
-    if (turn < n_tiles) rows_of(turn);
-    while (turn < n_tiles) {
-    // ask for the next tile now; the answer is needed when this one is done
-    int ticket = 0;
-    if (threadIdx.x == 0) ticket = atomicAdd(&sched[xcd * 32], 1);
-
-    // Neighbour rows of the tile's outputs -> LDS (offset-major), and the OR of their offset bitmasks.
-    if (threadIdx.x == 0) s_mask = 0;
-    __syncthreads();
-    {
-        int4 v[4];
+    auto fetch_table = [&](int rows) __attribute__((always_inline)) {
+        const int l = fresh(threadIdx.x & 63);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            v[i] = make_int4(-1, -1, -1, -1);
-            if (kk[i] >= 0) v[i] = reinterpret_cast<const int4 *>(nbr + (int64_t)kk[i] * stride)[row_ch];
+            const int u = (i * kWaves + wave) * 64;
+            if (u < table_units) {
+                const int r = (u + l) >> row_shift, c = (l ^ r) & unit_mask;
+                if (kk[i] >= 0) load_to_lds(nbr + (((int64_t)kk[i] << row_shift) + c) * 4, tab + u);
+                if ((l & unit_mask) == 0) s_row[rows + r] = kk[i];
+            }
         }
-        uint32_t mm = 0;
+    };
+    int turn = blockIdx.x, then = n_tiles;
+    if (turn < n_tiles) {
+        rows_of(turn);
+        fetch_table(0);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        __syncthreads();
+    }
+    // A wave fetches the rows of two blocks of 16 (2 wave, 2 wave + 1), KS loads each: 16-byte unit v = 64 i + lane of load i
+    // is place v % UN of row v / UN, and holds unit place ^ key(row) of the row.
+    auto key = [](int r) __attribute__((always_inline)) { return KS == 2 ? r >> 1 & 7 : r >> 2 & 3; };
+    int fetch_row[KS], fetch_at[KS];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (kk[i] == -2) continue;
-            const int col = i * rows_per_pass + row_sub;
-            const int32_t k = kk[i];
-            if (row_ch == 0) s_row[col] = k;
-            const int32_t e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+    for (int i = 0; i < KS; ++i) {
+        const int v = i * 64 + lane, r = v / UN;
+        fetch_row[i] = wave * 32 + r;
+        fetch_at[i] = ((v % UN) ^ key(r)) * 16;
+    }
+    // HALF: lanes that bring the second 32 channels of a stage
+    int second[KS];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int idx = row_ch * 4 + q;
-                if (idx < K3) {
-                    const int32_t j = idx == centre ? k : (k >= 0 ? e[q] : -1);
-                    lds_j[idx][col] = j;
-                    if (j >= 0) mm |= 1u << idx;
+    for (int i = 0; i < KS; ++i) second[i] = HALF && fetch_at[i] >= 64 ? kNoRow : 0;
+    // where the lane's operands lie: step ks of row block rb at read_at[ks] + rb * 16 * UN
+    int read_at[KS];
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) read_at[ks] = (wr * RB * 16 + m16) * UN + ((ks * 4 + g) ^ key(m16));
+
+    int rows_now = 0;   // where the tile's rows stand in s_row
+    while (turn < n_tiles) {
+        int ticket = 0;
+        // The offsets that each block of 16 rows meets, read off the entries: two threads a row (the row's bitmask word and its
+        // centre entry may not have been written yet, a map's row pass runs on demand).  What stays in LDS is where the input rows
+        // begin, in bytes, or, of a two-part input, their numbers.
+        {
+            const int t = fresh(threadIdx.x), r = t >> 1, h = t & 1;
+            const int32_t k = s_row[rows_now + r];
+            uint32_t have = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int c = 2 * i + h;
+                if (c <= unit_mask) {
+                    u32x4 &unit = tab[(r << row_shift) + (c ^ (r & unit_mask))];
+                    u32x4 e = unit;
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int idx = c * 4 + q;
+                        const int32_t j = k < 0 || idx >= K3 ? -1 : idx == centre ? k : (int32_t)e[q];
+                        if (j >= 0) have |= 1u << idx;
+                        e[q] = (uint32_t)(TWO ? j : j * row_bytes);   // (no row: -1, and a place beyond any buffer)
+                    }
+                    unit = e;
                 }
             }
+            have = or_row16(have);
+            const uint32_t first = (uint32_t)__builtin_amdgcn_readlane((int)have, 0) | (uint32_t)__builtin_amdgcn_readlane((int)have, 16);
+            const uint32_t second = (uint32_t)__builtin_amdgcn_readlane((int)have, 32) | (uint32_t)__builtin_amdgcn_readlane((int)have, 48);
+            if (lane < 2) s_m16[wave * 2 + lane] = lane ? second : first;
         }
-        for (int d = 32; d >= 1; d >>= 1) mm |= (uint32_t)__shfl_xor((int)mm, d, 64);
-        if (lane == 0 && mm) atomicOr(&s_mask, mm);
-    }
-    __syncthreads();
-    // the offsets present in the tile, as a bitmask in a scalar register: the stages walk its set bits
-    const uint32_t mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mask);
-    const int nchunks = cin / KC;
-    const int nstage = __builtin_popcount(mask) * nchunks;
-    const int cblocks = cout / 16;
-
-    floatx4 acc[NCO][2];
+        __syncthreads();
+        // Lane n: the row blocks that meet offset n, a bit each.
+        uint32_t blocks = 0;
 #pragma unroll
-    for (int cb = 0; cb < NCO; ++cb)
+        for (int i = 0; i < TR / 16; ++i) blocks |= (s_m16[i] >> (lane & 31) & 1u) << i;
+        const uint32_t mask = (uint32_t)__ballot(blocks != 0);   // the offsets that the tile meets
+        floatx4 acc[CB][RB];
 #pragma unroll
-        for (int c2 = 0; c2 < 2; ++c2) acc[cb][c2] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-    u32x4 wreg[DEPTH][WV];
-    half8v xreg[DEPTH][2][KSTEPS];
-    bool xlive[DEPTH];
-    // Issue the loads of stage s into register set d (d is a compile-time constant at every call).
-    // Every call issues the same number of loads, unconditionally (past the last stage it repeats
-    // that stage; rows without the offset read the zero row): the compiler counts outstanding
-    // loads to place its waits, and a load it cannot count would make every wait a full drain.
-    // Loads go through buffer descriptors: a 32-bit byte offset per lane plus a wave-uniform one, no
-    // 64-bit address arithmetic in the loop, and an offset beyond the buffer reads as zero without
-    // touching memory, which is what a row without the offset must contribute.  The loop body is
-    // short on purpose: with ~200 vector instructions per stage around 16 MFMAs this kernel was
-    // bound by instruction issue.
-    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(X), 0, x_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t xrsrc2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(TWO ? X2 : X), 0, TWO ? x2_bytes : x_bytes, 0x00020000);
-    const int row_bytes2 = (cin - cin1) * 2;
-    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
-    constexpr int kNoRow = (int)0x80000000u;   // beyond any buffer this kernel is launched with
-    const int row_bytes = cin1 * 2, xlane = g * 16;
-    // A fragment of the slab (16 output channels, 32 input channels) is 1 KiB; in memory LKS steps of one block of
-    // output channels follow each other, of which a stage takes KSTEPS.
-    int wlane[WV], wslot[WV];
+        for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-    for (int v = 0; v < WV; ++v) {
-        int idx = threadIdx.x + v * kThreads;
-        if (SLAB % kThreads != 0) idx = idx < SLAB ? idx : SLAB - 1;   // surplus threads repeat the last vector
-        wslot[v] = idx;
-        wlane[v] = ((idx >> 6) / KSTEPS * LKS + (idx >> 6) % KSTEPS) * 1024 + (idx & 63) * 16;
-    }
-    uint32_t it_rem = mask ? mask : 1u;   // offsets not issued yet; the lowest set bit is the one being issued
-    int it_ch = 0;                        // its chunk
-    // neighbour rows of the lane's two outputs for the stage issued next: read out of LDS one stage
-    // ahead, so that no stage waits for them
-    int32_t pj0 = lds_j[__builtin_ctz(it_rem)][r0], pj1 = lds_j[__builtin_ctz(it_rem)][r1];
-    // Issue the loads of stage s into register set d (a compile-time constant at every call).
-    // Every call issues the same loads, unconditionally (past the last stage it repeats that
-    // stage): the compiler counts outstanding loads to place its waits, and a load it cannot count
-    // makes every wait a full drain.
-    auto issue = [&](int s, auto dc) __attribute__((always_inline)) {
-        constexpr int d = decltype(dc)::value;
-        const bool real = s < nstage;
-        const int ch = it_ch, n = __builtin_ctz(it_rem);   // scalar: the weight slab's address stays in scalar registers
-        const int32_t j0 = pj0, j1 = pj1;
-        if (s + 1 < nstage) {   // stages are issued in order: step the pair, stay on the last one past the end
-            if (++it_ch == nchunks) {
-                it_ch = 0;
-                it_rem &= it_rem - 1;
+            for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+        const int nstage = __builtin_popcount(mask) * nch;
+        uint32_t rem = mask;
+        int in = mask ? __builtin_ctz(mask) : 0, ich = 0;   // the stage whose loads are issued next
+        auto advance = [&]() __attribute__((always_inline)) {
+            if (++ich == nch) {
+                ich = 0;
+                if (rem & (rem - 1)) rem &= rem - 1;
+                in = __builtin_ctz(rem | 0x80000000u);
             }
-        }
-        pj0 = lds_j[__builtin_ctz(it_rem)][r0];
-        pj1 = lds_j[__builtin_ctz(it_rem)][r1];
-        const uint32_t per = LKS / KSTEPS, group = (uint32_t)(n * nchunks + ch) / per;   // (an offset's chunks are whole groups)
-        const int wsoff = ((int)group * cblocks + cb0) * (LKS * 1024) + (n * nchunks + ch - (int)(group * per)) * (KSTEPS * 1024);
+        };
+        int32_t jn[2][KS];   // the input rows of that stage
+        auto load_j = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int v = 0; v < WV; ++v) wreg[d][v] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane[v], wsoff, 0);
-        xlive[d] = real && __ballot(j0 >= 0 || j1 >= 0) != 0;   // false: none of the wave's rows has this offset
-        const int off0 = j0 >= 0 ? j0 * row_bytes + xlane : kNoRow;
-        const int off1 = j1 >= 0 ? j1 * row_bytes + xlane : kNoRow;
-        const int xsoff = ch * (KC * 2);
-        int offb0 = 0, offb1 = 0;
-        if constexpr (TWO) {
-            offb0 = j0 >= 0 ? j0 * row_bytes2 + xlane : kNoRow;
-            offb1 = j1 >= 0 ? j1 * row_bytes2 + xlane : kNoRow;
-        }
-#pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            u32x4 v0, v1;
-            if constexpr (TWO) {
-                const int c0 = ch * KC + ks * 32;        // first input channel of this operand step
-                const bool second = c0 >= cin1;          // wave-uniform: the step lies in X2
-                const int so = second ? (c0 - cin1) * 2 : c0 * 2;
-                v0 = __builtin_amdgcn_raw_buffer_load_b128(second ? xrsrc2 : xrsrc, second ? offb0 : off0, so, 0);
-                v1 = __builtin_amdgcn_raw_buffer_load_b128(second ? xrsrc2 : xrsrc, second ? offb1 : off1, so, 0);
-            } else {
-                v0 = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off0, xsoff + ks * 64, 0);
-                v1 = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off1, xsoff + ks * 64, 0);
+            for (int i = 0; i < KS; ++i) {   // (16 rows on, a row's units stand in the same order)
+                const int at = ((fetch_row[i] << row_shift) + ((in >> 2) ^ (fetch_row[i] & unit_mask))) * 4 + (in & 3);
+                jn[0][i] = reinterpret_cast<const int32_t *>(tab)[at];
+                jn[1][i] = reinterpret_cast<const int32_t *>(tab)[at + (64 << row_shift)];
             }
-            __builtin_memcpy(&xreg[d][0][ks], &v0, 16);
-            __builtin_memcpy(&xreg[d][1][ks], &v1, 16);
-        }
-    };
-    auto run = [&](int s, auto dc) __attribute__((always_inline)) {
-        constexpr int d = decltype(dc)::value;
-        u32x4 *slab = lds_w[s & 1];
+        };
+        uint32_t met = 0;    // the row blocks of the stage being multiplied
+        auto issue = [&](u32x4 (&a)[CB][KS], int rows) __attribute__((always_inline)) {
+            met = (uint32_t)__builtin_amdgcn_readlane((int)blocks, in);
+            const bool of_x2 = TWO && HALF && ich >= nch1;
+            const int c0 = (of_x2 ? ich - nch1 : ich) * (KS * 32);   // first input channel of the stage, HALF: within its part
+            const int step = HALF ? (of_x2 ? cin1 : 0) + c0 : 0;
+            // The last 32 channels of a row: of the other half of the stage there are neither weights nor rows, and what is
+            // read beyond a buffer is zero.
+            const int beyond = HALF && c0 + 32 == (of_x2 ? cin - cin1 : cin1) ? kNoRow : 0;
+            const int base = HALF ? ((in * nk + step / 32) * cblocks + cb0) * 1024 : ((in * nch + ich) * cblocks + cb0) * (KS * 1024);
+            const int next_cb = HALF ? 1024 : KS * 1024, next_ks = HALF ? cblocks * 1024 : 1024;
 #pragma unroll
-        for (int v = 0; v < WV; ++v) slab[wslot[v]] = wreg[d][v];
-        __syncthreads();   // slab complete; everybody is done with the other slab
-        if (xlive[d]) {
+            for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-            for (int ks = 0; ks < KSTEPS; ++ks) {
-                // all weight fragments of the step out of LDS first, then the MFMAs: a read placed
-                // right before its MFMA costs one LDS latency per fragment
-                u32x4 raw[NCO];
+                for (int ks = 0; ks < KS; ++ks)
+                    a[cb][ks] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, HALF && ks ? lane * 16 | beyond : lane * 16, base + cb * next_cb + ks * next_ks, 0);
 #pragma unroll
-                for (int cb = 0; cb < NCO; ++cb) raw[cb] = slab[(cb * KSTEPS + ks) * 64 + lane];
+            for (int h = 0; h < 2; ++h)
+                if (met >> (wave * 2 + h) & 1u) {
+#pragma unroll
+                    for (int i = 0; i < KS; ++i) {
+                        u32x4 *dst = xrow + rows + (wave * 2 + h) * (16 * UN) + i * 64;
+                        const int32_t j = jn[h][i];
+                        if (HALF) {
+                            if (of_x2) load_to_lds(xrsrc2, dst, (j * row_bytes2 + fetch_at[i]) | (second[i] & beyond), c0 * 2);
+                            else load_to_lds(xrsrc, dst, ((TWO ? j * row_bytes : j) + fetch_at[i]) | (second[i] & beyond), c0 * 2);
+                        } else if (!TWO) {
+                            load_to_lds(xrsrc, dst, j + fetch_at[i], c0 * 2);
+                        } else if (c0 + KS * 32 <= cin1) {
+                            load_to_lds(xrsrc, dst, j * row_bytes + fetch_at[i], c0 * 2);
+                        } else if (c0 >= cin1) {
+                            load_to_lds(xrsrc2, dst, j * row_bytes2 + fetch_at[i], (c0 - cin1) * 2);
+                        } else {   // the first channels of the stage from X, the others from X2
+                            if (c0 * 2 + fetch_at[i] < row_bytes) load_to_lds(xrsrc, dst, j * row_bytes + fetch_at[i], c0 * 2);
+                            else load_to_lds(xrsrc2, dst, j * row_bytes2 + (c0 * 2 + fetch_at[i] - row_bytes), 0);
+                        }
+                    }
+                }
+        };
+        u32x4 a0[CB][KS], a1[CB][KS];
+        auto stage = [&](int s, const u32x4 (&a)[CB][KS], u32x4 (&a_next)[CB][KS], int rows, int rows_next) __attribute__((always_inline)) {
+            __builtin_amdgcn_s_waitcnt(kWaitAll);   // rows and weights of this stage
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_s_barrier();           // everybody's; and everybody has read the rows of the stage before
+            asm volatile("" ::: "memory");
+            const uint32_t now = met >> (wr * RB);
+            if (s + 1 < nstage) {
+                issue(a_next, rows_next);
+                advance();
+                load_j();
+            }
+#pragma unroll
+            for (int r0 = 0; r0 < RB; r0 += GB) {
+                asm volatile("" ::: "memory");   // (one group's operands at a time)
+                if ((now >> r0 & ((1u << GB) - 1)) == 0) continue;
+                u32x4 b[GB][KS];
+#pragma unroll
+                for (int q = 0; q < GB; ++q)
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks) b[q][ks] = xrow[rows + read_at[ks] + (r0 + q) * (16 * UN)];
                 __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-                for (int cb = 0; cb < NCO; ++cb) {
-                    half8v a;
-                    __builtin_memcpy(&a, &raw[cb], 16);
-                    acc[cb][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xreg[d][0][ks], acc[cb][0], 0, 0, 0);
-                    acc[cb][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xreg[d][1][ks], acc[cb][1], 0, 0, 0);
-                }
+                for (int q = 0; q < GB; ++q)
+                    if (now >> (r0 + q) & 1u) {
+#pragma unroll
+                        for (int ks = 0; ks < KS; ++ks) {
+                            half8v bv;
+                            __builtin_memcpy(&bv, &b[q][ks], 16);
+#pragma unroll
+                            for (int cb = 0; cb < CB; ++cb) {
+                                half8v av;
+                                __builtin_memcpy(&av, &a[cb][ks], 16);
+                                acc[cb][r0 + q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc[cb][r0 + q], 0, 0, 0);
+                            }
+                        }
+                    }
                 __builtin_amdgcn_s_setprio(0);
             }
+        };
+        if (nstage > 0) {
+            load_j();
+            issue(a0, 0);
+            advance();
+            load_j();
         }
-        issue(s + DEPTH, dc);
-    };
-    if (nstage > 0) {
-        static_for<DEPTH>([&](auto dc) __attribute__((always_inline)) { issue(decltype(dc)::value, dc); });
-        // whole rounds of DEPTH stages; stages past the end only repeat loads and skip the MFMAs
-        for (int s0 = 0; s0 < nstage; s0 += DEPTH) static_for<DEPTH>([&](auto dc) __attribute__((always_inline)) { run(s0 + decltype(dc)::value, dc); });
-    }
+        int s = 0, until = nstage > kAskAhead ? (nstage - kAskAhead) & ~1 : 0;
+#pragma nounroll
+        for (int phase = 0; phase < 3; ++phase) {
+#pragma nounroll
+            for (; s < until && s < nstage; s += 2) {
+                stage(s, a0, a1, 0, S::ROWS);
+                if (s + 1 < nstage) stage(s + 1, a1, a0, S::ROWS, 0);
+            }
+            if (phase == 0) {
+                if (threadIdx.x == 0) ticket = atomicAdd(&sched[xcd * 32], 1);
+                until += 4;
+            } else if (phase == 1) {
+                if (threadIdx.x == 0) s_tile = ticket;
+                __syncthreads();
+                then = (int)gridDim.x + xcd + 8 * __builtin_amdgcn_readfirstlane(s_tile);
+                if (then < n_tiles) rows_of(then);
+                until = nstage;
+            }
+        }
+        if (then < n_tiles) fetch_table(TR - rows_now);   // everybody has read the last of this tile's table
 
-    const int32_t out_row[2] = {s_row[r0], s_row[r1]};
-    RowStore<NCO> rows;
-    rows.open(acc, out_row, residual, cout, cb0 * 16);
-    if (threadIdx.x == 0) s_tile = ticket;
-    __syncthreads();   // the tile's LDS is free; s_tile is set
-    turn = (int64_t)gridDim.x + xcd + 8 * (int64_t)s_tile;
-    if (turn < n_tiles) rows_of(turn);
-    // (the pointer is made opaque per tile: loads the compiler can prove the same for every tile move to the
-    // top of the kernel and hold registers through the stage loop, which has none to spare)
-    const _Float16 *bp = bias;
-    asm volatile("" : "+s"(bp));
-    rows.store(&lds_w[0][0] + wave * (NCO * 32), out, bp, residual != nullptr, relu, cout, cb0 * 16);
+        // The sums, rounded once to fp16, go through LDS, so that rows leave, and the residual's come in, as whole lines.
+        typedef _Float16 half8u __attribute__((ext_vector_type(8)));
+        half4 sum[CB][RB];
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb) {
+                sum[cb][rb] = half4{(_Float16)acc[cb][rb][0], (_Float16)acc[cb][rb][1], (_Float16)acc[cb][rb][2], (_Float16)acc[cb][rb][3]};
+                asm volatile("" : "+v"(sum[cb][rb]));
+            }
+        // a thread stores unit c of rows r0, r0 + STEP, ...
+        constexpr int STEP = kThreads / UPR, PER = (TR + STEP - 1) / STEP;
+        const int tid = fresh(threadIdx.x), c = tid % UPR, r0 = tid / UPR;
+        const uint32_t out_bytes = (uint32_t)cout * 2;
+        const int col = (co0 + c * 8) * 2;
+        int32_t row[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int r = r0 + i * STEP;
+            row[i] = (STEP * UPR == kThreads || r0 < STEP) && (TR % STEP == 0 || r < TR) ? s_row[rows_now + r] : -1;
+        }
+        half8u res[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) res[i] = half8u{0, 0, 0, 0, 0, 0, 0, 0};   // (else their registers stay taken through the tile)
+        if (residual) {
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                if (row[i] >= 0) res[i] = *reinterpret_cast<const half8u *>(reinterpret_cast<const char *>(residual) + (uint64_t)(uint32_t)row[i] * out_bytes + col);
+        }
+        __syncthreads();   // everybody has read the last rows
+        auto swizzle = [](int r) __attribute__((always_inline)) { return NCO % 4 == 0 ? r & 7 : r & 3; };
+        {
+            const int m = tid & 15, q = tid >> 4 & 3;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    const int r = (wr * RB + rb) * 16 + m;
+                    reinterpret_cast<half4 *>(xrow + r * UPR + (((wc * CB + cb) * 2 + (q >> 1)) ^ swizzle(r)))[q & 1] = sum[cb][rb];
+                }
+        }
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);   // the next tile's table is there
+        __syncthreads();
+        half8u bv = {0, 0, 0, 0, 0, 0, 0, 0};
+        if (bias) bv = *reinterpret_cast<const half8u *>(reinterpret_cast<const char *>(bias) + col);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (row[i] < 0) continue;
+            const int r = r0 + i * STEP;
+            half8u v;
+            const u32x4 raw = xrow[r * UPR + (c ^ swizzle(r))];
+            __builtin_memcpy(&v, &raw, 16);
+            // if asked for, what ts_bias_act would do with it: fp32 sum, ReLU, one rounding
+            if (bias || residual || relu) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    float f = (float)v[e];
+                    if (bias) f += (float)bv[e];
+                    if (residual) f += (float)res[i][e];
+                    v[e] = (_Float16)(relu && f < 0.f ? 0.f : f);
+                }
+            }
+            *reinterpret_cast<half8u *>(reinterpret_cast<char *>(out) + (uint64_t)(uint32_t)row[i] * out_bytes + col) = v;
+        }
+        turn = then;
+        rows_now = TR - rows_now;
     }
     // the last workgroup to leave rearms the counters for the next launch on this map
     if (threadIdx.x == 0 && atomicAdd(&sched[8 * 32], 1) == (int)gridDim.x - 1) {
@@ -1211,11 +1372,7 @@ int run_fused_staged(const ts_tensor *feats, const ts_tensor *weights, const ts_
     return TS_OK;
 }
 
-constexpr int kTileDepth = 2;
-
-// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes, except
-// that stages of 96 channels are taken only while there is at most a tile per compute unit, where a stage's latency
-// decides (20 k points, 96 -> 96: 23.9 -> 19.8 us against stages of 32); on larger maps they cost a wave per SIMD.
+// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes.
 inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : cin_pad % 96 == 0 ? 3 : 1; }
 
 // What follows the layer's sum, if anything: y = act(conv + bias + residual) (see ts_sparse_conv_act).
@@ -1233,14 +1390,14 @@ struct Second {
     int cin1 = 0;
 };
 
-template <int NCO, int KSTEPS, bool TWO = false, int LKS = KSTEPS>
+template <int NCO, int KS, bool TWO, bool HALF = false>
 void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap, ts_tensor *out, int cin_pad,
-                      const Epilogue &ep, const Second &sec = Second()) {
+                      const Epilogue &ep, const Second &sec) {
     // as many workgroups as stay resident at once, fewer for small maps
     static int per_cu = 0;   // per instantiation
     if (per_cu == 0) {
         int n = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>, kThreads, 0) != hipSuccess || n <= 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_tile<NCO, KS, TWO, HALF>, kThreads, 0) != hipSuccess || n <= 0) {
             (void)hipGetLastError();
             n = 2;
         }
@@ -1250,8 +1407,9 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
     const int cin1 = TWO ? sec.cin1 : cin_pad;
     const int32_t *perm = row_order(kmap);
-    TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KSTEPS, LKS, kTileDepth, TWO>), grid, dim3(kThreads), x,
-              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
+    const int row_shift = kmap->stride == 32 ? 3 : kmap->stride == 16 ? 2 : 0;   // 16-byte units of a table row
+    TS_LAUNCH("k_conv_tile", (k_conv_tile<NCO, KS, TWO, HALF>), grid, dim3(kThreads), x, reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr,
+              row_shift, perm, kmap->d_perm != nullptr,
               !perm && (kmap->scan_done || (kmap->scan_enqueued && kmap->stream == stream())) ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
               static_cast<const _Float16 *>(ep.bias), static_cast<const _Float16 *>(ep.residual), ep.relu,
@@ -1315,7 +1473,6 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         x = xp;
     }
     const int cblocks = cout / 16;
-    const bool one_step = ksteps == 3 && kmap->n_tiles > compute_units();
     // 32 input channels and 27 offsets: the kernel with resident weights (for 2x2x2 maps and for 64 -> 32 it
     // measured no faster than k_conv_tile, and 64 -> 64 in two slices of output channels much slower: every
     // slice gathers all rows again)
@@ -1344,13 +1501,12 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     if (nco == N) {                                                                                \
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);    \
-            else if (one_step) launch_conv_tile<N, 1, true, 3>(x, wf, kmap, out, cin_pad, ep, sec); \
             else if (ksteps == 3) launch_conv_tile<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \
-            else launch_conv_tile<N, 1, true>(x, wf, kmap, out, cin_pad, ep, sec);                \
-        } else if (ksteps == 2) launch_conv_tile<N, 2>(x, wf, kmap, out, cin_pad, ep);            \
-        else if (one_step) launch_conv_tile<N, 1, false, 3>(x, wf, kmap, out, cin_pad, ep);       \
-        else if (ksteps == 3) launch_conv_tile<N, 3>(x, wf, kmap, out, cin_pad, ep);              \
-        else launch_conv_tile<N, 1>(x, wf, kmap, out, cin_pad, ep);                                \
+            else launch_conv_tile<N, 2, true, true>(x, wf, kmap, out, cin_pad, ep, sec);          \
+        } else if (ksteps == 2) launch_conv_tile<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else if (ksteps == 3) launch_conv_tile<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec);  \
+        else if (cin_pad == 32) launch_conv_tile<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else launch_conv_tile<N, 2, false, true>(x, wf, kmap, out, cin_pad, ep, sec);             \
     }
     TS_TILE_CASE(8) TS_TILE_CASE(6) TS_TILE_CASE(4) TS_TILE_CASE(2)
 #undef TS_TILE_CASE

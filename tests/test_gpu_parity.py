@@ -1282,6 +1282,37 @@ def test_async_build_reports_bad_input_late():
     assert fresh.num_pairs == ts.ts_build_kmap(ok, 3, 1).num_pairs
 
 
+# ---- the fused kernel at the edges of its tiles and stages ----
+
+@pytest.mark.parametrize("K,s,transposed", [(3, 1, False), (2, 2, False), (2, 2, True), (1, 1, False)])
+@pytest.mark.parametrize("n,c_in,c_out", [(1, 64, 32), (15, 32, 128), (16, 96, 64), (17, 160, 96), (127, 64, 128), (128, 192, 32),
+                                           (129, 128, 96), (257, 96, 128), (3000, 160, 64), (3000, 32, 96), (40000, 64, 64)])
+def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
+    """Rows around blocks of 16 and tiles of 128; stages of 32, 64 and 96 input channels and a last one that is half full;
+    every number of output blocks per workgroup; few tiles, and more of them than workgroups stay resident."""
+    coords = _rand_coords(5000 + n + c_in, n, 0, 4 if n < 60 else 40 if n > 4000 else 16, batches=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), K, s, transposed)
+    x_h = features(5100 + c_in, kmap.num_in, c_in, np.float16)
+    w_h = conv_weights(5200 + c_out, K ** 3, c_in, c_out, np.float16)
+    x, w = to_dev(x_h), to_dev(w_h)
+    first = ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FUSED)
+    check_features(first, oracle_conv(coords, x_h, w_h, K, s, transposed), torch.float16, f"{n}: {c_in}->{c_out} K{K} s{s} t{int(transposed)}")
+    assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), first)   # rows ordered, counters rearmed
+
+
+def test_weights_of_offsets_that_nothing_meets_are_not_multiplied():
+    """Points on a diagonal meet three of 27 offsets; the weights of the others are infinite, those next to the half-full
+    last stage of 160 channels among them."""
+    i = np.arange(300, dtype=np.int32)
+    coords = np.stack([0 * i, i, i, 0 * i], axis=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
+    x_h, w_h = features(5301, 300, 160, np.float16), conv_weights(5302, 27, 160, 64, np.float16)
+    want = oracle_conv(coords, x_h, w_h, 3, 1)
+    w_h[[n for n in range(27) if n not in (1, 13, 25)]] = np.inf
+    got = ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), kmap, dataflow=ts.TS_DATAFLOW_FUSED)
+    check_features(got, want, torch.float16, "infinite weights elsewhere")
+
+
 # ---- a layer on a two-part input (the skip connection of a U-Net decoder), the concatenation never formed ----
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
