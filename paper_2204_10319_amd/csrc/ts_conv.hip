@@ -1085,6 +1085,130 @@ __global__ void __launch_bounds__(kThreads) k_grouped_mm(const T *__restrict__ F
     store_rows<float, NCB>(G, valid ? p : -1, cout, co0, acc);
 }
 
+// The same matmul for fp16 rows of a multiple of 64 channels, the way k_conv_tile reads its operands: rows as whole lines
+// into LDS, a stage of 64 channels ahead, weights in operand order as whole KiB per wave.  The kernel above asks for 32
+// rows an instruction, which costs the address unit four times what whole lines cost, and waits for every stage's loads.
+// Blocks of 16 rows past the end of a list are not multiplied; the sums leave as whole lines through the LDS that only
+// their wave touches.  What bounds it now: the fp32 sums on their way to memory and back (64 MB each way for 62 k pairs
+// of 256 channels).  Layers, before -> after, us: 256 -> 256 on 8 k points 40.1 -> 33.5, (256, 256) -> 256 51.9 -> 42.1,
+// (128, 128) -> 128 on 22 k points 51.1 -> 45.3, 256 -> 256 on 2.7 k points 24.0 -> 22.0, 2x2x2 of 256 -> 256 channels
+// from 8 k points 16.0 -> 15.4.
+template <int NCO, bool TWO>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) k_grouped_lines(
+    const _Float16 *__restrict__ F, const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf, Offs offs, MmPlan plan,
+    float *__restrict__ G, int cin, int cout, int centre, const int32_t *__restrict__ in_idx, int x_bytes, int w_bytes,
+    const _Float16 *__restrict__ X2, int x2_bytes, int cin1) {
+    typedef TileShape<NCO, 2> S;
+    constexpr int WC = S::WC, RB = S::RB, CB = S::CB, GB = S::GB, ROWS = S::ROWS;
+    __shared__ u32x4 xrow[2 * ROWS];
+    int t = blockIdx.x, i = 0;
+    for (; i < plan.count; ++i) {
+        if (t < plan.tiles[i]) break;
+        t -= plan.tiles[i];
+    }
+    if (i >= plan.count) return;
+    const int n = plan.n[i];
+    const int lo = offs.v[n], hi = offs.v[n + 1], p0 = lo + t * kTileRows, rows = hi - p0;   // rows of the list in this tile, if positive
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
+    const int wr = wave / WC, wc = wave % WC;
+    const int cblocks = cout / 16, nch = cin / 64, cb0 = blockIdx.y * NCO + wc * CB;
+    const bool whole = n == centre || in_idx;   // rows of X, wherever they are; else F's own, one after the other
+    const int valid = rows < kTileRows ? (rows > 0 ? rows : 0) : kTileRows;
+    const u32x4 xrsrc = whole ? lds_source(X, x_bytes) : lds_source(F + (int64_t)p0 * cin, valid * cin * 2);
+    const u32x4 xrsrc2 = lds_source(TWO ? X2 : X, TWO ? x2_bytes : 0);
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
+    const int row_bytes = cin1 * 2, row_bytes2 = (cin - cin1) * 2;
+    int at[4], at2[4];   // where in X, and X2, the lane's 16 bytes of its four rows begin; no row: beyond any buffer
+#pragma unroll
+    for (int l = 0; l < 4; ++l) {
+        const int r = wave * 32 + l * 8 + (lane >> 3), unit = ((lane & 7) ^ (lane >> 4) ^ (l & 1) * 4) * 16;
+        const int j = r >= valid ? -1 : n == centre ? p0 - lo + r : in_idx ? in_idx[p0 + r] : r;
+        at[l] = j * row_bytes + unit;
+        at2[l] = j * row_bytes2 + unit;
+    }
+    const int read_at[2] = {(wr * RB * 16 + m16) * 8 + (g ^ (m16 >> 1)), (wr * RB * 16 + m16) * 8 + (g ^ (m16 >> 1) ^ 4)};
+    floatx4 acc[CB][RB];
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) acc[cb][rb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto issue = [&](int ch, u32x4 (&a)[CB][2], int into) __attribute__((always_inline)) {
+        const int base = ((n * nch + ch) * cblocks + cb0) * 2048, c0 = ch * 64;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+            for (int ks = 0; ks < 2; ++ks) a[cb][ks] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, lane * 16, base + (cb * 2 + ks) * 1024, 0);
+#pragma unroll
+        for (int l = 0; l < 4; ++l) {
+            u32x4 *dst = xrow + into + wave * 256 + l * 64;
+            if (!TWO || c0 < cin1) load_to_lds(xrsrc, dst, at[l], c0 * 2);
+            else load_to_lds(xrsrc2, dst, at2[l], (c0 - cin1) * 2);
+        }
+    };
+    const int blocks = (valid + 15) / 16 - wr * RB;   // blocks of 16 rows that are this wave's, counted from its first
+    auto stage = [&](int ch, const u32x4 (&a)[CB][2], u32x4 (&a_next)[CB][2], int from, int into) __attribute__((always_inline)) {
+        __builtin_amdgcn_s_waitcnt(kWaitAll);
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (ch + 1 < nch) issue(ch + 1, a_next, into);
+#pragma unroll
+        for (int r0 = 0; r0 < RB; r0 += GB) {
+            asm volatile("" ::: "memory");
+            if (blocks <= r0) continue;
+            u32x4 b[GB][2];
+#pragma unroll
+            for (int q = 0; q < GB; ++q)
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) b[q][ks] = xrow[from + read_at[ks] + (r0 + q) * 128];
+#pragma unroll
+            for (int q = 0; q < GB; ++q)
+                if (r0 + q < blocks) {
+#pragma unroll
+                    for (int ks = 0; ks < 2; ++ks) {
+                        half8v bv;
+                        __builtin_memcpy(&bv, &b[q][ks], 16);
+#pragma unroll
+                        for (int cb = 0; cb < CB; ++cb) {
+                            half8v av;
+                            __builtin_memcpy(&av, &a[cb][ks], 16);
+                            acc[cb][r0 + q] = __builtin_amdgcn_mfma_f32_16x16x32_f16(av, bv, acc[cb][r0 + q], 0, 0, 0);
+                        }
+                    }
+                }
+        }
+    };
+    u32x4 a0[CB][2], a1[CB][2];
+    issue(0, a0, 0);
+    for (int ch = 0; ch < nch; ch += 2) {
+        stage(ch, a0, a1, 0, ROWS);
+        if (ch + 1 < nch) stage(ch + 1, a1, a0, ROWS, 0);
+    }
+    __syncthreads();   // everybody has read the last rows
+    // 16 rows of the wave's CB blocks at a time: written as the accumulators lie, read as lines
+    u32x4 *buf = xrow + wave * (CB * 64);
+    constexpr int UPR = CB * 4;                       // 16-byte units of a row
+    const int col = cb0 * 16;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb) {
+        if (rb >= blocks) break;
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) {
+            u32x4 v;
+            __builtin_memcpy(&v, &acc[cb][rb], 16);
+            buf[m16 * UPR + ((cb * 4 + g) ^ (m16 & 3))] = v;
+        }
+        __builtin_amdgcn_wave_barrier();   // LDS serves a wave's accesses in order
+#pragma unroll
+        for (int l = 0; l < CB; ++l) {
+            const int u = l * 64 + lane, r = u / UPR, c = u % UPR, row = (wr * RB + rb) * 16 + r;
+            const u32x4 v = buf[r * UPR + (c ^ (r & 3))];
+            if (row < valid) *reinterpret_cast<u32x4 *>(G + (int64_t)(p0 + row) * cout + col + c * 4) = v;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // Scatter-accumulate, output-stationary: thread = (output row, 4 channels); partial sums are
 // added in offset order in fp32 registers and the row is written once.  The row of G that holds
 // the pair (k, n) follows from the offset's start, the base of k's 64-row block and the block's
@@ -1216,11 +1340,21 @@ struct ts_weights {
 
 namespace {
 
+// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes.
+inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : cin_pad % 96 == 0 ? 3 : 1; }
+
 struct Prepared {
     const void *x;    // features, rows padded to cin_pad channels
-    const void *wt;   // transposed, padded weights
+    const void *wt;   // transposed, padded weights, or, for k_grouped_lines, weights in operand order
     int cin_pad;
 };
+
+// Whether the grouped matmul of a layer is k_grouped_lines: the same for every way of asking for it, for the two kernels'
+// sums need not agree in their last bits.
+inline bool mm_by_lines(size_t elem, const ts_kmap *kmap, int cin_pad, int cin1, int cout) {
+    return elem == 2 && cin_pad % 64 == 0 && cin1 % 64 == 0 && (size_t)kmap->n_in * cin_pad * 2 < (1ull << 31) &&
+           (size_t)kmap->K3 * cin_pad * cout * 2 < (1ull << 31);   // 31-bit offsets
+}
 
 int check_tensor(const ts_tensor *t, const char *name) {
     if (!t) return fail(TS_ERR_INVALID_ARG, "%s is NULL", name);
@@ -1255,18 +1389,21 @@ int check_layer(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap 
 // the operand step.
 template <class T>
 int prepare(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap *kmap, Prepared *pr,
-            const ts_weights *pw = nullptr, void *wbuf = nullptr) {
+            const ts_weights *pw = nullptr, void *wbuf = nullptr, bool lines = false) {
     const int cin = feats->cols, cout = weights->cols, ks = Elem<T>::KSTEP;
     const int cin_pad = (cin + ks - 1) / ks * ks;
     pr->cin_pad = cin_pad;
     if (wbuf && cin_pad != cin) return fail(TS_ERR_UNSUPPORTED, "C_in must be a multiple of %d here", ks);
     if (pw) {
-        pr->wt = pw->wt;
+        pr->wt = lines ? pw->tile : pw->wt;
     } else {
         size_t wn = (size_t)kmap->K3 * cout * cin_pad;
         T *wt = static_cast<T *>(wbuf ? wbuf : scratch(2, wn * sizeof(T)));
         if (!wt) return last_fail_code();
-        TS_LAUNCH("k_pack_weights", k_pack_weights<T>, dim3(blocks_for((int64_t)wn, kThreads)), dim3(kThreads), static_cast<const T *>(weights->data), wt, kmap->K3, cin, cin_pad, cout);
+        if (lines)
+            TS_LAUNCH("k_pack_weights", k_pack_weights_tile, dim3(blocks_for((int64_t)wn, kThreads)), dim3(kThreads), static_cast<const _Float16 *>(weights->data), reinterpret_cast<_Float16 *>(wt), kmap->K3, cin, cin_pad, cout, tile_ksteps(cin_pad));
+        else
+            TS_LAUNCH("k_pack_weights", k_pack_weights<T>, dim3(blocks_for((int64_t)wn, kThreads)), dim3(kThreads), static_cast<const T *>(weights->data), wt, kmap->K3, cin, cin_pad, cout);
         pr->wt = wt;
     }
     pr->x = feats->data;
@@ -1371,9 +1508,6 @@ int run_fused_staged(const ts_tensor *feats, const ts_tensor *weights, const ts_
     TS_HIP(hipGetLastError());
     return TS_OK;
 }
-
-// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes.
-inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : cin_pad % 96 == 0 ? 3 : 1; }
 
 // What follows the layer's sum, if anything: y = act(conv + bias + residual) (see ts_sparse_conv_act).
 struct Epilogue {
@@ -1601,10 +1735,35 @@ int gather_impl(const void *x, int64_t /*rows*/, int cin_pad, int dtype, const t
     return TS_OK;
 }
 
+template <int NCO>
+void launch_grouped_lines(const void *F, const void *X, const void *wf, const ts_kmap *kmap, const MmPlan &plan, float *G, int cin,
+                          int cout, const int32_t *in_idx, const Second &sec) {
+    const int cin1 = sec.x2 ? sec.cin1 : cin;
+    const dim3 grid((unsigned)plan_tiles(plan), cout / (NCO * 16));
+    const int x_bytes = (int)((size_t)kmap->n_in * cin1 * 2), x2_bytes = (int)((size_t)kmap->n_in * (cin - cin1) * 2);
+    const int w_bytes = (int)((size_t)kmap->K3 * cin * cout * 2);
+#define TS_GROUPED_LINES(TWO) \
+    TS_LAUNCH("k_grouped_mm", (k_grouped_lines<NCO, TWO>), grid, dim3(kThreads), static_cast<const _Float16 *>(F), static_cast<const _Float16 *>(X), \
+              static_cast<const u32x4 *>(wf), offs_of(kmap), plan, G, cin, cout, kmap->centre, in_idx, x_bytes, w_bytes,                      \
+              static_cast<const _Float16 *>(sec.x2), x2_bytes, cin1)
+    if (sec.x2) TS_GROUPED_LINES(true);
+    else TS_GROUPED_LINES(false);
+#undef TS_GROUPED_LINES
+}
+
 template <class T>
 int grouped_mm_launch(const void *F, const void *X, const void *wt, const ts_kmap *kmap, const MmPlan &plan, float *G,
                       int cin_pad, int cout, const int32_t *in_idx = nullptr, const Second &sec = Second()) {
     if (plan_tiles(plan) == 0) return TS_OK;
+    if (mm_by_lines(sizeof(T), kmap, cin_pad, sec.x2 ? sec.cin1 : cin_pad, cout)) {
+        const int cblocks = cout / 16;
+        if (cblocks % 8 == 0) launch_grouped_lines<8>(F, X, wt, kmap, plan, G, cin_pad, cout, in_idx, sec);
+        else if (cblocks % 6 == 0) launch_grouped_lines<6>(F, X, wt, kmap, plan, G, cin_pad, cout, in_idx, sec);
+        else if (cblocks % 4 == 0) launch_grouped_lines<4>(F, X, wt, kmap, plan, G, cin_pad, cout, in_idx, sec);
+        else launch_grouped_lines<2>(F, X, wt, kmap, plan, G, cin_pad, cout, in_idx, sec);
+        TS_HIP(hipGetLastError());
+        return TS_OK;
+    }
     const T *zero = static_cast<const T *>(zero_row());
     if (!zero) return last_fail_code();
     // the chunk of input channels a step takes must divide both parts of a two-part input
@@ -1725,7 +1884,8 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
                  const Second &sec = Second()) {
     TS_TRY(resolve(kmap));
     Prepared pr;
-    TS_TRY(prepare<T>(feats, weights, kmap, &pr, pw));
+    const int cin_step = (feats->cols + Elem<T>::KSTEP - 1) / Elem<T>::KSTEP * Elem<T>::KSTEP;
+    TS_TRY(prepare<T>(feats, weights, kmap, &pr, pw, nullptr, mm_by_lines(sizeof(T), kmap, cin_step, sec.x2 ? sec.cin1 : cin_step, out->cols)));
     if (sec.x2 && (!fetch || pr.cin_pad != feats->cols)) return fail(TS_ERR_UNSUPPORTED, "a two-part input needs the fetch-on-demand dataflow and unpadded rows");
     const int64_t M = kmap->M;
     float *G = static_cast<float *>(scratch(1, (size_t)(M ? M : 1) * out->cols * sizeof(float)));
@@ -2046,7 +2206,7 @@ static int grouped_matmul_checked(const ts_tensor *F, const ts_tensor *feats, co
     const void *X = feats ? feats->data : nullptr;
     float *g = static_cast<float *>(G->data);
     if (F->dtype == TS_F16) {
-        TS_TRY(prepare<_Float16>(&none, weights, kmap, &pr));
+        TS_TRY(prepare<_Float16>(&none, weights, kmap, &pr, nullptr, nullptr, mm_by_lines(2, kmap, F->cols, F->cols, G->cols)));
         return adaptive ? grouped_mm_adaptive<_Float16>(F->data, X, pr.wt, kmap, g, F->cols, G->cols, epsilon, S, stats)
                         : grouped_mm_impl<_Float16>(F->data, X, pr.wt, kmap, g, F->cols, G->cols);
     }

@@ -1313,6 +1313,23 @@ def test_weights_of_offsets_that_nothing_meets_are_not_multiplied():
     check_features(got, want, torch.float16, "infinite weights elsewhere")
 
 
+@pytest.mark.parametrize("K,s,transposed", [(3, 1, False), (2, 2, False), (2, 2, True), (1, 1, False)])
+@pytest.mark.parametrize("n,c_in,c_out", [(1, 64, 32), (15, 128, 64), (16, 192, 96), (17, 64, 256), (127, 64, 160), (128, 256, 128),
+                                           (129, 128, 96), (257, 320, 64), (2500, 64, 32), (2500, 256, 256)])
+def test_grouped_matmul_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
+    """The grouped matmul on rows of whole 64-channel stages: lists around blocks of 16 and tiles of 128 pairs, one stage
+    and an odd number of them, every number of output blocks per workgroup; gathered rows and rows fetched in place, the
+    centre's among them, with the same bits."""
+    coords = _rand_coords(5400 + n + c_in, n, 0, 4 if n < 60 else 16, batches=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), K, s, transposed)
+    x_h = features(5500 + c_in, kmap.num_in, c_in, np.float16)
+    w_h = conv_weights(5600 + c_out, K ** 3, c_in, c_out, np.float16)
+    x, w = to_dev(x_h), to_dev(w_h)
+    got = ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_EXPLICIT)
+    check_features(got, oracle_conv(coords, x_h, w_h, K, s, transposed), torch.float16, f"{n}: {c_in}->{c_out} K{K} s{s} t{int(transposed)}")
+    assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FETCH), got)
+
+
 # ---- a layer on a two-part input (the skip connection of a U-Net decoder), the concatenation never formed ----
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
