@@ -1213,7 +1213,11 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
 // added in offset order in fp32 registers and the row is written once.  The row of G that holds
 // the pair (k, n) follows from the offset's start, the base of k's 64-row block and the block's
 // presence bitmap.
-template <class T>
+// LANES (rows of a multiple of 4 * LANES channels; else 0): so many lanes share a row, and work out its up to 27 positions
+// side by side while the row's bitmask is still on its way; the rows of G are asked for eight at a time.  Without, a thread
+// pays three dependent loads for every four offsets.  Layers on 3x3x3 maps, without -> with, us: 256 -> 256 on 2.7 k points
+// 22.0 -> 19.8, on 8 k 32.6 -> 30.8, (128, 128) -> 128 on 22 k 45.3 -> 42.2.
+template <class T, int LANES>
 __global__ void __launch_bounds__(kThreads) k_scatter_reduce(const float *__restrict__ G, const int32_t *__restrict__ nbr,
                                                              int stride, const uint64_t *__restrict__ colbits,
                                                              const int32_t *__restrict__ colbase, Offs offs,
@@ -1230,9 +1234,36 @@ __global__ void __launch_bounds__(kThreads) k_scatter_reduce(const float *__rest
     const int64_t b = k >> 6;
     const uint64_t before = (1ull << (k & 63)) - 1ull;
     floatx4 acc = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (LANES != 0) {
+        int32_t at[32 / LANES];
+#pragma unroll
+        for (int i = 0; i < 32 / LANES; ++i) {
+            const int n = i * LANES + (threadIdx.x & (LANES - 1));
+            at[i] = n < K3 ? offs.v[n] + colbase[n * n_blocks + b] + __popcll(colbits[n * n_blocks + b] & before) : 0;
+        }
+        while (mask) {
+            int32_t p[8];
+            floatx4 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                p[u] = -1;
+                if (mask) {
+                    const int n = __builtin_ctz(mask);
+                    p[u] = __shfl(n < LANES ? at[0] : at[32 / LANES - 1], n & (LANES - 1), LANES);
+                    mask &= mask - 1;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p[u] >= 0) v[u] = __builtin_nontemporal_load(reinterpret_cast<const floatx4 *>(G + (int64_t)p[u] * cout + q * 4));
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (p[u] >= 0) acc += v[u];
+        }
+    }
     // four offsets at a time: their positions first, then their rows of G (read once: streamed
     // past the caches), then the adds in offset order
-    while (mask) {
+    while (LANES == 0 && mask) {
         int64_t p[4];
         floatx4 v[4];
 #pragma unroll
@@ -1872,8 +1903,13 @@ int grouped_mm_adaptive(const void *F, const void *X, const void *wt, const ts_k
 template <class T>
 int reduce_impl(const float *G, const ts_kmap *kmap, ts_tensor *out, const Epilogue &ep = Epilogue()) {
     if (kmap->n_out == 0) return TS_OK;
-    int64_t threads = kmap->n_out * (out->cols / 4);
-    TS_LAUNCH("k_scatter_reduce", k_scatter_reduce<T>, dim3(blocks_for(threads, kThreads)), dim3(kThreads), G, kmap->d_nbr, kmap->stride, kmap->d_colbits, kmap->d_colbase, offs_of(kmap), kmap->n_blocks, static_cast<T *>(out->data), kmap->n_out, out->cols, kmap->K3, static_cast<const T *>(ep.bias), static_cast<const T *>(ep.residual), ep.relu);
+    const int64_t threads = kmap->n_out * (out->cols / 4);
+    if (out->cols % 128 == 0)
+        TS_LAUNCH("k_scatter_reduce", (k_scatter_reduce<T, 32>), dim3(blocks_for(threads, kThreads)), dim3(kThreads), G, kmap->d_nbr, kmap->stride, kmap->d_colbits, kmap->d_colbase, offs_of(kmap), kmap->n_blocks, static_cast<T *>(out->data), kmap->n_out, out->cols, kmap->K3, static_cast<const T *>(ep.bias), static_cast<const T *>(ep.residual), ep.relu);
+    else if (out->cols % 64 == 0)
+        TS_LAUNCH("k_scatter_reduce", (k_scatter_reduce<T, 16>), dim3(blocks_for(threads, kThreads)), dim3(kThreads), G, kmap->d_nbr, kmap->stride, kmap->d_colbits, kmap->d_colbase, offs_of(kmap), kmap->n_blocks, static_cast<T *>(out->data), kmap->n_out, out->cols, kmap->K3, static_cast<const T *>(ep.bias), static_cast<const T *>(ep.residual), ep.relu);
+    else
+        TS_LAUNCH("k_scatter_reduce", (k_scatter_reduce<T, 0>), dim3(blocks_for(threads, kThreads)), dim3(kThreads), G, kmap->d_nbr, kmap->stride, kmap->d_colbits, kmap->d_colbase, offs_of(kmap), kmap->n_blocks, static_cast<T *>(out->data), kmap->n_out, out->cols, kmap->K3, static_cast<const T *>(ep.bias), static_cast<const T *>(ep.residual), ep.relu);
     TS_HIP(hipGetLastError());
     return TS_OK;
 }
