@@ -196,8 +196,9 @@ struct ts_kmap {
     uint32_t *d_wavemask = nullptr;       // [n_blocks] offsets met by any of the block's outputs
     uint32_t *d_rowmask = nullptr;        // [n_out] offsets met by every output, 3x3x3 stride-1 maps searched in blocks (else NULL)
     // The same rows in another order, for the output-stationary kernel (ts::order_windows): inside a window of
-    // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it.
-    int32_t *d_window_perm = nullptr;     // [n_tiles*kTileRows] position -> output row, -1 = padding; tiles longest first
+    // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it; maps that
+    // go up from a 2x2x2 map are made with it.
+    int32_t *d_window_perm = nullptr;     // [n_tiles*kTileRows] position -> output row, -1 = padding
     hipStream_t window_stream = nullptr;  // where that order was enqueued
     bool window_settled = false;          // it is known to be there: other streams may read it
     int uses = 0;                         // layers that the output-stationary kernel has run on this map

@@ -585,9 +585,8 @@ __host__ __device__ __forceinline__ uint32_t mask_sort_key(uint32_t mask, int K3
 // presence bitmaps of the wave's 64 outputs, one per offset, their counts, and the wave's OR.
 template <int K3>
 __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict__ colbits, int32_t *__restrict__ colcnt,
-                                            uint32_t *__restrict__ wavemask, int64_t n_blocks) {
+                                            uint32_t *__restrict__ wavemask, int64_t n_blocks, int64_t block64) {
     const int lane = threadIdx.x & 63;
-    const int64_t block64 = (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);   // wave-uniform
     uint64_t mine = 0;
 #pragma unroll
     for (int n = 0; n < K3; ++n) {
@@ -601,6 +600,11 @@ __device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict_
     // offsets present anywhere in the wave's 64 rows (what a tile of the fused kernel has to visit)
     const uint64_t any = __ballot(lane < K3 && mine != 0);
     if (lane == 0 && block64 < n_blocks) wavemask[block64] = (uint32_t)any;
+}
+template <int K3>
+__device__ __forceinline__ void finish_rows(uint32_t mask, uint64_t *__restrict__ colbits, int32_t *__restrict__ colcnt,
+                                            uint32_t *__restrict__ wavemask, int64_t n_blocks) {
+    finish_rows<K3>(mask, colbits, colcnt, wavemask, n_blocks, (int64_t)blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6));   // wave-uniform
 }
 
 // Map search for stride 1, K = 3 (Alg. 1) through the block table: a thread per point.  All block lookups of
@@ -1454,30 +1458,76 @@ __global__ void __launch_bounds__(kThreads) k_down_scatter(const uint64_t *__res
 // The transposed map of such a map, in one pass over the fine points: a row has the one entry (offset of the
 // point, its coarse cell).  Keys of both point sets are copied and the tile counters cleared on the way.
 // (By scattering the forward rows into cleared rows and reading those again it took five launches.)
-__global__ void __launch_bounds__(kThreads) k_up_rows(const uint64_t *__restrict__ fine, const int32_t *__restrict__ parent, int64_t n,
-                                                      const uint64_t *__restrict__ coarse, int64_t n_coarse,
-                                                      uint64_t *__restrict__ fine_copy, uint64_t *__restrict__ coarse_copy,
-                                                      int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
-                                                      int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
-                                                      int64_t n_blocks, uint4 *__restrict__ sched) {
-    constexpr int STRIDE = nbr_stride(8);
-    const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    for (int64_t v = i; v < kMaxSchedSlices * kSchedWords / 4; v += (int64_t)gridDim.x * kThreads) sched[v] = make_uint4(0, 0, 0, 0);
-    if (i < n_coarse) coarse_copy[i] = coarse[i];   // (never more coarse points than fine ones)
-    uint32_t mask = 0;
-    if (i < n) {
-        const uint64_t key = fine[i];
-        const int32_t k = parent[i];
-        const int q = down_offset(key);
-        fine_copy[i] = key;
-        if (k >= 0) mask = 1u << q;
-        int4 *row = reinterpret_cast<int4 *>(nbr + i * STRIDE);
-        const int none = -1;
-        row[0] = make_int4(q == 0 ? k : none, q == 1 ? k : none, q == 2 ? k : none, q == 3 ? k : none);
-        row[1] = make_int4(q == 4 ? k : none, q == 5 ? k : none, q == 6 ? k : none, q == 7 ? k : none);
-        row[2] = make_int4((int)mask, none, none, none);
+// perm, if not NULL: the row order for the output-stationary kernel, made on the way.  A tile of 128 neighbouring rows
+// meets all eight offsets, each for an eighth of its rows; inside a window of 2048 rows those of one offset stand
+// together, and a tile meets 1.4; a layer's stages fall by that much (128 -> 64 channels on 153 k rows of a scan 29.9 -> 23.1 us,
+// on 100 k scattered ones 33.4 -> 23.3; 128 -> 96 on 64 k 21.8 -> 17.0).  Ranks come from ballots: the order is the same every
+// time and costs the pass 1 to 2 us.
+constexpr int kUpThreads = 1024, kUpPer = 2, kUpRows = kUpThreads * kUpPer;
+__global__ void __launch_bounds__(kUpThreads) k_up_rows(const uint64_t *__restrict__ fine, const int32_t *__restrict__ parent, int64_t n,
+                                                        const uint64_t *__restrict__ coarse, int64_t n_coarse,
+                                                        uint64_t *__restrict__ fine_copy, uint64_t *__restrict__ coarse_copy,
+                                                        int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
+                                                        int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
+                                                        int64_t n_blocks, uint4 *__restrict__ sched, int32_t *__restrict__ perm) {
+    constexpr int STRIDE = nbr_stride(8), WAVES = kUpThreads / 64, CHUNKS = WAVES * kUpPer, CLASSES = 9;   // offsets, and none
+    __shared__ int32_t before[CLASSES][CHUNKS], total[CLASSES];   // rows of a class in the chunks of 64 rows before
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kUpRows;
+    for (int64_t v = (int64_t)blockIdx.x * kUpThreads + threadIdx.x; v < kMaxSchedSlices * kSchedWords / 4; v += (int64_t)gridDim.x * kUpThreads)
+        sched[v] = make_uint4(0, 0, 0, 0);
+    int own[kUpPer], rank[kUpPer];   // the row's class, and how many of its chunk stand before it there
+#pragma unroll
+    for (int r = 0; r < kUpPer; ++r) {
+        const int64_t i = base + r * kUpThreads + threadIdx.x;
+        if (i < n_coarse) coarse_copy[i] = coarse[i];   // (never more coarse points than fine ones)
+        uint32_t mask = 0;
+        if (i < n) {
+            const uint64_t key = fine[i];
+            const int32_t k = parent[i];
+            const int q = down_offset(key);
+            fine_copy[i] = key;
+            if (k >= 0) mask = 1u << q;
+            int4 *row = reinterpret_cast<int4 *>(nbr + i * STRIDE);
+            const int none = -1;
+            row[0] = make_int4(q == 0 ? k : none, q == 1 ? k : none, q == 2 ? k : none, q == 3 ? k : none);
+            row[1] = make_int4(q == 4 ? k : none, q == 5 ? k : none, q == 6 ? k : none, q == 7 ? k : none);
+            row[2] = make_int4((int)mask, none, none, none);
+        }
+        finish_rows<8>(mask, colbits, colcnt, wavemask, n_blocks, base / 64 + r * WAVES + wave);
+        own[r] = i >= n ? -1 : mask ? __builtin_ctz(mask) : 8;
+        rank[r] = 0;
+#pragma unroll
+        for (int c = 0; c < CLASSES; ++c) {
+            const uint64_t of_c = __ballot(own[r] == c);
+            if (own[r] == c) rank[r] = __popcll(of_c & ((1ull << lane) - 1ull));
+            if (lane == c) before[c][r * WAVES + wave] = __popcll(of_c);
+        }
     }
-    finish_rows<8>(mask, colbits, colcnt, wavemask, n_blocks);
+    if (!perm) return;
+    __syncthreads();
+    if (wave < CLASSES) {
+        const int rows = lane < CHUNKS ? before[wave][lane] : 0;
+        int incl = rows;
+        for (int d = 1; d < CHUNKS; d <<= 1) {
+            const int up = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += up;
+        }
+        if (lane < CHUNKS) before[wave][lane] = incl - rows;
+        if (lane == CHUNKS - 1) total[wave] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kUpPer; ++r) {
+        const int64_t i = base + r * kUpThreads + threadIdx.x;
+        if (own[r] >= 0) {
+            int at = before[own[r]][r * WAVES + wave] + rank[r];
+            for (int c = 0; c < own[r]; ++c) at += total[c];
+            perm[base + at] = (int32_t)i;
+        } else if (i < (n + kTileRows - 1) / kTileRows * kTileRows) {
+            perm[i] = -1;
+        }
+    }
 }
 
 // Block n: exclusive scan in place of the counts col[n][*] -> col[n][b] = pairs of offset n in the 64-row
@@ -2558,9 +2608,11 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         int32_t *sizes;   // written by the scan, known already
         TS_TRY(tmp.get(&sizes, ST_WORDS));
         TS_TRY(alloc_outputs(m, nullptr));
-        TS_LAUNCH("k_up_rows", k_up_rows, dim3(blocks_for(m->n_out, kThreads)), dim3(kThreads), f->d_in_keys, f->d_parent, m->n_out,
+        if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) m->d_window_perm = nullptr;   // the natural order then
+        m->window_settled = true;   // whoever may read the map's rows may read their order
+        TS_LAUNCH("k_up_rows", k_up_rows, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), f->d_in_keys, f->d_parent, m->n_out,
                   f->d_out_keys, m->n_in, m->d_out_keys, m->d_in_keys, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks,
-                  reinterpret_cast<uint4 *>(m->d_sched));
+                  reinterpret_cast<uint4 *>(m->d_sched), m->d_window_perm);
         launch_scan(m, sizes);
         TS_HIP(hipGetLastError());
         return TS_OK;

@@ -1330,6 +1330,27 @@ def test_grouped_matmul_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out
     assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FETCH), got)
 
 
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("n", [1, 127, 128, 129, 2047, 2048, 2049, 9000])
+def test_rows_of_a_transposed_map_grouped_by_offset(n, dtype):
+    """The rows of a 2x2x2 map that goes up are grouped by offset in windows of 2048: whole and partial windows and tiles,
+    on the stream the map was made on and on another one, by the kernels of both types."""
+    coords = _rand_coords(5700 + n, n, -9, 14, batches=2)
+    down = ts.ts_build_kmap(to_dev(coords), 2, 2)
+    x_h = features(5800, down.num_out, 64, np_dtype(dtype))
+    w_h = conv_weights(5801, 8, 64, 32, np_dtype(dtype))
+    x, w = to_dev(x_h), to_dev(w_h)
+    want = oracle_conv(coords, x_h, w_h, 2, 2, True)
+    other = torch.cuda.Stream()
+    up = down.transpose()
+    got = ts.ts_sparse_conv(x, w, up, dataflow=ts.TS_DATAFLOW_FUSED)
+    check_features(got, want, dtype, f"{n} rows up")
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        assert torch.equal(ts.ts_sparse_conv(x, w, up, dataflow=ts.TS_DATAFLOW_FUSED), got)
+    other.synchronize()
+
+
 # ---- a layer on a two-part input (the skip connection of a U-Net decoder), the concatenation never formed ----
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
