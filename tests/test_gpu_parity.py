@@ -1351,6 +1351,22 @@ def test_rows_of_a_transposed_map_grouped_by_offset(n, dtype):
     other.synchronize()
 
 
+@pytest.mark.parametrize("n,c", [(1023, 128), (1024, 128), (3000, 256)])
+def test_dataflow_of_maps_by_two(n, c):
+    """Going up, fp16 layers of a tile per offset and more take the fused kernel however wide they are; both ways against
+    the oracle."""
+    coords = _rand_coords(5900 + n, n, -9, 14, batches=1)
+    down = ts.ts_build_kmap(to_dev(coords), 2, 2)
+    w_h = conv_weights(5901, 8, c, c, np.float16)
+    w = to_dev(w_h)
+    for kmap, transposed in ((down, False), (down.transpose(), True)):
+        x_h = features(5902, kmap.num_in, c, np.float16)
+        got = ts.ts_sparse_conv(to_dev(x_h), w, kmap)
+        check_features(got, oracle_conv(coords, x_h, w_h, 2, 2, transposed), torch.float16, f"{n} rows, {c} channels, up {transposed}")
+        if transposed and n >= 1024:
+            assert torch.equal(ts.ts_sparse_conv(to_dev(x_h), w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), got)
+
+
 # ---- a layer on a two-part input (the skip connection of a U-Net decoder), the concatenation never formed ----
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
