@@ -774,6 +774,244 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T
     }
 }
 
+// ---- the same layer with rows as operands, for launches of few workgroups ------------------------------------
+// D[co][m] as above, but a wave owns 32 rows and all 16 NCO channels, gathered rows go from memory straight into operand
+// registers (4 lanes per 64 bytes of a row) two stages ahead, and the weights of a stage (one offset, 32 KSTEPS channels)
+// through registers into LDS for the four waves.  Same bits as k_conv_tile.  Each load costs the address unit more, which
+// decides nothing while a CU has one or two workgroups: those wait out every stage's loads, and two stages in flight with
+// one short barrier each beat one stage ahead.  run_fused_f16 says which launches come here.
+template <int NCO, int KSTEPS, int DEPTH, bool TWO>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NCO * KSTEPS <= 8 && NCO < 8 ? 3 : 2))) k_conv_direct(const _Float16 *__restrict__ X, const u32x4 *__restrict__ Wf,
+                                                        const int32_t *__restrict__ nbr, int stride,
+                                                        const int32_t *__restrict__ perm, int from_end,
+                                                        const int32_t *__restrict__ tile_order, int64_t n_out,
+                                                        _Float16 *__restrict__ out, int *__restrict__ sched,
+                                                        int cin, int cout, int K3, const _Float16 *__restrict__ bias,
+                                                        const _Float16 *__restrict__ residual, int relu, int x_bytes,
+                                                        int w_bytes, int centre, const _Float16 *__restrict__ X2,
+                                                        int x2_bytes, int cin1) {
+    // TWO: the layer's input is the channel concatenation [X | X2], which is never formed: input channels
+    // below cin1 are read from X (rows of cin1 channels), the others from X2 (rows of cin - cin1 channels);
+    // cin1 is a multiple of 32, so each 32-channel operand step lies in one of the two.  Otherwise X2,
+    // x2_bytes are unused and cin1 = cin.
+    constexpr int KC = KSTEPS * 32, FRAGS = NCO * KSTEPS, SLAB = FRAGS * 64;   // slab in 16-byte vectors
+    constexpr int WV = (SLAB + kThreads - 1) / kThreads;
+    __shared__ u32x4 lds_w[2][SLAB];
+    __shared__ int32_t lds_j[kMaxK3][kTileRows], s_row[kTileRows];
+    __shared__ uint32_t s_mask;
+    __shared__ int s_tile;
+    // The launch holds as many workgroups as stay resident at once.  Workgroup b starts with tile b;
+    // the tiles beyond the grid are handed out through counters, so nobody waits for a second
+    // round of workgroups.  One counter per XCD (blockIdx % 8), on cache lines of their own:
+    // atomics on one address are served one after the other.
+    const int64_t n_tiles = (n_out + kTileRows - 1) / kTileRows;
+    sched += kSchedWords * blockIdx.y;
+    const int xcd = blockIdx.x & 7;
+    const int cb0 = blockIdx.y * NCO;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
+    const int r0 = wave * kWaveRows + m16, r1 = r0 + 16;   // the lane's two output rows (tile slots)
+    // Longest tiles first, so that they do not start when everything else is done: by the order
+    // the map build prepared (tiles of rows in input order by descending number of offsets); rows
+    // sorted by bitmask put the tiles with the most offsets last, so those are taken from the end.
+    int64_t turn = blockIdx.x;
+    // The rows of a tile, known one tile ahead (where they go through perm, that is a memory latency less per tile):
+    // in the prologue, the 16-byte chunks of a table row go to neighbouring lanes, so that one load instruction
+    // covers whole rows (a row touched by several instructions costs a request each).
+    const int row_chunks = stride / 4;                                           // 8, 4 or 1 lanes per row
+    const int row_ch = threadIdx.x % row_chunks, row_sub = threadIdx.x / row_chunks;
+    const int rows_per_pass = kThreads / row_chunks;                             // 32, 64 or 256
+    int32_t kk[4];                                                               // -2: no row of the tile in this pass
+    auto rows_of = [&](int64_t t) __attribute__((always_inline)) {
+        const int64_t tile = from_end ? n_tiles - 1 - t : (tile_order ? tile_order[t] : t);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int col = i * rows_per_pass + row_sub;
+            const int64_t pos = tile * kTileRows + col;
+            kk[i] = -2;
+            if (col < kTileRows) kk[i] = perm ? perm[pos] : (pos < n_out ? (int32_t)pos : -1);
+        }
+    };
+    if (turn < n_tiles) rows_of(turn);
+    while (turn < n_tiles) {
+    // ask for the next tile now; the answer is needed when this one is done
+    int ticket = 0;
+    if (threadIdx.x == 0) ticket = atomicAdd(&sched[xcd * 32], 1);
+
+    // Neighbour rows of the tile's outputs -> LDS (offset-major), and the OR of their offset bitmasks.
+    if (threadIdx.x == 0) s_mask = 0;
+    __syncthreads();
+    {
+        int4 v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = make_int4(-1, -1, -1, -1);
+            if (kk[i] >= 0) v[i] = reinterpret_cast<const int4 *>(nbr + (int64_t)kk[i] * stride)[row_ch];
+        }
+        uint32_t mm = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (kk[i] == -2) continue;
+            const int col = i * rows_per_pass + row_sub;
+            const int32_t k = kk[i];
+            if (row_ch == 0) s_row[col] = k;
+            const int32_t e[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int idx = row_ch * 4 + q;
+                if (idx < K3) {
+                    const int32_t j = idx == centre ? k : (k >= 0 ? e[q] : -1);
+                    lds_j[idx][col] = j;
+                    if (j >= 0) mm |= 1u << idx;
+                }
+            }
+        }
+        for (int d = 32; d >= 1; d >>= 1) mm |= (uint32_t)__shfl_xor((int)mm, d, 64);
+        if (lane == 0 && mm) atomicOr(&s_mask, mm);
+    }
+    __syncthreads();
+    // the offsets present in the tile, as a bitmask in a scalar register: the stages walk its set bits
+    const uint32_t mask = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_mask);
+    const int nchunks = cin / KC;
+    const int nstage = __builtin_popcount(mask) * nchunks;
+    const int cblocks = cout / 16;
+
+    floatx4 acc[NCO][2];
+#pragma unroll
+    for (int cb = 0; cb < NCO; ++cb)
+#pragma unroll
+        for (int c2 = 0; c2 < 2; ++c2) acc[cb][c2] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    u32x4 wreg[DEPTH][WV];
+    half8v xreg[DEPTH][2][KSTEPS];
+    bool xlive[DEPTH];
+    // Issue the loads of stage s into register set d (d is a compile-time constant at every call).
+    // Every call issues the same number of loads, unconditionally (past the last stage it repeats
+    // that stage; rows without the offset read the zero row): the compiler counts outstanding
+    // loads to place its waits, and a load it cannot count would make every wait a full drain.
+    // Loads go through buffer descriptors: a 32-bit byte offset per lane plus a wave-uniform one, no
+    // 64-bit address arithmetic in the loop, and an offset beyond the buffer reads as zero without
+    // touching memory, which is what a row without the offset must contribute.  The loop body is
+    // short on purpose: with ~200 vector instructions per stage around 16 MFMAs this kernel was
+    // bound by instruction issue.
+    const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(X), 0, x_bytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t xrsrc2 = __builtin_amdgcn_make_buffer_rsrc(const_cast<_Float16 *>(TWO ? X2 : X), 0, TWO ? x2_bytes : x_bytes, 0x00020000);
+    const int row_bytes2 = (cin - cin1) * 2;
+    const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
+    constexpr int kNoRow = (int)0x80000000u;   // beyond any buffer this kernel is launched with
+    const int row_bytes = cin1 * 2, xlane = g * 16;
+    // A fragment of the slab (16 output channels, 32 input channels) is 1 KiB; in memory the steps of a stage follow each
+    // other, block by block of output channels.
+    int wlane[WV], wslot[WV];
+#pragma unroll
+    for (int v = 0; v < WV; ++v) {
+        int idx = threadIdx.x + v * kThreads;
+        if (SLAB % kThreads != 0) idx = idx < SLAB ? idx : SLAB - 1;   // surplus threads repeat the last vector
+        wslot[v] = idx;
+        wlane[v] = idx * 16;
+    }
+    uint32_t it_rem = mask ? mask : 1u;   // offsets not issued yet; the lowest set bit is the one being issued
+    int it_ch = 0;                        // its chunk
+    // neighbour rows of the lane's two outputs for the stage issued next: read out of LDS one stage
+    // ahead, so that no stage waits for them
+    int32_t pj0 = lds_j[__builtin_ctz(it_rem)][r0], pj1 = lds_j[__builtin_ctz(it_rem)][r1];
+    // Issue the loads of stage s into register set d (a compile-time constant at every call).
+    // Every call issues the same loads, unconditionally (past the last stage it repeats that
+    // stage): the compiler counts outstanding loads to place its waits, and a load it cannot count
+    // makes every wait a full drain.
+    auto issue = [&](int s, auto dc) __attribute__((always_inline)) {
+        constexpr int d = decltype(dc)::value;
+        const bool real = s < nstage;
+        const int ch = it_ch, n = __builtin_ctz(it_rem);   // scalar: the weight slab's address stays in scalar registers
+        const int32_t j0 = pj0, j1 = pj1;
+        if (s + 1 < nstage) {   // stages are issued in order: step the pair, stay on the last one past the end
+            if (++it_ch == nchunks) {
+                it_ch = 0;
+                it_rem &= it_rem - 1;
+            }
+        }
+        pj0 = lds_j[__builtin_ctz(it_rem)][r0];
+        pj1 = lds_j[__builtin_ctz(it_rem)][r1];
+        const int wsoff = ((n * nchunks + ch) * cblocks + cb0) * (KSTEPS * 1024);
+#pragma unroll
+        for (int v = 0; v < WV; ++v) wreg[d][v] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane[v], wsoff, 0);
+        xlive[d] = real && __ballot(j0 >= 0 || j1 >= 0) != 0;   // false: none of the wave's rows has this offset
+        const int off0 = j0 >= 0 ? j0 * row_bytes + xlane : kNoRow;
+        const int off1 = j1 >= 0 ? j1 * row_bytes + xlane : kNoRow;
+        const int xsoff = ch * (KC * 2);
+        int offb0 = 0, offb1 = 0;
+        if constexpr (TWO) {
+            offb0 = j0 >= 0 ? j0 * row_bytes2 + xlane : kNoRow;
+            offb1 = j1 >= 0 ? j1 * row_bytes2 + xlane : kNoRow;
+        }
+#pragma unroll
+        for (int ks = 0; ks < KSTEPS; ++ks) {
+            u32x4 v0, v1;
+            if constexpr (TWO) {
+                const int c0 = ch * KC + ks * 32;        // first input channel of this operand step
+                const bool second = c0 >= cin1;          // wave-uniform: the step lies in X2
+                const int so = second ? (c0 - cin1) * 2 : c0 * 2;
+                v0 = __builtin_amdgcn_raw_buffer_load_b128(second ? xrsrc2 : xrsrc, second ? offb0 : off0, so, 0);
+                v1 = __builtin_amdgcn_raw_buffer_load_b128(second ? xrsrc2 : xrsrc, second ? offb1 : off1, so, 0);
+            } else {
+                v0 = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off0, xsoff + ks * 64, 0);
+                v1 = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, off1, xsoff + ks * 64, 0);
+            }
+            __builtin_memcpy(&xreg[d][0][ks], &v0, 16);
+            __builtin_memcpy(&xreg[d][1][ks], &v1, 16);
+        }
+    };
+    auto run = [&](int s, auto dc) __attribute__((always_inline)) {
+        constexpr int d = decltype(dc)::value;
+        u32x4 *slab = lds_w[s & 1];
+#pragma unroll
+        for (int v = 0; v < WV; ++v) slab[wslot[v]] = wreg[d][v];
+        __syncthreads();   // slab complete; everybody is done with the other slab
+        if (xlive[d]) {
+#pragma unroll
+            for (int ks = 0; ks < KSTEPS; ++ks) {
+                // all weight fragments of the step out of LDS first, then the MFMAs: a read placed
+                // right before its MFMA costs one LDS latency per fragment
+                u32x4 raw[NCO];
+#pragma unroll
+                for (int cb = 0; cb < NCO; ++cb) raw[cb] = slab[(cb * KSTEPS + ks) * 64 + lane];
+                __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+                for (int cb = 0; cb < NCO; ++cb) {
+                    half8v a;
+                    __builtin_memcpy(&a, &raw[cb], 16);
+                    acc[cb][0] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xreg[d][0][ks], acc[cb][0], 0, 0, 0);
+                    acc[cb][1] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, xreg[d][1][ks], acc[cb][1], 0, 0, 0);
+                }
+                __builtin_amdgcn_s_setprio(0);
+            }
+        }
+        issue(s + DEPTH, dc);
+    };
+    if (nstage > 0) {
+        static_for<DEPTH>([&](auto dc) __attribute__((always_inline)) { issue(decltype(dc)::value, dc); });
+        // whole rounds of DEPTH stages; stages past the end only repeat loads and skip the MFMAs
+        for (int s0 = 0; s0 < nstage; s0 += DEPTH) static_for<DEPTH>([&](auto dc) __attribute__((always_inline)) { run(s0 + decltype(dc)::value, dc); });
+    }
+
+    const int32_t out_row[2] = {s_row[r0], s_row[r1]};
+    RowStore<NCO> rows;
+    rows.open(acc, out_row, residual, cout, cb0 * 16);
+    if (threadIdx.x == 0) s_tile = ticket;
+    __syncthreads();   // the tile's LDS is free; s_tile is set
+    turn = (int64_t)gridDim.x + xcd + 8 * (int64_t)s_tile;
+    if (turn < n_tiles) rows_of(turn);
+    // (the pointer is made opaque per tile: loads the compiler can prove the same for every tile move to the
+    // top of the kernel and hold registers through the stage loop, which has none to spare)
+    const _Float16 *bp = bias;
+    asm volatile("" : "+s"(bp));
+    rows.store(&lds_w[0][0] + wave * (NCO * 32), out, bp, residual != nullptr, relu, cout, cb0 * 16);
+    }
+    // the last workgroup to leave rearms the counters for the next launch on this map
+    if (threadIdx.x == 0 && atomicAdd(&sched[8 * 32], 1) == (int)gridDim.x - 1) {
+        for (int i = 0; i <= 8; ++i) sched[i * 32] = 0;
+    }
+}
+
 // ---- fused kernel for narrow layers: all weights resident in LDS -----------------------------------
 // With C_in = 32 KSTEPS and a slice of 16 NCO output channels the weights, in operand order, are
 // K^3 NCO KSTEPS KiB (used with C_in <= 32 and C_out = 32 or 64: 54 or 108 KiB):
@@ -1582,6 +1820,34 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
               static_cast<const _Float16 *>(sec.x2), (int)((size_t)kmap->n_in * (cin_pad - cin1) * 2), cin1);
 }
 
+constexpr int kDirectDepth = 2;   // (3 took registers that two more waves can have: 2 to 4 % slower)
+
+template <int NCO, int KSTEPS, bool TWO>
+void launch_conv_direct(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap, ts_tensor *out, int cin_pad,
+                        const Epilogue &ep, const Second &sec) {
+    // as many workgroups as stay resident at once, fewer for small maps
+    static int per_cu = 0;   // per instantiation
+    if (per_cu == 0) {
+        int n = 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, k_conv_direct<NCO, KSTEPS, kDirectDepth, TWO>, kThreads, 0) != hipSuccess || n <= 0) {
+            (void)hipGetLastError();
+            n = 2;
+        }
+        per_cu = n;
+    }
+    const int64_t resident = (int64_t)compute_units() * per_cu;
+    dim3 grid((unsigned)(kmap->n_tiles < resident ? kmap->n_tiles : resident), out->cols / (NCO * 16));
+    const int cin1 = TWO ? sec.cin1 : cin_pad;
+    const int32_t *perm = row_order(kmap);
+    TS_LAUNCH("k_conv_direct", (k_conv_direct<NCO, KSTEPS, kDirectDepth, TWO>), grid, dim3(kThreads), x,
+              reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr, kmap->stride, perm, kmap->d_perm != nullptr,
+              !perm && (kmap->scan_done || (kmap->scan_enqueued && kmap->stream == stream())) ? kmap->d_tile_order : nullptr,
+              kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
+              static_cast<const _Float16 *>(ep.bias), static_cast<const _Float16 *>(ep.residual), ep.relu,
+              (int)((size_t)kmap->n_in * cin1 * 2), (int)((size_t)kmap->K3 * cin_pad * out->cols * 2), kmap->centre,
+              static_cast<const _Float16 *>(sec.x2), (int)((size_t)kmap->n_in * (cin_pad - cin1) * 2), cin1);
+}
+
 // Narrow layers (C_in <= 32, C_out = 32): the kernel that keeps all weights in LDS.  False if this
 // device does not give a workgroup that much LDS: the caller then takes k_conv_tile.
 template <int NCO, int KSTEPS>
@@ -1662,8 +1928,36 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             nco = c;
             break;
         }
+    // Launches of few workgroups that k_conv_direct does faster (us, k_conv_tile and k_conv_direct; layers after one halving
+    // of a scan):
+    //  - a two-part input with a part that is no multiple of 64 channels: stages of two sources, or half empty ones.  Up to
+    //    two tiles a CU: (96, 32) -> 96 on 2 k rows 29.7 and 23.0, on 32 k 47.3 and 38.8, on 60 k 46.6 and 38.6, but on 120 k
+    //    57.4 and 63.9; (96, 64) -> 96 on 16 k 51.5 and 48.7, on 60 k 58.5 and 54.1, on 120 k 69.0 and 84.9
+    //  - stages of 96 channels, up to a tile a CU: 96 -> 64 on 4 k rows 16.8 and 15.7, on 32 k 23.5 and 21.2, on 60 k 24.1 and 29.8;
+    //    96 -> 96 on 8 k 18.0 and 16.5, on 32 k 34.9 and 32.8, on 60 k 29.1 and 35.5
+    //  - stages of 32, up to two tiles a CU: 32 -> 96 on 4 k rows 11.9 and 11.2, on 60 k 20.3 and 19.3, on 120 k 27.7 and 32.2
+    //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 16 k rows
+    //    29.9 and 27.7, 128 -> 64 on 32 k 29.0 and 27.7; fewer and more are even or the other way round: 128 -> 128 on 2 k 20.2 and
+    //    21.2, on 24 k 35.0 and 35.4
+    const int64_t wgs = kmap->n_tiles * (cblocks / nco);
+    const bool direct = sec.x2 && (sec.cin1 % 64 != 0 || (cin - sec.cin1) % 64 != 0) && ksteps != 3 ? kmap->n_tiles <= 2 * cus
+                        : ksteps == 3                                                               ? kmap->n_tiles <= cus
+                        : cin_pad == 32                                                             ? kmap->n_tiles <= 2 * cus
+                                                                    : ksteps == 2 && cin_pad >= 128 && 2 * wgs > cus && wgs <= cus;
+#define TS_DIRECT_CASE(N)                                                                          \
+    if (direct && nco == N) {                                                                      \
+        if (sec.x2) {                                                                              \
+            if (ksteps == 2) launch_conv_direct<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);   \
+            else if (ksteps == 3) launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \
+            else launch_conv_direct<N, 1, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
+        } else if (ksteps == 2) launch_conv_direct<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else launch_conv_direct<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec);                  \
+    }
+    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)
+#undef TS_DIRECT_CASE
 #define TS_TILE_CASE(N)                                                                            \
-    if (nco == N) {                                                                                \
+    if (!direct && nco == N) {                                                                     \
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);    \
             else if (ksteps == 3) launch_conv_tile<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \

@@ -1300,6 +1300,23 @@ def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
     assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), first)   # rows ordered, counters rearmed
 
 
+@pytest.mark.parametrize("n,parts,c_out", [(129, (96,), 64), (32768, (96,), 64), (32769, (96,), 64), (129, (32,), 96), (66000, (32,), 96), (16000, (128,), 128),
+                                           (17, (96, 32), 96), (129, (96, 64), 96), (2000, (64, 32), 96), (40000, (64, 96), 32), (66000, (96, 32), 96), (66000, (96, 64), 96)])
+def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out):
+    """Few tiles and many, of layers whose kernel goes by their number; an input in two parts gives what it gives in one."""
+    coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
+    x_h = features(6100, n, sum(parts), np.float16)
+    w_h = conv_weights(6101, 27, sum(parts), c_out, np.float16)
+    w = ts.ts_weights_prepare(to_dev(w_h))
+    if len(parts) == 1:
+        got = ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap)
+    else:
+        got = ts.ts_sparse_conv_prepared2(to_dev(x_h[:, :parts[0]].copy()), to_dev(x_h[:, parts[0]:].copy()), w, kmap)
+        assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap), got)
+    check_features(got, oracle_conv(coords, x_h, w_h, 3, 1, False), torch.float16, f"{n}: {parts}->{c_out}")
+
+
 def test_weights_of_offsets_that_nothing_meets_are_not_multiplied():
     """Points on a diagonal meet three of 27 offsets; the weights of the others are infinite, those next to the half-full
     last stage of 160 channels among them."""
