@@ -1938,12 +1938,12 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     //  - stages of 32, up to two tiles a CU: 32 -> 96 on 4 k rows 11.9 and 11.2, on 60 k 20.3 and 19.3, on 120 k 27.7 and 32.2
     //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 16 k rows
     //    29.9 and 27.7, 128 -> 64 on 32 k 29.0 and 27.7; fewer and more are even or the other way round: 128 -> 128 on 2 k 20.2 and
-    //    21.2, on 24 k 35.0 and 35.4
+    //    21.2, on 24 k 35.0 and 35.4; so are the few stages of 1x1x1 maps ((128, 128) -> 128 on 22 k rows 15.2 and 15.8)
     const int64_t wgs = kmap->n_tiles * (cblocks / nco);
     const bool direct = sec.x2 && (sec.cin1 % 64 != 0 || (cin - sec.cin1) % 64 != 0) && ksteps != 3 ? kmap->n_tiles <= 2 * cus
                         : ksteps == 3                                                               ? kmap->n_tiles <= cus
                         : cin_pad == 32                                                             ? kmap->n_tiles <= 2 * cus
-                                                                    : ksteps == 2 && cin_pad >= 128 && 2 * wgs > cus && wgs <= cus;
+                                                                    : ksteps == 2 && cin_pad >= 128 && kmap->K3 > 8 && 2 * wgs > cus && wgs <= cus;
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \
