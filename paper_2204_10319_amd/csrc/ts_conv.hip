@@ -2262,27 +2262,27 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 //     of 32 k (2.6) 74 and 122; 128 -> 128, surfaces 16 k 199 and 78.  Narrower ones gain less than the wait takes.
 //     (Recorded on a map without pair lists, which need memory, such a layer goes by the typical number.)
 // (A build that found bad input, or whose sizes cannot be had now, leaves the fused kernel, which needs none.)
-// 2x2x2 maps in fp16 (us, fused and fetched).  Going up, rows of one offset stand together, so that a tile walks little more
+// 2x2x2 maps that go up, in fp16 (us, fused and fetched): rows of one offset stand together, so that a tile walks little more
 // than one offset, from about a tile per offset on: 128 -> 64 on 2.7 k rows 7.1, 8.4, on 30 k 9.5, 12.9; 256 -> 256 on
-// 2.7 k 9.2, 11.8, on 8 k 11.2, 15.4, on 32 k 19.0, 28.1.  Going down the line is drawn at 0.9 times the pairs' bytes:
-// 64 -> 128 from 8 k scattered points (0.63) 8.5, 10.6, 128 -> 256 from 32 k points of a scan (0.70) 18.8, 22.2,
-// 256 -> 256 from 60 k (0.82) 34.6, 36.0, from 85 k (0.86) 33.0, 49.6; from 22 k (0.93) 23.1, 19.1, from 30 k (1.45) 28.7, 23.3.
+// 2.7 k 9.2, 11.8, on 8 k 11.2, 15.4, on 32 k 19.0, 28.1.
+// Maps that go down share the line of the others.  Drawn at 0.9 times the pairs' bytes it gained on wide outputs (64 -> 128
+// from 16 k scattered points 9.9, 12.8, 256 -> 256 from 60 k points of surfaces 27.2, 33.7) but cost more where C_in is the larger one, whose
+// stages a tile walks one after the other: 128 -> 64 from 16 k scattered points 11.6, 9.8, 256 -> 64 from 24 k points of a scan 20.2, 11.9,
+// 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
-    const bool f16_by_two = elem == 2 && kmap->K3 == 8 && kmap->s == 2;
-    if (f16_by_two && kmap->transposed && kmap->d_window_perm && kmap->n_out >= 8 * kTileRows) return false;
-    const double fused_share = f16_by_two ? 0.9 : 0.6;
+    if (elem == 2 && kmap->K3 == 8 && kmap->s == 2 && kmap->transposed && kmap->d_window_perm && kmap->n_out >= 8 * kTileRows) return false;
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
     const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
     const double typical = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;
     const double slabs = tile_offsets * cin * cout * elem, fused_weight_bytes = (double)kmap->n_tiles * slabs;
     const double bytes_per_pair = 2.0 * cin * elem + 2.0 * cout * sizeof(float);
     const bool wide_f32 = elem == 4 && kmap->s == 1 && kmap->K3 == 27 && cin * cout >= 4096 && (kmap->d_in_idx || !stream_capturing(stream()));
-    if (!wide_f32 && fused_weight_bytes <= fused_share * typical * bytes_per_pair) return false;
+    if (!wide_f32 && fused_weight_bytes <= 0.6 * typical * bytes_per_pair) return false;
     if (resolve(kmap) != TS_OK) return false;
     const double pair_bytes = (double)kmap->M * bytes_per_pair;
     if (wide_f32) return pair_bytes < 1000 * slabs;
-    return (double)kmap->M <= typical || fused_weight_bytes > fused_share * pair_bytes || pair_bytes < 40 * slabs;
+    return (double)kmap->M <= typical || fused_weight_bytes > 0.6 * pair_bytes || pair_bytes < 40 * slabs;
 }
 
 // ---- the layer for callers that cannot allocate -----------------------------------------------------------

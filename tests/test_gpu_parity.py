@@ -1384,6 +1384,22 @@ def test_dataflow_of_maps_by_two(n, c):
             assert torch.equal(ts.ts_sparse_conv(to_dev(x_h), w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), got)
 
 
+@pytest.mark.parametrize("n,side,c_in,c_out,want", [
+    (16000, 60, 64, 128, "fetched"), (16000, 60, 128, 64, "fetched"), (16000, 60, 64, 64, "fused"), (16000, 60, 32, 64, "fused"),
+    (8000, 22, 128, 256, "fused"), (8000, 22, 256, 128, "fused"), (1500, 24, 96, 96, "fetched"), (1500, 24, 64, 32, "fused")])
+def test_dataflow_of_maps_that_go_down_by_two(n, side, c_in, c_out, want):
+    """Fused while a tile's weights are at most 0.6 times the bytes of its pairs: on both sides of that line and of 0.9,
+    told by the bits of the two dataflows, which add a row's products in another order."""
+    coords = _rand_coords(5950 + n, n, 0, side)
+    kmap = ts.ts_build_kmap(to_dev(coords), 2, 2)
+    share = -(-kmap.num_out // 128) * 8 * c_in * c_out * 2 / (n * (4 * c_in + 8 * c_out))
+    assert share < 0.55 if want == "fused" else 0.61 < share < 0.9
+    x, w = to_dev(features(5951, n, c_in, np.float16)), to_dev(conv_weights(5952, 8, c_in, c_out, np.float16))
+    fused, fetched = (ts.ts_sparse_conv(x, w, kmap, dataflow=df) for df in (ts.TS_DATAFLOW_FUSED, ts.TS_DATAFLOW_FETCH))
+    assert not torch.equal(fused, fetched)
+    assert torch.equal(ts.ts_sparse_conv(x, w, kmap), fused if want == "fused" else fetched)
+
+
 # ---- a layer on a two-part input (the skip connection of a U-Net decoder), the concatenation never formed ----
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
