@@ -1347,11 +1347,12 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     if (i >= plan.count) return;
     const int n = plan.n[i];
     const int lo = offs.v[n], hi = offs.v[n + 1], p0 = lo + t * kTileRows, rows = hi - p0;   // rows of the list in this tile, if positive
+    if (rows <= 0) return;   // a batched launch pads lists to the longest: nothing to store, and F may end before p0
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, m16 = lane & 15, g = lane >> 4;
     const int wr = wave / WC, wc = wave % WC;
     const int cblocks = cout / 16, nch = cin / 64, cb0 = blockIdx.y * NCO + wc * CB;
     const bool whole = n == centre || in_idx;   // rows of X, wherever they are; else F's own, one after the other
-    const int valid = rows < kTileRows ? (rows > 0 ? rows : 0) : kTileRows;
+    const int valid = rows < kTileRows ? rows : kTileRows;
     const u32x4 xrsrc = whole ? lds_source(X, x_bytes) : lds_source(F + (int64_t)p0 * cin, valid * cin * 2);
     const u32x4 xrsrc2 = lds_source(TWO ? X2 : X, TWO ? x2_bytes : 0);
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);

@@ -718,16 +718,18 @@ def _expected_launches(sizes, centre, eps, S):
     return launches + (1 if centre >= 0 and sizes[centre] > 0 else 0)
 
 
+@pytest.mark.parametrize("c_in", [32, 64, 128, 192])
 @pytest.mark.parametrize("K,s", [(3, 1), (2, 2), (3, 2)])
-def test_adaptive_grouping_same_result_in_the_launches_of_alg4(K, s):
+def test_adaptive_grouping_same_result_in_the_launches_of_alg4(K, s, c_in):
     """Sec. 4.2.3 / Appendix B, Alg. 4: whatever the tolerance and the threshold, the partial sums are those of
-    the single launch, bit for bit; the launches made and the padded rows follow the oracle's partition."""
+    the single launch, bit for bit; the launches made and the padded rows follow the oracle's partition.  Rows of
+    whole 64-channel stages are padded with tiles past the end of their list by another kernel, of one stage and more."""
     coords = lidar_scan_coords(31, n_beams=32, n_azimuth=1024)
     kmap = ts.ts_build_kmap(to_dev(coords), K, s)
     sizes = kmap.sizes()
     centre = 13 if (K, s) == (3, 1) else -1
-    x = to_dev(features(520, coords.shape[0], 32, np.float16))
-    w = to_dev(conv_weights(521, K ** 3, 32, 64, np.float16))
+    x = to_dev(features(520, coords.shape[0], c_in, np.float16))
+    w = to_dev(conv_weights(521, K ** 3, c_in, 64, np.float16))
     F = ts.ts_gather(x, kmap)
     G = ts.ts_grouped_matmul(F, x if centre >= 0 else None, w, kmap)
     for eps, S in [(-1.0, 0), (0.0, 0), (0.0, 1 << 40), (0.3, 1 << 40), (0.5, int(np.median(sizes))), (1.0, 1 << 40), (1.0, 0)]:
