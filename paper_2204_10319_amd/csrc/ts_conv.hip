@@ -368,8 +368,9 @@ struct RowStore {
 // ---- fused output-stationary kernel, fp16 -----------------------------------------------------------------
 // D[co][m] += Wt[co][ci] * X[m][ci] with v_mfma_f32_16x16x32_f16.  A workgroup of four waves owns 128 output rows and
 // 16 NCO output channels, a wave RB blocks of 16 rows and CB of 16 channels of them; a stage is one (offset, 32 KS
-// channels), with HALF also the 32 channels that are left over at the end of a row.  The accumulators stay in registers across all stages; rows of an output are added in offset order whatever
-// the tile holds, so results do not depend on how rows are grouped.
+// channels), with HALF also the 32 channels that are left over at the end of a row.  The accumulators stay in registers
+// across all stages; rows of an output are added in offset order whatever the tile holds, so results do not depend on how
+// rows are grouped.
 //
 // What bounds it, and the layout that follows (MI355X, measured):
 //  - A vector load costs the address unit 16 cycles per KiB when neighbouring lanes read neighbouring bytes (31 TB/s out of
@@ -477,6 +478,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T
     const u32x4 xrsrc = lds_source(X, x_bytes), xrsrc2 = lds_source(TWO ? X2 : X, TWO ? x2_bytes : x_bytes);
     const __amdgpu_buffer_rsrc_t wrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x4 *>(Wf), 0, w_bytes, 0x00020000);
     const int row_bytes = cin1 * 2, row_bytes2 = (cin - cin1) * 2;
+    constexpr bool BY_STEP = KS != 2 || HALF;   // weights: 32 channels of every output block together, else 64
     const int nch1 = (cin1 + 63) / 64, nch = HALF ? nch1 + (cin - cin1 + 63) / 64 : nk / KS;   // stages per offset, with HALF those of X first
 
     // The neighbour table's rows of a tile lie in LDS as they do in memory, 1 << row_shift units of 16 bytes each, unit c of
@@ -596,42 +598,49 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T
             }
         };
         uint32_t met = 0;    // the row blocks of the stage being multiplied
+        bool half = false;   // HALF: it is the last 32 channels of a row
         auto issue = [&](u32x4 (&a)[CB][KS], int rows) __attribute__((always_inline)) {
             met = (uint32_t)__builtin_amdgcn_readlane((int)blocks, in);
-            const bool of_x2 = TWO && HALF && ich >= nch1;
-            const int c0 = (of_x2 ? ich - nch1 : ich) * (KS * 32);   // first input channel of the stage, HALF: within its part
-            const int step = HALF ? (of_x2 ? cin1 : 0) + c0 : 0;
+            // Which part the stage lies in, and where there, is settled once for all its loads, in scalar registers: asked load
+            // by load, a lone workgroup's stage took 0.09 us longer ((64, 64) -> 64 on 4 k scattered points 32.4 -> 28.6 us).
+            const int stage0 = ich * (KS * 32);
+            const bool of_x2 = TWO && (HALF ? ich >= nch1 : stage0 >= cin1);
+            const int c0 = HALF ? (of_x2 ? ich - nch1 : ich) * 64 : of_x2 ? stage0 - cin1 : stage0;   // its first channel, within the part
+            const u32x4 src = of_x2 ? xrsrc2 : xrsrc;
+            const int src_row = of_x2 ? row_bytes2 : row_bytes;
             // The last 32 channels of a row: of the other half of the stage there are neither weights nor rows, and what is
             // read beyond a buffer is zero.
-            const int beyond = HALF && c0 + 32 == (of_x2 ? cin - cin1 : cin1) ? kNoRow : 0;
-            const int base = HALF ? ((in * nk + step / 32) * cblocks + cb0) * 1024 : ((in * nch + ich) * cblocks + cb0) * (KS * 1024);
-            const int next_cb = HALF ? 1024 : KS * 1024, next_ks = HALF ? cblocks * 1024 : 1024;
+            half = HALF && c0 * 2 + 64 == src_row;
+            const int beyond = half ? kNoRow : 0;
+            const int step = ((of_x2 ? cin1 : 0) + c0) >> 5;
+            const int base = BY_STEP ? ((in * nk + step) * cblocks + cb0) * 1024 : ((in * nch + ich) * cblocks + cb0) * (KS * 1024);
+            const int next_cb = BY_STEP ? 1024 : KS * 1024, next_ks = BY_STEP ? cblocks * 1024 : 1024;
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                 for (int ks = 0; ks < KS; ++ks)
                     a[cb][ks] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, HALF && ks ? lane * 16 | beyond : lane * 16, base + cb * next_cb + ks * next_ks, 0);
+            if (TWO && !HALF && !of_x2 && stage0 + KS * 32 > cin1) {   // the first channels of the stage from X, the others from X2
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
-                if (met >> (wave * 2 + h) & 1u) {
+                for (int h = 0; h < 2; ++h)
+                    if (met >> (wave * 2 + h) & 1u) {
 #pragma unroll
-                    for (int i = 0; i < KS; ++i) {
-                        u32x4 *dst = xrow + rows + (wave * 2 + h) * (16 * UN) + i * 64;
-                        const int32_t j = jn[h][i];
-                        if (HALF) {
-                            if (of_x2) load_to_lds(xrsrc2, dst, (j * row_bytes2 + fetch_at[i]) | (second[i] & beyond), c0 * 2);
-                            else load_to_lds(xrsrc, dst, ((TWO ? j * row_bytes : j) + fetch_at[i]) | (second[i] & beyond), c0 * 2);
-                        } else if (!TWO) {
-                            load_to_lds(xrsrc, dst, j + fetch_at[i], c0 * 2);
-                        } else if (c0 + KS * 32 <= cin1) {
-                            load_to_lds(xrsrc, dst, j * row_bytes + fetch_at[i], c0 * 2);
-                        } else if (c0 >= cin1) {
-                            load_to_lds(xrsrc2, dst, j * row_bytes2 + fetch_at[i], (c0 - cin1) * 2);
-                        } else {   // the first channels of the stage from X, the others from X2
+                        for (int i = 0; i < KS; ++i) {
+                            u32x4 *dst = xrow + rows + (wave * 2 + h) * (16 * UN) + i * 64;
+                            const int32_t j = jn[h][i];
                             if (c0 * 2 + fetch_at[i] < row_bytes) load_to_lds(xrsrc, dst, j * row_bytes + fetch_at[i], c0 * 2);
                             else load_to_lds(xrsrc2, dst, j * row_bytes2 + (c0 * 2 + fetch_at[i] - row_bytes), 0);
                         }
                     }
+                return;
+            }
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (met >> (wave * 2 + h) & 1u) {
+#pragma unroll
+                    for (int i = 0; i < KS; ++i)
+                        load_to_lds(src, xrow + rows + (wave * 2 + h) * (16 * UN) + i * 64,
+                                    ((TWO ? jn[h][i] * src_row : jn[h][i]) + fetch_at[i]) | (HALF ? second[i] & beyond : 0), c0 * 2);
                 }
         };
         u32x4 a0[CB][KS], a1[CB][KS];
@@ -641,6 +650,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T
             __builtin_amdgcn_s_barrier();           // everybody's; and everybody has read the rows of the stage before
             asm volatile("" ::: "memory");
             const uint32_t now = met >> (wr * RB);
+            const bool one_step = half;
             if (s + 1 < nstage) {
                 issue(a_next, rows_next);
                 advance();
@@ -661,6 +671,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(T
                     if (now >> (r0 + q) & 1u) {
 #pragma unroll
                         for (int ks = 0; ks < KS; ++ks) {
+                            if (HALF && ks && one_step) continue;
                             half8v bv;
                             __builtin_memcpy(&bv, &b[q][ks], 16);
 #pragma unroll
@@ -907,7 +918,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         int idx = threadIdx.x + v * kThreads;
         if (SLAB % kThreads != 0) idx = idx < SLAB ? idx : SLAB - 1;   // surplus threads repeat the last vector
         wslot[v] = idx;
-        wlane[v] = idx * 16;
+        wlane[v] = KSTEPS == 3 ? (((idx >> 6) % KSTEPS * cblocks + (idx >> 6) / KSTEPS) * 64 + (idx & 63)) * 16 : idx * 16;
     }
     uint32_t it_rem = mask ? mask : 1u;   // offsets not issued yet; the lowest set bit is the one being issued
     int it_ch = 0;                        // its chunk
@@ -931,7 +942,7 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(N
         }
         pj0 = lds_j[__builtin_ctz(it_rem)][r0];
         pj1 = lds_j[__builtin_ctz(it_rem)][r1];
-        const int wsoff = ((n * nchunks + ch) * cblocks + cb0) * (KSTEPS * 1024);
+        const int wsoff = KSTEPS == 3 ? ((n * nchunks + ch) * KSTEPS * cblocks + cb0) * 1024 : ((n * nchunks + ch) * cblocks + cb0) * (KSTEPS * 1024);
 #pragma unroll
         for (int v = 0; v < WV; ++v) wreg[d][v] = __builtin_amdgcn_raw_buffer_load_b128(wrsrc, wlane[v], wsoff, 0);
         xlive[d] = real && __ballot(j0 >= 0 || j1 >= 0) != 0;   // false: none of the wave's rows has this offset
@@ -1610,8 +1621,9 @@ struct ts_weights {
 
 namespace {
 
-// 32-channel operand steps that stand together in the weights of k_conv_tile: what one of its stages takes.
-inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : cin_pad % 96 == 0 ? 3 : 1; }
+// 32-channel operand steps that stand together in the weights of k_conv_tile: the whole stage where every stage takes 64
+// channels, else one, from which stages of any length are put together.
+inline int tile_ksteps(int cin_pad) { return cin_pad % 64 == 0 ? 2 : 1; }
 
 struct Prepared {
     const void *x;    // features, rows padded to cin_pad channels
@@ -1879,7 +1891,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     typedef _Float16 T;
     const int cin = feats->cols, cout = out->cols;
     const int cin_pad = (cin + 31) / 32 * 32;
-    const int ksteps = tile_ksteps(cin_pad);
+    const int wsteps = tile_ksteps(cin_pad), ksteps = cin_pad % 64 != 0 && cin_pad % 96 == 0 ? 3 : wsteps;
     // the kernel addresses features and weights with 31-bit byte offsets
     if ((size_t)kmap->n_in * cin_pad * 2 >= (1ull << 31) || (size_t)kmap->K3 * cin_pad * cout * 2 >= (1ull << 31)) {
         if (ep.any()) return fail(TS_ERR_UNSUPPORTED, "feature matrix of 2 GiB or more: call ts_sparse_conv and ts_bias_act");
@@ -1893,7 +1905,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         T *buf = static_cast<T *>(wbuf ? wbuf : scratch(2, wn * sizeof(T)));
         if (!buf) return last_fail_code();
         TS_LAUNCH("k_pack_weights", k_pack_weights_tile, dim3(blocks_for((int64_t)wn, kThreads)), dim3(kThreads),
-                  static_cast<const T *>(weights->data), buf, kmap->K3, cin, cin_pad, cout, ksteps);
+                  static_cast<const T *>(weights->data), buf, kmap->K3, cin, cin_pad, cout, wsteps);
         wf = buf;
     }
     const T *x = static_cast<const T *>(feats->data);
@@ -1929,29 +1941,46 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             nco = c;
             break;
         }
-    // Launches of few workgroups that k_conv_direct does faster (us, k_conv_tile and k_conv_direct; layers after one halving
-    // of a scan):
-    //  - a two-part input with a part that is no multiple of 64 channels: stages of two sources, or half empty ones.  Up to
-    //    two tiles a CU: (96, 32) -> 96 on 2 k rows 29.7 and 23.0, on 32 k 47.3 and 38.8, on 60 k 46.6 and 38.6, but on 120 k
-    //    57.4 and 63.9; (96, 64) -> 96 on 16 k 51.5 and 48.7, on 60 k 58.5 and 54.1, on 120 k 69.0 and 84.9
-    //  - stages of 96 channels, up to a tile a CU: 96 -> 64 on 4 k rows 16.8 and 15.7, on 32 k 23.5 and 21.2, on 60 k 24.1 and 29.8;
-    //    96 -> 96 on 8 k 18.0 and 16.5, on 32 k 34.9 and 32.8, on 60 k 29.1 and 35.5
-    //  - stages of 32, up to two tiles a CU: 32 -> 96 on 4 k rows 11.9 and 11.2, on 60 k 20.3 and 19.3, on 120 k 27.7 and 32.2
-    //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 16 k rows
-    //    29.9 and 27.7, 128 -> 64 on 32 k 29.0 and 27.7; fewer and more are even or the other way round: 128 -> 128 on 2 k 20.2 and
-    //    21.2, on 24 k 35.0 and 35.4; so are the few stages of 1x1x1 maps ((128, 128) -> 128 on 22 k rows 15.2 and 15.8)
+    // Layers that k_conv_direct does faster (us, k_conv_tile and k_conv_direct, on scattered points, surfaces, a scan and a scan
+    // after one halving; the lines lie where most of these four change sides).  It keeps two stages in flight and issues less
+    // for each, which decides while a CU has a workgroup or two; k_conv_tile skips the blocks that do not meet an offset, which
+    // is why scattered points change sides last.  On 1x1x1 and 2x2x2 maps, whose tiles walk few stages, k_conv_tile is even
+    // or ahead.
+    //  - a two-part input with a part that is no multiple of 64 channels, so that a stage has two sources: up to two tiles a CU,
+    //    (96, 32) -> 96 on 8 k rows 33 26, 31 24, 26 22, 32 26, on 65 k 48 40, 45 42, 43 37, 45 40, on 98 k 51 55, 51 56, 49 52,
+    //    48 53; with one stage an offset up to three, (32, 32) -> 32 on 98 k 26 23, 26 28, 26 23, 24 24, on 150 k 32 33, 38 40,
+    //    28 32, 32 35
+    //  - stages of 96 channels: up to a tile a CU, 96 -> 96 on 4 k rows 19 17, 16 15, 15 14, 12 11, on 32 k 45 32, 34 32, 28 31,
+    //    38 35, on 40 k 30 30, 31 33, 28 27, 29 30, on 98 k 36 43, 38 48, 35 43, 37 44
+    //  - stages of 64 and a half empty one: between one tile a CU and 1.75, 160 -> 64 on 16 k rows 41 37, 35 36, 30 33, 37 37, on
+    //    40 k 50 43, 49 47, 46 41, 46 43, on 65 k 51 45, 45 48, 44 42, 43 45.  Not in two parts: (96, 64) -> 96 on 8 k 38 44,
+    //    37 41, 31 36, 38 43, on 32 k 60 60, 50 56, 48 53, 58 60
+    //  - stages of 32: up to two tiles a CU, 32 -> 96 on 4 k rows 13.0 12.3, 11.4 11.2, 10.8 10.5, 9.2 8.8, on 65 k 21 20, 20 21,
+    //    19 20, 21 21, on 98 k 25 25, 24 28, 25 25, 24 26
+    //  - stages of 64 of two sources in turn: up to 1.5 workgroups a CU, (64, 64) -> 64 on 16 k rows 30 27, 29 26, 25 24, 29 26, on
+    //    40 k 36 32, 36 36, 34 31, 34 34, on 65 k 39 34, 35 37, 33 33, 34 36
+    //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 8 k rows
+    //    24 24, 23 24, 20 22, 24 23, on 16 k 32 29, 29 29, 25 26, 29 29, on 20 k 37 35, 31 36, 27 29, 32 34
+    const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32;
     const int64_t wgs = kmap->n_tiles * (cblocks / nco);
-    const bool direct = sec.x2 && (sec.cin1 % 64 != 0 || (cin - sec.cin1) % 64 != 0) && ksteps != 3 ? kmap->n_tiles <= 2 * cus
-                        : ksteps == 3                                                               ? kmap->n_tiles <= cus
-                        : cin_pad == 32                                                             ? kmap->n_tiles <= 2 * cus
-                                                                    : ksteps == 2 && cin_pad >= 128 && kmap->K3 > 8 && 2 * wgs > cus && wgs <= cus;
+    const bool direct = split           ? kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus
+                        : kmap->K3 <= 8 ? false
+                        : ksteps == 3   ? kmap->n_tiles <= cus
+                        : half_empty    ? !sec.x2 && nco <= 4 && kmap->n_tiles > cus && 4 * kmap->n_tiles <= 7 * cus
+                        : cin_pad == 32 ? kmap->n_tiles <= 2 * cus
+                        : nco > 4       ? false
+                        : sec.x2        ? 2 * wgs <= 3 * cus
+                                        : cin_pad >= 128 && 2 * wgs > cus && wgs <= cus;
+    // Rows in order of their offset leave a 2x2x2 map's tile few stages, for which three workgroups a CU beat the two that stages
+    // of 96 channels leave room for: 96 -> 96 going up to 150 k scattered points 27.6 and, by 32 channels a stage, 25.3; to
+    // 300 k 44.4 and 39.2.
+    const bool by_32 = ksteps == 3 && !sec.x2 && kmap->K3 == 8 && kmap->transposed && kmap->n_tiles > 2 * cus;
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_direct<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);   \
-            else if (ksteps == 3) launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \
-            else launch_conv_direct<N, 1, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
-        } else if (ksteps == 2) launch_conv_direct<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+            else launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
+        } else if (ksteps == 2) launch_conv_direct<(N <= 4 ? N : 4), 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_direct<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec);                  \
     }
@@ -1960,12 +1989,11 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
 #define TS_TILE_CASE(N)                                                                            \
     if (!direct && nco == N) {                                                                     \
         if (sec.x2) {                                                                              \
-            if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);    \
-            else if (ksteps == 3) launch_conv_tile<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec); \
+            if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);     \
             else launch_conv_tile<N, 2, true, true>(x, wf, kmap, out, cin_pad, ep, sec);          \
         } else if (ksteps == 2) launch_conv_tile<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
-        else if (ksteps == 3) launch_conv_tile<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec);  \
-        else if (cin_pad == 32) launch_conv_tile<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else if (ksteps == 3 && !by_32) launch_conv_tile<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else if (cin_pad == 32 || by_32) launch_conv_tile<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_tile<N, 2, false, true>(x, wf, kmap, out, cin_pad, ep, sec);             \
     }
     TS_TILE_CASE(8) TS_TILE_CASE(6) TS_TILE_CASE(4) TS_TILE_CASE(2)

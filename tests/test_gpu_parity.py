@@ -1303,7 +1303,9 @@ def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
 
 
 @pytest.mark.parametrize("n,parts,c_out", [(129, (96,), 64), (32768, (96,), 64), (32769, (96,), 64), (129, (32,), 96), (66000, (32,), 96), (16000, (128,), 128),
-                                           (17, (96, 32), 96), (129, (96, 64), 96), (2000, (64, 32), 96), (40000, (64, 96), 32), (66000, (96, 32), 96), (66000, (96, 64), 96)])
+                                           (17, (96, 32), 96), (129, (96, 64), 96), (2000, (64, 32), 96), (40000, (64, 96), 32), (66000, (96, 32), 96), (66000, (96, 64), 96),
+                                           (32769, (160,), 64), (57344, (160,), 64), (57345, (160,), 64), (33000, (64, 32), 96), (32768, (64, 96), 64),
+                                           (49152, (64, 64), 64), (49153, (64, 64), 64), (98304, (32, 32), 32), (98305, (32, 32), 32), (32768, (128,), 64), (32769, (128,), 64)])
 def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out):
     """Few tiles and many, of layers whose kernel goes by their number; an input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
@@ -1317,6 +1319,16 @@ def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, part
         got = ts.ts_sparse_conv_prepared2(to_dev(x_h[:, :parts[0]].copy()), to_dev(x_h[:, parts[0]:].copy()), w, kmap)
         assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap), got)
     check_features(got, oracle_conv(coords, x_h, w_h, 3, 1, False), torch.float16, f"{n}: {parts}->{c_out}")
+
+
+@pytest.mark.parametrize("n,c_in", [(65536, 96), (65537, 96), (70001, 96), (65553, 288)])
+def test_layers_up_on_both_sides_of_stages_of_32(n, c_in):
+    """Maps that go up, rows of 96 channels and a multiple of them: whole stages up to two tiles a compute unit, a third of one beyond."""
+    coords = _rand_coords(6200 + n, n, 0, 70, batches=1)
+    up = ts.ts_build_kmap(to_dev(coords), 2, 2).transpose()
+    x_h, w_h = features(6300, up.num_in, c_in, np.float16), conv_weights(6301, 8, c_in, 96, np.float16)
+    got = ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), up, dataflow=ts.TS_DATAFLOW_FUSED)
+    check_features(got, oracle_conv(coords, x_h, w_h, 2, 2, True), torch.float16, f"{n} rows up from {c_in} channels")
 
 
 def test_weights_of_offsets_that_nothing_meets_are_not_multiplied():
