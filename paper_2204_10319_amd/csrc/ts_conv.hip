@@ -2292,15 +2292,15 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 //     (Recorded on a map without pair lists, which need memory, such a layer goes by the typical number.)
 // (A build that found bad input, or whose sizes cannot be had now, leaves the fused kernel, which needs none.)
 // 2x2x2 maps that go up, in fp16 (us, fused and fetched): rows of one offset stand together, so that a tile walks little more
-// than one offset, from about a tile per offset on: 128 -> 64 on 2.7 k rows 7.1, 8.4, on 30 k 9.5, 12.9; 256 -> 256 on
-// 2.7 k 9.2, 11.8, on 8 k 11.2, 15.4, on 32 k 19.0, 28.1.
+// than one offset, and the two dataflows give the same bits: 64 -> 64 on 300 rows 8.4, 11.1, on 20 k 9.4, 12.3; 256 -> 256 on
+// 1 k 13.0, 14.1, on 20 k 16.8, 24.1, but on 300, where three tiles walk 32 stages each, 14.8, 12.4; 160 -> 64 11.7, 10.9.
 // Maps that go down share the line of the others.  Drawn at 0.9 times the pairs' bytes it gained on wide outputs (64 -> 128
 // from 16 k scattered points 9.9, 12.8, 256 -> 256 from 60 k points of surfaces 27.2, 33.7) but cost more where C_in is the larger one, whose
 // stages a tile walks one after the other: 128 -> 64 from 16 k scattered points 11.6, 9.8, 256 -> 64 from 24 k points of a scan 20.2, 11.9,
 // 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
-    if (elem == 2 && kmap->K3 == 8 && kmap->s == 2 && kmap->transposed && kmap->d_window_perm && kmap->n_out >= 8 * kTileRows) return false;
+    if (elem == 2 && kmap->K3 == 8 && kmap->s == 2 && kmap->transposed && (cin <= 128 || kmap->n_out >= 4 * kTileRows)) return false;
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
     const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
     const double typical = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;

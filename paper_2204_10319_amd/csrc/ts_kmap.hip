@@ -1455,47 +1455,20 @@ __global__ void __launch_bounds__(kThreads) k_down_scatter(const uint64_t *__res
     parent[i] = k;
 }
 
-// The transposed map of such a map, in one pass over the fine points: a row has the one entry (offset of the
-// point, its coarse cell).  Keys of both point sets are copied and the tile counters cleared on the way.
-// (By scattering the forward rows into cleared rows and reading those again it took five launches.)
-// perm, if not NULL: the row order for the output-stationary kernel, made on the way.  A tile of 128 neighbouring rows
-// meets all eight offsets, each for an eighth of its rows; inside a window of 2048 rows those of one offset stand
-// together, and a tile meets 1.4; a layer's stages fall by that much (128 -> 64 channels on 153 k rows of a scan 29.9 -> 23.1 us,
-// on 100 k scattered ones 33.4 -> 23.3; 128 -> 96 on 64 k 21.8 -> 17.0).  Ranks come from ballots: the order is the same every
-// time and costs the pass 1 to 2 us.
+// A row order for the output-stationary kernel on 2x2x2 maps that go up, where a row has one entry: a tile of 128
+// neighbouring rows meets all eight offsets, each for an eighth of its rows; inside a window of 2048 rows those of one offset
+// stand together, and a tile meets 1.4; a layer's stages fall by that much (128 -> 64 channels on 153 k rows of a scan 29.9 ->
+// 23.1 us, on 100 k scattered ones 33.4 -> 23.3; 128 -> 96 on 64 k 21.8 -> 17.0).  Ranks come from ballots: the order is the
+// same every time.  A workgroup takes a window, each thread kUpPer rows of it, own[r] being the offset of row
+// base + r * kUpThreads + threadIdx.x: 0 to 7, 8 for a row without an entry, -1 past the last row.
 constexpr int kUpThreads = 1024, kUpPer = 2, kUpRows = kUpThreads * kUpPer;
-__global__ void __launch_bounds__(kUpThreads) k_up_rows(const uint64_t *__restrict__ fine, const int32_t *__restrict__ parent, int64_t n,
-                                                        const uint64_t *__restrict__ coarse, int64_t n_coarse,
-                                                        uint64_t *__restrict__ fine_copy, uint64_t *__restrict__ coarse_copy,
-                                                        int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
-                                                        int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
-                                                        int64_t n_blocks, uint4 *__restrict__ sched, int32_t *__restrict__ perm) {
-    constexpr int STRIDE = nbr_stride(8), WAVES = kUpThreads / 64, CHUNKS = WAVES * kUpPer, CLASSES = 9;   // offsets, and none
+__device__ __forceinline__ void group_by_offset(const int (&own)[kUpPer], int64_t base, int64_t n, int32_t *__restrict__ perm) {
+    constexpr int WAVES = kUpThreads / 64, CHUNKS = WAVES * kUpPer, CLASSES = 9;   // offsets, and none
     __shared__ int32_t before[CLASSES][CHUNKS], total[CLASSES];   // rows of a class in the chunks of 64 rows before
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int64_t base = (int64_t)blockIdx.x * kUpRows;
-    for (int64_t v = (int64_t)blockIdx.x * kUpThreads + threadIdx.x; v < kMaxSchedSlices * kSchedWords / 4; v += (int64_t)gridDim.x * kUpThreads)
-        sched[v] = make_uint4(0, 0, 0, 0);
-    int own[kUpPer], rank[kUpPer];   // the row's class, and how many of its chunk stand before it there
+    int rank[kUpPer];   // how many of the row's chunk stand before it in its class
 #pragma unroll
     for (int r = 0; r < kUpPer; ++r) {
-        const int64_t i = base + r * kUpThreads + threadIdx.x;
-        if (i < n_coarse) coarse_copy[i] = coarse[i];   // (never more coarse points than fine ones)
-        uint32_t mask = 0;
-        if (i < n) {
-            const uint64_t key = fine[i];
-            const int32_t k = parent[i];
-            const int q = down_offset(key);
-            fine_copy[i] = key;
-            if (k >= 0) mask = 1u << q;
-            int4 *row = reinterpret_cast<int4 *>(nbr + i * STRIDE);
-            const int none = -1;
-            row[0] = make_int4(q == 0 ? k : none, q == 1 ? k : none, q == 2 ? k : none, q == 3 ? k : none);
-            row[1] = make_int4(q == 4 ? k : none, q == 5 ? k : none, q == 6 ? k : none, q == 7 ? k : none);
-            row[2] = make_int4((int)mask, none, none, none);
-        }
-        finish_rows<8>(mask, colbits, colcnt, wavemask, n_blocks, base / 64 + r * WAVES + wave);
-        own[r] = i >= n ? -1 : mask ? __builtin_ctz(mask) : 8;
         rank[r] = 0;
 #pragma unroll
         for (int c = 0; c < CLASSES; ++c) {
@@ -1504,7 +1477,6 @@ __global__ void __launch_bounds__(kUpThreads) k_up_rows(const uint64_t *__restri
             if (lane == c) before[c][r * WAVES + wave] = __popcll(of_c);
         }
     }
-    if (!perm) return;
     __syncthreads();
     if (wave < CLASSES) {
         const int rows = lane < CHUNKS ? before[wave][lane] : 0;
@@ -1528,6 +1500,62 @@ __global__ void __launch_bounds__(kUpThreads) k_up_rows(const uint64_t *__restri
             perm[i] = -1;
         }
     }
+}
+
+// That order for a map whose rows are there already (2.9 us for 153 k rows).
+__global__ void __launch_bounds__(kUpThreads) k_up_order(const int32_t *__restrict__ nbr, int64_t n, int32_t *__restrict__ perm) {
+    const int64_t base = (int64_t)blockIdx.x * kUpRows;
+    int own[kUpPer];
+#pragma unroll
+    for (int r = 0; r < kUpPer; ++r) {
+        const int64_t i = base + r * kUpThreads + threadIdx.x;
+        own[r] = -1;
+        if (i < n) {
+            const int4 *row = reinterpret_cast<const int4 *>(nbr + i * nbr_stride(8));
+            const int4 a = row[0], b = row[1];
+            own[r] = a.x >= 0 ? 0 : a.y >= 0 ? 1 : a.z >= 0 ? 2 : a.w >= 0 ? 3 : b.x >= 0 ? 4 : b.y >= 0 ? 5 : b.z >= 0 ? 6 : b.w >= 0 ? 7 : 8;
+        }
+    }
+    group_by_offset(own, base, n, perm);
+}
+
+// The transposed map of such a map, in one pass over the fine points: a row has the one entry (offset of the
+// point, its coarse cell).  Keys of both point sets are copied and the tile counters cleared on the way.
+// (By scattering the forward rows into cleared rows and reading those again it took five launches.)
+// perm, if not NULL: the rows' order, which costs the pass 1 to 2 us.
+__global__ void __launch_bounds__(kUpThreads) k_up_rows(const uint64_t *__restrict__ fine, const int32_t *__restrict__ parent, int64_t n,
+                                                        const uint64_t *__restrict__ coarse, int64_t n_coarse,
+                                                        uint64_t *__restrict__ fine_copy, uint64_t *__restrict__ coarse_copy,
+                                                        int32_t *__restrict__ nbr, uint64_t *__restrict__ colbits,
+                                                        int32_t *__restrict__ colcnt, uint32_t *__restrict__ wavemask,
+                                                        int64_t n_blocks, uint4 *__restrict__ sched, int32_t *__restrict__ perm) {
+    constexpr int STRIDE = nbr_stride(8);
+    const int wave = threadIdx.x >> 6;
+    const int64_t base = (int64_t)blockIdx.x * kUpRows;
+    for (int64_t v = (int64_t)blockIdx.x * kUpThreads + threadIdx.x; v < kMaxSchedSlices * kSchedWords / 4; v += (int64_t)gridDim.x * kUpThreads)
+        sched[v] = make_uint4(0, 0, 0, 0);
+    int own[kUpPer];
+#pragma unroll
+    for (int r = 0; r < kUpPer; ++r) {
+        const int64_t i = base + r * kUpThreads + threadIdx.x;
+        if (i < n_coarse) coarse_copy[i] = coarse[i];   // (never more coarse points than fine ones)
+        uint32_t mask = 0;
+        if (i < n) {
+            const uint64_t key = fine[i];
+            const int32_t k = parent[i];
+            const int q = down_offset(key);
+            fine_copy[i] = key;
+            if (k >= 0) mask = 1u << q;
+            int4 *row = reinterpret_cast<int4 *>(nbr + i * STRIDE);
+            const int none = -1;
+            row[0] = make_int4(q == 0 ? k : none, q == 1 ? k : none, q == 2 ? k : none, q == 3 ? k : none);
+            row[1] = make_int4(q == 4 ? k : none, q == 5 ? k : none, q == 6 ? k : none, q == 7 ? k : none);
+            row[2] = make_int4((int)mask, none, none, none);
+        }
+        finish_rows<8>(mask, colbits, colcnt, wavemask, n_blocks, base / 64 + r * (kUpThreads / 64) + wave);
+        own[r] = i >= n ? -1 : mask ? __builtin_ctz(mask) : 8;
+    }
+    if (perm) group_by_offset(own, base, n, perm);
 }
 
 // Block n: exclusive scan in place of the counts col[n][*] -> col[n][b] = pairs of offset n in the 64-row
@@ -2080,6 +2108,21 @@ void launch_rows(const ts_kmap *m) {
 #undef TS_ROWS
 }
 
+// Room for the row order of a 2x2x2 map that goes up (see group_by_offset), which is written on the stream that its rows are
+// written on: whoever may read the rows may read it.  Without memory for it the rows keep their order.
+void make_up_order(ts_kmap *m) {
+    if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) m->d_window_perm = nullptr;
+    m->window_settled = true;
+}
+
+// ... of a map whose rows have been written.
+void order_up(ts_kmap *m) {
+    if (m->K3 != 8 || m->s != 2 || !m->transposed || m->n_out == 0) return;
+    make_up_order(m);
+    if (m->d_window_perm)
+        TS_LAUNCH("k_up_order", k_up_order, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), m->d_nbr, m->n_out, m->d_window_perm);
+}
+
 // Counts of the 64-row blocks -> ranks, sizes (into the status words at `status`) and tile order.
 void launch_scan(const ts_kmap *m, int32_t *status) {
     TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), m->d_colbase, m->n_blocks, status, m->K3, m->d_wavemask,
@@ -2468,6 +2511,7 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
             }
         }
         launch_rows(m);
+        order_up(m);
         *reports = true;
         return finish(m, slot, wait);
     }
@@ -2497,6 +2541,7 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
         else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
     }
     TS_TRY(search(m, table, d_status));
+    order_up(m);
     *reports = true;
     return finish(m, slot, wait);
 }
@@ -2608,8 +2653,7 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         int32_t *sizes;   // written by the scan, known already
         TS_TRY(tmp.get(&sizes, ST_WORDS));
         TS_TRY(alloc_outputs(m, nullptr));
-        if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) m->d_window_perm = nullptr;   // the natural order then
-        m->window_settled = true;   // whoever may read the map's rows may read their order
+        make_up_order(m);
         TS_LAUNCH("k_up_rows", k_up_rows, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), f->d_in_keys, f->d_parent, m->n_out,
                   f->d_out_keys, m->n_in, m->d_out_keys, m->d_in_keys, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks,
                   reinterpret_cast<uint4 *>(m->d_sched), m->d_window_perm);
@@ -2632,6 +2676,7 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         else TS_LAUNCH("k_transpose", k_transpose<1>, gf, block, f->d_nbr, f->n_out, m->d_nbr);
     }
     launch_rows(m);
+    order_up(m);
     launch_scan(m, sizes);
     TS_HIP(hipGetLastError());
     return TS_OK;

@@ -1382,10 +1382,50 @@ def test_rows_of_a_transposed_map_grouped_by_offset(n, dtype):
     other.synchronize()
 
 
+def _kernels_of(fn):
+    """Names of the kernels that a call launches, and what it returns."""
+    ts.ts_profile_enable(True)
+    try:
+        ts.ts_profile_read()
+        result = fn()
+        return set(ts.ts_profile_read()), result
+    finally:
+        ts.ts_profile_enable(False)
+
+
+@pytest.mark.parametrize("way", ["measured box", "stated box", "hash", "boundary", "transposed from a sorted map"])
+@pytest.mark.parametrize("n,c_in", [(1, 64), (129, 32), (511, 160), (512, 160), (2049, 256), (9000, 64)])
+def test_maps_that_go_up_are_alike_however_they_are_made(n, c_in, way):
+    """Rows of 2x2x2 maps that go up are grouped by offset in every build; which dataflow a layer on them takes goes by
+    sizes alone, and the bits are one map's whichever way it came."""
+    coords = _rand_coords(5750 + n, n, 0, 30, batches=2)
+    x_h, w_h = features(5850, n, c_in, np.float16), conv_weights(5851, 8, c_in, 96, np.float16)
+    derived = ts.ts_build_kmap(to_dev(coords), 2, 2).transpose()
+    x, w = to_dev(x_h[:derived.num_in]), to_dev(w_h)
+    kernels, want = _kernels_of(lambda: ts.ts_sparse_conv(x, w, derived))
+    assert ("k_conv_tile" in kernels) == (c_in <= 128 or n >= 512)
+    check_features(want, oracle_conv(coords, x_h[:derived.num_in], w_h, 2, 2, True), torch.float16, f"{n} rows up")
+
+    def build():
+        if way == "transposed from a sorted map":
+            return ts.ts_build_kmap(to_dev(coords), 2, 2, search=ts.TS_SEARCH_HASH).transpose()
+        kw = dict(grid=grid_of(coords)) if way == "stated box" else dict(search=ts.TS_SEARCH_HASH) if way == "hash" else dict(boundary=(64, 64, 64)) if way == "boundary" else {}
+        return ts.ts_build_kmap(to_dev(coords), 2, 2, True, **kw)
+
+    kernels_built, own = _kernels_of(build)
+    assert "k_up_order" in kernels_built
+    got_kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(x, w, own))
+    assert got_kernels == kernels and torch.equal(got, want)
+    assert torch.equal(ts.ts_sparse_conv(x, w, own, dataflow=ts.TS_DATAFLOW_FUSED), want)
+    assert torch.equal(ts.ts_sparse_conv(x, w, own, dataflow=ts.TS_DATAFLOW_FETCH), want)
+    x32, w32 = to_dev(x_h[:derived.num_in].astype(np.float32)), to_dev(w_h.astype(np.float32))
+    check_features(ts.ts_sparse_conv(x32, w32, own, dataflow=ts.TS_DATAFLOW_FUSED),
+                   oracle_conv(coords, x_h[:derived.num_in].astype(np.float32), w_h.astype(np.float32), 2, 2, True), torch.float32, f"{n} rows up")
+
+
 @pytest.mark.parametrize("n,c", [(1023, 128), (1024, 128), (3000, 256)])
 def test_dataflow_of_maps_by_two(n, c):
-    """Going up, fp16 layers of a tile per offset and more take the fused kernel however wide they are; both ways against
-    the oracle."""
+    """Going up and down, against the oracle; going up the dataflows give the same bits."""
     coords = _rand_coords(5900 + n, n, -9, 14, batches=1)
     down = ts.ts_build_kmap(to_dev(coords), 2, 2)
     w_h = conv_weights(5901, 8, c, c, np.float16)
@@ -1394,7 +1434,7 @@ def test_dataflow_of_maps_by_two(n, c):
         x_h = features(5902, kmap.num_in, c, np.float16)
         got = ts.ts_sparse_conv(to_dev(x_h), w, kmap)
         check_features(got, oracle_conv(coords, x_h, w_h, 2, 2, transposed), torch.float16, f"{n} rows, {c} channels, up {transposed}")
-        if transposed and n >= 1024:
+        if transposed:
             assert torch.equal(ts.ts_sparse_conv(to_dev(x_h), w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), got)
 
 
