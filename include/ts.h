@@ -107,9 +107,9 @@ typedef struct ts_tensor {
 
 /*
  * Opaque, device-resident kernel map (Sec. 2.1: the maps M plus P_out).  What it maps never changes; the library
- * adds to it what later calls can use, when it is first wanted: sizes, pair lists, and on large 3x3x3 maps that
- * serve more than one layer an order of the output rows (4 bytes per output; results do not depend on it).  2x2x2 maps
- * that go up are made with theirs.
+ * adds to it what later calls can use, when it is first wanted: sizes, pair lists, and on large 3x3x3 maps, and 2x2x2
+ * maps that go up, an order of the output rows (4 bytes per output; results do not depend on it) once they serve more than
+ * one layer or a wide one.
  */
 typedef struct ts_kmap ts_kmap;
 

@@ -1743,9 +1743,10 @@ inline int compute_units() {
 // Single precision gains more, a pair's work there takes some ten times as long: 153 k LiDAR points, 32 -> 32 channels
 // 63 -> 47 us, 64 -> 64 192 -> 127; 200 k scattered points 120 -> 64, 403 -> 195; 40 k LiDAR points 29 -> 27, 80 -> 71.
 // A map that has served a layer will serve more; one that has not is ordered only for a layer that gains more than
-// the ordering takes (at_once).
+// the ordering takes (at_once).  2x2x2 maps that go up gain at every size (the order takes 4 to 6 us; 64 -> 64 on 4 k rows
+// 8.0 -> 6.2, 128 -> 64 on 16 k 10.4 -> 8.5, 128 -> 128 14.6 -> 9.0, on 150 k of a scan 35 -> 26).
 inline void order_for_layer(const ts_kmap *kmap, bool at_once) {
-    if (kmap->n_tiles > compute_units() && (kmap->uses > 0 || at_once)) order_windows(kmap);
+    if ((kmap->n_tiles > compute_units() || (goes_up_by_two(kmap) && kmap->n_tiles > 1)) && (kmap->uses > 0 || at_once)) order_windows(kmap);
 }
 // Single precision, map and first layer together, with the order and without it (us), by tiles * C_in * C_out, which the
 // gain follows; the ordering itself takes 5 to 9:
@@ -1757,7 +1758,7 @@ inline void order_for_layer(const ts_kmap *kmap, bool at_once) {
 // on a scan, 98 and 83 on surfaces; from 282 on every layer gains.
 inline bool order_at_once(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (elem == 4) return kmap->n_tiles > compute_units() * 17 / 16 && kmap->n_tiles * cin * cout >= 1000000;
-    return kmap->n_tiles > 2 * compute_units() && cin * cout >= 128 * 128;
+    return (kmap->n_tiles > 2 * compute_units() || goes_up_by_two(kmap)) && cin * cout >= 128 * 128;
 }
 
 template <class T>
@@ -1974,7 +1975,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     // Rows in order of their offset leave a 2x2x2 map's tile few stages, for which three workgroups a CU beat the two that stages
     // of 96 channels leave room for: 96 -> 96 going up to 150 k scattered points 27.6 and, by 32 channels a stage, 25.3; to
     // 300 k 44.4 and 39.2.
-    const bool by_32 = ksteps == 3 && !sec.x2 && kmap->K3 == 8 && kmap->transposed && kmap->n_tiles > 2 * cus;
+    const bool by_32 = ksteps == 3 && !sec.x2 && goes_up_by_two(kmap) && kmap->n_tiles > 2 * cus;
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \
@@ -2300,7 +2301,7 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
-    if (elem == 2 && kmap->K3 == 8 && kmap->s == 2 && kmap->transposed && (cin <= 128 || kmap->n_out >= 4 * kTileRows)) return false;
+    if (elem == 2 && goes_up_by_two(kmap) && (cin <= 128 || kmap->n_out >= 4 * kTileRows)) return false;
     const double tile_offsets = kmap->K3 < 20 ? kmap->K3 : 20;
     const double fine = kmap->transposed ? kmap->n_out : kmap->n_in;
     const double typical = kmap->s == 1 ? (kmap->K3 > 1 ? 7.5 : 1.0) * fine : fine * kmap->K3 / 8.0;

@@ -97,7 +97,8 @@ int settle(const struct ::ts_kmap *kmap);
 int prepare(const struct ::ts_kmap *kmap);
 
 // Enqueues the ordering of a map's rows for the output-stationary kernel (d_window_perm).  Without effect, and
-// without an error, where it cannot be done: no bitmasks by row, no memory, a stream that is being captured.
+// without an error, where it cannot be done: neither bitmasks by row nor a 2x2x2 map that goes up, no memory, a stream that is
+// being captured.
 void order_windows(const struct ::ts_kmap *kmap);
 
 // The row order of a map that a layer on the current stream may read, or NULL for the natural one: what
@@ -196,8 +197,8 @@ struct ts_kmap {
     uint32_t *d_wavemask = nullptr;       // [n_blocks] offsets met by any of the block's outputs
     uint32_t *d_rowmask = nullptr;        // [n_out] offsets met by every output, 3x3x3 stride-1 maps searched in blocks (else NULL)
     // The same rows in another order, for the output-stationary kernel (ts::order_windows): inside a window of
-    // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it; maps that
-    // go up from a 2x2x2 map are made with it.
+    // consecutive outputs, rows that meet the same offsets stand together.  NULL until a map is worth it; maps transposed
+    // from a 2x2x2 map are made with it.
     int32_t *d_window_perm = nullptr;     // [n_tiles*kTileRows] position -> output row, -1 = padding
     hipStream_t window_stream = nullptr;  // where that order was enqueued
     bool window_settled = false;          // it is known to be there: other streams may read it
@@ -212,3 +213,8 @@ struct ts_kmap {
     // last workgroup of a launch rearms them).
     int32_t *d_sched = nullptr;           // [kMaxSchedSlices][kSchedWords]
 };
+
+namespace ts {
+// A 2x2x2 map to the finer points: a row has one entry.
+inline bool goes_up_by_two(const ts_kmap *m) { return m->K3 == 8 && m->s == 2 && m->transposed; }
+}  // namespace ts

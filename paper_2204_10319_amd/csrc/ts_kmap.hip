@@ -1502,7 +1502,8 @@ __device__ __forceinline__ void group_by_offset(const int (&own)[kUpPer], int64_
     }
 }
 
-// That order for a map whose rows are there already (2.9 us for 153 k rows).
+// That order for a map that was not transposed from one that goes down and has served a layer, or is about to serve one that
+// gains by it (ts::order_windows).
 __global__ void __launch_bounds__(kUpThreads) k_up_order(const int32_t *__restrict__ nbr, int64_t n, int32_t *__restrict__ perm) {
     const int64_t base = (int64_t)blockIdx.x * kUpRows;
     int own[kUpPer];
@@ -2108,21 +2109,6 @@ void launch_rows(const ts_kmap *m) {
 #undef TS_ROWS
 }
 
-// Room for the row order of a 2x2x2 map that goes up (see group_by_offset), which is written on the stream that its rows are
-// written on: whoever may read the rows may read it.  Without memory for it the rows keep their order.
-void make_up_order(ts_kmap *m) {
-    if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) m->d_window_perm = nullptr;
-    m->window_settled = true;
-}
-
-// ... of a map whose rows have been written.
-void order_up(ts_kmap *m) {
-    if (m->K3 != 8 || m->s != 2 || !m->transposed || m->n_out == 0) return;
-    make_up_order(m);
-    if (m->d_window_perm)
-        TS_LAUNCH("k_up_order", k_up_order, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), m->d_nbr, m->n_out, m->d_window_perm);
-}
-
 // Counts of the 64-row blocks -> ranks, sizes (into the status words at `status`) and tile order.
 void launch_scan(const ts_kmap *m, int32_t *status) {
     TS_LAUNCH("k_scan", k_scan, dim3(m->K3 + 1), dim3(kScanThreads), m->d_colbase, m->n_blocks, status, m->K3, m->d_wavemask,
@@ -2511,7 +2497,6 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
             }
         }
         launch_rows(m);
-        order_up(m);
         *reports = true;
         return finish(m, slot, wait);
     }
@@ -2541,7 +2526,6 @@ int build_strided(Temps &tmp, const int32_t *coords, uint64_t *given, int64_t N,
         else TS_LAUNCH("k_insert", k_insert<Table>, per_coarse, block, coarse, n_coarse, table.t, d_status);
     }
     TS_TRY(search(m, table, d_status));
-    order_up(m);
     *reports = true;
     return finish(m, slot, wait);
 }
@@ -2653,7 +2637,8 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         int32_t *sizes;   // written by the scan, known already
         TS_TRY(tmp.get(&sizes, ST_WORDS));
         TS_TRY(alloc_outputs(m, nullptr));
-        make_up_order(m);
+        if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) m->d_window_perm = nullptr;   // the natural order then
+        m->window_settled = true;   // whoever may read the map's rows may read their order
         TS_LAUNCH("k_up_rows", k_up_rows, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), f->d_in_keys, f->d_parent, m->n_out,
                   f->d_out_keys, m->n_in, m->d_out_keys, m->d_in_keys, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks,
                   reinterpret_cast<uint4 *>(m->d_sched), m->d_window_perm);
@@ -2676,7 +2661,6 @@ int transpose(const ts_kmap *f, ts_kmap *m) {
         else TS_LAUNCH("k_transpose", k_transpose<1>, gf, block, f->d_nbr, f->n_out, m->d_nbr);
     }
     launch_rows(m);
-    order_up(m);
     launch_scan(m, sizes);
     TS_HIP(hipGetLastError());
     return TS_OK;
@@ -2820,9 +2804,11 @@ int prepare(const ts_kmap *kmap) {
 
 void order_windows(const ts_kmap *kmap) {
     ts_kmap *m = const_cast<ts_kmap *>(kmap);
-    if (!m->d_rowmask || m->d_window_perm || m->d_perm || m->n_out == 0 || stream_capturing(stream())) return;
+    const bool up = goes_up_by_two(m);
+    if (!(m->d_rowmask || up) || m->d_window_perm || m->d_perm || m->n_out == 0 || stream_capturing(stream())) return;
     if (alloc_n(&m->d_window_perm, (size_t)m->n_tiles * kTileRows) != TS_OK) return;
-    TS_LAUNCH("k_window_sort", k_window_sort, dim3(blocks_for(m->n_out, kWindowRows)), dim3(kWindowThreads), m->d_rowmask, m->n_out, m->d_window_perm);
+    if (up) TS_LAUNCH("k_up_order", k_up_order, dim3(blocks_for(m->n_out, kUpRows)), dim3(kUpThreads), m->d_nbr, m->n_out, m->d_window_perm);
+    else TS_LAUNCH("k_window_sort", k_window_sort, dim3(blocks_for(m->n_out, kWindowRows)), dim3(kWindowThreads), m->d_rowmask, m->n_out, m->d_window_perm);
     m->window_stream = stream();
 }
 
