@@ -297,10 +297,11 @@ __device__ __forceinline__ void static_for(Fn &&fn) {
     static_for_impl(fn, std::make_integer_sequence<int, N>{});
 }
 
-// Epilogue of k_conv_res.  A lane holds, per block of 16 output channels, channels 4 (l / 16) .. +3 of rows
-// l % 16 and 16 + l % 16 of the wave's 32: stored from there, an instruction writes 32 bytes each of 16 rows, in
-// 64 separate accesses.  Through LDS (16 rows at a time, `buf`: NCO KiB / 2 that only this wave touches, 16-byte units
-// swizzled by row) rows leave, and the residual's come in, as whole lines.
+// Epilogue of k_conv_res and k_conv_direct.  A lane holds, per block of 16 output channels, channels 4 (l / 16) .. +3 of
+// rows l % 16 and 16 + l % 16 of the wave's 32: stored from there, an instruction writes 32 bytes each of 16 rows, in
+// 64 separate accesses.  Through LDS (16 rows at a time, `buf`: NCO KiB / 2 that only this wave touches, in k_conv_direct a part
+// of the weight slabs, which are free by then; 16-byte units swizzled by row) rows leave, and the residual's come in, as
+// whole lines.
 template <int NCO>
 struct RowStore {
     static constexpr int UPR = NCO * 2, PER = NCO / 2;   // 16-byte units per row; units per lane and half of the rows
@@ -2097,6 +2098,7 @@ void launch_grouped_lines(const void *F, const void *X, const void *wf, const ts
     const dim3 grid((unsigned)plan_tiles(plan), cout / (NCO * 16));
     const int x_bytes = (int)((size_t)kmap->n_in * cin1 * 2), x2_bytes = (int)((size_t)kmap->n_in * (cin - cin1) * 2);
     const int w_bytes = (int)((size_t)kmap->K3 * cin * cout * 2);
+// (under the name of the stage, which k_grouped_mm computes for other rows)
 #define TS_GROUPED_LINES(TWO) \
     TS_LAUNCH("k_grouped_mm", (k_grouped_lines<NCO, TWO>), grid, dim3(kThreads), static_cast<const _Float16 *>(F), static_cast<const _Float16 *>(X), \
               static_cast<const u32x4 *>(wf), offs_of(kmap), plan, G, cin, cout, kmap->centre, in_idx, x_bytes, w_bytes,                      \

@@ -1286,12 +1286,23 @@ def test_async_build_reports_bad_input_late():
 
 # ---- the fused kernel at the edges of its tiles and stages ----
 
+def _kernels_of(fn):
+    """Names of the kernels that a call launches, and what it returns."""
+    ts.ts_profile_enable(True)
+    try:
+        ts.ts_profile_read()
+        result = fn()
+        return set(ts.ts_profile_read()), result
+    finally:
+        ts.ts_profile_enable(False)
+
+
 @pytest.mark.parametrize("K,s,transposed", [(3, 1, False), (2, 2, False), (2, 2, True), (1, 1, False)])
 @pytest.mark.parametrize("n,c_in,c_out", [(1, 64, 32), (15, 32, 128), (16, 96, 64), (17, 160, 96), (127, 64, 128), (128, 192, 32),
                                            (129, 128, 96), (257, 96, 128), (3000, 160, 64), (3000, 32, 96), (40000, 64, 64)])
 def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
     """Rows around blocks of 16 and tiles of 128; stages of 32, 64 and 96 input channels and a last one that is half full;
-    every number of output blocks per workgroup; few tiles, and more of them than workgroups stay resident."""
+    every number of output blocks per workgroup.  (27 offsets and few tiles: k_conv_direct for some widths, see below.)"""
     coords = _rand_coords(5000 + n + c_in, n, 0, 4 if n < 60 else 40 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), K, s, transposed)
     x_h = features(5100 + c_in, kmap.num_in, c_in, np.float16)
@@ -1302,11 +1313,48 @@ def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
     assert torch.equal(ts.ts_sparse_conv(x, w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), first)   # rows ordered, counters rearmed
 
 
-@pytest.mark.parametrize("n,parts,c_out", [(129, (96,), 64), (32768, (96,), 64), (32769, (96,), 64), (129, (32,), 96), (66000, (32,), 96), (16000, (128,), 128),
-                                           (17, (96, 32), 96), (129, (96, 64), 96), (2000, (64, 32), 96), (40000, (64, 96), 32), (66000, (96, 32), 96), (66000, (96, 64), 96),
-                                           (32769, (160,), 64), (57344, (160,), 64), (57345, (160,), 64), (33000, (64, 32), 96), (32768, (64, 96), 64),
-                                           (49152, (64, 64), 64), (49153, (64, 64), 64), (98304, (32, 32), 32), (98305, (32, 32), 32), (32768, (128,), 64), (32769, (128,), 64)])
-def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out):
+@pytest.mark.parametrize("K,s,transposed", [(3, 1, False), (2, 2, True), (1, 1, False)])
+@pytest.mark.parametrize("n,parts,c_out", [(98305, (64,), 64), (98319, (160,), 64), (98431, (96,), 96), (65553, (96,), 64), (163857, (32,), 96),
+                                           (98321, (64, 64), 64), (98319, (32, 64), 128), (98305, (64, 32), 96), (98431, (96, 32), 64)])
+def test_tiles_beyond_those_that_start_resident(K, s, transposed, n, parts, c_out):
+    """More tiles than a launch of k_conv_tile has workgroups (three a compute unit for stages of 64 channels, two for 96, four
+    at most for 32), so that tiles are handed out and a tile's table is brought in behind another's rows; stages of every length and of
+    two inputs; a last tile of 1, 15, 17 and 127 rows."""
+    coords = _rand_coords(5050 + n, n, 0, 64, batches=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), K, s, transposed)
+    c_in = sum(parts)
+    x_h, w_h = features(5150 + c_in, kmap.num_in, c_in, np.float16), conv_weights(5250 + c_out, K ** 3, c_in, c_out, np.float16)
+    w, xs = ts.ts_weights_prepare(to_dev(w_h)), [to_dev(p) for p in np.split(x_h, np.cumsum(parts)[:-1], axis=1)]
+    want = oracle_conv(coords, x_h, w_h, K, s, transposed)
+    for again in range(2):   # rows in natural order, then ordered; counters rearmed
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared2(xs[0], xs[1], w, kmap) if len(xs) == 2 else ts.ts_sparse_conv_prepared(xs[0], w, kmap))
+        assert "k_conv_tile" in kernels
+        if not again:
+            check_features(got, want, torch.float16, f"{n}: {parts}->{c_out} K{K} s{s} t{int(transposed)}")
+            first = got
+        assert torch.equal(got, first)
+
+
+@pytest.mark.parametrize("n,c_in,c_out", [(32769, 96, 64), (32783, 96, 96), (32785, 192, 64), (32895, 96, 128), (65537, 32, 96), (65551, 32, 128), (65553, 32, 160), (65663, 20, 96)])
+def test_stages_of_32_and_96_channels_on_27_offsets(n, c_in, c_out):
+    """The fewest tiles from which k_conv_tile takes such layers, with a last one of 1, 15, 17 and 127 rows."""
+    coords = _rand_coords(5060 + n, n, 0, 50, batches=1)
+    kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
+    x_h, w_h = features(5160 + c_in, n, c_in, np.float16), conv_weights(5260 + c_out, 27, c_in, c_out, np.float16)
+    kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), kmap, dataflow=ts.TS_DATAFLOW_FUSED))
+    assert "k_conv_tile" in kernels
+    check_features(got, oracle_conv(coords, x_h, w_h, 3, 1), torch.float16, f"{n}: {c_in}->{c_out}")
+
+
+@pytest.mark.parametrize("n,parts,c_out,kernel", [
+    (129, (96,), 64, "k_conv_direct"), (32768, (96,), 64, "k_conv_direct"), (32769, (96,), 64, "k_conv_tile"), (129, (32,), 96, "k_conv_direct"),
+    (65536, (32,), 96, "k_conv_direct"), (66000, (32,), 96, "k_conv_tile"), (16000, (128,), 128, "k_conv_direct"), (8000, (128,), 32, "k_conv_tile"),
+    (32768, (128,), 64, "k_conv_direct"), (32769, (128,), 64, "k_conv_tile"), (32768, (160,), 64, "k_conv_tile"), (32769, (160,), 64, "k_conv_direct"),
+    (57344, (160,), 64, "k_conv_direct"), (57345, (160,), 64, "k_conv_tile"), (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, "k_conv_direct"),
+    (66000, (96, 32), 96, "k_conv_tile"), (129, (96, 64), 96, "k_grouped_mm"), (40000, (64, 96), 32, "k_conv_tile"), (32768, (64, 96), 64, "k_conv_tile"),
+    (66000, (96, 64), 96, "k_conv_tile"), (2000, (64, 32), 96, "k_conv_direct"), (32768, (64, 32), 96, "k_conv_direct"), (33000, (64, 32), 96, "k_conv_tile"),
+    (49152, (64, 64), 64, "k_conv_direct"), (49153, (64, 64), 64, "k_conv_tile"), (98304, (32, 32), 32, "k_conv_direct"), (98305, (32, 32), 32, "k_conv_tile")])
+def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out, kernel):
     """Few tiles and many, of layers whose kernel goes by their number; an input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
@@ -1314,10 +1362,11 @@ def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, part
     w_h = conv_weights(6101, 27, sum(parts), c_out, np.float16)
     w = ts.ts_weights_prepare(to_dev(w_h))
     if len(parts) == 1:
-        got = ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap)
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap))
     else:
-        got = ts.ts_sparse_conv_prepared2(to_dev(x_h[:, :parts[0]].copy()), to_dev(x_h[:, parts[0]:].copy()), w, kmap)
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared2(to_dev(x_h[:, :parts[0]].copy()), to_dev(x_h[:, parts[0]:].copy()), w, kmap))
         assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap), got)
+    assert kernel in kernels
     check_features(got, oracle_conv(coords, x_h, w_h, 3, 1, False), torch.float16, f"{n}: {parts}->{c_out}")
 
 
@@ -1382,17 +1431,6 @@ def test_rows_of_a_transposed_map_grouped_by_offset(n, dtype):
     other.synchronize()
 
 
-def _kernels_of(fn):
-    """Names of the kernels that a call launches, and what it returns."""
-    ts.ts_profile_enable(True)
-    try:
-        ts.ts_profile_read()
-        result = fn()
-        return set(ts.ts_profile_read()), result
-    finally:
-        ts.ts_profile_enable(False)
-
-
 @pytest.mark.parametrize("way", ["measured box", "stated box", "hash", "boundary", "transposed from a sorted map"])
 @pytest.mark.parametrize("n,c_in", [(1, 64), (129, 32), (511, 160), (512, 160), (2049, 256), (9000, 64)])
 def test_maps_that_go_up_are_alike_however_they_are_made(n, c_in, way):
@@ -1434,7 +1472,8 @@ def test_dataflow_of_maps_by_two(n, c):
     w = to_dev(w_h)
     for kmap, transposed in ((down, False), (down.transpose(), True)):
         x_h = features(5902, kmap.num_in, c, np.float16)
-        got = ts.ts_sparse_conv(to_dev(x_h), w, kmap)
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), w, kmap))
+        assert ("k_conv_tile" in kernels) == transposed
         check_features(got, oracle_conv(coords, x_h, w_h, 2, 2, transposed), torch.float16, f"{n} rows, {c} channels, up {transposed}")
         if transposed:
             assert torch.equal(ts.ts_sparse_conv(to_dev(x_h), w, kmap, dataflow=ts.TS_DATAFLOW_FUSED), got)
