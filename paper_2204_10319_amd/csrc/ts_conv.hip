@@ -374,8 +374,9 @@ struct RowStore {
 // rows are grouped.
 //
 // What bounds it, and the layout that follows (MI355X, measured):
-//  - A vector load costs the address unit 16 cycles per KiB when neighbouring lanes read neighbouring bytes (31 TB/s out of
-//    L2 over the chip), 40 to 48 when 16 neighbouring lanes are 16 rows, as an MFMA operand wants them (13 TB/s).  So the
+//  - A vector load costs the address unit 16 cycles per KiB when neighbouring lanes read neighbouring bytes, 40 to 48 when 16
+//    neighbouring lanes are 16 rows, as an MFMA operand wants them (loads alone: 31 and 13 TB/s out of L2 over the chip; counted,
+//    TA_BUSY by loads: 16 to 18 in this kernel, 25 in one whose rows are operands and whose weights are whole lines).  So the
 //    rows of a stage go from memory straight into LDS, whole lines at a time (eight lanes a row of 64 channels), and operands
 //    are read from there, 16-byte units being swizzled so that 16 lanes meet 16 different banks.  Rows for the next stage are
 //    under way while this one is multiplied.  Only blocks of 16 rows that meet the offset are fetched, read and multiplied.
@@ -386,8 +387,12 @@ struct RowStore {
 //  - The next tile is asked for shortly before this one ends: asked for at its start, the workgroups with the longest
 //    tiles took as many more as the others.
 // Layers with their tail on kept maps, against a kernel that loaded rows as operands and weights through LDS (us; 64 -> 64,
-// 128 -> 128, 96 -> 96): 153 k points of a scan 39 -> 31, 79 -> 60, 61 -> 57; 97 k of surfaces 34 -> 27, 69 -> 54, 51 -> 46;
-// 1.53 M of scans 311 -> 282, 705 -> 595, 546 -> 551; 64 k after one halving 26 -> 22, 52 -> 46, 41 -> 36.
+// 128 -> 128, 96 -> 96): 153 k points of a scan 40 -> 28, 69 -> 51, 58 -> 49; 98 k of surfaces 32 -> 26, 63 -> 51, 47 -> 40;
+// 1.53 M of scans 279 -> 249, 624 -> 516, 472 -> 454; 65 k after one halving 23 -> 20, 46 -> 41, 38 -> 31; 150 k scattered
+// 33 -> 31, 73 -> 58, 59 -> 52.
+// What is left at 64 channels on a map's first layer, 38 us: 1.6 times the matrix work there is (15 % of the cycles), the address
+// unit busy 41 %, LDS 17 %, and 10 k instructions a SIMD, as many scalar ones as vector ones.  Stages of 96 channels also meet
+// bank conflicts (44 % of their LDS cycles).
 
 // A raw buffer descriptor for load_to_lds, in scalar registers.
 __device__ __forceinline__ u32x4 lds_source(const void *p, int bytes) {
@@ -1947,7 +1952,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     // after one halving; the lines lie where most of these four change sides).  It keeps two stages in flight and issues less
     // for each, which decides while a CU has a workgroup or two; k_conv_tile skips the blocks that do not meet an offset, which
     // is why scattered points change sides last.  On 1x1x1 and 2x2x2 maps, whose tiles walk few stages, k_conv_tile is even
-    // or ahead.
+    // or ahead but for the first and the last kind.
     //  - a two-part input with a part that is no multiple of 64 channels, so that a stage has two sources: up to two tiles a CU,
     //    (96, 32) -> 96 on 8 k rows 33 26, 31 24, 26 22, 32 26, on 65 k 48 40, 45 42, 43 37, 45 40, on 98 k 51 55, 51 56, 49 52,
     //    48 53; with one stage an offset up to three, (32, 32) -> 32 on 98 k 26 23, 26 28, 26 23, 24 24, on 150 k 32 33, 38 40,
@@ -1963,20 +1968,24 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     //    40 k 36 32, 36 36, 34 31, 34 34, on 65 k 39 34, 35 37, 33 33, 34 36
     //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 8 k rows
     //    24 24, 23 24, 20 22, 24 23, on 16 k 32 29, 29 29, 25 26, 29 29, on 20 k 37 35, 31 36, 27 29, 32 34
+    //    (down by 2x2x2 to 6.5 k rows of surfaces 12.9 11.7, to 12.6 k 14.9 13.7; 128 -> 64 12.9 11.9)
     const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32;
     const int64_t wgs = kmap->n_tiles * (cblocks / nco);
+    const bool up = goes_up_by_two(kmap), several = !sec.x2 && ksteps == 2 && cin_pad >= 128 && nco <= 4;
     const bool direct = split           ? kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus
+                        : several       ? kmap->K3 > 1 && !up && 2 * wgs > cus && wgs <= cus
                         : kmap->K3 <= 8 ? false
                         : ksteps == 3   ? kmap->n_tiles <= cus
                         : half_empty    ? !sec.x2 && nco <= 4 && kmap->n_tiles > cus && 4 * kmap->n_tiles <= 7 * cus
                         : cin_pad == 32 ? kmap->n_tiles <= 2 * cus
-                        : nco > 4       ? false
-                        : sec.x2        ? 2 * wgs <= 3 * cus
-                                        : cin_pad >= 128 && 2 * wgs > cus && wgs <= cus;
+                                        : sec.x2 && nco <= 4 && 2 * wgs <= 3 * cus;
     // Rows in order of their offset leave a 2x2x2 map's tile few stages, for which three workgroups a CU beat the two that stages
     // of 96 channels leave room for: 96 -> 96 going up to 150 k scattered points 27.6 and, by 32 channels a stage, 25.3; to
     // 300 k 44.4 and 39.2.
-    const bool by_32 = ksteps == 3 && !sec.x2 && goes_up_by_two(kmap) && kmap->n_tiles > 2 * cus;
+    // So do the rows of 1x1x1 maps, by 64 and 32 channels, beyond four tiles a CU: 96 -> 96 on 150 k points 24.8, 23.4, on 300 k
+    // 39.6, 34.5; on 98 k 18.1, 19.2.
+    const bool by_32 = ksteps == 3 && !sec.x2 && up && kmap->n_tiles > 2 * cus;
+    const bool by_64 = ksteps == 3 && !sec.x2 && kmap->K3 == 1 && kmap->n_tiles > 4 * cus;
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \
@@ -1994,7 +2003,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             if (ksteps == 2) launch_conv_tile<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);     \
             else launch_conv_tile<N, 2, true, true>(x, wf, kmap, out, cin_pad, ep, sec);          \
         } else if (ksteps == 2) launch_conv_tile<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
-        else if (ksteps == 3 && !by_32) launch_conv_tile<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        else if (ksteps == 3 && !by_32 && !by_64) launch_conv_tile<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else if (cin_pad == 32 || by_32) launch_conv_tile<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_tile<N, 2, false, true>(x, wf, kmap, out, cin_pad, ep, sec);             \
     }
@@ -2298,9 +2307,9 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // than one offset, and the two dataflows give the same bits: 64 -> 64 on 300 rows 8.4, 11.1, on 20 k 9.4, 12.3; 256 -> 256 on
 // 1 k 13.0, 14.1, on 20 k 16.8, 24.1, but on 300, where three tiles walk 32 stages each, 14.8, 12.4; 160 -> 64 11.7, 10.9.
 // Maps that go down share the line of the others.  Drawn at 0.9 times the pairs' bytes it gained on wide outputs (64 -> 128
-// from 16 k scattered points 9.9, 12.8, 256 -> 256 from 60 k points of surfaces 27.2, 33.7) but cost more where C_in is the larger one, whose
-// stages a tile walks one after the other: 128 -> 64 from 16 k scattered points 11.6, 9.8, 256 -> 64 from 24 k points of a scan 20.2, 11.9,
-// 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
+// from 16 k scattered points 9.9, 12.8, 256 -> 256 from 60 k points of surfaces 27.2, 33.7) but cost more where C_in is the
+// larger one, whose stages a tile walks one after the other: 128 -> 64 from 16 k scattered points 11.6, 9.8, 256 -> 64 from 24 k
+// points of a scan 20.2, 11.9, 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
     if (elem == 2 && goes_up_by_two(kmap) && (cin <= 128 || kmap->n_out >= 4 * kTileRows)) return false;

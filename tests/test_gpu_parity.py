@@ -1314,7 +1314,7 @@ def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
 
 
 @pytest.mark.parametrize("K,s,transposed", [(3, 1, False), (2, 2, True), (1, 1, False)])
-@pytest.mark.parametrize("n,parts,c_out", [(98305, (64,), 64), (98319, (160,), 64), (98431, (96,), 96), (65553, (96,), 64), (163857, (32,), 96),
+@pytest.mark.parametrize("n,parts,c_out", [(98305, (64,), 64), (98319, (160,), 64), (98431, (96,), 96), (65553, (96,), 64), (163857, (32,), 96), (131089, (96,), 96),
                                            (98321, (64, 64), 64), (98319, (32, 64), 128), (98305, (64, 32), 96), (98431, (96, 32), 64)])
 def test_tiles_beyond_those_that_start_resident(K, s, transposed, n, parts, c_out):
     """More tiles than a launch of k_conv_tile has workgroups (three a compute unit for stages of 64 channels, two for 96, four
