@@ -1948,54 +1948,59 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             nco = c;
             break;
         }
-    // Layers that k_conv_direct does faster (us, k_conv_tile and k_conv_direct, on scattered points, surfaces, a scan and a scan
-    // after one halving; the lines lie where most of these four change sides).  It keeps two stages in flight and issues less
-    // for each, which decides while a CU has a workgroup or two; k_conv_tile skips the blocks that do not meet an offset, which
-    // is why scattered points change sides last.  On 1x1x1 and 2x2x2 maps, whose tiles walk few stages, k_conv_tile is even
-    // or ahead but for the first and the last kind.
-    //  - a two-part input with a part that is no multiple of 64 channels, so that a stage has two sources: up to two tiles a CU,
-    //    (96, 32) -> 96 on 8 k rows 33 26, 31 24, 26 22, 32 26, on 65 k 48 40, 45 42, 43 37, 45 40, on 98 k 51 55, 51 56, 49 52,
-    //    48 53; with one stage an offset up to three, (32, 32) -> 32 on 98 k 26 23, 26 28, 26 23, 24 24, on 150 k 32 33, 38 40,
-    //    28 32, 32 35
-    //  - stages of 96 channels: up to a tile a CU, 96 -> 96 on 4 k rows 19 17, 16 15, 15 14, 12 11, on 32 k 45 32, 34 32, 28 31,
-    //    38 35, on 40 k 30 30, 31 33, 28 27, 29 30, on 98 k 36 43, 38 48, 35 43, 37 44
-    //  - stages of 64 and a half empty one: between one tile a CU and 1.75, 160 -> 64 on 16 k rows 41 37, 35 36, 30 33, 37 37, on
-    //    40 k 50 43, 49 47, 46 41, 46 43, on 65 k 51 45, 45 48, 44 42, 43 45.  Not in two parts: (96, 64) -> 96 on 8 k 38 44,
-    //    37 41, 31 36, 38 43, on 32 k 60 60, 50 56, 48 53, 58 60
-    //  - stages of 32: up to two tiles a CU, 32 -> 96 on 4 k rows 13.0 12.3, 11.4 11.2, 10.8 10.5, 9.2 8.8, on 65 k 21 20, 20 21,
-    //    19 20, 21 21, on 98 k 25 25, 24 28, 25 25, 24 26
-    //  - stages of 64 of two sources in turn: up to 1.5 workgroups a CU, (64, 64) -> 64 on 16 k rows 30 27, 29 26, 25 24, 29 26, on
-    //    40 k 36 32, 36 36, 34 31, 34 34, on 65 k 39 34, 35 37, 33 33, 34 36
-    //  - several stages of 64 an offset while the workgroups number from half the CUs up to all of them: 128 -> 128 on 8 k rows
-    //    24 24, 23 24, 20 22, 24 23, on 16 k 32 29, 29 29, 25 26, 29 29, on 20 k 37 35, 31 36, 27 29, 32 34
-    //    (down by 2x2x2 to 6.5 k rows of surfaces 12.9 11.7, to 12.6 k 14.9 13.7; 128 -> 64 12.9 11.9)
-    const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32;
+    // Layers that k_conv_direct does faster.  It keeps two stages in flight and issues less for each, which decides while a CU
+    // has a workgroup or two, the more the further rows have to come; k_conv_tile skips the blocks that do not meet an offset.
+    // The lines lie where most scenes change sides (us, k_conv_tile and k_conv_direct, on kept maps whose rows come new from memory
+    // every time, as a network's do: scattered points, surfaces, a scan, a scan after one halving).  Scattered points change
+    // sides last: 64 -> 64 on 65 k rows 24 and 21, 128 -> 64 39 and 32, where the others are ahead with k_conv_tile.
+    //  - stages of two sources, a part of the input being no multiple of 64 channels: up to two tiles a CU, (96, 32) -> 96 on 8 k rows
+    //    35 25, 32 24, 27 22, 34 25, on 65 k 50 40, 47 42, 45 38, 47 41, on 98 k 55 55, 53 58, 51 54, 51 56; with one stage an
+    //    offset, (32, 32) -> 32, up to three
+    //  - maps that go up, and 1x1x1 ones, leave a tile a stage or two: k_conv_tile at every size
+    //  - 2x2x2 maps that go down: while one workgroup has at most 64 output channels (32 input channels: up to two tiles a CU; 96:
+    //    while there is one slice), 128 -> 64 from 20 k rows 11.2 11.3, 12.5 11.0, 12.8 10.9, from 65 k 22 18, 17 13, 18 15, from
+    //    300 k 62 52, 28 30, 42 39; 64 -> 64 from 65 k 16 15, 12 10, 13 12
+    //  - stages of 96 channels: up to a tile a CU, 96 -> 96 on 4 k rows 20 17, 16 15, 15 15, 12 11, on 32 k 45 32, 34 32, 28 31,
+    //    38 35, on 40 k 32 30, 32 33, 29 28, 31 31; in two parts up to two, (64, 32) -> 96 on 65 k 45 34, 40 36, 39 32, 40 35, on 80 k
+    //    46 43, 45 50, 42 43, 44 47
+    //  - stages of 32: up to two tiles a CU, 32 -> 96 on 4 k rows 16 12, 12 11, 11 11, 9.3 8.7, on 65 k 22 20, 21 22, 20 20, 21 21, on
+    //    98 k 26 26, 25 29, 26 26, 25 27
+    //  - stages of 64 and a half empty one: from a few tiles to 1.6 a CU, 160 -> 64 on 1 k rows 41 39, 16 17, 17 18, 16 17, on 16 k
+    //    43 37, 38 36, 34 33, 39 37, on 50 k 54 47, 51 50, 42 40, 51 46, on 65 k 55 47, 47 49, 47 45, 45 47; not in two parts, where
+    //    the kernel with stages of 32 walks twice as many
+    //  - stages of 64: while there is at most a workgroup a CU, 64 -> 64 on 8 k rows 18 15, 15.3 14.9, 14.0 14.2, 17 15, on 32 k 22 20,
+    //    18 18, 18 17, 20 18, on 40 k 21 20, 21 22, 20 19, 20 21, 64 -> 128 on 16 k (250 workgroups) 21 19, 19 18, 17 17, 19 18, on 20 k
+    //    (314) 23 22, 20 23, 18 19, 20 21; with several an offset and one slice, which gathers no row twice, up to 1.6,
+    //    128 -> 64 on 8 k 30 23, 24 24, 22 21, 27 23, on 50 k 38 31, 35 36, 30 29, 35 35, on 65 k 39 32, 34 37, 33 33, 32 36
+    const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32, up = goes_up_by_two(kmap);
+    const bool one_slice = nco == cblocks;
     const int64_t wgs = kmap->n_tiles * (cblocks / nco);
-    const bool up = goes_up_by_two(kmap), several = !sec.x2 && ksteps == 2 && cin_pad >= 128 && nco <= 4;
-    const bool direct = split           ? kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus
-                        : several       ? kmap->K3 > 1 && !up && 2 * wgs > cus && wgs <= cus
-                        : kmap->K3 <= 8 ? false
-                        : ksteps == 3   ? kmap->n_tiles <= cus
-                        : half_empty    ? !sec.x2 && nco <= 4 && kmap->n_tiles > cus && 4 * kmap->n_tiles <= 7 * cus
-                        : cin_pad == 32 ? kmap->n_tiles <= 2 * cus
-                                        : sec.x2 && nco <= 4 && 2 * wgs <= 3 * cus;
-    // Rows in order of their offset leave a 2x2x2 map's tile few stages, for which three workgroups a CU beat the two that stages
-    // of 96 channels leave room for: 96 -> 96 going up to 150 k scattered points 27.6 and, by 32 channels a stage, 25.3; to
-    // 300 k 44.4 and 39.2.
-    // So do the rows of 1x1x1 maps, by 64 and 32 channels, beyond four tiles a CU: 96 -> 96 on 150 k points 24.8, 23.4, on 300 k
-    // 39.6, 34.5; on 98 k 18.1, 19.2.
-    const bool by_32 = ksteps == 3 && !sec.x2 && up && kmap->n_tiles > 2 * cus;
+    bool direct;
+    if (split) direct = kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus;
+    else if (kmap->K3 == 1 || up) direct = false;
+    else if (ksteps == 3) direct = kmap->K3 == 8 ? one_slice : kmap->n_tiles <= (sec.x2 ? 2 : 1) * cus;
+    else if (cin_pad == 32) direct = kmap->n_tiles <= 2 * cus && (kmap->K3 > 8 || nco <= 4);
+    else if (half_empty && sec.x2) direct = false;
+    else if (kmap->K3 == 8) direct = nco <= 4;
+    else if ((half_empty || cin_pad == 64) && 16 * kmap->n_tiles <= cus) direct = false;   // 64 -> 64 on 1 k rows 14.8 14.6, 9.3 10.6, 9.3 9.3, 9.2 9.0
+    else if (half_empty) direct = nco <= 4 && 5 * kmap->n_tiles <= 8 * cus;
+    else direct = wgs <= cus || (cin_pad >= 128 && one_slice && nco <= 6 && 5 * wgs <= 8 * cus);
+    // Maps that go up, their rows in order of their offset, and 1x1x1 ones leave a tile few stages, for which three workgroups a CU
+    // beat the two that stages of 96 channels leave room for, beyond four tiles a CU: 96 -> 96 up to 130 k scattered points 25 and,
+    // by 32 channels a stage, 27, to 200 k 36.9 and 35.5, to 300 k 44 and 39; 1x1x1 on 200 k, by 64 and 32, 31.4 and 29.1, on
+    // 300 k 41.7 and 35.5.
+    const bool by_32 = ksteps == 3 && !sec.x2 && up && kmap->n_tiles > 4 * cus;
     const bool by_64 = ksteps == 3 && !sec.x2 && kmap->K3 == 1 && kmap->n_tiles > 4 * cus;
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_direct<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);   \
             else launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
-        } else if (ksteps == 2) launch_conv_direct<(N <= 4 ? N : 4), 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        } else if (ksteps == 2) launch_conv_direct<(N <= 6 ? N : 6), 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_direct<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec);                  \
     }
-    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)
+    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)   // (one part, stages of 64: 8 blocks never come here)
 #undef TS_DIRECT_CASE
 #define TS_TILE_CASE(N)                                                                            \
     if (!direct && nco == N) {                                                                     \

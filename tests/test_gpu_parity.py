@@ -1335,7 +1335,7 @@ def test_tiles_beyond_those_that_start_resident(K, s, transposed, n, parts, c_ou
         assert torch.equal(got, first)
 
 
-@pytest.mark.parametrize("n,c_in,c_out", [(32769, 96, 64), (32783, 96, 96), (32785, 192, 64), (32895, 96, 128), (65537, 32, 96), (65551, 32, 128), (65553, 32, 160), (65663, 20, 96)])
+@pytest.mark.parametrize("n,c_in,c_out", [(32769, 96, 64), (32783, 96, 96), (52369, 192, 64), (32895, 96, 128), (65537, 32, 96), (65551, 32, 128), (65553, 32, 160), (65663, 20, 96)])
 def test_stages_of_32_and_96_channels_on_27_offsets(n, c_in, c_out):
     """The fewest tiles from which k_conv_tile takes such layers, with a last one of 1, 15, 17 and 127 rows."""
     coords = _rand_coords(5060 + n, n, 0, 50, batches=1)
@@ -1348,12 +1348,13 @@ def test_stages_of_32_and_96_channels_on_27_offsets(n, c_in, c_out):
 
 @pytest.mark.parametrize("n,parts,c_out,kernel", [
     (129, (96,), 64, "k_conv_direct"), (32768, (96,), 64, "k_conv_direct"), (32769, (96,), 64, "k_conv_tile"), (129, (32,), 96, "k_conv_direct"),
-    (65536, (32,), 96, "k_conv_direct"), (66000, (32,), 96, "k_conv_tile"), (16000, (128,), 128, "k_conv_direct"), (8000, (128,), 32, "k_conv_tile"),
-    (32768, (128,), 64, "k_conv_direct"), (32769, (128,), 64, "k_conv_tile"), (32768, (160,), 64, "k_conv_tile"), (32769, (160,), 64, "k_conv_direct"),
-    (57344, (160,), 64, "k_conv_direct"), (57345, (160,), 64, "k_conv_tile"), (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, "k_conv_direct"),
+    (65536, (32,), 96, "k_conv_direct"), (66000, (32,), 96, "k_conv_tile"), (16000, (128,), 128, "k_conv_direct"), (16500, (128,), 128, "k_conv_tile"),
+    (2048, (64,), 64, "k_conv_tile"), (2049, (64,), 64, "k_conv_direct"), (32768, (64,), 64, "k_conv_direct"), (32769, (64,), 64, "k_conv_tile"),
+    (52352, (128,), 64, "k_conv_direct"), (52353, (128,), 64, "k_conv_tile"), (40000, (128,), 96, "k_conv_direct"), (40000, (128,), 128, "k_conv_tile"),
+    (52352, (160,), 64, "k_conv_direct"), (52353, (160,), 64, "k_conv_tile"), (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, "k_conv_direct"),
     (66000, (96, 32), 96, "k_conv_tile"), (129, (96, 64), 96, "k_grouped_mm"), (40000, (64, 96), 32, "k_conv_tile"), (32768, (64, 96), 64, "k_conv_tile"),
-    (66000, (96, 64), 96, "k_conv_tile"), (2000, (64, 32), 96, "k_conv_direct"), (32768, (64, 32), 96, "k_conv_direct"), (33000, (64, 32), 96, "k_conv_tile"),
-    (49152, (64, 64), 64, "k_conv_direct"), (49153, (64, 64), 64, "k_conv_tile"), (98304, (32, 32), 32, "k_conv_direct"), (98305, (32, 32), 32, "k_conv_tile")])
+    (66000, (96, 64), 96, "k_conv_tile"), (2000, (64, 32), 96, "k_conv_direct"), (65536, (64, 32), 96, "k_conv_direct"), (65537, (64, 32), 96, "k_conv_tile"),
+    (52352, (64, 64), 64, "k_conv_direct"), (52353, (64, 64), 64, "k_conv_tile"), (98304, (32, 32), 32, "k_conv_direct"), (98305, (32, 32), 32, "k_conv_tile")])
 def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out, kernel):
     """Few tiles and many, of layers whose kernel goes by their number; an input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
@@ -1370,9 +1371,22 @@ def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, part
     check_features(got, oracle_conv(coords, x_h, w_h, 3, 1, False), torch.float16, f"{n}: {parts}->{c_out}")
 
 
-@pytest.mark.parametrize("n,c_in", [(65536, 96), (65537, 96), (70001, 96), (65553, 288)])
+@pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
+    (2600, 40, 64, 64, "k_conv_direct"), (9000, 22, 128, 128, "k_conv_direct"), (9000, 22, 256, 64, "k_conv_direct"), (40000, 36, 160, 64, "k_conv_direct"), (40000, 36, 96, 96, "k_conv_tile"), (70000, 60, 96, 96, "k_conv_direct"),
+    (30000, 60, 32, 64, "k_conv_direct"), (130000, 100, 32, 64, "k_conv_tile"), (90000, 60, 64, 128, "k_conv_tile"), (250000, 70, 128, 64, "k_conv_direct")])
+def test_layers_down_by_both_kernels(n, side, c_in, c_out, kernel):
+    """2x2x2 maps that go down, on both sides of the lines between the two fp16 kernels."""
+    coords = _rand_coords(6250 + n, n, 0, side)
+    down = ts.ts_build_kmap(to_dev(coords), 2, 2)
+    x_h, w_h = features(6350, n, c_in, np.float16), conv_weights(6351, 8, c_in, c_out, np.float16)
+    kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), down, dataflow=ts.TS_DATAFLOW_FUSED))
+    assert kernel in kernels, (down.num_out, kernels)
+    check_features(got, oracle_conv(coords, x_h, w_h, 2, 2), torch.float16, f"{n}: {c_in}->{c_out} down")
+
+
+@pytest.mark.parametrize("n,c_in", [(131072, 96), (131073, 96), (131199, 288)])
 def test_layers_up_on_both_sides_of_stages_of_32(n, c_in):
-    """Maps that go up, rows of 96 channels and a multiple of them: whole stages up to two tiles a compute unit, a third of one beyond."""
+    """Maps that go up, rows of 96 channels and a multiple of them: whole stages up to four tiles a compute unit, a third of one beyond."""
     coords = _rand_coords(6200 + n, n, 0, 70, batches=1)
     up = ts.ts_build_kmap(to_dev(coords), 2, 2).transpose()
     x_h, w_h = features(6300, up.num_in, c_in, np.float16), conv_weights(6301, 8, c_in, 96, np.float16)
