@@ -118,6 +118,44 @@ def test_row_order_of_a_map_in_use_on_other_streams(dtype):
         del graph
 
 
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+@pytest.mark.parametrize("n,c", [(9000, 64), (9000, 128), (60000, 128)])
+def test_row_order_of_a_map_that_goes_up_on_other_streams(n, c, dtype):
+    """A 2x2x2 map that goes up is ordered by its second layer, or a wide first one: layers that follow at once on other streams,
+    eager or recorded, give the bits of the natural order; a layer recorded first leaves the ordering to others."""
+    streams = [torch.cuda.Stream() for _ in range(3)]
+    nd = np_dtype(dtype)
+    dev, w = to_dev(_coords(980, n, 40)), ts.ts_weights_prepare(to_dev(conv_weights(6, 8, c, 64, nd)))
+    derived = ts.ts_build_kmap(dev, 2, 2).transpose()
+    x = to_dev(features(7, derived.num_in, c, nd))
+    want = ts.ts_sparse_conv_prepared(x, w, derived)
+    outs = [torch.zeros_like(want) for _ in range(4)]
+    for recorded_first in (False, True) if dtype == torch.float16 else (False,):   # (fetched fp32 layers make pair lists first)
+        kmap = ts.ts_build_kmap(dev, 2, 2, True)
+        graph = torch.cuda.CUDAGraph()
+        torch.cuda.synchronize()
+        if recorded_first:
+            with torch.cuda.graph(graph, stream=streams[2]):
+                ts.ts_sparse_conv_prepared(x, w, kmap, out=outs[0])
+        for out, stream in zip(outs[1:], streams):
+            for other in streams:
+                stream.wait_stream(other)          # fp16 layers on one map share its tile counters
+            with torch.cuda.stream(stream):
+                ts.ts_sparse_conv_prepared(x, w, kmap, out=out.zero_())
+        torch.cuda.synchronize()
+        assert all(torch.equal(out, want) for out in outs[1:])
+        if not recorded_first:
+            with torch.cuda.graph(graph, stream=streams[2]):
+                ts.ts_sparse_conv_prepared(x, w, kmap, out=outs[0])
+        for _ in range(3):
+            outs[0].zero_()
+            graph.replay()
+            assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), want)   # eager work between the replays
+            torch.cuda.synchronize()
+            assert torch.equal(outs[0], want)
+        del graph
+
+
 def _far_spread(seed, n):
     """Points whose box is too large for the bitmap of a 2x2x2 stride-2 build: it is built by sorting once its number of
     outputs is asked for."""
