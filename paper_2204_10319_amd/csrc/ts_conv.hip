@@ -1886,7 +1886,7 @@ struct Second {
 
 template <int NCO, int KS, bool TWO, bool HALF = false, int GR = 1>
 void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap, ts_tensor *out, int cin_pad,
-                      const Epilogue &ep, const Second &sec, const char *name = "k_conv_tile") {
+                      const Epilogue &ep, const Second &sec) {
     // as many workgroups as stay resident at once, fewer for small maps
     static int per_cu = 0;   // per instantiation
     if (per_cu == 0) {
@@ -1902,7 +1902,7 @@ void launch_conv_tile(const _Float16 *x, const _Float16 *wf, const ts_kmap *kmap
     const int cin1 = TWO ? sec.cin1 : cin_pad;
     const int32_t *perm = row_order(kmap);
     const int row_shift = kmap->stride == 32 ? 3 : kmap->stride == 16 ? 2 : 0;   // 16-byte units of a table row
-    TS_LAUNCH(name, (k_conv_tile<NCO, KS, TWO, HALF, GR>), grid, dim3(kThreads * GR), x, reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr,
+    TS_LAUNCH(GR > 1 ? "k_conv_tile_groups" : "k_conv_tile", (k_conv_tile<NCO, KS, TWO, HALF, GR>), grid, dim3(kThreads * GR), x, reinterpret_cast<const u32x4 *>(wf), kmap->d_nbr,
               row_shift, perm, kmap->d_perm != nullptr,
               !perm && (kmap->scan_done || (kmap->scan_enqueued && kmap->stream == stream())) ? kmap->d_tile_order : nullptr,
               kmap->n_out, static_cast<_Float16 *>(out->data), kmap->d_sched, cin_pad, out->cols, kmap->K3,
@@ -2026,6 +2026,23 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     }
     if (!wbuf) order_for_layer(kmap, order_at_once(kmap, cin_pad, cout, sizeof(T)));
     ++const_cast<ts_kmap *>(kmap)->uses;
+    if (group_nco) {
+#define TS_GROUPS_CASE(N)                                                                                      \
+    if (group_nco == N) {                                                                                      \
+        if (sec.x2) {                                                                                          \
+            if (ksteps == 2) launch_conv_tile<N, 2, true, false, 3>(x, wf, kmap, out, cin_pad, ep, sec);       \
+            else if (ksteps == 3) launch_conv_tile<N, 2, true, true, 2>(x, wf, kmap, out, cin_pad, ep, sec);   \
+            else launch_conv_tile<N, 2, true, true, 3>(x, wf, kmap, out, cin_pad, ep, sec);                    \
+        } else if (ksteps == 2) launch_conv_tile<N, 2, false, false, 3>(x, wf, kmap, out, cin_pad, ep, sec);   \
+        else if (ksteps == 3) launch_conv_tile<N, 3, false, false, 2>(x, wf, kmap, out, cin_pad, ep, sec);     \
+        else if (cin_pad == 32) launch_conv_tile<N, 1, false, false, 3>(x, wf, kmap, out, cin_pad, ep, sec);   \
+        else launch_conv_tile<N, 2, false, true, 3>(x, wf, kmap, out, cin_pad, ep, sec);                       \
+    }
+        TS_GROUPS_CASE(8) TS_GROUPS_CASE(6) TS_GROUPS_CASE(4) TS_GROUPS_CASE(2)
+#undef TS_GROUPS_CASE
+        TS_HIP(hipGetLastError());
+        return TS_OK;
+    }
     // Output channels per workgroup: as many as divide C_out (every slice gathers the rows again), fewer
     // when the launch would leave most of the chip idle: a lone workgroup per CU walks its stages one
     // after the other, and a stage of eight output blocks takes twice as long as one of four.
@@ -2038,9 +2055,9 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             nco = c;
             break;
         }
-    // Layers that k_conv_direct did faster than one group.  Those of few workgroups are the groups' now (group_nco), and only timed under its
-    // name; beyond, it still takes 2x2x2 maps that go down and the widths below 128 channels that the lines give it.  It keeps two stages in flight and issues less for each, which decides while a CU
-    // has a workgroup or two, the more the further rows have to come; k_conv_tile skips the blocks that do not meet an offset.
+    // Layers that k_conv_direct does faster than one group.  It keeps two stages in flight and issues less for each, which
+    // decides while a CU has a workgroup or two, the more the further rows have to come; k_conv_tile skips the blocks that do not
+    // meet an offset.
     // The lines lie where most scenes change sides (us, k_conv_tile and k_conv_direct, on kept maps whose rows come new from memory
     // every time, as a network's do: scattered points, surfaces, a scan, a scan after one halving).  Scattered points change
     // sides last: 64 -> 64 on 65 k rows 24 and 21, 128 -> 64 39 and 32, where the others are ahead with k_conv_tile.
@@ -2082,24 +2099,6 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     // 300 k 41.7 and 35.5.
     const bool by_32 = ksteps == 3 && !sec.x2 && up && kmap->n_tiles > 4 * cus;
     const bool by_64 = ksteps == 3 && !sec.x2 && kmap->K3 == 1 && kmap->n_tiles > 4 * cus;
-    if (group_nco) {
-        const char *name = direct ? "k_conv_direct" : "k_conv_tile";   // timed under the name of the side of the lines that they lie on
-#define TS_GROUPS_CASE(N)                                                                               \
-    if (group_nco == N) {                                                                               \
-        if (sec.x2) {                                                                                   \
-            if (ksteps == 2) launch_conv_tile<N, 2, true, false, 3>(x, wf, kmap, out, cin_pad, ep, sec, name); \
-            else if (ksteps == 3) launch_conv_tile<N, 2, true, true, 2>(x, wf, kmap, out, cin_pad, ep, sec, name); \
-            else launch_conv_tile<N, 2, true, true, 3>(x, wf, kmap, out, cin_pad, ep, sec, name);       \
-        } else if (ksteps == 2) launch_conv_tile<N, 2, false, false, 3>(x, wf, kmap, out, cin_pad, ep, sec, name); \
-        else if (ksteps == 3) launch_conv_tile<N, 3, false, false, 2>(x, wf, kmap, out, cin_pad, ep, sec, name); \
-        else if (cin_pad == 32) launch_conv_tile<N, 1, false, false, 3>(x, wf, kmap, out, cin_pad, ep, sec, name); \
-        else launch_conv_tile<N, 2, false, true, 3>(x, wf, kmap, out, cin_pad, ep, sec, name);          \
-    }
-        TS_GROUPS_CASE(8) TS_GROUPS_CASE(6) TS_GROUPS_CASE(4) TS_GROUPS_CASE(2)
-#undef TS_GROUPS_CASE
-        TS_HIP(hipGetLastError());
-        return TS_OK;
-    }
 #define TS_DIRECT_CASE(N)                                                                          \
     if (direct && nco == N) {                                                                      \
         if (sec.x2) {                                                                              \

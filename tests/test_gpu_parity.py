@@ -1392,9 +1392,9 @@ def test_tiles_beyond_those_that_start_resident(K, s, transposed, n, parts, c_ou
         assert torch.equal(got, first)
 
 
-@pytest.mark.parametrize("n,c_in,c_out", [(32769, 96, 64), (32783, 96, 96), (52369, 192, 64), (32895, 96, 128), (65537, 32, 96), (65551, 32, 128), (65553, 32, 160), (65663, 20, 96)])
+@pytest.mark.parametrize("n,c_in,c_out", [(32769, 96, 64), (32783, 96, 96), (81937, 192, 64), (32895, 96, 128), (65537, 32, 96), (65551, 32, 128), (65553, 32, 160), (65663, 20, 96)])
 def test_stages_of_32_and_96_channels_on_27_offsets(n, c_in, c_out):
-    """The fewest tiles from which k_conv_tile takes such layers, with a last one of 1, 15, 17 and 127 rows."""
+    """The fewest tiles from which one group of k_conv_tile takes such layers, with a last one of 1, 15, 17 and 127 rows."""
     coords = _rand_coords(5060 + n, n, 0, 50, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
     x_h, w_h = features(5160 + c_in, n, c_in, np.float16), conv_weights(5260 + c_out, 27, c_in, c_out, np.float16)
@@ -1403,17 +1403,23 @@ def test_stages_of_32_and_96_channels_on_27_offsets(n, c_in, c_out):
     check_features(got, oracle_conv(coords, x_h, w_h, 3, 1), torch.float16, f"{n}: {c_in}->{c_out}")
 
 
+GROUPS, DIRECT, TILE = "k_conv_tile_groups", "k_conv_direct", "k_conv_tile"
+
+
 @pytest.mark.parametrize("n,parts,c_out,kernel", [
-    (129, (96,), 64, "k_conv_direct"), (32768, (96,), 64, "k_conv_direct"), (32769, (96,), 64, "k_conv_tile"), (129, (32,), 96, "k_conv_direct"),
-    (65536, (32,), 96, "k_conv_direct"), (66000, (32,), 96, "k_conv_tile"), (16000, (128,), 128, "k_conv_direct"), (16500, (128,), 128, "k_conv_tile"),
-    (2048, (64,), 64, "k_conv_tile"), (2049, (64,), 64, "k_conv_direct"), (32768, (64,), 64, "k_conv_direct"), (32769, (64,), 64, "k_conv_tile"),
-    (52352, (128,), 64, "k_conv_direct"), (52353, (128,), 64, "k_conv_tile"), (40000, (128,), 96, "k_conv_direct"), (40000, (128,), 128, "k_conv_tile"),
-    (52352, (160,), 64, "k_conv_direct"), (52353, (160,), 64, "k_conv_tile"), (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, "k_conv_direct"),
-    (66000, (96, 32), 96, "k_conv_tile"), (129, (96, 64), 96, "k_grouped_mm"), (40000, (64, 96), 32, "k_conv_tile"), (32768, (64, 96), 64, "k_conv_tile"),
-    (66000, (96, 64), 96, "k_conv_tile"), (2000, (64, 32), 96, "k_conv_direct"), (65536, (64, 32), 96, "k_conv_direct"), (65537, (64, 32), 96, "k_conv_tile"),
-    (52352, (64, 64), 64, "k_conv_direct"), (52353, (64, 64), 64, "k_conv_tile"), (98304, (32, 32), 32, "k_conv_direct"), (98305, (32, 32), 32, "k_conv_tile")])
-def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, parts, c_out, kernel):
-    """Few tiles and many, of layers whose kernel goes by their number; an input in two parts gives what it gives in one."""
+    (129, (32,), 96, GROUPS), (32768, (32,), 96, GROUPS), (32769, (32,), 96, DIRECT), (65536, (32,), 96, DIRECT), (66000, (32,), 96, TILE),
+    (2048, (64,), 64, GROUPS), (2049, (64,), 64, GROUPS), (32768, (64,), 64, GROUPS), (32769, (64,), 64, TILE), (129, (96,), 64, GROUPS),
+    (32768, (96,), 64, GROUPS), (32769, (96,), 64, TILE), (52352, (128,), 64, GROUPS), (52353, (128,), 64, GROUPS), (40000, (128,), 96, GROUPS),
+    (16000, (128,), 128, GROUPS), (16500, (128,), 128, GROUPS), (40000, (128,), 128, GROUPS), (65536, (128,), 128, GROUPS), (65537, (128,), 128, TILE),
+    (52352, (160,), 64, GROUPS), (52353, (160,), 64, GROUPS), (81920, (160,), 64, GROUPS), (81921, (160,), 64, TILE), (32769, (32, 32), 32, DIRECT),
+    (98304, (32, 32), 32, DIRECT), (98305, (32, 32), 32, TILE), (2000, (64, 32), 96, GROUPS), (32769, (64, 32), 96, DIRECT),
+    (65536, (64, 32), 96, DIRECT), (65537, (64, 32), 96, TILE), (52352, (64, 64), 64, GROUPS), (52353, (64, 64), 64, GROUPS),
+    (65536, (64, 64), 64, GROUPS), (65537, (64, 64), 64, TILE), (40000, (64, 96), 32, GROUPS), (32768, (64, 96), 64, GROUPS),
+    (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, GROUPS), (66000, (96, 32), 96, TILE), (129, (96, 64), 96, "k_grouped_mm"),
+    (66000, (96, 64), 96, GROUPS), (81921, (96, 64), 96, TILE)])
+def test_fused_layers_on_both_sides_of_the_lines_between_the_kernels(n, parts, c_out, kernel):
+    """Few tiles and many, of layers whose kernel goes by their number: groups of waves up to a tile a compute unit, or two, or two
+    and a half; k_conv_direct where those end, and one group.  An input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
     x_h = features(6100, n, sum(parts), np.float16)
@@ -1424,7 +1430,7 @@ def test_fused_layers_on_both_sides_of_the_lines_between_the_two_kernels(n, part
     else:
         kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared2(to_dev(x_h[:, :parts[0]].copy()), to_dev(x_h[:, parts[0]:].copy()), w, kmap))
         assert torch.equal(ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap), got)
-    assert kernel in kernels
+    assert kernels & {GROUPS, DIRECT, TILE, "k_grouped_mm"} == {kernel}
     check_features(got, oracle_conv(coords, x_h, w_h, 3, 1, False), torch.float16, f"{n}: {parts}->{c_out}")
 
 
@@ -1448,6 +1454,11 @@ def test_layers_whose_tiles_are_shared_by_groups_of_waves(K, s, n, parts, c_out)
         res, bias = (features(6430 + q, r, c_out, np.float16) for q, r in enumerate((kmap.num_out, 1)))
         w, xs = ts.ts_weights_prepare(to_dev(w_h)), [to_dev(p) for p in np.split(x_h, np.cumsum(parts)[:-1], axis=1)]
         want = oracle_conv(coords, x_h, w_h, K, s)
+        kernels, fused = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), kmap, dataflow=ts.TS_DATAFLOW_FUSED))
+        tiles, slices = -(-kmap.num_out // 128), c_out // 16 // max(c for c in (8, 6, 4, 2) if c_out // 16 % c == 0)
+        beyond = 1 if K == 2 or sum(parts) < 128 or slices > 1 else 2 if sum(parts) == 128 else 2.5
+        assert (GROUPS in kernels) == (tiles * slices <= beyond * torch.cuda.get_device_properties(0).multi_processor_count)
+        check_features(fused, want, torch.float16, f"{scene} {n}: {parts}->{c_out} K{K} s{s} fused")
         first = ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap)
         check_features(first, want, torch.float16, f"{scene} {n}: {parts}->{c_out} K{K} s{s}")
         for again in range(2):   # counters rearmed, rows ordered
@@ -1459,15 +1470,15 @@ def test_layers_whose_tiles_are_shared_by_groups_of_waves(K, s, n, parts, c_out)
 
 
 @pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
-    (2600, 40, 64, 64, "k_conv_direct"), (9000, 22, 128, 128, "k_conv_direct"), (9000, 22, 256, 64, "k_conv_direct"), (40000, 36, 160, 64, "k_conv_direct"), (40000, 36, 96, 96, "k_conv_tile"), (70000, 60, 96, 96, "k_conv_direct"),
-    (30000, 60, 32, 64, "k_conv_direct"), (130000, 100, 32, 64, "k_conv_tile"), (90000, 60, 64, 128, "k_conv_tile"), (250000, 70, 128, 64, "k_conv_direct")])
-def test_layers_down_by_both_kernels(n, side, c_in, c_out, kernel):
-    """2x2x2 maps that go down, on both sides of the lines between the two fp16 kernels."""
+    (2600, 40, 64, 64, GROUPS), (9000, 22, 128, 128, GROUPS), (9000, 22, 256, 64, GROUPS), (40000, 36, 160, 64, GROUPS), (40000, 36, 96, 96, GROUPS),
+    (70000, 60, 96, 96, GROUPS), (30000, 60, 32, 64, GROUPS), (130000, 100, 32, 64, TILE), (90000, 60, 64, 128, GROUPS), (250000, 70, 128, 64, DIRECT)])
+def test_layers_down_by_every_kernel(n, side, c_in, c_out, kernel):
+    """2x2x2 maps that go down, on both sides of the lines between the fp16 kernels."""
     coords = _rand_coords(6250 + n, n, 0, side)
     down = ts.ts_build_kmap(to_dev(coords), 2, 2)
     x_h, w_h = features(6350, n, c_in, np.float16), conv_weights(6351, 8, c_in, c_out, np.float16)
     kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), down, dataflow=ts.TS_DATAFLOW_FUSED))
-    assert kernel in kernels, (down.num_out, kernels)
+    assert kernels & {GROUPS, DIRECT, TILE} == {kernel}, (down.num_out, kernels)
     check_features(got, oracle_conv(coords, x_h, w_h, 2, 2), torch.float16, f"{n}: {c_in}->{c_out} down")
 
 
