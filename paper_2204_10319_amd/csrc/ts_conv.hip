@@ -2024,7 +2024,16 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             return TS_OK;
         }
     }
-    if (!wbuf) order_for_layer(kmap, order_at_once(kmap, cin_pad, cout, sizeof(T)));
+    // With more tiles than CUs the groups are ahead in sorted rows alone: in natural order a workgroup, which has its CU to itself, has
+    // tiles of nearly all offsets, and one round too many of them.  So a new map's rows are sorted for its first such layer; in
+    // time with the map (us, one group in natural order, groups in natural order, sorting and groups; a scan, a scan after one halving,
+    // surfaces, scattered points): 128 -> 64 on 46 k rows 50 48 49, 54 55 50, 52 50 48, 54 63 53; 128 -> 128 on 64 k 55 59 59, 61 67 62,
+    // 58 61 64, 70 75 65; 192 -> 96 on 52 k 68 69 60, 74 80 60, 74 71 60, 79 89 67; 192 -> 64 on 76 k 66 70 67, 70 85 68, 73 82 67,
+    // 92 111 79.  With hardly more than a tile a CU the longest tile decides, as elsewhere (192 -> 64 on 34 k 56 51 52, 55 48 54,
+    // 56 45 53, 64 77 57), and 128 -> 32 gains too little (46 k 47 42 45, 50 48 46, 48 43 44, 48 56 49; 192 -> 32 57 48 48,
+    // 62 60 51, 61 53 47, 58 69 55).
+    const bool groups_at_once = group_nco && 16 * kmap->n_tiles > 17 * cus && cin_pad * cout > 128 * 32;
+    if (!wbuf) order_for_layer(kmap, groups_at_once || order_at_once(kmap, cin_pad, cout, sizeof(T)));
     ++const_cast<ts_kmap *>(kmap)->uses;
     if (group_nco) {
 #define TS_GROUPS_CASE(N)                                                                                      \

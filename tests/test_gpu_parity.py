@@ -1469,6 +1469,36 @@ def test_layers_whose_tiles_are_shared_by_groups_of_waves(K, s, n, parts, c_out)
         assert torch.equal(tail, torch.relu(first.float() + to_dev(bias).float() + to_dev(res).float()).half())
 
 
+@pytest.mark.parametrize("n,c_in,c_out,at_once", [
+    (32768, 128, 128, False), (34816, 128, 64, False), (34817, 128, 64, True), (40000, 128, 32, False), (40000, 160, 32, True), (65536, 128, 128, True), (65537, 128, 64, False),
+    (81919, 160, 64, True), (81921, 160, 64, False)])
+def test_rows_are_sorted_at_once_for_groups_of_waves_beyond_a_tile_a_unit(n, c_in, c_out, at_once):
+    """The first layer on a new map, whose rows would be in natural order: with the order made for it, on a map that nobody
+    waited for, and on another stream than the map's, the same bits."""
+    coords = to_dev(_rand_coords(6150 + n, n, 0, 64))
+    x, w = to_dev(features(6151, n, c_in, np.float16)), ts.ts_weights_prepare(to_dev(conv_weights(6152, 27, c_in, c_out, np.float16)))
+    kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared(x, w, ts.ts_build_kmap(coords, 3, 1, wait=False)))
+    assert ("k_window_sort" in kernels) == at_once
+    kmap = ts.ts_build_kmap(coords, 3, 1)
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(other):
+        assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), got)
+    other.synchronize()
+    kmap.sort_rows()
+    assert torch.equal(ts.ts_sparse_conv_prepared(x, w, kmap), got)
+    graph, recorded = torch.cuda.CUDAGraph(), ts.ts_build_kmap(coords, 3, 1)
+    out = torch.zeros_like(got)
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):   # (nothing is allocated here: rows in natural order)
+        ts.ts_sparse_conv_prepared(x, w, recorded, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, got)
+
+
 @pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
     (2600, 40, 64, 64, GROUPS), (9000, 22, 128, 128, GROUPS), (9000, 22, 256, 64, GROUPS), (40000, 36, 160, 64, GROUPS), (40000, 36, 96, 96, GROUPS),
     (70000, 60, 96, 96, GROUPS), (30000, 60, 32, 64, GROUPS), (130000, 100, 32, 64, TILE), (90000, 60, 64, 128, GROUPS), (250000, 70, 128, 64, DIRECT)])
