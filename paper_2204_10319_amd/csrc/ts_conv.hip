@@ -2009,6 +2009,11 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         for (int c : {8, 6, 4, 2}) {
             if (cblocks % c != 0) continue;
             if (most < c) most = c;
+            // 96 output channels in one slice, of at most 96: no faster than three slices of one group before nearly half of the CUs
+            // have a tile (us, one group and three; a scan, a scan after one halving, surfaces, scattered points): 96 -> 96 on 11 k
+            // rows 18.9 20.8, 22.1 24.4, 20.0 20.3, 23.6 24.8, on 14 k 20.0 21.6, 25.0 24.9, 19.9 20.3, 24.3 25.1, on 16 k 23.5 21.1,
+            // 25.8 25.0, 23.3 21.2, 25.2 25.2; 32 -> 96 down to 12 k rows 10.6 11.7, 10.9 11.4, 11.0 11.6, 10.4 11.6
+            if (c == 6 && cblocks == 6 && cin_pad <= 96 && 20 * kmap->n_tiles <= 9 * cus) continue;
             if (kmap->n_tiles * (cblocks / c) <= cus) group_nco = c;
         }
         if (!group_nco && kmap->K3 == 27 && cin_pad >= 128 && cblocks == most && 2 * kmap->n_tiles <= (cin_pad > 128 ? 5 : 4) * cus) group_nco = most;

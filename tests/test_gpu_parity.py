@@ -1416,10 +1416,12 @@ GROUPS, DIRECT, TILE = "k_conv_tile_groups", "k_conv_direct", "k_conv_tile"
     (65536, (64, 32), 96, DIRECT), (65537, (64, 32), 96, TILE), (52352, (64, 64), 64, GROUPS), (52353, (64, 64), 64, GROUPS),
     (65536, (64, 64), 64, GROUPS), (65537, (64, 64), 64, TILE), (40000, (64, 96), 32, GROUPS), (32768, (64, 96), 64, GROUPS),
     (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, GROUPS), (66000, (96, 32), 96, TILE), (129, (96, 64), 96, "k_grouped_mm"),
-    (66000, (96, 64), 96, GROUPS), (81921, (96, 64), 96, TILE)])
+    (66000, (96, 64), 96, GROUPS), (81921, (96, 64), 96, TILE), (10880, (96,), 96, GROUPS), (10881, (96,), 96, DIRECT),
+    (14720, (96,), 96, DIRECT), (14721, (96,), 96, GROUPS), (14720, (64,), 96, TILE), (14720, (32,), 96, DIRECT),
+    (14720, (64, 32), 96, DIRECT), (14720, (128,), 96, GROUPS)])
 def test_fused_layers_on_both_sides_of_the_lines_between_the_kernels(n, parts, c_out, kernel):
     """Few tiles and many, of layers whose kernel goes by their number: groups of waves up to a tile a compute unit, or two, or two
-    and a half; k_conv_direct where those end, and one group.  An input in two parts gives what it gives in one."""
+    and a half, with a gap below half a tile where 96 channels go into 96; k_conv_direct where those end, and one group.  An input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
     x_h = features(6100, n, sum(parts), np.float16)
@@ -1501,7 +1503,8 @@ def test_rows_are_sorted_at_once_for_groups_of_waves_beyond_a_tile_a_unit(n, c_i
 
 @pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
     (2600, 40, 64, 64, GROUPS), (9000, 22, 128, 128, GROUPS), (9000, 22, 256, 64, GROUPS), (40000, 36, 160, 64, GROUPS), (40000, 36, 96, 96, GROUPS),
-    (70000, 60, 96, 96, GROUPS), (30000, 60, 32, 64, GROUPS), (130000, 100, 32, 64, TILE), (90000, 60, 64, 128, GROUPS), (250000, 70, 128, 64, DIRECT)])
+    (70000, 60, 96, 96, GROUPS), (30000, 60, 32, 64, GROUPS), (130000, 100, 32, 64, TILE), (90000, 60, 64, 128, GROUPS), (250000, 70, 128, 64, DIRECT),
+    (16000, 50, 96, 96, GROUPS), (20000, 50, 96, 96, TILE), (20000, 50, 32, 96, DIRECT), (20000, 50, 128, 96, GROUPS)])
 def test_layers_down_by_every_kernel(n, side, c_in, c_out, kernel):
     """2x2x2 maps that go down, on both sides of the lines between the fp16 kernels."""
     coords = _rand_coords(6250 + n, n, 0, side)
