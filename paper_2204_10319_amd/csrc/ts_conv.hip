@@ -2231,11 +2231,13 @@ template <int NCO>
 void launch_grouped_lines(const void *F, const void *X, const void *wf, const ts_kmap *kmap, const MmPlan &plan, float *G, int cin,
                           int cout, const int32_t *in_idx, const Second &sec) {
     const int cin1 = sec.x2 ? sec.cin1 : cin;
-    // A tile's slices start together, while its rows are on their way (256 -> 256 on 7.5 k points 30.6 -> 30.1 us, (256, 256) -> 256 38.7 ->
-    // 37.2, on 16 k 72.7 -> 69.8; on 2.7 k 19.7 -> 20.2 and 22.9 -> 22.2), if there are two (192 -> 160 on 13 k points, five: 38.5 -> 39.6) and
-    // no more tiles than a grid's second axis holds.
+    // Where there are two slices, and more tiles than CUs, a tile's slices start together, while its rows are on their way.  Slice
+    // after slice and tile after tile (us; a scan after three halvings | scattered points): 256 -> 256 on 2.7 k points 19.7 20.2 |
+    // 14.8 14.8, on 7.5 k 30.3 30.3 | 20.2 20.3, on 16 k 55.8 55.1 | 30.1 29.5; (256, 256) -> 256 on 4.5 k 25.3 25.0 | 18.4 18.8, on
+    // 7.5 k 38.5 37.2 | 24.7 24.3, on 16 k 74.6 72.4 | 39.1 36.4; with five slices 192 -> 160 on 13 k points 38.5 39.6.  Not on
+    // 2x2x2 maps, whose pairs share few input rows (256 -> 256 from 60 k points of a scan 46.9 52.2).
     dim3 grid((unsigned)plan_tiles(plan), cout / (NCO * 16));
-    const int slices_first = grid.x < 65536 && grid.y == 2;
+    const int slices_first = kmap->K3 == 27 && grid.x > (unsigned)compute_units() && grid.x < 65536 && grid.y == 2;
     if (slices_first) grid = dim3(grid.y, grid.x);
     const int x_bytes = (int)((size_t)kmap->n_in * cin1 * 2), x2_bytes = (int)((size_t)kmap->n_in * (cin - cin1) * 2);
     const int w_bytes = (int)((size_t)kmap->K3 * cin * cout * 2);
