@@ -2071,42 +2071,33 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         }
     // Layers that k_conv_direct does faster than one group.  It keeps two stages in flight and issues less for each, which
     // decides while a CU has a workgroup or two, the more the further rows have to come; k_conv_tile skips the blocks that do not
-    // meet an offset.
-    // The lines lie where most scenes change sides (us, k_conv_tile and k_conv_direct, on kept maps whose rows come new from memory
-    // every time, as a network's do: scattered points, surfaces, a scan, a scan after one halving).  Scattered points change
-    // sides last: 64 -> 64 on 65 k rows 24 and 21, 128 -> 64 39 and 32, where the others are ahead with k_conv_tile.
-    //  - stages of two sources, a part of the input being no multiple of 64 channels: up to two tiles a CU, (96, 32) -> 96 on 8 k rows
-    //    35 25, 32 24, 27 22, 34 25, on 65 k 50 40, 47 42, 45 38, 47 41, on 98 k 55 55, 53 58, 51 54, 51 56; with one stage an
-    //    offset, (32, 32) -> 32, up to three
+    // meet an offset.  The lines lie where most scenes change sides (us, k_conv_tile and k_conv_direct, on kept maps whose rows
+    // come new from memory every time, as a network's do: scattered points, surfaces, a scan, a scan after one halving).
+    //  - stages of two sources, a part of the input being no multiple of 64 channels: up to two tiles a CU, (96, 32) -> 192 on 33 k
+    //    rows 51 42, 48 41, 41 34, 48 42, on 65 k 61 52, 62 56, 52 49, 58 51, on 97 k 74 77, 77 77, 69 71, 76 74; with one stage an
+    //    offset up to three, (32, 32) -> 32 on 33 k 23 16, 21 16, 18 14, 21 15, on 97 k 26 22, 28 23, 25 22, 25 22
     //  - maps that go up, and 1x1x1 ones, leave a tile a stage or two: k_conv_tile at every size
     //  - 2x2x2 maps that go down: while one workgroup has at most 64 output channels (32 input channels: up to two tiles a CU; 96:
-    //    while there is one slice), 128 -> 64 from 20 k rows 11.2 11.3, 12.5 11.0, 12.8 10.9, from 65 k 22 18, 17 13, 18 15, from
-    //    300 k 62 52, 28 30, 42 39; 64 -> 64 from 65 k 16 15, 12 10, 13 12
-    //  - stages of 96 channels: up to a tile a CU, 96 -> 96 on 4 k rows 20 17, 16 15, 15 15, 12 11, on 32 k 45 32, 34 32, 28 31,
-    //    38 35, on 40 k 32 30, 32 33, 29 28, 31 31; in two parts up to two, (64, 32) -> 96 on 65 k 45 34, 40 36, 39 32, 40 35, on 80 k
-    //    46 43, 45 50, 42 43, 44 47
-    //  - stages of 32: up to two tiles a CU, 32 -> 96 on 4 k rows 16 12, 12 11, 11 11, 9.3 8.7, on 65 k 22 20, 21 22, 20 20, 21 21, on
-    //    98 k 26 26, 25 29, 26 26, 25 27
-    //  - stages of 64 and a half empty one: from a few tiles to 1.6 a CU, 160 -> 64 on 1 k rows 41 39, 16 17, 17 18, 16 17, on 16 k
-    //    43 37, 38 36, 34 33, 39 37, on 50 k 54 47, 51 50, 42 40, 51 46, on 65 k 55 47, 47 49, 47 45, 45 47; not in two parts, where
-    //    the kernel with stages of 32 walks twice as many
-    //  - stages of 64: while there is at most a workgroup a CU, 64 -> 64 on 8 k rows 18 15, 15.3 14.9, 14.0 14.2, 17 15, on 32 k 22 20,
-    //    18 18, 18 17, 20 18, on 40 k 21 20, 21 22, 20 19, 20 21, 64 -> 128 on 16 k (250 workgroups) 21 19, 19 18, 17 17, 19 18, on 20 k
-    //    (314) 23 22, 20 23, 18 19, 20 21; with several an offset and one slice, which gathers no row twice, up to 1.6,
-    //    128 -> 64 on 8 k 30 23, 24 24, 22 21, 27 23, on 50 k 38 31, 35 36, 30 29, 35 35, on 65 k 39 32, 34 37, 33 33, 32 36
+    //    while there is one slice), 128 -> 64 from 160 k points 39 32, 21 22, 26 26, 23 22, from 300 k 52 46, 27 29, 34 33, 33 30,
+    //    64 -> 64 from 300 k 38 34, 21 22, 26 26, 27 25, 96 -> 96 from 80 k 23 22, 14 14, 18 18, 17 17
+    //  - stages of 96 channels on 27 offsets: in two parts up to two tiles a CU, (64, 32) -> 96 on 33 k rows 39 28, 35 28, 30 24,
+    //    35 27, on 65 k 40 31, 38 33, 36 29, 36 31, on 97 k 43 41, 43 45, 41 40, 39 42; in one part never, 96 -> 96 on 14 k 26 25,
+    //    20 20, 20 21, 26 26, 96 -> 192 on 20 k 37 39, 30 31, 27 28, 33 35, 96 -> 256 on 32 k 43 49, 38 42, 32 39, 44 49
+    //  - stages of 32: up to two tiles a CU, 32 -> 96 on 33 k rows 20 18, 20 18, 17 17, 19 18, on 65 k 23 21, 23 23, 21 20, 21 21, on
+    //    97 k 25 25, 27 27, 26 26, 25 26
+    //  - stages of 64 and a half empty one, in slices of at most 64 output channels: from a few tiles to 1.6 a CU, 160 -> 160 on 11 k rows
+    //    51 47, 40 38, 41 39, 49 45, on 50 k 95 84, 98 104, 76 75, 92 96, 160 -> 320 on 20 k 108 97, 72 69, 53 50, 72 65, on 50 k 111 97,
+    //    113 112, 88 85, 109 105; not in two parts, where the kernel with stages of 32 walks twice as many
+    //  - whole stages of 64 in one part on 27 offsets: what it was ahead in, up to a workgroup a CU, goes to the groups
     const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32, up = goes_up_by_two(kmap);
-    const bool one_slice = nco == cblocks;
-    const int64_t wgs = kmap->n_tiles * (cblocks / nco);
     bool direct;
     if (split) direct = kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus;
     else if (kmap->K3 == 1 || up) direct = false;
-    else if (ksteps == 3) direct = kmap->K3 == 8 ? one_slice : kmap->n_tiles <= (sec.x2 ? 2 : 1) * cus;
+    else if (ksteps == 3) direct = kmap->K3 == 8 ? nco == cblocks : sec.x2 && kmap->n_tiles <= 2 * cus;
     else if (cin_pad == 32) direct = kmap->n_tiles <= 2 * cus && (kmap->K3 > 8 || nco <= 4);
     else if (half_empty && sec.x2) direct = false;
     else if (kmap->K3 == 8) direct = nco <= 4;
-    else if ((half_empty || cin_pad == 64) && 16 * kmap->n_tiles <= cus) direct = false;   // 64 -> 64 on 1 k rows 14.8 14.6, 9.3 10.6, 9.3 9.3, 9.2 9.0
-    else if (half_empty) direct = nco <= 4 && 5 * kmap->n_tiles <= 8 * cus;
-    else direct = wgs <= cus || (cin_pad >= 128 && one_slice && nco <= 6 && 5 * wgs <= 8 * cus);
+    else direct = half_empty && nco <= 4 && 16 * kmap->n_tiles > cus && 5 * kmap->n_tiles <= 8 * cus;
     // Maps that go up, their rows in order of their offset, and 1x1x1 ones leave a tile few stages, for which three workgroups a CU
     // beat the two that stages of 96 channels leave room for, beyond four tiles a CU: 96 -> 96 up to 130 k scattered points 25 and,
     // by 32 channels a stage, 27, to 200 k 36.9 and 35.5, to 300 k 44 and 39; 1x1x1 on 200 k, by 64 and 32, 31.4 and 29.1, on
@@ -2118,11 +2109,13 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
         if (sec.x2) {                                                                              \
             if (ksteps == 2) launch_conv_direct<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);   \
             else launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
-        } else if (ksteps == 2) launch_conv_direct<(N <= 4 ? N : 4), 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
-        else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+        } else if (ksteps == 2) {                                                                  \
+            if constexpr (N <= 4) launch_conv_direct<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+            else return fail(TS_ERR_UNSUPPORTED, "no k_conv_direct for %d blocks of output channels in stages of 64", N); \
+        } else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_direct<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec);                  \
     }
-    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)   // (one part, stages of 64: 6 and 8 blocks never come here)
+    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)   // (one part, stages of 64: only 2x2x2 maps, 2 and 4 blocks)
 #undef TS_DIRECT_CASE
 #define TS_TILE_CASE(N)                                                                            \
     if (!direct && nco == N) {                                                                     \

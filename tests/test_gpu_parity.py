@@ -1416,12 +1416,16 @@ GROUPS, DIRECT, TILE = "k_conv_tile_groups", "k_conv_direct", "k_conv_tile"
     (65536, (64, 32), 96, DIRECT), (65537, (64, 32), 96, TILE), (52352, (64, 64), 64, GROUPS), (52353, (64, 64), 64, GROUPS),
     (65536, (64, 64), 64, GROUPS), (65537, (64, 64), 64, TILE), (40000, (64, 96), 32, GROUPS), (32768, (64, 96), 64, GROUPS),
     (17, (96, 32), 96, "k_grouped_mm"), (16000, (96, 32), 96, GROUPS), (66000, (96, 32), 96, TILE), (129, (96, 64), 96, "k_grouped_mm"),
-    (66000, (96, 64), 96, GROUPS), (81921, (96, 64), 96, TILE), (10880, (96,), 96, GROUPS), (10881, (96,), 96, DIRECT),
-    (14720, (96,), 96, DIRECT), (14721, (96,), 96, GROUPS), (14720, (64,), 96, TILE), (14720, (32,), 96, DIRECT),
-    (14720, (64, 32), 96, DIRECT), (14720, (128,), 96, GROUPS)])
+    (66000, (96, 64), 96, GROUPS), (81921, (96, 64), 96, TILE), (10880, (96,), 96, GROUPS), (10881, (96,), 96, TILE),
+    (14720, (96,), 96, TILE), (14721, (96,), 96, GROUPS), (14720, (64,), 96, TILE), (14720, (32,), 96, DIRECT),
+    (14720, (64, 32), 96, DIRECT), (14720, (128,), 96, GROUPS), (20000, (96,), 192, TILE), (11500, (160,), 160, DIRECT),
+    (33000, (160,), 320, DIRECT), (6700, (32,), 320, DIRECT), (33000, (32,), 128, DIRECT), (33000, (32, 32), 64, DIRECT),
+    (33000, (32, 32), 96, DIRECT), (33000, (32, 32), 128, DIRECT), (33000, (64, 32), 32, DIRECT), (33000, (64, 32), 64, DIRECT),
+    (33000, (64, 32), 128, DIRECT), (33000, (96, 32), 192, DIRECT)])
 def test_fused_layers_on_both_sides_of_the_lines_between_the_kernels(n, parts, c_out, kernel):
     """Few tiles and many, of layers whose kernel goes by their number: groups of waves up to a tile a compute unit, or two, or two
-    and a half, with a gap below half a tile where 96 channels go into 96; k_conv_direct where those end, and one group.  An input in two parts gives what it gives in one."""
+    and a half, with a gap below half a tile where 96 channels go into 96; k_conv_direct where those end, in every form that it
+    has on 27 offsets, and one group.  An input in two parts gives what it gives in one."""
     coords = _rand_coords(6000 + n, n, 0, 64 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), 3, 1)
     x_h = features(6100, n, sum(parts), np.float16)
@@ -1504,13 +1508,26 @@ def test_rows_are_sorted_at_once_for_groups_of_waves_beyond_a_tile_a_unit(n, c_i
 @pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
     (2600, 40, 64, 64, GROUPS), (9000, 22, 128, 128, GROUPS), (9000, 22, 256, 64, GROUPS), (40000, 36, 160, 64, GROUPS), (40000, 36, 96, 96, GROUPS),
     (70000, 60, 96, 96, GROUPS), (30000, 60, 32, 64, GROUPS), (130000, 100, 32, 64, TILE), (90000, 60, 64, 128, GROUPS), (250000, 70, 128, 64, DIRECT),
-    (16000, 50, 96, 96, GROUPS), (20000, 50, 96, 96, TILE), (20000, 50, 32, 96, DIRECT), (20000, 50, 128, 96, GROUPS)])
+    (16000, 50, 96, 96, GROUPS), (20000, 50, 96, 96, TILE), (20000, 50, 32, 96, DIRECT), (20000, 50, 128, 96, GROUPS),
+    (90000, 80, 32, 32, DIRECT), (90000, 80, 32, 64, DIRECT), (90000, 80, 32, 96, TILE), (90000, 80, 64, 32, DIRECT), (90000, 80, 64, 96, TILE),
+    (90000, 80, 160, 32, DIRECT), (90000, 80, 160, 64, DIRECT), (90000, 80, 96, 32, DIRECT), (90000, 80, 96, 64, DIRECT),
+    (90000, 80, 96, 96, DIRECT), (90000, 80, 96, 128, DIRECT), (90000, 80, (32, 32), 32, DIRECT), (90000, 80, (32, 32), 64, DIRECT),
+    (90000, 80, (32, 32), 96, DIRECT), (90000, 80, (32, 32), 128, DIRECT), (90000, 80, (32, 64), 32, DIRECT), (90000, 80, (32, 64), 64, DIRECT),
+    (90000, 80, (32, 64), 96, DIRECT), (90000, 80, (32, 64), 128, DIRECT)])
 def test_layers_down_by_every_kernel(n, side, c_in, c_out, kernel):
-    """2x2x2 maps that go down, on both sides of the lines between the fp16 kernels."""
+    """2x2x2 maps that go down, on both sides of the lines between the fp16 kernels, and every form of k_conv_direct on them; an
+    input in two parts gives what it gives in one."""
     coords = _rand_coords(6250 + n, n, 0, side)
     down = ts.ts_build_kmap(to_dev(coords), 2, 2)
-    x_h, w_h = features(6350, n, c_in, np.float16), conv_weights(6351, 8, c_in, c_out, np.float16)
-    kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), down, dataflow=ts.TS_DATAFLOW_FUSED))
+    parts = c_in if isinstance(c_in, tuple) else (c_in,)
+    x_h, w_h = features(6350, n, sum(parts), np.float16), conv_weights(6351, 8, sum(parts), c_out, np.float16)
+    x, w = to_dev(x_h), to_dev(w_h)
+    if len(parts) == 1:
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(x, w, down, dataflow=ts.TS_DATAFLOW_FUSED))
+    else:
+        xs, pw = [to_dev(p) for p in np.split(x_h, parts[:1], axis=1)], ts.ts_weights_prepare(w)
+        kernels, got = _kernels_of(lambda: ts.ts_sparse_conv_prepared2(xs[0], xs[1], pw, down))
+        assert torch.equal(ts.ts_sparse_conv_prepared(x, pw, down), got)
     assert kernels & {GROUPS, DIRECT, TILE} == {kernel}, (down.num_out, kernels)
     check_features(got, oracle_conv(coords, x_h, w_h, 2, 2), torch.float16, f"{n}: {c_in}->{c_out} down")
 
