@@ -131,8 +131,8 @@ typedef struct ts_kmap ts_kmap;
  * complete as far as it was enqueued before; that the runtime has noticed is not promised.)  The map may be reused by
  * any number of ts_sparse_conv calls.
  * Memory: the map keeps about 145 bytes per point (3x3x3) or 86 (2x2x2; a stride-2 map counts its inputs, which
- * bound its outputs).  A 3x3x3 stride-1 build takes another 408 to 816 bytes per point while it runs, or, where that
- * cannot be had, 34 to 64 and a sixth to a third more time.
+ * bound its outputs).  A 3x3x3 stride-1 build of more than 5120 points takes another 408 to 816 bytes per point while it
+ * runs, or, where that cannot be had, 34 to 64 and a sixth to a third more time.
  */
 int ts_build_kmap(const int32_t *coords, int64_t N, int kernel_size, int stride, int transposed,
                   ts_kmap **out_kmap);

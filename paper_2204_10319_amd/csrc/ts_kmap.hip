@@ -2702,13 +2702,8 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
         TS_TRY(alloc_outputs(m, &fill));
         const int4 *c4 = reinterpret_cast<const int4 *>(coords);
         if (K == 3 && !opt.grid) {
-            BlockTable bt;
-            int32_t *counter = nullptr;
             TS_TRY(alloc_n(&m->d_rowmask, ((size_t)N + 3) & ~size_t(3)));   // what the map keeps comes before what the build can do without
-            TS_TRY(make_block_table(tmp, N, &bt, &counter, &fill));
-            // (After the table, which this does without: what an allocator is asked for, and which way a build goes where that is
-            // refused, is the same at every size.)
-            if (N <= kSmallPoints && !bt.base) {
+            if (N <= kSmallPoints) {   // no table in memory, and nothing to clear
                 int cap = 64;
                 while (cap < 4 * N && cap < kSmallSlots) cap <<= 1;
                 TS_LAUNCH("k_small_map", k_small_map, dim3(blocks_for(N, kSmallRows)), dim3(kSmallThreads), c4, (int)N, cap, given, m->d_nbr,
@@ -2716,6 +2711,9 @@ int build(const int32_t *coords, int64_t N, int K, int s, int transposed, ts_kma
                 guard.committed = true;
                 return finish(m, slot, wait, true);
             }
+            BlockTable bt;
+            int32_t *counter = nullptr;
+            TS_TRY(make_block_table(tmp, N, &bt, &counter, &fill));
             TS_TRY(launch_fill(fill));
 #define TS_BLOCK_SEARCH(...) TS_LAUNCH("k_block_search", (k_block_search<__VA_ARGS__>), per_point, block, given, N, bt, m->d_nbr, m->d_colbits, m->d_colbase, m->d_wavemask, m->n_blocks, m->d_rowmask, d_status)
             if (bt.base) {   // (the points' slots stand where the search puts the bitmasks)

@@ -161,6 +161,37 @@ def test_kmap_on_both_sides_of_one_launch(n, shape):
             assert e.value.code == code
 
 
+@pytest.mark.parametrize("n,in_lds", [(1, True), (700, True), (5120, True), (5121, False)])
+def test_builds_with_the_table_in_lds_take_no_memory_but_the_maps(n, in_lds):
+    """A 3x3x3 build of up to 5120 points asks for what its map keeps and nothing else; where no block for a table of more points
+    can be had it is built all the same, by the one launch."""
+    coords = _rand_coords(7350 + n, n, -12, 12)
+    held, given_back = {}, []
+
+    def alloc(size):
+        block = torch.empty(size, dtype=torch.uint8, device="cuda")
+        held[block.data_ptr()] = block
+        return block.data_ptr()
+
+    def release(ptr):
+        given_back.append(ptr)
+        held.pop(ptr, None)
+
+    ts.ts_set_allocator(alloc, release)
+    try:
+        kernels, kmap = _kernels_of(lambda: ts.ts_build_kmap(to_dev(coords), 3, 1, wait=False))
+        assert ("k_small_map" in kernels) == in_lds and ("k_block_search" in kernels) != in_lds
+        assert (not given_back) == in_lds
+        kmap.status()
+        kmap.free()
+    finally:
+        ts.ts_set_allocator(None, None)
+    with _no_block_above(2 << 20) as refused:
+        kernels, kmap = _kernels_of(lambda: _check_map(coords, 3, 1))
+        assert ("k_small_map" in kernels) == in_lds and (not refused) == in_lds
+        kmap.free()
+
+
 @pytest.mark.parametrize("K,s", [(1, 1), (3, 1), (2, 2)])
 @pytest.mark.parametrize("n", [1, 64, 257, 5000])
 def test_pair_lists_that_a_caller_asks_for(K, s, n):
@@ -184,12 +215,12 @@ def test_pair_lists_that_a_caller_asks_for(K, s, n):
         kmap.free()
 
 
-@pytest.mark.parametrize("n", [1, 255, 1365, 1366, 60000])
+@pytest.mark.parametrize("n", [5121, 5461, 5462, 10923, 60000])
 @pytest.mark.parametrize("span", [2, 9, 4000])
 def test_kmap_blocks_without_memory_for_a_row_number_per_cell(n, span):
     """A 3x3x3 map whose block table cannot have its row numbers by cell has them packed: full blocks, blocks with
-    a few points and with one, on both sides of a size of the table (1024 entries up to 682 points, 2048 up to
-    1365); points given twice or out of range; then a map is built the usual way again."""
+    a few points and with one, on both sides of a size of the table (8192 entries up to 5461 points, 16384 up to
+    10922); points given twice or out of range; then a map is built the usual way again."""
     side = max(int(np.ceil(n ** (1 / 3))), round(n ** (1 / 3) * span / 2))
     coords = _rand_coords(7300 + n + span, n, -side // 2, side // 2 + 1, batches=2)
     cap = 1024
