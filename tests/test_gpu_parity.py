@@ -100,12 +100,12 @@ def _no_block_above(limit):
         ts.ts_set_allocator(None, None)
 
 
-@pytest.mark.parametrize("n", [63, 64, 65, 255, 257, 3000])
+@pytest.mark.parametrize("n", [63, 64, 65, 255, 257, 3000, 5183, 5185, 5375, 5377, 8000])
 @pytest.mark.parametrize("order", ["raster", "shuffled", "column", "far apart"])
 def test_kmap_blocks_of_4x4x4(n, order):
     """The 3x3x3 stride-1 search looks neighbours up in 4x4x4 blocks: runs of points in one block that cross a wave
     of 64, full blocks, blocks cut at negative coordinates and at the ends of the range, points alone in theirs; and
-    a point given twice, next to itself and far from itself."""
+    a point given twice, next to itself and far from itself.  (The same scenes of up to 5120 points go to the table in LDS.)"""
     side = int(np.ceil(n ** (1 / 3)))
     grid = np.stack(np.meshgrid(*[np.arange(side)] * 3, indexing="ij"), -1).reshape(-1, 3)[:n]
     if order == "column":
@@ -113,12 +113,14 @@ def test_kmap_blocks_of_4x4x4(n, order):
     if order == "far apart":
         grid = grid * 11
     xyz = grid + (ts.TS_COORD_MIN if n % 2 else -(side // 2) - 1)
-    if n == 3000:
+    if n in (3000, 8000):
         xyz = xyz - xyz.max() + ts.TS_COORD_MAX
     coords = np.concatenate([np.zeros((n, 1), np.int64), xyz], 1).astype(np.int32)
     if order == "shuffled":
         coords = coords[np.random.Generator(np.random.PCG64(n)).permutation(n)]
-    _check_map(coords, 3, 1).free()
+    kernels, kmap = _kernels_of(lambda: _check_map(coords, 3, 1))
+    kmap.free()
+    assert ("k_block_search" in kernels) == (n > 5120)
     for at, of in ((1, 0), (n - 1, 0), (n // 2, n // 2 + 1)):
         twice = coords.copy()
         twice[at] = twice[of]
