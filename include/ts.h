@@ -123,9 +123,10 @@ typedef struct ts_kmap ts_kmap;
  *   out_kmap     receives the new map; *out_kmap = NULL on error.
  * Internally: coordinates are packed to 64-bit keys.  A 3x3x3 stride-1 map is searched in a table of the occupied
  * blocks of 4x4x4 cells, one thread per point (at most 8 lookups for the 27 offsets), and leaves one row of neighbour
- * indices per output; of at most 5120 points in one launch, every workgroup with a table of all points in LDS.  A strided build first finds its output coordinates (Alg. 3) and chooses its route by the
- * bounding box of its input, see ts_build_kmap_ex (TS_SEARCH_AUTO).  The sizes are counted per offset after that; the
- * per-offset pair lists are derived when first asked for (ts_kmap_pairs, the explicit dataflow).
+ * indices per output; of at most 5120 points in one launch, every workgroup with a table of all points in LDS.  A strided
+ * build first finds its output coordinates (Alg. 3) and chooses its route by the bounding box of its input, see
+ * ts_build_kmap_ex (TS_SEARCH_AUTO).  The sizes are counted per offset after that; the per-offset pair lists are derived
+ * when first asked for (ts_kmap_pairs, the explicit dataflow).
  * Waits until the map is complete, which any stream may use then, and its sizes and the verdict on the input are on
  * the host.  (The wait is for words that the build's last kernel writes to pinned memory.  Other work on the stream is
  * complete as far as it was enqueued before; that the runtime has noticed is not promised.)  The map may be reused by
@@ -172,7 +173,7 @@ int ts_kmap_prepare(const ts_kmap *kmap);
  * The map of a 1x1x1 convolution at stride 1 over n distinct points, made without coordinates: by
  * Eq. 1 with delta = 0 output k takes input k and nothing else, so M = {(k, k, 0)} whatever the points
  * are, as long as no two of them coincide (which the caller knows from any other build on the same
- * points; nothing is checked here).  n_in = n_out = |M| = n, kernel volume 1.  Two launches, no host
+ * points; nothing is checked here).  n_in = n_out = |M| = n, kernel volume 1.  One launch, no host
  * wait, no search; every layer call accepts the map.  It holds no coordinates: ts_kmap_out_coords and
  * ts_kmap_in_coords fail on it with TS_ERR_UNSUPPORTED.  Errors: TS_ERR_INVALID_ARG (NULL out_kmap, n < 0
  * or n >= 2^31), TS_ERR_OOM.  Free with ts_free.

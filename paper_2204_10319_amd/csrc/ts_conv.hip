@@ -462,7 +462,8 @@ struct TileShape {
 // registers beyond; stages of 96 channels leave LDS for two.
 // Layers on kept maps, rows from memory, one group or k_conv_direct -> groups (us; a scan after one halving | scattered):
 // 64 -> 64 on 8 k rows 14.7 -> 11.4 | 15.0 -> 12.4, on 32 k 18.2 -> 15.1 | 20.1 -> 17.2; 96 -> 96 on 32 k 34.3 -> 23.9 | 32.0 -> 25.7;
-// 128 -> 128 on 8 k 23.3 -> 18.0 | 23.7 -> 19.2, on 32 k 36.0 -> 29.0 | 37.5 -> 30.4; (96, 64) -> 96 on 8 k 40.0 -> 24.6 | 43.7 -> 26.7.
+// 128 -> 128 on 8 k 23.3 -> 18.0 | 23.7 -> 19.2, on 32 k 36.0 -> 29.0 | 37.5 -> 30.4; (96, 64) -> 96 on 8 k 40.0 -> 24.6 |
+// 43.7 -> 26.7.
 
 // Offsets of a 3x3x3 map by the sum of their steps modulo 3: a plane of nine has three in each share.
 constexpr uint32_t share27(int q) {
@@ -1832,6 +1833,8 @@ inline void order_for_layer(const ts_kmap *kmap, bool at_once) {
 //   7.7 M ( 80 k, 128 -> 96)          62 67, 61 66, 84 73       9.6 M (300 k, 64 -> 64)    89 88, 91 86, 138 120
 //   9.8 M (153 k, 64 -> 128)          66 65, 72 67, 90 78       9.8 M (153 k, 128 -> 64)   81 73, 87 74, 110 89
 //   14.7 M (153 k, 128 -> 96)         92 82, 106 87, 124 98     48 M (1.5 M, 64 -> 64)     446 434, 487 455, 694 567
+// From 9 M on every scene gains; below, scattered points do and scans and surfaces mostly lose, but for 96 -> 96.  Layers on 513 to
+// 549 tiles of 128 -> 128 lie just below: 64 57, 68 59, 71 80 (66 k points, with the order and without it).
 inline bool order_at_once(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (elem == 4) return kmap->n_tiles > compute_units() * 17 / 16 && kmap->n_tiles * cin * cout >= 1000000;
     if (goes_up_by_two(kmap)) return cin * cout >= 128 * 128;
@@ -1996,12 +1999,14 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     }
     const int cblocks = cout / 16;
     // Launches of hardly more than a workgroup a CU: several groups of waves to a tile (k_conv_tile<..., GR>), and the fewest
-    // output blocks a workgroup with which each still has a CU (64 -> 64 on 8 k rows of a scan, by 2 and 4 blocks, 11.4 and 13.8 us,
-    // on 26 k, where 2 blocks make 408 workgroups, 18.4 and 14.5).  With 128 input channels and more the groups stay ahead
-    // until a CU has two, or two and a half, workgroups, if those take all output channels (128 -> 160 on 12 k rows, five slices, 30.5 32.7; one group and three; a scan, scattered): 128 -> 128 on 65 k rows 40.1 38.0, 41.1 36.1, on
-    // 80 k 42.8 44.1, 46.9 47.3; 192 -> 64 on 80 k 50.6 43.8, 53.3 51.2, on 110 k 60.3 61.8, 57.4 70.6; 64 -> 64 on 40 k 20.1 20.3,
+    // output blocks a workgroup with which each still has a CU (64 -> 64 on 8 k rows of a scan, by 2 and 4 blocks, 11.4 and
+    // 13.8 us, on 26 k, where 2 blocks make 408 workgroups, 18.4 and 14.5).  With 128 input channels and more the groups stay ahead
+    // on kept maps until a CU has two, or two and a half, workgroups, if those take all output channels (one group and three; a
+    // scan, scattered points): 128 -> 128 on 65 k rows 40.1 38.0, 41.1 36.1, on 80 k 42.8 44.1, 46.9 47.3; 192 -> 64 on 80 k
+    // 50.6 43.8, 53.3 51.2, on 110 k 60.3 61.8, 57.4 70.6; in five slices 128 -> 160 on 12 k 30.5 32.7; 64 -> 64 on 40 k 20.1 20.3,
     // 21.0 19.5, on 65 k 20.3 21.4, 22.2 23.2.  Going up, and on 1x1x1 maps, a tile has a stage or two: nothing to share.
-    // Which layers these are goes by sizes alone, not by the parts of an input: the sums of groups are not those of one.
+    // Which layers these are goes by sizes alone, not by the parts of an input or the order of the rows: the sums of groups are
+    // not those of one.
     const int64_t cus = compute_units();
     int group_nco = 0;
     if (kmap->K3 > 1 && !goes_up_by_two(kmap)) {
@@ -2021,7 +2026,8 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     // 32 input channels and 27 offsets: the kernel with resident weights (for 2x2x2 maps and for 64 -> 32 it
     // measured no faster than k_conv_tile, and 64 -> 64 in two slices of output channels much slower: every
     // slice gathers all rows again)
-    // (In groups instead while every tile has a CU: 32 -> 32 on 1 k rows 9.3 -> 7.1 us, on 32 k 12.6 -> 9.9, 4 -> 32 12.4 -> 9.4, 15.8 -> 13.1.)
+    // (In groups instead while every tile has a CU: 32 -> 32 on 1 k rows 9.3 -> 7.1 us, on 32 k 12.6 -> 9.9, 4 -> 32 12.4 -> 9.4,
+    // 15.8 -> 13.1.)
     if (!group_nco && cin_pad == 32 && kmap->K3 > 8 && kmap->n_out > 0 && (cout == 32 || cout == 64) && !sec.x2) {
         const bool done = cout == 32 ? launch_conv_res<2, 1>(x, wf, kmap, out, ep) : launch_conv_res<4, 1>(x, wf, kmap, out, ep);
         if (done) {
@@ -2029,14 +2035,14 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             return TS_OK;
         }
     }
-    // With more tiles than CUs the groups are ahead in sorted rows alone: in natural order a workgroup, which has its CU to itself, has
-    // tiles of nearly all offsets, and one round too many of them.  So a new map's rows are sorted for its first such layer; in
-    // time with the map (us, one group in natural order, groups in natural order, sorting and groups; a scan, a scan after one halving,
-    // surfaces, scattered points): 128 -> 64 on 46 k rows 50 48 49, 54 55 50, 52 50 48, 54 63 53; 128 -> 128 on 64 k 55 59 59, 61 67 62,
-    // 58 61 64, 70 75 65; 192 -> 96 on 52 k 68 69 60, 74 80 60, 74 71 60, 79 89 67; 192 -> 64 on 76 k 66 70 67, 70 85 68, 73 82 67,
-    // 92 111 79.  With hardly more than a tile a CU the longest tile decides, as elsewhere (192 -> 64 on 34 k 56 51 52, 55 48 54,
-    // 56 45 53, 64 77 57), and 128 -> 32 gains too little (46 k 47 42 45, 50 48 46, 48 43 44, 48 56 49; 192 -> 32 57 48 48,
-    // 62 60 51, 61 53 47, 58 69 55).
+    // With more tiles than CUs the groups are ahead in sorted rows alone: in natural order a workgroup, which has its CU to
+    // itself, has tiles of nearly all offsets, and one round too many of them.  So a new map's rows are sorted for its first
+    // such layer; in time with the map (us, one group in natural order, groups in natural order, sorting and groups; a scan, a scan
+    // after one halving, surfaces, scattered points): 128 -> 64 on 46 k rows 50 48 49, 54 55 50, 52 50 48, 54 63 53; 128 -> 128 on 64 k
+    // 55 59 59, 61 67 62, 58 61 64, 70 75 65; 192 -> 96 on 52 k 68 69 60, 74 80 60, 74 71 60, 79 89 67; 192 -> 64 on 76 k 66 70 67,
+    // 70 85 68, 73 82 67, 92 111 79.  With hardly more than a tile a CU the longest tile decides, as elsewhere (192 -> 64 on 34 k
+    // 56 51 52, 55 48 54, 56 45 53, 64 77 57), and 128 -> 32 gains too little (46 k 47 42 45, 50 48 46, 48 43 44, 48 56 49; 192 -> 32
+    // 57 48 48, 62 60 51, 61 53 47, 58 69 55).
     const bool groups_at_once = group_nco && 16 * kmap->n_tiles > 17 * cus && cin_pad * cout > 128 * 32;
     if (!wbuf) order_for_layer(kmap, groups_at_once || order_at_once(kmap, cin_pad, cout, sizeof(T)));
     ++const_cast<ts_kmap *>(kmap)->uses;
@@ -2085,9 +2091,9 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     //    20 20, 20 21, 26 26, 96 -> 192 on 20 k 37 39, 30 31, 27 28, 33 35, 96 -> 256 on 32 k 43 49, 38 42, 32 39, 44 49
     //  - stages of 32: up to two tiles a CU, 32 -> 96 on 33 k rows 20 18, 20 18, 17 17, 19 18, on 65 k 23 21, 23 23, 21 20, 21 21, on
     //    97 k 25 25, 27 27, 26 26, 25 26
-    //  - stages of 64 and a half empty one, in slices of at most 64 output channels: from a few tiles to 1.6 a CU, 160 -> 160 on 11 k rows
-    //    51 47, 40 38, 41 39, 49 45, on 50 k 95 84, 98 104, 76 75, 92 96, 160 -> 320 on 20 k 108 97, 72 69, 53 50, 72 65, on 50 k 111 97,
-    //    113 112, 88 85, 109 105; not in two parts, where the kernel with stages of 32 walks twice as many
+    //  - stages of 64 and a half empty one, in slices of at most 64 output channels: from a few tiles to 1.6 a CU, 160 -> 160 on
+    //    11 k rows 51 47, 40 38, 41 39, 49 45, on 50 k 95 84, 98 104, 76 75, 92 96, 160 -> 320 on 20 k 108 97, 72 69, 53 50, 72 65, on
+    //    50 k 111 97, 113 112, 88 85, 109 105; not in two parts, where the kernel with stages of 32 walks twice as many
     //  - whole stages of 64 in one part on 27 offsets: what it was ahead in, up to a workgroup a CU, goes to the groups
     const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32, up = goes_up_by_two(kmap);
     bool direct;
@@ -2415,14 +2421,18 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // dataflows differ in bits.  So:
 //   - fp16 goes by the typical number of surface-like scenes, or the map's own where that is larger: a solid has up to 27 a
 //     point where scans and surfaces have 7 to 9, and fetching them costs three times the fused kernel (192 -> 192 on 32 k points
-//     of a solid 307 us and 97, 256 -> 256 on 20 k 266 and 133).  Where the layer comes out fused by the typical number it
+//     of a solid 292 us and 77, 256 -> 256 on 20 k 238 and 97).  Where the layer comes out fused by the typical number it
 //     does so by any larger one, and nothing is waited for; where it does not, the explicit dataflow waits in any case.
 //     On so few points that the pairs' bytes are less than 40 times the weights that one workgroup goes through, fetching stays
-//     ahead however dense they are (192 -> 192, fused and fetched, surfaces 1 k 24 us and 20, 3 k (41 times) 24 and 25, a solid of
-//     1 k 46 and 30, of 8 k (300 times) 51 and 77).
-//     A smaller number does not count, though fetching gains on scattered points, which have 3 (96 -> 96 on 1 k points 20 us
-//     fused and 13 fetched, on 32 k 35 and 29; 128 -> 128 on 8 k 27 and 21; nothing on a thinned-out scan): the wait would take more
-//     from a step (96 -> 96 on 1 k scattered points 31 us without it and 40 with it, on 8 k of a scan 34 and 53).
+//     ahead however dense they are (192 -> 192, fused and fetched, surfaces 1 k 18 us and 18, 3 k (41 times) 18 and 24, a solid of
+//     1 k 33 and 25, of 8 k (300 times) 39 and 68).
+//     A smaller number does not count, though fetching gains on scattered points, which have 3 (96 -> 96 on 1 k points 18 us
+//     fused and 13 fetched, 128 -> 128 on 8 k 23 and 20; nothing on 32 k or on a thinned-out scan): the wait would take more
+//     from a step.
+//     The factor was drawn before groups of waves shared a tile (k_conv_tile<..., GR>), and is the same since, so that it is on the
+//     safe side for scans and surfaces: fused and fetched, 256 -> 256 on a scan after two halvings, 7.5 k points 42 and 36, 16 k
+//     50 and 58, 30 k 75 and 104, 192 -> 192 33 and 30, 39 and 45, 56 and 78, and all of these are fetched; on 30 k scattered
+//     points 90 and 55, 62 and 44.
 //   - Single precision with weights of 16 KiB an offset and more goes by its own number, and waits for it: the fused kernel
 //     walks a tile's offsets at 2.3 us each (64 -> 64; 8.6 at 128 -> 128), however few tiles there are, so that what decides is
 //     the pairs' bytes against the weights that one workgroup goes through, a thousand to one by the rates measured: 64 -> 64,
@@ -2433,10 +2443,10 @@ int run_explicit(const ts_tensor *feats, const ts_tensor *weights, const ts_kmap
 // 2x2x2 maps that go up, in fp16 (us, fused and fetched): rows of one offset stand together, so that a tile walks little more
 // than one offset, and the two dataflows give the same bits: 64 -> 64 on 300 rows 8.4, 11.1, on 20 k 9.4, 12.3; 256 -> 256 on
 // 1 k 13.0, 14.1, on 20 k 16.8, 24.1, but on 300, where three tiles walk 32 stages each, 14.8, 12.4; 160 -> 64 11.7, 10.9.
-// Maps that go down share the line of the others.  Drawn at 0.9 times the pairs' bytes it gained on wide outputs (64 -> 128
-// from 16 k scattered points 9.9, 12.8, 256 -> 256 from 60 k points of surfaces 27.2, 33.7) but cost more where C_in is the
-// larger one, whose stages a tile walks one after the other: 128 -> 64 from 16 k scattered points 11.6, 9.8, 256 -> 64 from 24 k
-// points of a scan 20.2, 11.9, 256 -> 128 from 11 k after one halving 19.2, 12.7.  And the two dataflows differ in bits.
+// Maps that go down share the line of the others.  Drawn at 0.9 times the pairs' bytes it gains on wide outputs (64 -> 128
+// from 16 k scattered points 11.8, 15.8, 256 -> 256 from 60 k points of surfaces 26.6, 39.0) but costs more where C_in is the
+// larger one, whose stages a tile walks one after the other: 256 -> 64 from 24 k points of a scan 17.2, 14.9, 256 -> 128 from
+// 11 k after one halving 17.3, 16.3.  And the two dataflows differ in bits.
 bool prefer_explicit(const ts_kmap *kmap, int cin, int cout, size_t elem) {
     if (kmap->n_tiles > compute_units()) return false;
     if (elem == 2 && goes_up_by_two(kmap) && (cin <= 128 || kmap->n_out >= 4 * kTileRows)) return false;

@@ -3,9 +3,9 @@
 // Keys: (b,x,y,z) -> order-preserving 64 bits, one integer per coordinate (Sec. 2.1.2).  Every build leaves, per output,
 // the row of neighbour indices and its offset bitmask, and per 64 outputs and offset a presence bitmap with its count.
 // By kind of map, on one stream:
-//   3x3x3, stride 1   up to 5120 points: small_map, one launch.  Beyond: fill (clears the block entries), block_insert (pack, insert by blocks of 4x4x4 cells), block_search
-//            (a thread per point: Alg. 1's 27 offsets from at most 8 blocks).  Row numbers are packed, by block_base and
-//            block_place, only where memory for one per cell is lacking.
+//   3x3x3, stride 1   up to 5120 points: small_map, one launch.  Beyond: fill (clears the block entries), block_insert (pack,
+//            insert by blocks of 4x4x4 cells), block_search (a thread per point: Alg. 1's 27 offsets from at most 8 blocks).  Row
+//            numbers are packed, by block_base and block_place, only where memory for one per cell is lacking.
 //   2x2x2, stride 2   down_pack, _clear, _mark, _count, _expand, _scatter, rows: the box, the number of outputs and what
 //            is sized by them stay on the device, nothing waits in between; its transposed map: up_rows
 //   other strided and transposed maps   pack; candidate keys (p - delta)/s (Alg. 3, stages 1-4), made distinct and sorted

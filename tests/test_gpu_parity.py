@@ -1392,7 +1392,7 @@ def _kernels_of(fn):
                                            (129, 128, 96), (257, 96, 128), (3000, 160, 64), (3000, 32, 96), (40000, 64, 64)])
 def test_fused_layer_at_tile_and_stage_edges(K, s, transposed, n, c_in, c_out):
     """Rows around blocks of 16 and tiles of 128; stages of 32, 64 and 96 input channels and a last one that is half full;
-    every number of output blocks per workgroup.  (27 offsets and few tiles: k_conv_direct for some widths, see below.)"""
+    every number of output blocks per workgroup.  (27 offsets and few tiles: groups of waves.)"""
     coords = _rand_coords(5000 + n + c_in, n, 0, 4 if n < 60 else 40 if n > 4000 else 16, batches=1)
     kmap = ts.ts_build_kmap(to_dev(coords), K, s, transposed)
     x_h = features(5100 + c_in, kmap.num_in, c_in, np.float16)
