@@ -2004,7 +2004,9 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     // on kept maps until a CU has two, or two and a half, workgroups, if those take all output channels (one group and three; a
     // scan, scattered points): 128 -> 128 on 65 k rows 40.1 38.0, 41.1 36.1, on 80 k 42.8 44.1, 46.9 47.3; 192 -> 64 on 80 k
     // 50.6 43.8, 53.3 51.2, on 110 k 60.3 61.8, 57.4 70.6; in five slices 128 -> 160 on 12 k 30.5 32.7; 64 -> 64 on 40 k 20.1 20.3,
-    // 21.0 19.5, on 65 k 20.3 21.4, 22.2 23.2.  Going up, and on 1x1x1 maps, a tile has a stage or two: nothing to share.
+    // 21.0 19.5, on 65 k 20.3 21.4, 22.2 23.2.  Not on maps with a stride, whose rows are never sorted by the library (down to
+    // 44 k rows of a scan after one halving, 128 -> 64 32.4 38.2, 192 -> 96 51.6 62.8, of scattered points 32.2 41.8, 57.9 68.6).
+    // Going up, and on 1x1x1 maps, a tile has a stage or two: nothing to share.
     // Which layers these are goes by sizes alone, not by the parts of an input or the order of the rows: the sums of groups are
     // not those of one.
     const int64_t cus = compute_units();
@@ -2021,7 +2023,7 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             if (c == 6 && cblocks == 6 && cin_pad <= 96 && 20 * kmap->n_tiles <= 9 * cus) continue;
             if (kmap->n_tiles * (cblocks / c) <= cus) group_nco = c;
         }
-        if (!group_nco && kmap->K3 == 27 && cin_pad >= 128 && cblocks == most && 2 * kmap->n_tiles <= (cin_pad > 128 ? 5 : 4) * cus) group_nco = most;
+        if (!group_nco && kmap->K3 == 27 && kmap->s == 1 && cin_pad >= 128 && cblocks == most && 2 * kmap->n_tiles <= (cin_pad > 128 ? 5 : 4) * cus) group_nco = most;
     }
     // 32 input channels and 27 offsets: the kernel with resident weights (for 2x2x2 maps and for 64 -> 32 it
     // measured no faster than k_conv_tile, and 64 -> 64 in two slices of output channels much slower: every
@@ -2094,7 +2096,9 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     //  - stages of 64 and a half empty one, in slices of at most 64 output channels: from a few tiles to 1.6 a CU, 160 -> 160 on
     //    11 k rows 51 47, 40 38, 41 39, 49 45, on 50 k 95 84, 98 104, 76 75, 92 96, 160 -> 320 on 20 k 108 97, 72 69, 53 50, 72 65, on
     //    50 k 111 97, 113 112, 88 85, 109 105; not in two parts, where the kernel with stages of 32 walks twice as many
-    //  - whole stages of 64 in one part on 27 offsets: what it was ahead in, up to a workgroup a CU, goes to the groups
+    //  - whole stages of 64 in one part on 27 offsets: what it was ahead in goes to the groups, but for maps with a stride and several
+    //    stages an offset, one slice of at most 96 output channels: up to 1.6 tiles a CU, up to 40 k rows of scattered points, a scan, a
+    //    scan after one halving 128 -> 64 37 33, 32 28, 32 29, of surfaces, a scan, a scan after one halving 192 -> 96 42 40, 51 46, 51 48
     const bool split = sec.x2 && ksteps == 2 && sec.cin1 % 64 != 0, half_empty = ksteps == 1 && cin_pad != 32, up = goes_up_by_two(kmap);
     bool direct;
     if (split) direct = kmap->K3 > 1 && kmap->n_tiles <= (cin_pad == 64 ? 3 : 2) * cus;
@@ -2103,7 +2107,8 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
     else if (cin_pad == 32) direct = kmap->n_tiles <= 2 * cus && (kmap->K3 > 8 || nco <= 4);
     else if (half_empty && sec.x2) direct = false;
     else if (kmap->K3 == 8) direct = nco <= 4;
-    else direct = half_empty && nco <= 4 && 16 * kmap->n_tiles > cus && 5 * kmap->n_tiles <= 8 * cus;
+    else if (half_empty) direct = nco <= 4 && 16 * kmap->n_tiles > cus && 5 * kmap->n_tiles <= 8 * cus;
+    else direct = cin_pad >= 128 && nco == cblocks && nco <= 6 && 5 * kmap->n_tiles <= 8 * cus;
     // Maps that go up, their rows in order of their offset, and 1x1x1 ones leave a tile few stages, for which three workgroups a CU
     // beat the two that stages of 96 channels leave room for, beyond four tiles a CU: 96 -> 96 up to 130 k scattered points 25 and,
     // by 32 channels a stage, 27, to 200 k 36.9 and 35.5, to 300 k 44 and 39; 1x1x1 on 200 k, by 64 and 32, 31.4 and 29.1, on
@@ -2116,12 +2121,12 @@ int run_fused_f16(const ts_tensor *feats, const ts_tensor *weights, const ts_kma
             if (ksteps == 2) launch_conv_direct<N, 2, true>(x, wf, kmap, out, cin_pad, ep, sec);   \
             else launch_conv_direct<N, 3, true>(x, wf, kmap, out, cin_pad, ep, sec);               \
         } else if (ksteps == 2) {                                                                  \
-            if constexpr (N <= 4) launch_conv_direct<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
+            if constexpr (N <= 6) launch_conv_direct<N, 2, false>(x, wf, kmap, out, cin_pad, ep, sec); \
             else return fail(TS_ERR_UNSUPPORTED, "no k_conv_direct for %d blocks of output channels in stages of 64", N); \
         } else if (ksteps == 3) launch_conv_direct<N, 3, false>(x, wf, kmap, out, cin_pad, ep, sec); \
         else launch_conv_direct<N, 1, false>(x, wf, kmap, out, cin_pad, ep, sec);                  \
     }
-    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)   // (one part, stages of 64: only 2x2x2 maps, 2 and 4 blocks)
+    TS_DIRECT_CASE(8) TS_DIRECT_CASE(6) TS_DIRECT_CASE(4) TS_DIRECT_CASE(2)   // (one part, stages of 64: never 8 blocks)
 #undef TS_DIRECT_CASE
 #define TS_TILE_CASE(N)                                                                            \
     if (!direct && nco == N) {                                                                     \

@@ -1476,7 +1476,7 @@ def test_fused_layers_on_both_sides_of_the_lines_between_the_kernels(n, parts, c
 @pytest.mark.parametrize("K,s", [(3, 1), (2, 2), (3, 2)])
 @pytest.mark.parametrize("n,parts,c_out", [(1, (64,), 64), (127, (32,), 32), (129, (20,), 64), (300, (96,), 96), (1000, (160,), 160), (2049, (96, 32), 96),
                                            (3000, (96, 64), 96), (4097, (64, 32), 128), (8000, (128,), 256), (32768, (64,), 64), (32769, (64,), 64), (16400, (96,), 128),
-                                           (38417, (128,), 64), (65553, (128,), 128), (79999, (96, 64), 64), (80001, (192,), 32)])
+                                           (38417, (128,), 64), (65553, (128,), 128), (79999, (96, 64), 64), (80001, (192,), 32), (26000, (160,), 96)])
 def test_layers_whose_tiles_are_shared_by_groups_of_waves(K, s, n, parts, c_out):
     """Launches of about a workgroup a CU give a tile's offsets to groups of waves: stages of every length and of two inputs, one tile and
     more than start resident, the line at a workgroup a CU and at two or two and a half; points with no neighbour (one group
@@ -1495,7 +1495,7 @@ def test_layers_whose_tiles_are_shared_by_groups_of_waves(K, s, n, parts, c_out)
         want = oracle_conv(coords, x_h, w_h, K, s)
         kernels, fused = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), kmap, dataflow=ts.TS_DATAFLOW_FUSED))
         tiles, slices = -(-kmap.num_out // 128), c_out // 16 // max(c for c in (8, 6, 4, 2) if c_out // 16 % c == 0)
-        beyond = 1 if K == 2 or sum(parts) < 128 or slices > 1 else 2 if sum(parts) == 128 else 2.5
+        beyond = 1 if s == 2 or sum(parts) < 128 or slices > 1 else 2 if sum(parts) == 128 else 2.5
         assert (GROUPS in kernels) == (tiles * slices <= beyond * torch.cuda.get_device_properties(0).multi_processor_count)
         check_features(fused, want, torch.float16, f"{scene} {n}: {parts}->{c_out} K{K} s{s} fused")
         first = ts.ts_sparse_conv_prepared(to_dev(x_h), w, kmap)
@@ -1563,6 +1563,19 @@ def test_layers_down_by_every_kernel(n, side, c_in, c_out, kernel):
         assert torch.equal(ts.ts_sparse_conv_prepared(x, pw, down), got)
     assert kernels & {GROUPS, DIRECT, TILE} == {kernel}, (down.num_out, kernels)
     check_features(got, oracle_conv(coords, x_h, w_h, 2, 2), torch.float16, f"{n}: {c_in}->{c_out} down")
+
+
+@pytest.mark.parametrize("n,side,c_in,c_out,kernel", [
+    (24000, 64, 128, 64, GROUPS), (30000, 64, 128, 32, DIRECT), (30000, 64, 128, 64, DIRECT), (30000, 64, 192, 96, DIRECT), (30000, 64, 128, 128, TILE),
+    (30000, 64, 160, 64, DIRECT), (40000, 80, 128, 64, TILE), (40000, 80, 160, 96, TILE)])
+def test_layers_of_strided_3x3x3_maps(n, side, c_in, c_out, kernel):
+    """Rows that the library never sorts: groups of waves up to a tile a compute unit whatever the width, then k_conv_direct and one group."""
+    coords = _rand_coords(6260 + n, n, 0, side)
+    down = ts.ts_build_kmap(to_dev(coords), 3, 2)
+    x_h, w_h = features(6360, n, c_in, np.float16), conv_weights(6361, 27, c_in, c_out, np.float16)
+    kernels, got = _kernels_of(lambda: ts.ts_sparse_conv(to_dev(x_h), to_dev(w_h), down, dataflow=ts.TS_DATAFLOW_FUSED))
+    assert kernels & {GROUPS, DIRECT, TILE} == {kernel}, (down.num_out, kernels)
+    check_features(got, oracle_conv(coords, x_h, w_h, 3, 2), torch.float16, f"{n}: {c_in}->{c_out} 3x3x3 down")
 
 
 @pytest.mark.parametrize("n,c_in", [(131072, 96), (131073, 96), (131199, 288)])
